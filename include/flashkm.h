@@ -92,7 +92,10 @@ size_t fk_workspace_bytes(int B, int64_t N, int d, int K, fk_dtype t);
  * fp16/bf16: the x.c contraction runs on MFMA with fp32 accumulation against
  * -||c_k||^2/2, the running (max, index) pair stays in registers over all centroid tiles
  * (the paper's online argmin, with the row-constant ||x||^2 dropped); fp32: plain fp32
- * direct differences.  HBM traffic is X + C read once, assign written once.
+ * direct differences, except that larger problems first decide on the matrix cores every point
+ * whose answer no rounding can change (split bf16 products with a proven error bound) and measure
+ * only the others: same assignments bit for bit, min_dist in another summation order.
+ * HBM traffic is X + C read once, assign written once.
  */
 fk_status fk_assign(const void* X, const void* C, int32_t* assign, float* min_dist,
                     int B, int64_t N, int d, int K, fk_dtype t,
@@ -218,6 +221,7 @@ fk_status fk_standard_update(const void* X, const int32_t* assign, const float* 
  *   "assign_variant" v   tile shape v in 0..3 of the sweeping assign kernel
  *   "assign_stream"  0/1 few centroids: never / always (when they fit one LDS stage) take the
  *                        persistent streaming assign kernel
+ *   "assign_f32_filter" 0/1 fp32: never / always decide on the matrix cores first (see fk_assign)
  *   "sort_stage_bins" n  the counting sort's scatter orders its tile in LDS before writing
  *                        when a pass has 32..n bins (default 1024; 0 = never)
  *   "sort_min_rounds" r  sort workgroups own at least r sub-tiles of 4096 keys (the rule gives

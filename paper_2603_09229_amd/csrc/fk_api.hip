@@ -79,6 +79,12 @@ bool make_geometry(int B, int64_t N, int d_user, int K, fk_dtype t, Geometry* g)
     if (B > 65535) return false;                 // instances are the y dimension of every launch
     g->B = B; g->N = N; g->d = d; g->K = K; g->t = t;
     g->dchunks = d <= 32 ? 2 : (d <= 64 ? 4 : (d <= 128 ? 8 : (d <= 256 ? 16 : 32)));
+    if (t == FK_F32) {
+        // the filtered fp32 assignment is compiled for widths of every chunk up to 8, every second
+        // up to 16, every fourth up to 32
+        const int c = (d + 15) / 16;
+        g->dchunks = c <= 8 ? c : c <= 16 ? (c + 1) / 2 * 2 : (c + 3) / 4 * 4;
+    }
     g->ktiles = (int)cdiv(K, 32);
     int nbmax;
     if (K <= 2048) {
@@ -160,11 +166,15 @@ Workspace carve(const Geometry& g, void* base, bool padded_x) {
     (void)sort_end;
     // shape/dtype dependent part
     const size_t BKd = (size_t)g.B * g.K * g.d;
-    w.c_lp = take(BKd * elem_size(g.t));
     if (g.t != FK_F32) {
+        w.c_lp = take(BKd * elem_size(g.t));
         w.c_frag = take((size_t)g.B * g.ktiles * g.dchunks * 64 * 16);
-        w.c_bias = (float*)take((size_t)g.B * g.ktiles * 32 * 4);
+    } else {
+        w.c_frag = take((size_t)g.B * g.ktiles * (2 * g.dchunks + 1) * 64 * 16);
+        w.f32_shift = (float*)take((size_t)g.B * g.dchunks * 16 * 4);
+        w.f32_list_len = (int32_t*)take((size_t)g.B * 4);
     }
+    w.c_bias = (float*)take((size_t)g.B * g.ktiles * 32 * 4);
     const size_t fused_rows = (size_t)g.K * std::max({g.fused_grid_cap, g.table_grid_cap, g.f32_grid_cap});
     w.partial = (float*)take((size_t)g.B * std::max((size_t)g.max_items, fused_rows) * g.d * 4);
     if (fused_rows > 0) w.wg_counts = (int32_t*)take((size_t)g.B * fused_rows * 4);
@@ -438,6 +448,10 @@ int fk_set_option(const char* name, int value) {
         g_timer.repeat = value < 1 ? 1 : value;
         return FK_OK;
     }
+    if (name && strcmp(name, "assign_f32_filter") == 0 && value >= -1 && value <= 1) {
+        set_f32_filter_option(value);
+        return FK_OK;
+    }
     if (name && strcmp(name, "fused_update") == 0 && value >= -1 && value <= 1) {
         set_fused_update_option(value);
         return FK_OK;
@@ -457,8 +471,10 @@ int fk_plan(int B, int64_t N, int d, int K, fk_dtype t, char* buf, size_t buf_by
         return FK_EUNSUPPORTED;
     }
     char assign[96];
-    if (t == FK_F32)
-        snprintf(assign, sizeof(assign), "%s", g.d > 128 ? "f32_wide" : ((int64_t)B * N < (1 << 18) ? "f32_split" : "f32"));
+    if (f32_filter_enabled(g))
+        snprintf(assign, sizeof(assign), "f32_filter(chunks=%d)", g.dchunks);
+    else if (t == FK_F32)
+        snprintf(assign, sizeof(assign), "%s", g.d > 128 ? "f32_wide" : (f32_direct_is_split(g) ? "f32_split" : "f32"));
     else if (g.dchunks > 8)
         snprintf(assign, sizeof(assign), "mfma_wide(chunks=%d,points_per_wg=256)", g.dchunks);
     else if (assign_uses_stream_kernel(g))
@@ -531,7 +547,7 @@ fk_status fk_assign(const void* X, const void* C, int32_t* assign, float* min_di
         X = w.x_pad;
         C = w.c_pad_lp;
     }
-    if (t == FK_F32) return launch_assign(g, X, C, nullptr, assign, min_dist, s);
+    if (t == FK_F32) return launch_assign(g, X, C, nullptr, assign, min_dist, s, &w);
     FK_TRY(launch_prepare_centroids(g, C, w.c_frag, w.c_bias, s));
     return launch_assign(g, X, w.c_frag, w.c_bias, assign, min_dist, s);
 }
@@ -726,7 +742,7 @@ fk_status fk_lloyd_iter(const void* X, float* C_f32, void* C_lp, int32_t* assign
             const int rep = timer_repeat();
             for (int r = 0; r < rep; ++r) {
                 if (t == FK_F32)
-                    FK_TRY(launch_assign(g, X, C_f32, nullptr, assign, nullptr, s));
+                    FK_TRY(launch_assign(g, X, C_f32, nullptr, assign, nullptr, s, &w));
                 else
                     FK_TRY(launch_assign(g, X, w.c_frag, w.c_bias, assign, nullptr, s));
             }

@@ -935,11 +935,13 @@ static fk_status launch_mfma_d(const Geometry& g, const void* X, const void* fra
 }
 
 fk_status launch_assign(const Geometry& g, const void* X, const void* C_or_frag,
-                        const float* c_bias, int32_t* assign, float* min_dist, hipStream_t s) {
+                        const float* c_bias, int32_t* assign, float* min_dist, hipStream_t s,
+                        const Workspace* w) {
     if (g.t == FK_F16) return launch_mfma_d<false>(g, X, C_or_frag, c_bias, assign, min_dist, s);
     if (g.t == FK_BF16) return launch_mfma_d<true>(g, X, C_or_frag, c_bias, assign, min_dist, s);
     const float* Xf = (const float*)X;
     const float* Cf = (const float*)C_or_frag;
+    if (w && f32_filter_enabled(g)) return launch_f32_filter(g, *w, Xf, Cf, assign, min_dist, s);
     if (g.d > 128) {
         hipLaunchKernelGGL(assign_f32_wide_kernel, dim3((unsigned)cdiv(g.N, 256), g.B), dim3(256),
                            (size_t)16 * g.d * sizeof(float), s, Xf, Cf, assign, min_dist, g.N, g.d, g.K);
@@ -948,7 +950,7 @@ fk_status launch_assign(const Geometry& g, const void* X, const void* C_or_frag,
     }
     // small problems: split each centroid tile over the waves, so that even 16K points spread
     // over the chip
-    const bool small = (int64_t)g.B * g.N < ((int64_t)1 << 18);
+    const bool small = f32_direct_is_split(g);
     dim3 grid((unsigned)cdiv(g.N, small ? 64 : 256), g.B), block(256);
 #define FK_F32_LAUNCH(DM)                                                                         \
     do {                                                                                          \

@@ -95,8 +95,9 @@ struct Geometry {
 // Carved device workspace (all pointers 256-byte aligned inside the caller's buffer).
 struct Workspace {
     void* c_lp;          // [B,K,d] low-precision centroids consumed by assign (lloyd only)
-    void* c_frag;        // [B,ktiles,dchunks,64,8] fragment-ordered centroids (16-bit types)
-    float* c_bias;       // [B,ktiles*32] -||c||^2/2, -inf for padding rows
+    void* c_frag;        // [B,ktiles,dchunks,64,8] fragment-ordered centroids (16-bit types);
+                         // FK_F32: [B,ktiles,2*dchunks+1,64,8], see fk_f32_filter.hip
+    float* c_bias;       // [B,ktiles*32] -||c||^2/2, -inf for padding rows (FK_F32: squared norms)
     int32_t* sorted_idx; // [B,N]
     int32_t* seg_off;    // [B,K+1]
     int32_t* item_off;   // [B,K+1] exclusive scan of ceil(n_k / R)
@@ -108,6 +109,8 @@ struct Workspace {
     float* partial;      // [B,max(max_items, K*(largest one-pass grid cap)),d] per-item segment sums
     int32_t* wg_counts;  // [B,K,grid cap] per-workgroup counts (one-pass updates only)
     float* sums;         // [B,K,d] accumulated sums (chunked mode)
+    float* f32_shift;    // [B,dchunks*16] shift of the filtered fp32 assignment (fk_f32_filter.hip)
+    int32_t* f32_list_len; // [B] points it has left open (the points themselves: sorted_idx)
     void* x_pad;         // [B,N,d] zero-padded copy of X            (only when d != d_user)
     float* c_pad_f32;    // [B,K,d] zero-padded fp32 centroids       (only when d != d_user)
     void* c_pad_lp;      // [B,K,d] zero-padded centroids, dtype t   (only when d != d_user)
@@ -129,8 +132,18 @@ fk_status launch_prepare_centroids(const Geometry& g, const void* C_lp, void* c_
 fk_status launch_round_centroids(const Geometry& g, const float* C_f32, void* C_lp,
                                  void* c_frag, float* c_bias, hipStream_t s);
 // Fused distance + online argmin.  16-bit: reads c_frag/c_bias; fp32: reads C directly.
+// fp32 with a workspace may take the filtered form (fk_f32_filter.hip), which uses the centroid
+// buffers and sorted_idx of it; without one (nullptr) the direct kernels.
 fk_status launch_assign(const Geometry& g, const void* X, const void* C_or_frag,
-                        const float* c_bias, int32_t* assign, float* min_dist, hipStream_t s);
+                        const float* c_bias, int32_t* assign, float* min_dist, hipStream_t s,
+                        const Workspace* w = nullptr);
+// fp32: candidates from split bf16 products on the matrix cores, the open points by direct differences
+fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* X, const float* C,
+                            int32_t* assign, float* min_dist, hipStream_t s);
+bool f32_filter_enabled(const Geometry& g);
+// direct kernels, d <= 128: the four waves of a workgroup share a centroid tile (few points)
+inline bool f32_direct_is_split(const Geometry& g) { return g.d <= 128 && (int64_t)g.B * g.N < ((int64_t)1 << 18); }
+void set_f32_filter_option(int v);         // -1 = by shape, 0 = never, 1 = always
 // Tile shape the sweeping assign kernel would use for this problem (see fk_assign.hip).
 int choose_assign_variant(const Geometry& g);
 void set_assign_variant_override(int v);   // -1 = choose from the shape

@@ -189,7 +189,7 @@ fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_
             g.max_items = rows / g.rows_per_item + K;
             int32_t* a = assign ? assign + r0 : chunk_assign;
             if (t == FK_F32)
-                OOC_TRY(launch_assign(g, xbuf[bi], C_f32, nullptr, a, nullptr, cs));
+                OOC_TRY(launch_assign(g, xbuf[bi], C_f32, nullptr, a, nullptr, cs, &w));
             else
                 OOC_TRY(launch_assign(g, xbuf[bi], w.c_frag, w.c_bias, a, nullptr, cs));
             OOC_TRY(launch_sort_inverse(g, w, a, w.sorted_idx, w.seg_off, w.item_off, cs));

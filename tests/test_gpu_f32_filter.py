@@ -1,0 +1,75 @@
+"""fp32 assignment through the matrix-core filter (csrc/fk_f32_filter.hip): the same bits as the direct
+fp32 kernels, whatever the data -- the filter may only decide points whose answer no rounding can
+change, everything else is measured by the direct kernels' arithmetic."""
+import pytest
+import torch
+
+from paper_2603_09229_amd import binding as fk
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture
+def both():
+    """Assignments (and distances) of the filtered and of the direct kernels."""
+    def run(X, C):
+        res = []
+        for v in (1, 0):
+            fk.fk_set_option("assign_f32_filter", v)
+            assert ("f32_filter" in fk.fk_plan(X.shape[0], X.shape[1], X.shape[2], C.shape[1], X.dtype)) == (v == 1)
+            res.append(fk.fk_assign(X, C, min_dist=True))
+        return res
+    yield run
+    fk.fk_set_option("assign_f32_filter", -1)
+
+
+def _data(kind, B, N, d, K, seed):
+    g = torch.Generator().manual_seed(seed)
+    X = torch.randn((B, N, d), generator=g)
+    pick = torch.stack([torch.randint(0, N, (K,), generator=g) for _ in range(B)])
+    if kind == "mixture":
+        X += 4 * torch.randn((B, K, d), generator=g).gather(1, torch.randint(0, K, (B, N, 1), generator=g).expand(B, N, d))
+    elif kind == "far":             # a common offset far larger than the spread
+        X += 1000.0
+    elif kind == "whole":           # exact ties: small whole numbers
+        X = torch.randint(-2, 3, (B, N, d), generator=g).float()
+    elif kind == "large":           # squares near and beyond the end of the range
+        X *= 3e18
+    elif kind == "small":           # squares that vanish
+        X *= 1e-21
+    C = torch.stack([X[b, pick[b]] for b in range(B)])
+    if kind == "twins":             # every centroid twice
+        C = torch.cat([C[:, : (K + 1) // 2]] * 2, 1)[:, :K]
+    elif kind == "outlier":         # one centroid far away, the first
+        C[:, 0] = 1e6
+    return X.to(DEV), C.contiguous().to(DEV)
+
+
+@pytest.mark.parametrize("kind", ["gauss", "mixture", "far", "whole", "large", "small", "twins", "outlier"])
+@pytest.mark.parametrize("B,N,d,K", [(1, 3001, 64, 100), (2, 517, 8, 33), (1, 1000, 96, 257), (1, 4100, 128, 64),
+                                     (1, 700, 256, 97), (1, 300, 512, 70), (3, 130, 32, 1), (1, 333, 392, 31)])
+def test_filter_gives_the_direct_answer(both, kind, B, N, d, K):
+    X, C = _data(kind, B, N, d, K, seed=N + d + K)
+    (a1, m1), (a0, m0) = both(X, C)
+    assert torch.equal(a1, a0)
+    # the distances are sums of d squares in two orders: d 2^-23 apart at most
+    fine = torch.isfinite(m0)
+    assert torch.equal(fine, torch.isfinite(m1))
+    assert ((m1 - m0).abs()[fine] <= d * 2.0 ** -23 * m0[fine] + 1e-37).all()
+
+
+def test_filtered_iterations_equal_direct_ones():
+    g = torch.Generator().manual_seed(5)
+    X = (torch.randn((2, 20011, 100), generator=g) + 3 * torch.randn((2, 1, 100), generator=g)).to(DEV)
+    res = []
+    try:
+        for v in (1, 0):
+            fk.fk_set_option("assign_f32_filter", v)
+            C = X[:, :150].clone()
+            a, n, _ = fk.fk_lloyd_iter(X, C, 3)
+            res.append((a, n, C))
+    finally:
+        fk.fk_set_option("assign_f32_filter", -1)
+    for u, v in zip(*res):
+        assert torch.equal(u, v)
