@@ -221,6 +221,9 @@ fk_status fk_standard_update(const void* X, const int32_t* assign, const float* 
  *   "assign_variant" v   tile shape v in 0..3 of the sweeping assign kernel
  *   "assign_stream"  0/1 few centroids: never / always (when they fit one LDS stage) take the
  *                        persistent streaming assign kernel
+ *   "assign_few"     0..4 fp16 / bf16: never / always one form of the few-point assign kernel (1
+ *                        centroids as the caller has them, 2 in fragment order with 32 points per
+ *                        workgroup, 3 and 4 with 64 and 8 or 16 waves)
  *   "assign_f32_filter" 0/1 fp32: never / always decide on the matrix cores first (see fk_assign)
  *   "sort_stage_bins" n  the counting sort's scatter orders its tile in LDS before writing
  *                        when a pass has 32..n bins (default 1024; 0 = never)

@@ -448,6 +448,10 @@ int fk_set_option(const char* name, int value) {
         g_timer.repeat = value < 1 ? 1 : value;
         return FK_OK;
     }
+    if (name && strcmp(name, "assign_few") == 0 && value >= -1 && value <= 4) {
+        set_assign_few_option(value);
+        return FK_OK;
+    }
     if (name && strcmp(name, "assign_f32_filter") == 0 && value >= -1 && value <= 1) {
         set_f32_filter_option(value);
         return FK_OK;
@@ -475,6 +479,8 @@ int fk_plan(int B, int64_t N, int d, int K, fk_dtype t, char* buf, size_t buf_by
         snprintf(assign, sizeof(assign), "f32_filter(chunks=%d)", g.dchunks);
     else if (t == FK_F32)
         snprintf(assign, sizeof(assign), "%s", g.d > 128 ? "f32_wide" : (f32_direct_is_split(g) ? "f32_split" : "f32"));
+    else if (assign_uses_few_kernel(g))
+        snprintf(assign, sizeof(assign), "mfma_few(%s)", assign_few_takes_rows(g) ? "rows" : "fragments");
     else if (g.dchunks > 8)
         snprintf(assign, sizeof(assign), "mfma_wide(chunks=%d,points_per_wg=256)", g.dchunks);
     else if (assign_uses_stream_kernel(g))
@@ -548,6 +554,7 @@ fk_status fk_assign(const void* X, const void* C, int32_t* assign, float* min_di
         C = w.c_pad_lp;
     }
     if (t == FK_F32) return launch_assign(g, X, C, nullptr, assign, min_dist, s, &w);
+    if (assign_few_takes_rows(g)) return launch_assign_rows(g, X, C, assign, min_dist, s);
     FK_TRY(launch_prepare_centroids(g, C, w.c_frag, w.c_bias, s));
     return launch_assign(g, X, w.c_frag, w.c_bias, assign, min_dist, s);
 }
@@ -580,6 +587,7 @@ fk_status fk_assign_static(const void* X, const void* C, int32_t* assign, float*
     FK_OPTIONAL_PTR(fn, min_dist);
     hipStream_t s = (hipStream_t)stream;
     if (t == FK_F32) return launch_assign(g, X, C, nullptr, assign, min_dist, s);   // no scratch at all
+    // (the size limit holds for every shape, whether or not its kernel needs the scratch)
     const size_t frag_bytes = (size_t)B * g.ktiles * g.dchunks * 64 * 16;
     const size_t bias_bytes = (size_t)B * g.ktiles * 32 * 4;
     if (frag_bytes > kStaticFragBytes || bias_bytes > kStaticBiasBytes) {
@@ -587,6 +595,7 @@ fk_status fk_assign_static(const void* X, const void* C, int32_t* assign, float*
                   fn, g.dchunks, frag_bytes, kStaticFragBytes);
         return FK_EWORKSPACE;
     }
+    if (assign_few_takes_rows(g)) return launch_assign_rows(g, X, C, assign, min_dist, s);
     unsigned char* base = nullptr;
     FK_TRY(static_scratch(&base));
     void* c_frag = base;

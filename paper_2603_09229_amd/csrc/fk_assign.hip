@@ -607,6 +607,182 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_stream_kernel(
 }
 
 // ------------------------------------------------------------------------------------
+// Few points: the sweeping kernels give a workgroup 128 points or more and let it walk through all
+// centroid tiles one after the other, so a request of a thousand vectors keeps eight compute
+// units busy for 20 us.  Here a workgroup has 32 points and its waves share out the centroid tiles
+// (every workgroup reads all of C once, from L2); there is no barrier between the one that the
+// points arrive at and the end, where the waves' candidates meet in LDS.  Same scores, packing and
+// tie rules as the sweeping kernels: within a wave the earlier tile wins, between waves and halves
+// the lower index.
+//   FRAG: centroids in fragment order with their bias, as the layout kernel or an iteration's
+// update leave them; the A operands come straight from memory.  Otherwise C as the caller has it,
+// [K][d], which saves the layout launch: a tile is one contiguous piece of memory, copied in whole
+// lines to the wave's own part of LDS (pieces XOR-swizzled by row) and read back as A operands, and
+// the bias is computed here with the layout kernel's association.
+template <bool BF, int DCH, int WAVES, bool FRAG, int P>
+__global__ __launch_bounds__(WAVES * 64) void assign_mfma_few_kernel(
+    const uint16_t* __restrict__ X, const void* __restrict__ Cv, const float* __restrict__ c_bias,
+    int32_t* __restrict__ assign, float* __restrict__ min_dist, int64_t N, int d, int K, int ktiles) {
+    __shared__ __align__(16) float sbias[FRAG ? 1 : WAVES][32];
+    __shared__ float cand_m[WAVES][P * 32];
+    __shared__ int cand_k[WAVES][P * 32];
+    extern __shared__ uintx4 dyn_lds[];                      // the points, then (rows) a tile per wave
+    const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = lane & 31, h = lane >> 5;
+    X += (size_t)b * N * d;
+    assign += (size_t)b * N;
+    if (min_dist) min_dist += (size_t)b * N;
+    const uintx4* frag = (const uintx4*)Cv + (size_t)b * ktiles * DCH * 64;
+    const uint16_t* C = (const uint16_t*)Cv + (size_t)b * K * d;
+    c_bias += (size_t)b * ktiles * 32;
+    const int64_t point0 = (int64_t)blockIdx.x * (P * 32);
+    const int ppr = d >> 3;                                  // 16-byte pieces per row
+    const int swz = (ppr & (ppr - 1)) == 0 ? min(ppr, 8) - 1 : 0;
+    const int loads = (32 * ppr + 63) >> 6;                  // copies of 1 KiB per 32 rows
+    uintx4* own = dyn_lds + (size_t)(P + wave) * DCH * 64;
+
+    // slot j holds piece (j % ppr) ^ (row & swz) of row j / ppr; rows past the end repeat the last
+    auto copy_rows = [&](const uint16_t* src, int64_t row0, int64_t rows, uintx4* to, int q) {
+        const int j = q * 64 + lane;
+        int row = j / ppr;
+        const int piece = (j - row * ppr) ^ (row & swz);
+        row = min(row, 31);
+        copy16_to_lds((const uintx4*)(src + (size_t)min(row0 + row, rows - 1) * d + piece * 8), to + q * 64);
+    };
+    auto row_piece = [&](const uintx4* at, int s) {          // features [16 s + 8 h, + 8) of row n
+        const int piece = 2 * s + h;
+        return piece < ppr ? at[n * ppr + (piece ^ (n & swz))] : uintx4{0u, 0u, 0u, 0u};
+    };
+#pragma unroll
+    for (int pt = 0; pt < P; ++pt)
+        for (int q = wave; q < loads; q += WAVES) copy_rows(X, point0 + pt * 32, N, dyn_lds + pt * DCH * 64, q);
+    if (!FRAG && wave < ktiles)
+        for (int q = 0; q < loads; ++q) copy_rows(C, (int64_t)wave * 32, K, own, q);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    uintx4 xf[P][DCH];
+    float best[P];
+    int btile[P];
+#pragma unroll
+    for (int pt = 0; pt < P; ++pt) {
+        best[pt] = -INFINITY;
+        btile[pt] = 0;
+#pragma unroll
+        for (int s = 0; s < DCH; ++s) xf[pt][s] = row_piece(dyn_lds + pt * DCH * 64, s);
+    }
+    for (int tile = wave; tile < ktiles; tile += WAVES) {
+        floatx16 bias16;
+        uintx4 a[DCH];
+        if constexpr (FRAG) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const floatx4 bv = *(const floatx4*)(c_bias + tile * 32 + 8 * q + 4 * h);
+                bias16[4 * q + 0] = bv[0]; bias16[4 * q + 1] = bv[1]; bias16[4 * q + 2] = bv[2]; bias16[4 * q + 3] = bv[3];
+            }
+#pragma unroll
+            for (int s = 0; s < DCH; ++s) a[s] = frag[((size_t)tile * DCH + s) * 64 + lane];
+        } else {
+            const int k = tile * 32 + n;
+#pragma unroll
+            for (int s = 0; s < DCH; ++s) a[s] = row_piece(own, s);
+            // the tile is in registers: its place takes the next one
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (tile + WAVES < ktiles)
+                for (int q = 0; q < loads; ++q) copy_rows(C, (int64_t)(tile + WAVES) * 32, K, own, q);
+            float n2 = 0.f;
+#pragma unroll
+            for (int s = 0; s < DCH; ++s) {
+                float ss = 0.f;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float lo = lp_to_float((uint16_t)(a[s][q] & 0xFFFFu), BF), hi = lp_to_float((uint16_t)(a[s][q] >> 16), BF);
+                    ss = __fadd_rn(ss, __fmul_rn(lo, lo));
+                    ss = __fadd_rn(ss, __fmul_rn(hi, hi));
+                }
+                const float other = __shfl_xor(ss, 32);
+                n2 = __fadd_rn(n2, h ? other : ss);          // groups of eight features in order
+                n2 = __fadd_rn(n2, h ? ss : other);
+            }
+            if (h == 0) sbias[wave][n] = k < K ? -0.5f * n2 : kPadBias;
+            __builtin_amdgcn_wave_barrier();                 // LDS runs a wave's operations in order
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const floatx4 bv = *(const floatx4*)&sbias[wave][8 * q + 4 * h];
+                bias16[4 * q + 0] = bv[0]; bias16[4 * q + 1] = bv[1]; bias16[4 * q + 2] = bv[2]; bias16[4 * q + 3] = bv[3];
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+        floatx16 acc[P];
+#pragma unroll
+        for (int pt = 0; pt < P; ++pt) acc[pt] = bias16;
+#pragma unroll
+        for (int s = 0; s < DCH; ++s)
+#pragma unroll
+            for (int pt = 0; pt < P; ++pt) acc[pt] = mfma32<BF>(a[s], xf[pt][s], acc[pt]);
+#pragma unroll
+        for (int pt = 0; pt < P; ++pt) {
+            const uint32_t bb = __float_as_uint(best[pt]);
+            const uint32_t fill = ~(uint32_t)((int32_t)bb >> 31) & 15u;
+            const float guard = __uint_as_float((bb & 0xFFFFFFF0u) | fill);
+            float m = guard;
+#pragma unroll
+            for (int i = 0; i < 16; i += 2) {
+                const float k0 = __uint_as_float((__float_as_uint(acc[pt][i]) & 0xFFFFFFF0u) | (uint32_t)(15 - i));
+                const float k1 = __uint_as_float((__float_as_uint(acc[pt][i + 1]) & 0xFFFFFFF0u) | (uint32_t)(14 - i));
+                m = __builtin_fmaxf(__builtin_fmaxf(m, k0), k1);
+            }
+            const bool improved = m != guard;
+            best[pt] = improved ? m : best[pt];
+            btile[pt] = improved ? tile : btile[pt];
+        }
+        if (!FRAG) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+#pragma unroll
+    for (int pt = 0; pt < P; ++pt) {
+        const uint32_t bits = __float_as_uint(best[pt]);
+        const int i = 15 - (int)(bits & 15u);
+        int k = btile[pt] * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
+        float m = __uint_as_float(bits & 0xFFFFFFF0u);       // a wave without a tile: still below every score
+        const float om = __shfl_xor(m, 32);
+        const int ok = __shfl_xor(k, 32);
+        if (om > m || (om == m && ok < k)) { m = om; k = ok; }
+        if (h == 0) { cand_m[wave][pt * 32 + n] = m; cand_k[wave][pt * 32 + n] = k; }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int pt = 0; pt < P; ++pt) {
+        if (wave != pt) continue;                            // wave pt finishes point tile pt
+        const int64_t point = point0 + pt * 32 + n;
+        float m = cand_m[0][pt * 32 + n];
+        int k = cand_k[0][pt * 32 + n];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) {
+            const float wm = cand_m[w][pt * 32 + n];
+            const int wk = cand_k[w][pt * 32 + n];
+            if (wm > m || (wm == m && wk < k)) { m = wm; k = wk; }
+        }
+        k = min(k, K - 1);
+        float xn = 0.f;
+        if (min_dist) {
+#pragma unroll
+            for (int s = 0; s < DCH; ++s) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float lo = lp_to_float((uint16_t)(xf[pt][s][q] & 0xFFFFu), BF);
+                    const float hi = lp_to_float((uint16_t)(xf[pt][s][q] >> 16), BF);
+                    xn += lo * lo + hi * hi;
+                }
+            }
+            xn += __shfl_xor(xn, 32);
+        }
+        if (h == 0 && point < N) {
+            assign[point] = k;
+            if (min_dist) min_dist[point] = fmaxf(0.f, xn - 2.f * m);
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------
 // fp32: one point per thread, features in registers, centroid tiles of TK rows in LDS,
 // D_ik by direct differences in fp32; ascending k with strict '<'.
 template <int DMAX, int TK, int THREADS>
@@ -865,11 +1041,105 @@ bool assign_uses_stream_kernel(const Geometry& g) {
     return g.ktiles <= limit;
 }
 
+// Few points: which form of the few-point kernel, if any.  With t tiles of 32 points, U compute
+// units and c centroid tiles (all times per fk_assign call, layout launch included, against the
+// sweeping kernel):
+//   t <= U, rows: any few centroids (1000 points, d = 128: K = 256 5.4 against 9.0 us, K = 1024 10.1
+//     against 22.0; d = 512, K = 64: 8.6 against 14.5).  Where a wave would walk through several
+//     tiles of rows the copies in fragment order are read faster (d = 256, K = 1024: 15.8 against
+//     17.7; d = 512, K = 256: 12.2 against 18.2).
+//   more: 64 points per workgroup, so that each A operand serves two products, while there are
+//     centroids enough for the waves (16384 points, d = 128: K = 256 7.4 against 9.7, K = 4096 24.7
+//     against 74; 32768: K = 1024 14.1 against 22.9, but d = 32, K = 256: 6.6 against 5.7).
+//   t >= 8 U the sweeping kernel's workgroups fill the chip (65536 points, d = 128, K = 1024: 25.5
+//     against 23.7; d = 256: 46 against 49).
+enum FewForm { kFewNone = 0, kFewRows = 1, kFewOne = 2, kFewTwo8 = 3, kFewTwo16 = 4 };
+static std::atomic<int> g_few_option{-1};      // -1: by shape, 0: never, 1..4: that form where it exists
+
+void set_assign_few_option(int v) { g_few_option.store(v, std::memory_order_relaxed); }
+
+static FewForm choose_few(const Geometry& g, bool have_rows) {
+    const int opt = g_few_option.load(std::memory_order_relaxed);
+    if (g.t == FK_F32 || opt == 0) return kFewNone;
+    if (opt > 0) {
+        if (opt == kFewRows && have_rows) return kFewRows;
+        return opt == kFewRows || g.dchunks > 16 ? kFewOne : (FewForm)opt;
+    }
+    // a choice forced between the other kernels is meant
+    if (g_variant_override.load(std::memory_order_relaxed) >= 0 || g_stream_option.load(std::memory_order_relaxed) >= 0)
+        return kFewNone;
+    const int64_t t = cdiv(g.N, 32) * g.B, U = device_cu_count();
+    const int dch = g.dchunks, c = g.ktiles;
+    if (t <= U) {
+        if (have_rows && c <= (dch <= 8 ? 32 : dch <= 16 ? 16 : 4)) return kFewRows;
+        if (dch <= 8 && c <= 8) return kFewNone;
+        return dch == 8 && c > 32 ? kFewTwo16 : kFewOne;
+    }
+    if (t <= 2 * U) {
+        if (dch > 16) return c >= 8 ? kFewOne : kFewNone;
+        if (dch == 16) return c >= 32 ? kFewTwo8 : c >= 2 ? kFewOne : kFewNone;
+        if (c < (dch == 2 ? 16 : 8)) return kFewNone;
+        return c >= 32 ? kFewTwo16 : kFewTwo8;
+    }
+    if (t <= 4 * U) return dch <= 16 && c >= (dch <= 4 ? 16 : 8) ? kFewTwo8 : kFewNone;
+    if (t < 8 * U) return dch <= 8 && c >= 32 ? kFewTwo8 : kFewNone;
+    return kFewNone;
+}
+
+bool assign_uses_few_kernel(const Geometry& g) { return choose_few(g, true) != kFewNone; }
+bool assign_few_takes_rows(const Geometry& g) { return choose_few(g, true) == kFewRows; }
+
+template <bool BF, int DCH, int WAVES, bool FRAG, int P>
+static fk_status launch_few_w(const Geometry& g, const void* X, const void* C, const float* bias,
+                              int32_t* assign, float* min_dist, hipStream_t s) {
+    auto kern = assign_mfma_few_kernel<BF, DCH, WAVES, FRAG, P>;
+    const size_t lds = (size_t)(FRAG ? P : P + WAVES) * DCH * 1024;
+    if (lds > 48 * 1024) {
+        static PerDeviceInt attr_set;
+        if (!attr_set.get()) {
+            FK_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            attr_set.set(1);
+        }
+    }
+    dim3 grid((unsigned)cdiv(g.N, 32 * P), g.B), block(WAVES * 64);
+    hipLaunchKernelGGL(kern, grid, block, lds, s, (const uint16_t*)X, C, bias, assign, min_dist, g.N, g.d, g.K, g.ktiles);
+    FK_HIP(hipGetLastError());
+    return FK_OK;
+}
+
+template <bool BF, int DCH>
+static fk_status launch_few(const Geometry& g, FewForm form, const void* X, const void* C, const float* bias,
+                            int32_t* assign, float* min_dist, hipStream_t s) {
+    // as many waves as 160 KiB of LDS hold a tile of rows each for; 8 where registers are the limit
+    constexpr int kRowsWaves = DCH <= 8 ? 16 : DCH <= 16 ? 8 : 3, kWaves = DCH <= 8 ? 16 : 8;
+    if (form == kFewRows) return launch_few_w<BF, DCH, kRowsWaves, false, 1>(g, X, C, nullptr, assign, min_dist, s);
+    if constexpr (DCH <= 16) {
+        if (form == kFewTwo8) return launch_few_w<BF, DCH, 8, true, 2>(g, X, C, bias, assign, min_dist, s);
+        if (form == kFewTwo16) return launch_few_w<BF, DCH, kWaves, true, 2>(g, X, C, bias, assign, min_dist, s);
+    }
+    return launch_few_w<BF, DCH, kWaves, true, 1>(g, X, C, bias, assign, min_dist, s);
+}
+
+fk_status launch_assign_rows(const Geometry& g, const void* X, const void* C, int32_t* assign,
+                             float* min_dist, hipStream_t s) {
+    const bool bf = g.t == FK_BF16;
+#define FK_FEW(DCH)                                                                              \
+    case DCH:                                                                                    \
+        return bf ? launch_few<true, DCH>(g, kFewRows, X, C, nullptr, assign, min_dist, s)       \
+                  : launch_few<false, DCH>(g, kFewRows, X, C, nullptr, assign, min_dist, s)
+    switch (g.dchunks) { FK_FEW(2); FK_FEW(4); FK_FEW(8); FK_FEW(16); FK_FEW(32); }
+#undef FK_FEW
+    set_error("assign: no kernel for %d feature chunks", g.dchunks);
+    return FK_EUNSUPPORTED;
+}
+
 template <bool BF, int DCH>
 static fk_status launch_mfma(const Geometry& g, const void* X, const void* frag,
                              const float* bias, int32_t* assign, float* min_dist,
                              hipStream_t s) {
     constexpr int ST = (16 / DCH) < 8 ? (16 / DCH) : 8;
+    if (const FewForm few = choose_few(g, false); few != kFewNone)
+        return launch_few<BF, DCH>(g, few, X, frag, bias, assign, min_dist, s);
     if (g.ktiles <= ST && assign_uses_stream_kernel(g)) {
         // persistent waves: as many workgroups as fit the chip, each wave striding over
         // 32-point batches
@@ -910,6 +1180,8 @@ template <bool BF, int DCH>
 static fk_status launch_mfma_wide(const Geometry& g, const void* X, const void* frag,
                                   const float* bias, int32_t* assign, float* min_dist,
                                   hipStream_t s) {
+    if (const FewForm few = choose_few(g, false); few != kFewNone)
+        return launch_few<BF, DCH>(g, few, X, frag, bias, assign, min_dist, s);
     constexpr int WAVES = 8;
     dim3 grid((unsigned)cdiv(g.N, WAVES * 32), g.B), block(WAVES * 64);
     hipLaunchKernelGGL((assign_mfma_wide_kernel<BF, DCH, WAVES>), grid, block, 0, s,

@@ -150,6 +150,13 @@ void set_assign_variant_override(int v);   // -1 = choose from the shape
 // Few centroids: persistent streaming kernel instead of the sweeping one (see fk_assign.hip).
 bool assign_uses_stream_kernel(const Geometry& g);
 void set_assign_stream_option(int v);      // -1 = by shape, 0 = never, 1 = whenever eligible
+// Few points: the waves of a workgroup share the centroid tiles of 32 or 64 points (see fk_assign.hip).
+bool assign_uses_few_kernel(const Geometry& g);
+void set_assign_few_option(int v);         // -1 = by shape, 0 = never, 1..4 = one of its forms
+// ... straight from C [B,K,d] of dtype t, without launch_prepare_centroids
+bool assign_few_takes_rows(const Geometry& g);
+fk_status launch_assign_rows(const Geometry& g, const void* X, const void* C, int32_t* assign,
+                             float* min_dist, hipStream_t s);
 // Stable argsort by cluster id -> sorted_idx, seg_off (+ item_off when w.item_off != NULL).
 fk_status launch_sort_inverse(const Geometry& g, const Workspace& w, const int32_t* assign,
                               int32_t* sorted_idx, int32_t* seg_off, int32_t* item_off,
