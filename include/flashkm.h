@@ -34,11 +34,12 @@
  *     enqueue kernels only (no memset, no allocation), so after one eager call for a shape
  *     they can be recorded into a HIP graph by stream capture and replayed.
  *   - Supported shapes: 1 <= K <= 65536, 1 <= N, B*N < 2^31, 1 <= B <= 65535, 1 <= d <= 512.
- *     The kernels work on rows whose width is a multiple of 8; for any other d the in-core
- *     entry points first copy X and C into zero-padded rows inside the workspace (zeros change
- *     no distance and no mean; costs one extra pass over X per call and room for the copy,
- *     which fk_workspace_bytes includes) and copy the centroids back without the padding;
- *     fk_lloyd_ooc lands the host rows in padded chunk buffers with a pitched copy instead.
+ *     Rows are read and written as they are stored, whatever their width.  Two kinds of shape
+ *     whose d is not a multiple of 8 are first copied into zero-padded rows inside the workspace
+ *     (zeros change no distance and no mean; one extra pass over X per call and room for the copy,
+ *     which fk_workspace_bytes includes): d < 8, and fk_update / fk_lloyd_iter with the one-pass
+ *     update for few clusters (see below).  fk_lloyd_ooc lands rows of d < 8 in padded chunk
+ *     buffers with a pitched copy, all others as they are.
  *     The fk_standard_* comparators need d to be a multiple of 8.  Anything else returns
  *     FK_EUNSUPPORTED or FK_EINVAL; there is no fallback path.
  *   - Calls act on the device that is current in the calling thread.  Kernel attributes,

@@ -74,6 +74,7 @@ bool make_geometry(int B, int64_t N, int d_user, int K, fk_dtype t, Geometry* g)
     if (B < 1 || N < 1 || K < 1 || K > 65536 || d_user < 1 || d_user > 512) return false;
     const int d = (d_user + 7) / 8 * 8;
     g->d_user = d_user;
+    g->len = d;
     if (t != FK_F32 && t != FK_F16 && t != FK_BF16) return false;
     if ((int64_t)B * N >= ((int64_t)1 << 31)) return false;
     if (B > 65535) return false;                 // instances are the y dimension of every launch
@@ -180,7 +181,7 @@ Workspace carve(const Geometry& g, void* base, bool padded_x) {
     if (fused_rows > 0) w.wg_counts = (int32_t*)take((size_t)g.B * fused_rows * 4);
     w.sums = (float*)take(BKd * 4);
     if (g.d != g.d_user) {
-        if (padded_x) w.x_pad = take(BN * g.d * elem_size(g.t));
+        if (padded_x && needs_padded_rows(g)) w.x_pad = take(BN * g.d * elem_size(g.t));
         w.c_pad_f32 = (float*)take(BKd * 4);
         w.c_pad_lp = take(BKd * elem_size(g.t));
     }
@@ -336,6 +337,12 @@ static fk_status run_stream_update(const Geometry& g, const Workspace& w, const 
     FK_TRY(launch_finalize(gm, w, nullptr, nullptr, fa, s, w.wg_counts, G));
     timer_mark(s, kStageFinalize);
     return FK_OK;
+}
+
+// Whether fk_update / fk_lloyd_iter copy the rows into zero-padded ones for this call (see
+// needs_padded_rows; the one-pass update for few clusters may be switched off).
+static bool rows_are_padded(const Geometry& g) {
+    return g.d != g.d_user && (g.d_user < 8 || fused_update_enabled(g));
 }
 
 // update = sort-inverse + segment reduce + merge/normalise, all into the carved workspace
@@ -546,8 +553,10 @@ fk_status fk_assign(const void* X, const void* C, int32_t* assign, float* min_di
     FK_OPTIONAL_PTR("fk_assign", min_dist);
     hipStream_t s = (hipStream_t)stream;
     const Workspace w = carve(g, ws);
-    if (g.d != g.d_user) {
-        // rows that are not a multiple of 8 wide: work on zero-padded copies
+    if (g.d_user >= 8) {
+        g.len = g.d_user;                      // the kernels read the caller's rows
+    } else {
+        // rows of fewer than 8 elements: work on zero-padded copies
         FK_TRY(launch_copy_rows(X, w.x_pad, (int64_t)B * N, g.d_user, g.d, (int)elem_size(t), s));
         FK_TRY(launch_copy_rows(C, w.c_pad_lp, (int64_t)B * K, g.d_user, g.d, (int)elem_size(t), s));
         X = w.x_pad;
@@ -646,8 +655,10 @@ fk_status fk_update(const void* X, const int32_t* assign, const float* C_prev_f3
     FK_REQUIRE_PTR("fk_update", counts);
     const Workspace w = carve(g, ws);
     hipStream_t s = (hipStream_t)stream;
-    const bool pad = g.d != g.d_user;
-    if (pad) {
+    const bool pad = rows_are_padded(g);
+    if (!pad) {
+        g.len = g.d_user;                      // the kernels read the caller's rows
+    } else {
         FK_TRY(launch_copy_rows(X, w.x_pad, (int64_t)B * N, g.d_user, g.d, (int)elem_size(t), s));
         FK_TRY(launch_copy_rows(C_prev_f32, w.c_pad_f32, (int64_t)B * K, g.d_user, g.d, 4, s));
         X = w.x_pad;
@@ -728,12 +739,14 @@ fk_status fk_lloyd_iter(const void* X, float* C_f32, void* C_lp, int32_t* assign
     if (iters == 0) return FK_OK;
     hipStream_t s = (hipStream_t)stream;
     const Workspace w = carve(g, ws);
-    const bool pad = g.d != g.d_user;
+    const bool pad = rows_are_padded(g);
     float* const C_user = C_f32;
     void* const C_lp_user = C_lp;
-    if (pad) {
-        // rows that are not a multiple of 8 wide: iterate on zero-padded copies of X and C,
-        // copy the centroids back without the padding at the end
+    if (!pad) {
+        g.len = g.d_user;                      // the kernels read and write the caller's rows
+    } else {
+        // iterate on zero-padded copies of X and C, copy the centroids back without the padding
+        // at the end
         FK_TRY(launch_copy_rows(X, w.x_pad, (int64_t)B * N, g.d_user, g.d, (int)elem_size(t), s));
         FK_TRY(launch_copy_rows(C_f32, w.c_pad_f32, (int64_t)B * K, g.d_user, g.d, 4, s));
         X = w.x_pad;

@@ -31,7 +31,7 @@ namespace fk {
 template <bool SRC_F32>
 __global__ __launch_bounds__(512) void centroid_layout_kernel(
     const void* __restrict__ src, uint16_t* __restrict__ C_lp, uint16_t* __restrict__ c_frag,
-    float* __restrict__ c_bias, int d, int K, int ktiles, int dch, int bf) {
+    float* __restrict__ c_bias, int d, int len, int K, int ktiles, int dch, int bf) {
     __shared__ float part[32][65];
     const int b = blockIdx.y, kt = blockIdx.x;
     for (int g = threadIdx.x; g < 64 * dch; g += blockDim.x) {
@@ -43,19 +43,23 @@ __global__ __launch_bounds__(512) void centroid_layout_kernel(
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = 0;
         if (live) {
-            const size_t o = ((size_t)b * K + k) * d + j0;
+            const size_t o = ((size_t)b * K + k) * len;
             if (SRC_F32) {
-                const float* p = (const float*)src + o;
+                const floatx4 lo = row_piece32((const float*)src + o, j0, len), hi = row_piece32((const float*)src + o, j0 + 4, len);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = float_to_lp(p[e], bf);
+                for (int e = 0; e < 4; ++e) {
+                    v[e] = float_to_lp(lo[e], bf);
+                    v[e + 4] = float_to_lp(hi[e], bf);
+                }
                 if (C_lp) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) C_lp[o + e] = v[e];
+                    for (int e = 0; e < 8; ++e)
+                        if (j0 + e < len) C_lp[o + j0 + e] = v[e];
                 }
             } else {
-                const uint16_t* p = (const uint16_t*)src + o;
+                const uintx4 p = row_piece16((const uint16_t*)src + o, j0, len);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = p[e];
+                for (int e = 0; e < 8; ++e) v[e] = (uint16_t)(p[e >> 1] >> (16 * (e & 1)));
             }
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -82,35 +86,45 @@ fk_status launch_prepare_centroids(const Geometry& g, const void* C_lp, void* c_
                                    float* c_bias, hipStream_t s) {
     dim3 grid(g.ktiles, g.B), block(std::min(512, 64 * g.dchunks));
     hipLaunchKernelGGL(centroid_layout_kernel<false>, grid, block, 0, s, C_lp, (uint16_t*)nullptr,
-                       (uint16_t*)c_frag, c_bias, g.d, g.K, g.ktiles, g.dchunks,
+                       (uint16_t*)c_frag, c_bias, g.d, g.len, g.K, g.ktiles, g.dchunks,
                        g.t == FK_BF16 ? 1 : 0);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }
 
 // dst[r][j] = j < d_src ? src[r][j] : 0 for j < d_dst: pads rows with zeros (d_dst > d_src) or
-// drops the padding again (d_dst < d_src)
-template <typename T>
-__global__ void copy_rows_kernel(const T* __restrict__ src, T* __restrict__ dst, size_t total,
-                                 int d_src, int d_dst) {
-    for (size_t o = (size_t)blockIdx.x * blockDim.x + threadIdx.x; o < total;
-         o += (size_t)gridDim.x * blockDim.x) {
-        const size_t r = o / (size_t)d_dst;
-        const int j = (int)(o - r * (size_t)d_dst);
-        dst[o] = j < d_src ? src[r * (size_t)d_src + j] : T(0);
+// drops the padding again (d_dst < d_src).  VEC elements per thread: padding rows of 8 elements or
+// more to a multiple of 8 is bound by memory and takes 16 bytes at a time; what is left is small.
+template <typename T, int VEC>
+__global__ __launch_bounds__(256) void copy_rows_kernel(const T* __restrict__ src, T* __restrict__ dst,
+                                                        int64_t rows, int d_src, int d_dst) {
+    const int per_row = d_dst / VEC;
+    const int64_t total = rows * per_row;
+    for (int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x; o < total; o += (int64_t)gridDim.x * 256) {
+        const int64_t r = total < ((int64_t)1 << 32) ? (int64_t)((uint32_t)o / (uint32_t)per_row) : o / per_row;
+        const int j = (int)(o - r * per_row) * VEC;
+        if constexpr (VEC == 8)
+            *(uintx4*)(dst + r * d_dst + j) = row_piece16((const uint16_t*)src + r * d_src, j, d_src);
+        else if constexpr (VEC == 4)
+            *(floatx4*)(dst + r * d_dst + j) = row_piece32((const float*)src + r * d_src, j, d_src);
+        else
+            dst[r * d_dst + j] = j < d_src ? src[r * d_src + j] : T(0);
     }
 }
 
 fk_status launch_copy_rows(const void* src, void* dst, int64_t rows, int d_src, int d_dst,
                            int elem, hipStream_t s) {
-    const size_t total = (size_t)rows * d_dst;
-    const unsigned blocks = (unsigned)std::min<size_t>(cdiv((int64_t)total, 256), (size_t)1 << 20);
-    if (elem == 2)
-        hipLaunchKernelGGL(copy_rows_kernel<uint16_t>, dim3(blocks), dim3(256), 0, s,
-                           (const uint16_t*)src, (uint16_t*)dst, total, d_src, d_dst);
+    const bool whole = d_src >= 8 && d_dst > d_src && d_dst % 8 == 0;
+    const int64_t total = rows * (whole ? d_dst * elem / 16 : d_dst);
+    const dim3 grid((unsigned)std::min<int64_t>(cdiv(total, 256), (int64_t)1 << 20)), block(256);
+    if (elem == 2 && whole)
+        hipLaunchKernelGGL((copy_rows_kernel<uint16_t, 8>), grid, block, 0, s, (const uint16_t*)src, (uint16_t*)dst, rows, d_src, d_dst);
+    else if (elem == 2)
+        hipLaunchKernelGGL((copy_rows_kernel<uint16_t, 1>), grid, block, 0, s, (const uint16_t*)src, (uint16_t*)dst, rows, d_src, d_dst);
+    else if (whole)
+        hipLaunchKernelGGL((copy_rows_kernel<float, 4>), grid, block, 0, s, (const float*)src, (float*)dst, rows, d_src, d_dst);
     else
-        hipLaunchKernelGGL(copy_rows_kernel<uint32_t>, dim3(blocks), dim3(256), 0, s,
-                           (const uint32_t*)src, (uint32_t*)dst, total, d_src, d_dst);
+        hipLaunchKernelGGL((copy_rows_kernel<float, 1>), grid, block, 0, s, (const float*)src, (float*)dst, rows, d_src, d_dst);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }
@@ -124,7 +138,7 @@ fk_status launch_round_centroids(const Geometry& g, const float* C_f32, void* C_
                                  void* c_frag, float* c_bias, hipStream_t s) {
     if (g.t == FK_F32) {
         if (C_lp && C_lp != (const void*)C_f32) {
-            const size_t n = (size_t)g.B * g.K * g.d;
+            const size_t n = (size_t)g.B * g.K * g.len;
             hipLaunchKernelGGL(copy_f32_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s,
                                C_f32, (float*)C_lp, n);
             FK_HIP(hipGetLastError());
@@ -133,7 +147,7 @@ fk_status launch_round_centroids(const Geometry& g, const float* C_f32, void* C_
     }
     dim3 grid(g.ktiles, g.B), block(std::min(512, 64 * g.dchunks));
     hipLaunchKernelGGL(centroid_layout_kernel<true>, grid, block, 0, s, (const void*)C_f32,
-                       (uint16_t*)C_lp, (uint16_t*)c_frag, c_bias, g.d, g.K, g.ktiles, g.dchunks,
+                       (uint16_t*)C_lp, (uint16_t*)c_frag, c_bias, g.d, g.len, g.K, g.ktiles, g.dchunks,
                        g.t == FK_BF16 ? 1 : 0);
     FK_HIP(hipGetLastError());
     return FK_OK;
@@ -164,7 +178,7 @@ template <bool BF, int DCH, int P, int WAVES, int ST>
 __global__ __launch_bounds__(WAVES * 64) void assign_mfma_kernel(
     const uint16_t* __restrict__ X, const uintx4* __restrict__ c_frag,
     const float* __restrict__ c_bias, int32_t* __restrict__ assign,
-    float* __restrict__ min_dist, int64_t N, int d, int K, int ktiles) {
+    float* __restrict__ min_dist, int64_t N, int d, int len, int K, int ktiles) {
     constexpr int kThreads = WAVES * 64;
     constexpr int kStageVec = ST * DCH * 64;            // 16-byte vectors per stage
     constexpr int kPieces = ST * DCH;                   // 1 KiB pieces per stage
@@ -173,7 +187,7 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_kernel(
     static_assert(ST * 32 <= kThreads, "one bias value per thread per stage");
 
     const int b = blockIdx.y;
-    X += (size_t)b * N * d;
+    X += (size_t)b * N * len;
     c_frag += (size_t)b * ktiles * DCH * 64;
     c_bias += (size_t)b * ktiles * 32;
     assign += (size_t)b * N;
@@ -215,9 +229,16 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_kernel(
         for (int s = 0; s < DCH; ++s) {
             const int j0 = s * 16 + h * 8;
             uintx4 v = {0u, 0u, 0u, 0u};
-            if (point < N && j0 < d) v = *(const uintx4*)(X + (size_t)point * d + j0);
+            if (point < N && j0 < d) v = raw_piece16(X + (size_t)point * len, j0, len);
             xf[pt][s] = v;
         }
+    }
+    if (len & 7) {
+#pragma unroll
+        for (int s = 0; s < DCH; ++s)
+            if (s == len >> 4)                               // the chunk that the row ends in
+#pragma unroll
+                for (int pt = 0; pt < P; ++pt) xf[pt][s] = settle16(xf[pt][s], s * 16 + h * 8, len);
     }
 
     float best[P];   // packed: score with low 4 bits = 15 - slot
@@ -324,7 +345,7 @@ template <bool BF, int DCH, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void assign_mfma_wide_kernel(
     const uint16_t* __restrict__ X, const uintx4* __restrict__ c_frag,
     const float* __restrict__ c_bias, int32_t* __restrict__ assign,
-    float* __restrict__ min_dist, int64_t N, int d, int K, int ktiles) {
+    float* __restrict__ min_dist, int64_t N, int d, int len, int K, int ktiles) {
     constexpr int SC = 16;                  // chunks (1 KiB pieces) per stage
     constexpr int SPT = DCH / SC;           // stages per centroid tile
     constexpr int kThreads = WAVES * 64;
@@ -333,7 +354,7 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_wide_kernel(
     __shared__ float sbias[2][32];
 
     const int b = blockIdx.y;
-    X += (size_t)b * N * d;
+    X += (size_t)b * N * len;
     c_frag += (size_t)b * ktiles * DCH * 64;
     c_bias += (size_t)b * ktiles * 32;
     assign += (size_t)b * N;
@@ -361,8 +382,13 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_wide_kernel(
     for (int s = 0; s < DCH; ++s) {
         const int j0 = s * 16 + h * 8;
         uintx4 v = {0u, 0u, 0u, 0u};
-        if (point < N && j0 < d) v = *(const uintx4*)(X + (size_t)point * d + j0);
+        if (point < N && j0 < d) v = raw_piece16(X + (size_t)point * len, j0, len);
         xf[s] = v;
+    }
+    if (len & 7) {
+#pragma unroll
+        for (int s = 0; s < DCH; ++s)
+            if (s == len >> 4) xf[s] = settle16(xf[s], s * 16 + h * 8, len);   // the chunk that the row ends in
     }
     float best = -INFINITY;
     int btile = 0;
@@ -622,18 +648,18 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_stream_kernel(
 template <bool BF, int DCH, int WAVES, bool FRAG, int P>
 __global__ __launch_bounds__(WAVES * 64) void assign_mfma_few_kernel(
     const uint16_t* __restrict__ X, const void* __restrict__ Cv, const float* __restrict__ c_bias,
-    int32_t* __restrict__ assign, float* __restrict__ min_dist, int64_t N, int d, int K, int ktiles) {
+    int32_t* __restrict__ assign, float* __restrict__ min_dist, int64_t N, int d, int len, int K, int ktiles) {
     __shared__ __align__(16) float sbias[FRAG ? 1 : WAVES][32];
     __shared__ float cand_m[WAVES][P * 32];
     __shared__ int cand_k[WAVES][P * 32];
     extern __shared__ uintx4 dyn_lds[];                      // the points, then (rows) a tile per wave
     const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 31, h = lane >> 5;
-    X += (size_t)b * N * d;
+    X += (size_t)b * N * len;
     assign += (size_t)b * N;
     if (min_dist) min_dist += (size_t)b * N;
     const uintx4* frag = (const uintx4*)Cv + (size_t)b * ktiles * DCH * 64;
-    const uint16_t* C = (const uint16_t*)Cv + (size_t)b * K * d;
+    const uint16_t* C = (const uint16_t*)Cv + (size_t)b * K * len;
     c_bias += (size_t)b * ktiles * 32;
     const int64_t point0 = (int64_t)blockIdx.x * (P * 32);
     const int ppr = d >> 3;                                  // 16-byte pieces per row
@@ -647,7 +673,9 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_few_kernel(
         int row = j / ppr;
         const int piece = (j - row * ppr) ^ (row & swz);
         row = min(row, 31);
-        copy16_to_lds((const uintx4*)(src + (size_t)min(row0 + row, rows - 1) * d + piece * 8), to + q * 64);
+        const uint16_t* from = src + (size_t)min(row0 + row, rows - 1) * len;
+        if (len == d) copy16_to_lds((const uintx4*)(from + piece * 8), to + q * 64);
+        else to[j] = row_piece16(from, piece * 8, len);
     };
     auto row_piece = [&](const uintx4* at, int s) {          // features [16 s + 8 h, + 8) of row n
         const int piece = 2 * s + h;
@@ -685,7 +713,7 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_few_kernel(
             const int k = tile * 32 + n;
 #pragma unroll
             for (int s = 0; s < DCH; ++s) a[s] = row_piece(own, s);
-            // the tile is in registers: its place takes the next one
+            // the tile is in registers: its place takes the next one (LDS runs a wave's operations in order)
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             if (tile + WAVES < ktiles)
                 for (int q = 0; q < loads; ++q) copy_rows(C, (int64_t)(tile + WAVES) * 32, K, own, q);
@@ -788,11 +816,11 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_few_kernel(
 template <int DMAX, int TK, int THREADS>
 __global__ __launch_bounds__(THREADS) void assign_f32_kernel(
     const float* __restrict__ X, const float* __restrict__ C, int32_t* __restrict__ assign,
-    float* __restrict__ min_dist, int64_t N, int d, int K) {
+    float* __restrict__ min_dist, int64_t N, int d, int len, int K) {
     __shared__ float sc[TK][DMAX];
     const int b = blockIdx.y;
-    X += (size_t)b * N * d;
-    C += (size_t)b * K * d;
+    X += (size_t)b * N * len;
+    C += (size_t)b * K * len;
     assign += (size_t)b * N;
     if (min_dist) min_dist += (size_t)b * N;
     const int64_t i = (int64_t)blockIdx.x * THREADS + threadIdx.x;
@@ -800,16 +828,17 @@ __global__ __launch_bounds__(THREADS) void assign_f32_kernel(
 #pragma unroll
     for (int j = 0; j < DMAX; j += 4) {
         floatx4 v = {0.f, 0.f, 0.f, 0.f};
-        if (i < N && j < d) v = *(const floatx4*)(X + (size_t)i * d + j);
+        if (i < N && j < len) v = raw_piece32(X + (size_t)i * len, j, len);
         x[j] = v[0]; x[j + 1] = v[1]; x[j + 2] = v[2]; x[j + 3] = v[3];
     }
+    settle_row32<DMAX>(x, len);
     float m = INFINITY;
     int a = 0;
     for (int k0 = 0; k0 < K; k0 += TK) {
         __syncthreads();
         for (int o = threadIdx.x; o < TK * DMAX; o += THREADS) {
             const int r = o / DMAX, j = o % DMAX;
-            sc[r][j] = (k0 + r < K && j < d) ? C[(size_t)(k0 + r) * d + j] : 0.f;
+            sc[r][j] = (k0 + r < K && j < len) ? C[(size_t)(k0 + r) * len + j] : 0.f;
         }
         __syncthreads();
         const int nk = min(TK, K - k0);
@@ -836,31 +865,34 @@ __global__ __launch_bounds__(THREADS) void assign_f32_kernel(
 // row of X in blocks of 32 features, once per centroid tile (the re-reads come from cache).
 __global__ __launch_bounds__(256) void assign_f32_wide_kernel(
     const float* __restrict__ X, const float* __restrict__ C, int32_t* __restrict__ assign,
-    float* __restrict__ min_dist, int64_t N, int d, int K) {
+    float* __restrict__ min_dist, int64_t N, int d, int len, int K) {
     constexpr int TK = 16;
     extern __shared__ float sc_dyn[];                  // [TK][d]
     const int b = blockIdx.y;
-    X += (size_t)b * N * d;
-    C += (size_t)b * K * d;
+    X += (size_t)b * N * len;
+    C += (size_t)b * K * len;
     assign += (size_t)b * N;
     if (min_dist) min_dist += (size_t)b * N;
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const float* xrow = X + (size_t)(i < N ? i : 0) * d;
+    const float* xrow = X + (size_t)(i < N ? i : 0) * len;
     float m = INFINITY;
     int a = 0;
     for (int k0 = 0; k0 < K; k0 += TK) {
         __syncthreads();
         for (int o = threadIdx.x; o < TK * d; o += 256) {
             const int r = o / d, j = o - r * d;
-            sc_dyn[o] = k0 + r < K ? C[(size_t)(k0 + r) * d + j] : 0.f;
+            sc_dyn[o] = k0 + r < K && j < len ? C[(size_t)(k0 + r) * len + j] : 0.f;
         }
         __syncthreads();
         float D[TK];
 #pragma unroll
         for (int r = 0; r < TK; ++r) D[r] = 0.f;
         for (int j0 = 0; j0 < d; j0 += 8) {             // d is a multiple of 8
-            const floatx4 xa = *(const floatx4*)(xrow + j0);
-            const floatx4 xb = *(const floatx4*)(xrow + j0 + 4);
+            floatx4 xa = raw_piece32(xrow, j0, len), xb = raw_piece32(xrow, j0 + 4, len);
+            if (j0 + 8 > len) {
+                xa = settle32(xa, j0, len);
+                xb = settle32(xb, j0 + 4, len);
+            }
 #pragma unroll
             for (int r = 0; r < TK; ++r) {
                 const floatx4 ca = *(const floatx4*)&sc_dyn[r * d + j0];
@@ -891,14 +923,14 @@ __global__ __launch_bounds__(256) void assign_f32_wide_kernel(
 template <int DMAX>
 __global__ __launch_bounds__(256) void assign_f32_split_kernel(
     const float* __restrict__ X, const float* __restrict__ C, int32_t* __restrict__ assign,
-    float* __restrict__ min_dist, int64_t N, int d, int K) {
+    float* __restrict__ min_dist, int64_t N, int d, int len, int K) {
     constexpr int TK = 32;
     __shared__ float sc[TK][DMAX];
     __shared__ float cand_d[4][64];
     __shared__ int cand_k[4][64];
     const int b = blockIdx.y;
-    X += (size_t)b * N * d;
-    C += (size_t)b * K * d;
+    X += (size_t)b * N * len;
+    C += (size_t)b * K * len;
     assign += (size_t)b * N;
     if (min_dist) min_dist += (size_t)b * N;
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
@@ -907,16 +939,17 @@ __global__ __launch_bounds__(256) void assign_f32_split_kernel(
 #pragma unroll
     for (int j = 0; j < DMAX; j += 4) {
         floatx4 v = {0.f, 0.f, 0.f, 0.f};
-        if (i < N && j < d) v = *(const floatx4*)(X + (size_t)i * d + j);
+        if (i < N && j < len) v = raw_piece32(X + (size_t)i * len, j, len);
         x[j] = v[0]; x[j + 1] = v[1]; x[j + 2] = v[2]; x[j + 3] = v[3];
     }
+    settle_row32<DMAX>(x, len);
     float m = INFINITY;
     int a = 0x7FFFFFFF;
     for (int k0 = 0; k0 < K; k0 += TK) {
         __syncthreads();
         for (int o = threadIdx.x; o < TK * DMAX; o += 256) {
             const int r = o / DMAX, j = o % DMAX;
-            sc[r][j] = (k0 + r < K && j < d) ? C[(size_t)(k0 + r) * d + j] : 0.f;
+            sc[r][j] = (k0 + r < K && j < len) ? C[(size_t)(k0 + r) * len + j] : 0.f;
         }
         __syncthreads();
         for (int rr = 0; rr < 8; ++rr) {
@@ -960,7 +993,7 @@ static fk_status launch_mfma_v(const Geometry& g, const void* X, const void* fra
     dim3 grid((unsigned)cdiv(g.N, per_wg), g.B), block(WAVES * 64);
     hipLaunchKernelGGL((assign_mfma_kernel<BF, DCH, P, WAVES, ST>), grid, block, 0, s,
                        (const uint16_t*)X, (const uintx4*)frag, bias, assign, min_dist, g.N,
-                       g.d, g.K, g.ktiles);
+                       g.d, g.len, g.K, g.ktiles);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }
@@ -1027,7 +1060,7 @@ static std::atomic<int> g_stream_option{[] {
 void set_assign_stream_option(int v) { g_stream_option.store(v, std::memory_order_relaxed); }
 
 bool assign_uses_stream_kernel(const Geometry& g) {
-    if (g.t == FK_F32 || g.dchunks > 8) return false;
+    if (g.t == FK_F32 || g.dchunks > 8 || g.len != g.d) return false;   // copies whole 16-byte pieces to LDS
     const int st = (16 / g.dchunks) < 8 ? (16 / g.dchunks) : 8;
     const int opt = g_stream_option.load(std::memory_order_relaxed);
     if (g.ktiles > st || opt == 0) return false;
@@ -1102,7 +1135,7 @@ static fk_status launch_few_w(const Geometry& g, const void* X, const void* C, c
         }
     }
     dim3 grid((unsigned)cdiv(g.N, 32 * P), g.B), block(WAVES * 64);
-    hipLaunchKernelGGL(kern, grid, block, lds, s, (const uint16_t*)X, C, bias, assign, min_dist, g.N, g.d, g.K, g.ktiles);
+    hipLaunchKernelGGL(kern, grid, block, lds, s, (const uint16_t*)X, C, bias, assign, min_dist, g.N, g.d, g.len, g.K, g.ktiles);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }
@@ -1186,7 +1219,7 @@ static fk_status launch_mfma_wide(const Geometry& g, const void* X, const void* 
     dim3 grid((unsigned)cdiv(g.N, WAVES * 32), g.B), block(WAVES * 64);
     hipLaunchKernelGGL((assign_mfma_wide_kernel<BF, DCH, WAVES>), grid, block, 0, s,
                        (const uint16_t*)X, (const uintx4*)frag, bias, assign, min_dist, g.N, g.d,
-                       g.K, g.ktiles);
+                       g.len, g.K, g.ktiles);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }
@@ -1216,7 +1249,7 @@ fk_status launch_assign(const Geometry& g, const void* X, const void* C_or_frag,
     if (w && f32_filter_enabled(g)) return launch_f32_filter(g, *w, Xf, Cf, assign, min_dist, s);
     if (g.d > 128) {
         hipLaunchKernelGGL(assign_f32_wide_kernel, dim3((unsigned)cdiv(g.N, 256), g.B), dim3(256),
-                           (size_t)16 * g.d * sizeof(float), s, Xf, Cf, assign, min_dist, g.N, g.d, g.K);
+                           (size_t)16 * g.d * sizeof(float), s, Xf, Cf, assign, min_dist, g.N, g.d, g.len, g.K);
         FK_HIP(hipGetLastError());
         return FK_OK;
     }
@@ -1228,10 +1261,10 @@ fk_status launch_assign(const Geometry& g, const void* X, const void* C_or_frag,
     do {                                                                                          \
         if (small)                                                                                \
             hipLaunchKernelGGL((assign_f32_split_kernel<DM>), grid, block, 0, s, Xf, Cf, assign,  \
-                               min_dist, g.N, g.d, g.K);                                          \
+                               min_dist, g.N, g.d, g.len, g.K);                                          \
         else                                                                                      \
             hipLaunchKernelGGL((assign_f32_kernel<DM, 32, 256>), grid, block, 0, s, Xf, Cf, assign, \
-                               min_dist, g.N, g.d, g.K);                                          \
+                               min_dist, g.N, g.d, g.len, g.K);                                          \
     } while (0)
     if (g.d <= 32) FK_F32_LAUNCH(32);
     else if (g.d <= 64) FK_F32_LAUNCH(64);

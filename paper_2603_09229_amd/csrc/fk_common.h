@@ -65,9 +65,10 @@ struct Geometry {
     int B;
     int64_t N;        // points per instance
     int d, K;         // d: row width the kernels see (a multiple of 8)
-    int d_user;       // row width of the caller's arrays; when it differs from d, X and C are
-                      // first copied into zero-padded rows of width d (zeros change no distance
-                      // and no mean) and the centroids copied back without the padding
+    int d_user;       // row width of the caller's arrays
+    int len;          // elements of a row of X and C as the kernels are given them: d_user where they
+                      // read the caller's rows (row_piece16 / row_piece32), d after the rows have
+                      // been copied into zero-padded ones (zeros change no distance and no mean)
     fk_dtype t;
     int dchunks;      // ceil(d / 16)
     int ktiles;       // ceil(K / 32)
@@ -111,11 +112,15 @@ struct Workspace {
     float* sums;         // [B,K,d] accumulated sums (chunked mode)
     float* f32_shift;    // [B,dchunks*16] shift of the filtered fp32 assignment (fk_f32_filter.hip)
     int32_t* f32_list_len; // [B] points it has left open (the points themselves: sorted_idx)
-    void* x_pad;         // [B,N,d] zero-padded copy of X            (only when d != d_user)
+    void* x_pad;         // [B,N,d] zero-padded copy of X            (only when needs_padded_rows)
     float* c_pad_f32;    // [B,K,d] zero-padded fp32 centroids       (only when d != d_user)
     void* c_pad_lp;      // [B,K,d] zero-padded centroids, dtype t   (only when d != d_user)
     size_t bytes;        // total bytes carved
 };
+
+// Shapes whose rows are copied into zero-padded ones first: the one-pass update for few clusters
+// copies whole 16-byte pieces straight to LDS, and rows of fewer than 8 elements hold no piece.
+inline bool needs_padded_rows(const Geometry& g) { return g.d != g.d_user && (g.d_user < 8 || g.fused_grid_cap > 0); }
 
 bool make_geometry(int B, int64_t N, int d, int K, fk_dtype t, Geometry* g);
 // Lays the workspace out from `base` (may be NULL to only compute the size).  padded_x = false

@@ -13,6 +13,9 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
+// the same 16 bytes at any element's address
+typedef uint32_t uintx4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef float floatx4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 // Score bias of centroid rows beyond K: it must survive having its low mantissa bits
 // overwritten by the packed argmax (-inf would turn into a NaN pattern) and still lose against
@@ -43,6 +46,61 @@ __device__ __forceinline__ floatx16 mfma32(uintx4 a, uintx4 b, floatx16 c) {
     else
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, a),
                                                       __builtin_bit_cast(half8, b), c, 0, 0, 0);
+}
+
+// Rows as the caller stores them: `len` elements, no padding, at any element's address.  The kernels
+// work on widths d = len rounded up to a multiple of 8 and read a row in pieces of 16 bytes that
+// start at j, a multiple of 8 (fp32: of 4) below d.  Nothing outside the row is ever read (len >= 8):
+// raw_* reads the piece that would cross the row's end so that it ends there, settle* then moves
+// its elements down to where they belong and fills up with zeros.  The two are apart so that a
+// kernel can issue all its loads first and settle them under one test of len, which keeps rows
+// that need none of it on straight-line code.
+__device__ __forceinline__ uintx4 raw_piece16(const uint16_t* __restrict__ row, int j, int len) {
+    return *(const uintx4_any*)(row + min(j, len - 8));
+}
+
+__device__ __forceinline__ uintx4 settle16(uintx4 v, int j, int len) {
+    const int s = (8 - (len & 7)) * 16;                     // wave-uniform; 16 .. 112 where it matters
+    const uint64_t lo = (uint64_t)v[0] | ((uint64_t)v[1] << 32), hi = (uint64_t)v[2] | ((uint64_t)v[3] << 32);
+    const uint64_t a = s >= 64 ? hi >> ((s - 64) & 63) : (lo >> s) | (hi << ((64 - s) & 63)), c = s >= 64 ? 0 : hi >> s;
+    return j + 8 > len ? uintx4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)c, (uint32_t)(c >> 32)} : v;
+}
+
+__device__ __forceinline__ uintx4 row_piece16(const uint16_t* __restrict__ row, int j, int len) {
+    uintx4 v = raw_piece16(row, j, len);
+    if (len & 7) v = settle16(v, j, len);
+    return v;
+}
+
+__device__ __forceinline__ floatx4 raw_piece32(const float* __restrict__ row, int j, int len) {
+    return *(const floatx4_any*)(row + min(j, len - 4));
+}
+
+__device__ __forceinline__ floatx4 settle32(floatx4 v, int j, int len) {
+    const int past = j + 4 - len;                           // elements of the piece past the end
+    return past <= 0 ? v
+         : past == 1 ? floatx4{v[1], v[2], v[3], 0.f}
+         : past == 2 ? floatx4{v[2], v[3], 0.f, 0.f}
+         : past == 3 ? floatx4{v[3], 0.f, 0.f, 0.f} : floatx4{0.f, 0.f, 0.f, 0.f};
+}
+
+__device__ __forceinline__ floatx4 row_piece32(const float* __restrict__ row, int j, int len) {
+    floatx4 v = raw_piece32(row, j, len);
+    if (len & 7) v = settle32(v, j, len);
+    return v;
+}
+
+// a whole row in registers, read piece by piece with raw_piece32
+template <int DMAX>
+__device__ __forceinline__ void settle_row32(float (&x)[DMAX], int len) {
+    if (len & 3) {
+#pragma unroll
+        for (int j = 0; j < DMAX; j += 4)
+            if (j == (len & ~3)) {
+                const floatx4 v = settle32(floatx4{x[j], x[j + 1], x[j + 2], x[j + 3]}, j, len);
+                x[j] = v[0]; x[j + 1] = v[1]; x[j + 2] = v[2]; x[j + 3] = v[3];
+            }
+    }
 }
 
 // 32-bit LDS address of a pointer into shared memory (for hand-issued LDS instructions)

@@ -76,13 +76,13 @@ constexpr int kLayoutThreads = 512;
 
 __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
     const float* __restrict__ C, uintx4* __restrict__ frag, float* __restrict__ c2,
-    float* __restrict__ shift, int32_t* __restrict__ list_len, int d, int K, int ktiles, int dch) {
+    float* __restrict__ shift, int32_t* __restrict__ list_len, int d, int len, int K, int ktiles, int dch) {
     __shared__ float m[512];
     __shared__ double part[32][65];
     __shared__ int fits[32];
     const int b = blockIdx.y, kt = blockIdx.x, tid = threadIdx.x;
     const int width = dch * 16;
-    C += (size_t)b * K * d;
+    C += (size_t)b * K * len;
     frag += ((size_t)b * ktiles + kt) * (2 * dch + 1) * 64;
     // this thread's groups of eight features: group g = tid + i * threads is lane g % 64 of chunk g / 64
     constexpr int kGroups = 64 * 32 / kLayoutThreads;
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
 #pragma unroll
         for (int e = 0; e < 8; ++e) own[i][e] = 0.f;
         if (g < 64 * dch && k < K && j0 < d) {
-            const floatx4 u = *(const floatx4*)(C + (size_t)k * d + j0), v = *(const floatx4*)(C + (size_t)k * d + j0 + 4);
+            const floatx4 u = row_piece32(C + (size_t)k * len, j0, len), v = row_piece32(C + (size_t)k * len, j0 + 4, len);
 #pragma unroll
             for (int e = 0; e < 4; ++e) { own[i][e] = u[e]; own[i][e + 4] = v[e]; }
         }
@@ -102,11 +102,11 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
     const int rows = min(K, 32);
     if (tid < width) {
         float s = 0.f;
-        if (tid < d)
+        if (tid < len)
             for (int i0 = 0; i0 < rows; i0 += 8) {
                 float v[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = C[(size_t)((int64_t)min(i0 + i, rows - 1) * K / rows) * d + tid];
+                for (int i = 0; i < 8; ++i) v[i] = C[(size_t)((int64_t)min(i0 + i, rows - 1) * K / rows) * len + tid];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) s += i0 + i < rows ? v[i] : 0.f;
             }
@@ -182,7 +182,7 @@ template <int DCH, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void assign_f32_filter_kernel(
     const float* __restrict__ X, const uintx4* __restrict__ frag, const float* __restrict__ c2,
     const float* __restrict__ shift, int32_t* __restrict__ assign, int32_t* __restrict__ list,
-    int32_t* __restrict__ list_len, int64_t N, int d, int K, int ktiles) {
+    int32_t* __restrict__ list_len, int64_t N, int d, int len, int K, int ktiles) {
     constexpr int kTile = 2 * DCH + 1;                       // 1 KiB pieces per centroid tile
     constexpr int ST = DCH < 8 ? 8 / DCH : 1;                // tiles per stage ...
     constexpr int SPT = DCH <= 8 ? 1 : DCH <= 16 ? 2 : 4;    // ... or stages per tile
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(WAVES * 64) void assign_f32_filter_kernel(
     __shared__ uintx4 stage[2][kPieces * 64];
 
     const int b = blockIdx.y;
-    X += (size_t)b * N * d;
+    X += (size_t)b * N * len;
     frag += (size_t)b * ktiles * kTile * 64;
     c2 += (size_t)b * ktiles * 32;
     shift += (size_t)b * DCH * 16;
@@ -219,15 +219,12 @@ __global__ __launch_bounds__(WAVES * 64) void assign_f32_filter_kernel(
 
     uintx4 xh[DCH], xl[DCH];
     float x2 = 0.f;
-#pragma unroll
-    for (int s = 0; s < DCH; ++s) {
+    auto take = [&](int s, floatx4 a, floatx4 c) {           // features [16 s + 8 h, + 8) of the point
         const int j0 = s * 16 + h * 8;
         float v[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = 0.f;
         if (point < N && j0 < d) {
-            const floatx4 a = *(const floatx4*)(X + (size_t)point * d + j0);
-            const floatx4 c = *(const floatx4*)(X + (size_t)point * d + j0 + 4);
             const floatx4 ma = *(const floatx4*)(shift + j0), mc = *(const floatx4*)(shift + j0 + 4);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -238,6 +235,31 @@ __global__ __launch_bounds__(WAVES * 64) void assign_f32_filter_kernel(
             for (int e = 0; e < 8; ++e) x2 = fmaf(v[e], v[e], x2);
         }
         split8(v, xh[s], xl[s]);
+    };
+    const float* row = X + (size_t)(point < N ? point : 0) * len;
+    if (len == d) {
+#pragma unroll
+        for (int s = 0; s < DCH; ++s) {
+            const int j0 = min(s * 16 + h * 8, d - 8);
+            take(s, *(const floatx4*)(row + j0), *(const floatx4*)(row + j0 + 4));
+        }
+    } else {
+        constexpr int kAhead = DCH % 4 == 0 ? 4 : DCH % 3 == 0 ? 3 : DCH % 5 == 0 ? 5 : DCH % 2 == 0 ? 2 : 1;
+#pragma unroll
+        for (int s0 = 0; s0 < DCH; s0 += kAhead) {           // a few chunks' loads at a time, then settle them
+            floatx4 a[kAhead], c[kAhead];
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) {
+                const int j0 = min((s0 + q) * 16 + h * 8, d - 8);
+                a[q] = raw_piece32(row, j0, len);
+                c[q] = raw_piece32(row, j0 + 4, len);
+            }
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) {
+                const int j0 = min((s0 + q) * 16 + h * 8, d - 8);
+                take(s0 + q, settle32(a[q], j0, len), settle32(c[q], j0 + 4, len));
+            }
+        }
     }
     // the ones that the bias piece is multiplied by
     const uintx4 ones = {h == 0 ? 0x3F803F80u : 0u, h == 0 ? 0x3F80u : 0u, 0u, 0u};
@@ -334,7 +356,7 @@ constexpr int kListFloats = 4096;                      // points held by a workg
 template <int P>
 __device__ __forceinline__ void list_points(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list, int len,
-    int32_t* __restrict__ assign, int d, int K, int none, int teams, float* xs, float (*cand_d)[8], int (*cand_k)[8]) {
+    int32_t* __restrict__ assign, int d, int row_len, int K, int none, int teams, float* xs, float (*cand_d)[8], int (*cand_k)[8]) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int size = 8 / teams, team = wave / size, part = wave - team * size;   // waves of a team share the centroids
     const int held = teams * P;
@@ -343,7 +365,7 @@ __device__ __forceinline__ void list_points(
         // one wave per row (past the end of the list: the last point again)
         for (int r = wave; r < held; r += 8) {
             const int own = list[min(g + r, (int64_t)len - 1)];
-            for (int j = lane * 4; j < d; j += 256) *(floatx4*)(xs + r * d + j) = *(const floatx4*)(X + (size_t)own * d + j);
+            for (int j = lane * 4; j < d; j += 256) *(floatx4*)(xs + r * d + j) = row_piece32(X + (size_t)own * row_len, j, row_len);
         }
         float best[P];
         int at[P];
@@ -352,14 +374,18 @@ __device__ __forceinline__ void list_points(
         __syncthreads();
         for (int k0 = part * 64; k0 < K; k0 += size * 64) {
             const int k = k0 + lane;
-            const float* row = C + (size_t)min(k, K - 1) * d;
+            const float* row = C + (size_t)min(k, K - 1) * row_len;
             float D[P];
 #pragma unroll
             for (int p = 0; p < P; ++p) D[p] = 0.f;
             floatx4 c[8], next[8];                           // 32 features; d is a multiple of 8
             auto load = [&](floatx4 (&to)[8], int j) {
 #pragma unroll
-                for (int q = 0; q < 8; ++q) to[q] = *(const floatx4*)(row + min(j + 4 * q, d - 4));
+                for (int q = 0; q < 8; ++q) to[q] = raw_piece32(row, min(j + 4 * q, d - 4), row_len);
+                if (j + 32 > row_len) {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) to[q] = settle32(to[q], min(j + 4 * q, d - 4), row_len);
+                }
             };
             load(c, 0);
             for (int j0 = 0; j0 < d; j0 += 32) {
@@ -415,7 +441,7 @@ __device__ __forceinline__ void list_points(
 template <int DMAX>
 __device__ __forceinline__ void list_by_thread(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list, int len,
-    int32_t* __restrict__ assign, int d, int K, int none, float* sc) {
+    int32_t* __restrict__ assign, int d, int row_len, int K, int none, float* sc) {
     constexpr int TK = 32;
     for (int64_t g = (int64_t)blockIdx.x * 512; g < len; g += (int64_t)gridDim.x * 512) {
         const int64_t at = g + threadIdx.x;
@@ -424,16 +450,17 @@ __device__ __forceinline__ void list_by_thread(
 #pragma unroll
         for (int j = 0; j < DMAX; j += 4) {
             floatx4 v = {0.f, 0.f, 0.f, 0.f};
-            if (j < d) v = *(const floatx4*)(X + (size_t)own * d + j);
+            if (j < row_len) v = raw_piece32(X + (size_t)own * row_len, j, row_len);
             x[j] = v[0]; x[j + 1] = v[1]; x[j + 2] = v[2]; x[j + 3] = v[3];
         }
+        settle_row32<DMAX>(x, row_len);
         float m = INFINITY;
         int a = none;
         for (int k0 = 0; k0 < K; k0 += TK) {
             __syncthreads();
             for (int o = threadIdx.x; o < TK * DMAX; o += 512) {
                 const int r = o / DMAX, j = o % DMAX;
-                sc[o] = (k0 + r < K && j < d) ? C[(size_t)(k0 + r) * d + j] : 0.f;
+                sc[o] = (k0 + r < K && j < row_len) ? C[(size_t)(k0 + r) * row_len + j] : 0.f;
             }
             __syncthreads();
             const int nk = min(TK, K - k0);
@@ -457,39 +484,39 @@ __device__ __forceinline__ void list_by_thread(
 template <int DMAX>
 __global__ __launch_bounds__(512, 4) void assign_f32_list_kernel(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list,
-    const int32_t* __restrict__ list_len, int32_t* __restrict__ assign, int64_t N, int d, int K,
-    int none) {
+    const int32_t* __restrict__ list_len, int32_t* __restrict__ assign, int64_t N, int d, int row_len,
+    int K, int none) {
     __shared__ __align__(16) float xs[kListFloats];
     __shared__ float cand_d[8][8];
     __shared__ int cand_k[8][8];
     const int b = blockIdx.y;
     const int len = list_len[b];
-    X += (size_t)b * N * d;
-    C += (size_t)b * K * d;
+    X += (size_t)b * N * row_len;
+    C += (size_t)b * K * row_len;
     assign += (size_t)b * N;
     list += (size_t)b * N;
     int teams = K <= 64 ? 8 : K <= 128 ? 4 : K <= 256 ? 2 : 1;
     while (teams * 8 * d > kListFloats) teams >>= 1;         // d <= 512: ends at 1 or more
     if (len <= 2 * teams * (int)gridDim.x)
-        list_points<2>(X, C, list, len, assign, d, K, none, teams, xs, cand_d, cand_k);
+        list_points<2>(X, C, list, len, assign, d, row_len, K, none, teams, xs, cand_d, cand_k);
     else if (DMAX == 0 || K > 128 || len < 256 * (int)gridDim.x)
-        list_points<8>(X, C, list, len, assign, d, K, none, teams, xs, cand_d, cand_k);
+        list_points<8>(X, C, list, len, assign, d, row_len, K, none, teams, xs, cand_d, cand_k);
     else
-        list_by_thread<DMAX == 0 ? 32 : DMAX>(X, C, list, len, assign, d, K, none, xs);
+        list_by_thread<DMAX == 0 ? 32 : DMAX>(X, C, list, len, assign, d, row_len, K, none, xs);
 }
 
 // min_dist[i] = |x_i - c_a(i)|^2 by direct differences: 16 lanes a point, whole rows per load
 __global__ __launch_bounds__(256) void f32_distance_kernel(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ assign,
-    float* __restrict__ min_dist, int64_t N, int d, int K) {
+    float* __restrict__ min_dist, int64_t N, int len, int K) {
     const int b = blockIdx.y, l = threadIdx.x & 15;
     const int64_t i = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
     if (i >= N) return;
-    const float* x = X + ((size_t)b * N + i) * d;
-    const float* c = C + ((size_t)b * K + assign[(size_t)b * N + i]) * d;
+    const float* x = X + ((size_t)b * N + i) * len;
+    const float* c = C + ((size_t)b * K + assign[(size_t)b * N + i]) * len;
     float s = 0.f;
-    for (int j = l * 4; j < d; j += 64) {
-        const floatx4 u = *(const floatx4*)(x + j), v = *(const floatx4*)(c + j);
+    for (int j = l * 4; j < len; j += 64) {
+        const floatx4 u = row_piece32(x, j, len), v = row_piece32(c, j, len);
 #pragma unroll
         for (int e = 0; e < 4; ++e) { const float t = u[e] - v[e]; s = fmaf(t, t, s); }
     }
@@ -524,7 +551,7 @@ template <int DCH, int WAVES>
 static fk_status launch_filter_t(const Geometry& g, const Workspace& w, const float* X, int32_t* assign, hipStream_t s) {
     dim3 grid((unsigned)cdiv(g.N, WAVES * 32), g.B), block(WAVES * 64);
     hipLaunchKernelGGL((assign_f32_filter_kernel<DCH, WAVES>), grid, block, 0, s, X, (const uintx4*)w.c_frag,
-                       w.c_bias, w.f32_shift, assign, w.sorted_idx, w.f32_list_len, g.N, g.d, g.K, g.ktiles);
+                       w.c_bias, w.f32_shift, assign, w.sorted_idx, w.f32_list_len, g.N, g.d, g.len, g.K, g.ktiles);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }
@@ -532,7 +559,7 @@ static fk_status launch_filter_t(const Geometry& g, const Workspace& w, const fl
 fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* X, const float* C, int32_t* assign,
                             float* min_dist, hipStream_t s) {
     hipLaunchKernelGGL(f32_split_layout_kernel, dim3(g.ktiles, g.B), dim3(kLayoutThreads), 0, s, C, (uintx4*)w.c_frag, w.c_bias,
-                       w.f32_shift, w.f32_list_len, g.d, g.K, g.ktiles, g.dchunks);
+                       w.f32_shift, w.f32_list_len, g.d, g.len, g.K, g.ktiles, g.dchunks);
     FK_HIP(hipGetLastError());
     // Workgroups of four waves fill the chip best; with very many points eight waves share each
     // copy of the centroids (2^20 points, 64 features, K = 256: 138 against 142 us; 128 features, K =
@@ -554,11 +581,11 @@ fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* 
     auto list_kernel = g.d <= 32 ? assign_f32_list_kernel<32> : g.d <= 64 ? assign_f32_list_kernel<64>
                                                                           : assign_f32_list_kernel<0>;
     hipLaunchKernelGGL(list_kernel, dim3((unsigned)G, g.B), dim3(512), 0, s, X, C, w.sorted_idx,
-                       w.f32_list_len, assign, g.N, g.d, g.K, f32_direct_is_split(g) ? g.K - 1 : 0);
+                       w.f32_list_len, assign, g.N, g.d, g.len, g.K, f32_direct_is_split(g) ? g.K - 1 : 0);
     FK_HIP(hipGetLastError());
     if (min_dist) {
         hipLaunchKernelGGL(f32_distance_kernel, dim3((unsigned)cdiv(g.N, 16), g.B), dim3(256), 0, s, X, C, assign,
-                           min_dist, g.N, g.d, g.K);
+                           min_dist, g.N, g.len, g.K);
         FK_HIP(hipGetLastError());
     }
     return FK_OK;

@@ -29,7 +29,7 @@ constexpr int kF32FusedMaxK = 64;
 template <int DMAX>
 __global__ __launch_bounds__(256) void f32_update_kernel(
     const float* __restrict__ X, const float* __restrict__ C, int32_t* __restrict__ assign,
-    float* __restrict__ partial, int32_t* __restrict__ wg_counts, int64_t N, int d, int K) {
+    float* __restrict__ partial, int32_t* __restrict__ wg_counts, int64_t N, int d, int len, int K) {
     constexpr int NR = DMAX > 64 ? 2 : 1;              // table elements per cluster and lane
     extern __shared__ float lds_f32[];
     float* sc = lds_f32;                               // [K][DMAX], zero beyond d
@@ -40,8 +40,8 @@ __global__ __launch_bounds__(256) void f32_update_kernel(
     int* tcnt = cand_k + 256;                          // [K] counts
 
     const int b = blockIdx.y, G = gridDim.x, wg = blockIdx.x;
-    X += (size_t)b * N * d;
-    C += (size_t)b * K * d;
+    X += (size_t)b * N * len;
+    C += (size_t)b * K * len;
     assign += (size_t)b * N;
     const int tid = threadIdx.x, lane = tid & 63;
     const int q = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -54,15 +54,16 @@ __global__ __launch_bounds__(256) void f32_update_kernel(
 #pragma unroll
         for (int j = 0; j < DMAX; j += 4) {
             floatx4 v = {0.f, 0.f, 0.f, 0.f};
-            if (i < N && j < d) v = *(const floatx4*)(X + (size_t)i * d + j);
+            if (i < N && j < len) v = raw_piece32(X + (size_t)i * len, j, len);
             x[j] = v[0]; x[j + 1] = v[1]; x[j + 2] = v[2]; x[j + 3] = v[3];
         }
+        settle_row32<DMAX>(x, len);
     };
     load_x(wg);                                        // in flight while the centroids are staged
 
     for (int o = tid; o < K * DMAX; o += 256) {
         const int r = o / DMAX, j = o % DMAX;
-        sc[o] = j < d ? C[(size_t)r * d + j] : 0.f;
+        sc[o] = j < len ? C[(size_t)r * len + j] : 0.f;
         tab[o] = 0.f;
     }
     if (tid < kF32FusedMaxK) tcnt[tid] = 0;
@@ -73,9 +74,17 @@ __global__ __launch_bounds__(256) void f32_update_kernel(
         // the previous batch's readers of xs / cand are done (first pass: sc is complete)
         __syncthreads();
         {
-            const floatx4* src = (const floatx4*)(X + (size_t)base * d);
-            const int nvec = rows * d / 4;             // d is a multiple of 8
-            for (int o = tid; o < nvec; o += 256) ((floatx4*)xs)[o] = src[o];
+            const int per_row = d / 4;                 // d is a multiple of 8
+            const int nvec = rows * per_row;
+            if (len == d) {
+                const floatx4* src = (const floatx4*)(X + (size_t)base * d);
+                for (int o = tid; o < nvec; o += 256) ((floatx4*)xs)[o] = src[o];
+            } else {
+                for (int o = tid; o < nvec; o += 256) {
+                    const int r = o / per_row;
+                    ((floatx4*)xs)[o] = row_piece32(X + (size_t)(base + r) * len, (o - r * per_row) * 4, len);
+                }
+            }
         }
         const int64_t i = base + lane;
         float m = INFINITY;
@@ -166,7 +175,7 @@ static fk_status launch_f32_update_t(const Geometry& g, const Workspace& w, cons
     G = std::min<int64_t>(G, cdiv(g.N, 64));
     G = std::max<int64_t>(G, 1);
     dim3 grid((unsigned)G, g.B), block(256);
-    hipLaunchKernelGGL(kern, grid, block, lds, s, X, C, assign, w.partial, w.wg_counts, g.N, g.d, g.K);
+    hipLaunchKernelGGL(kern, grid, block, lds, s, X, C, assign, w.partial, w.wg_counts, g.N, g.d, g.len, g.K);
     FK_HIP(hipGetLastError());
     *grid_out = (int)G;
     return FK_OK;

@@ -42,7 +42,7 @@ template <bool BF, int DCH>
 __global__ __launch_bounds__(512) void table_update_kernel(
     const uint16_t* __restrict__ X, const uintx4* __restrict__ c_frag,
     const float* __restrict__ c_bias, int32_t* __restrict__ assign, float* __restrict__ partial,
-    int32_t* __restrict__ wg_counts, int64_t N, int d, int K, int ktiles) {
+    int32_t* __restrict__ wg_counts, int64_t N, int d, int len, int K, int ktiles) {
     constexpr int kThreads = 512, kRows = 256;
     constexpr int CB = DCH / 2;                                // 32-feature column blocks of the table
     constexpr int kList = kRows + 32;                          // list entries per wave (padded to whole chunks)
@@ -57,7 +57,7 @@ __global__ __launch_bounds__(512) void table_update_kernel(
     int* slist = sa + kRows;
 
     const int b = blockIdx.y, G = gridDim.x, wg = blockIdx.x;
-    X += (size_t)b * N * d;
+    X += (size_t)b * N * len;
     assign += (size_t)b * N;
     c_frag += (size_t)b * ktiles * DCH * 64;
     c_bias += (size_t)b * ktiles * 32;
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(512) void table_update_kernel(
 #pragma unroll
         for (int i = 0; i < DCH; ++i) {
             const int64_t point = min(batch * kRows + i * kRowsPerRound + my_row0, N - 1);
-            if (piece_live) xn[i] = *(const uintx4*)(X + (size_t)point * d + my_piece * 8);
+            if (piece_live) xn[i] = raw_piece16(X + (size_t)point * len, my_piece * 8, len);
         }
     };
 
@@ -108,6 +108,10 @@ __global__ __launch_bounds__(512) void table_update_kernel(
         // 1. the prefetched rows go to LDS, swizzled so that the 16 lanes that share a piece
         //    index hit 16 different bank groups
         if (piece_live) {
+            if (len & 7) {
+#pragma unroll
+                for (int i = 0; i < DCH; ++i) xn[i] = settle16(xn[i], my_piece * 8, len);
+            }
 #pragma unroll
             for (int i = 0; i < DCH; ++i) {
                 const int row = i * kRowsPerRound + my_row0;
@@ -295,7 +299,7 @@ static fk_status launch_table_update_t(const Geometry& g, const Workspace& w, co
     G = std::min<int64_t>(G, cdiv(g.N, 256));
     dim3 grid((unsigned)G, g.B), block(512);
     hipLaunchKernelGGL(kern, grid, block, lds, s, (const uint16_t*)X, (const uintx4*)w.c_frag,
-                       (const float*)w.c_bias, assign, w.partial, w.wg_counts, g.N, g.d, g.K, g.ktiles);
+                       (const float*)w.c_bias, assign, w.partial, w.wg_counts, g.N, g.d, g.len, g.K, g.ktiles);
     FK_HIP(hipGetLastError());
     *grid_out = (int)G;
     return FK_OK;

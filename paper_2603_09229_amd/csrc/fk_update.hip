@@ -43,7 +43,7 @@ template <int EPL, bool BF, int WPI>
 __global__ __launch_bounds__(256) void segment_reduce_kernel(
     const void* __restrict__ Xv, const int32_t* __restrict__ sorted_idx,
     const int32_t* __restrict__ seg_off, const int32_t* __restrict__ item_off,
-    float* __restrict__ partial, int64_t N, int d, int K, int R, int64_t max_items,
+    float* __restrict__ partial, int64_t N, int d, int len, int K, int R, int64_t max_items,
     int lpr_log2) {
     __shared__ float wsum[WPI == 4 ? 4 : 1][WPI == 4 ? 512 : 1];
     const int b = blockIdx.y;
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
 
     const int LPR = 1 << lpr_log2, S = 64 >> lpr_log2;
     const int slot = lane >> lpr_log2;
-    const char* X = (const char*)Xv + (size_t)b * N * d * (16 / EPL);
+    const char* X = (const char*)Xv + (size_t)b * N * len * (16 / EPL);
     // rows wider than one wave-load (64 lanes x 16 bytes) are reduced one column block at a time
     const int ncb = (d + 64 * EPL - 1) / (64 * EPL);
     for (int cb = 0; cb < ncb; ++cb) {
@@ -84,7 +84,11 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
                     const int idx = __shfl(myidx, rr & 63);
                     ok[u] = active && rr < nrows;
                     v[u] = uintx4{0u, 0u, 0u, 0u};
-                    if (ok[u]) v[u] = *(const uintx4*)(X + ((size_t)idx * d + col) * (16 / EPL));
+                    if (ok[u]) {
+                        const char* row = X + (size_t)idx * len * (16 / EPL);
+                        if constexpr (EPL == 8) v[u] = raw_piece16((const uint16_t*)row, col, len);
+                        else v[u] = __builtin_bit_cast(uintx4, raw_piece32((const float*)row, col, len));
+                    }
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -100,6 +104,17 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
                     }
                 }
             }
+        }
+        // a lane whose piece crosses the row's end has summed the piece that ends there: move the
+        // sums down to their columns (a piece that starts past the end has none)
+        if (len & 7) {
+            const int past = col + EPL - len;
+#pragma unroll
+            for (int step = 0; step < EPL; ++step)
+                if (step < past) {
+#pragma unroll
+                    for (int e = 0; e < EPL; ++e) acc[e] = e + 1 < EPL ? acc[e + 1] : 0.f;
+                }
         }
         // add the row slots of the wave together (fixed butterfly order)
         for (int o = LPR; o < 64; o <<= 1) {
@@ -139,7 +154,7 @@ __global__ __launch_bounds__(1024) void finalize_kernel(
     const int32_t* __restrict__ item_off, const float* C_prev, float* C_out,
     uint16_t* __restrict__ C_lp_out, float* __restrict__ C_lp_f32_out,
     uint16_t* __restrict__ c_frag, float* __restrict__ c_bias, int32_t* __restrict__ counts,
-    float* __restrict__ sums, int d, int K, int64_t max_items, int ktiles, int dch,
+    float* __restrict__ sums, int d, int len, int K, int64_t max_items, int ktiles, int dch,
     int accumulate, int normalise, int bf, const int32_t* __restrict__ wg_counts, int G) {
     // dynamic LDS: 4 floats per thread for the row sums, then d floats for the squared entries
     // (a fixed worst-case array would cap the small workgroups of many-cluster shapes at a
@@ -203,11 +218,15 @@ __global__ __launch_bounds__(1024) void finalize_kernel(
         if (accumulate) s += sums[o];
         if (sums) sums[o] = s;
         if (normalise) {
-            const float c = n > 0 ? (float)((double)s / (double)n) : C_prev[o];
-            C_out[o] = c;
+            // the caller's rows have no padding; past their end everything is zero
+            const size_t at = ((size_t)b * K + k) * len + j;
+            const float c = j >= len ? 0.f : n > 0 ? (float)((double)s / (double)n) : C_prev[at];
             const uint16_t lp = float_to_lp(c, bf);
-            if (C_lp_out) C_lp_out[o] = lp;
-            if (C_lp_f32_out) C_lp_f32_out[o] = c;
+            if (j < len) {
+                C_out[at] = c;
+                if (C_lp_out) C_lp_out[at] = lp;
+                if (C_lp_f32_out) C_lp_f32_out[at] = c;
+            }
             if (c_frag) {
                 // fragment order: tile k/32, chunk j/16, lane (j%16)/8*32 + k%32, element j%8
                 const size_t pos = ((((size_t)b * ktiles + (k >> 5)) * dch + (j >> 4)) * 64 +
@@ -255,11 +274,11 @@ fk_status launch_segment_reduce(const Geometry& g, const Workspace& w, const voi
     do {                                                                                          \
         if (wide)                                                                                 \
             hipLaunchKernelGGL((segment_reduce_kernel<EPL, BF, 4>), grid, block, 0, s, X,         \
-                               sorted_idx, seg_off, item_off, w.partial, g.N, g.d, g.K,           \
+                               sorted_idx, seg_off, item_off, w.partial, g.N, g.d, g.len, g.K,    \
                                g.rows_per_item, g.max_items, lpr_log2);                           \
         else                                                                                      \
             hipLaunchKernelGGL((segment_reduce_kernel<EPL, BF, 1>), grid, block, 0, s, X,         \
-                               sorted_idx, seg_off, item_off, w.partial, g.N, g.d, g.K,           \
+                               sorted_idx, seg_off, item_off, w.partial, g.N, g.d, g.len, g.K,    \
                                g.rows_per_item, g.max_items, lpr_log2);                           \
     } while (0)
     if (g.t == FK_F32) FK_REDUCE(4, false);
@@ -285,7 +304,7 @@ fk_status launch_finalize(const Geometry& g, const Workspace& w, const int32_t* 
     const size_t lds = ((size_t)4 * threads + g.d) * sizeof(float);
     hipLaunchKernelGGL(finalize_kernel, dim3(g.K, g.B), dim3(threads), lds, s, w.partial, seg_off,
                        item_off, a.C_prev_f32, a.C_out_f32, lp16, lp32, frag, a.c_bias, a.counts,
-                       a.sums, g.d, g.K, g.max_items, g.ktiles, g.dchunks, a.accumulate ? 1 : 0,
+                       a.sums, g.d, g.len, g.K, g.max_items, g.ktiles, g.dchunks, a.accumulate ? 1 : 0,
                        a.normalise ? 1 : 0, g.t == FK_BF16 ? 1 : 0, wg_counts, wg_per_cluster);
     FK_HIP(hipGetLastError());
     return FK_OK;
