@@ -116,9 +116,13 @@ bool make_geometry(int B, int64_t N, int d_user, int K, fk_dtype t, Geometry* g)
     if (min_rounds > 1 && T < (int64_t)4096 * min_rounds) T = (int64_t)4096 * min_rounds;
     g->sort_tile = (int)T;
     g->sort_blocks = (int)cdiv(N, T);
-    // rows reduced into one partial row: 256 by one wave, or, for N above 4M points, N/4096 by
+    // rows reduced into one partial row: up to 256 by one wave, or, for N above 4M points, N/4096 by
     // the four waves of a workgroup (at most ~4096 + K partial rows to merge afterwards)
     int64_t R = 256;
+    // ... fewer where the items would not fill the chip: a wave of 256 rows is one long chain of loads
+    // (fk_update, 2^18 points, d = 300, K = 500: 64.6 us with 256 rows per item, 59 with 64; 10^5 points,
+    // K = 64: 32.4 and 28.1)
+    while (R > 32 && B * (N / R + K) < 3000) R /= 2;
     g->waves_per_item = 1;
     if (N > ((int64_t)1 << 22)) { R = cdiv(N, 4096); g->waves_per_item = 4; }
     g->rows_per_item = (int)R;

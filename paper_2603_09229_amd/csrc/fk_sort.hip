@@ -97,11 +97,12 @@ __device__ __forceinline__ void load_round(const int32_t* __restrict__ keys, int
     }
 }
 
-// Per-workgroup digit histogram, written transposed: H[b][bin][blk].
+// Per-workgroup digit histogram, written transposed, H[b][bin][blk], for the scan kernel, or
+// (by_block) H[b][blk][bin] for scatter workgroups that add the earlier ones' up themselves.
 template <int kSortWaves>
 __global__ __launch_bounds__(kSortWaves * 64) void sort_hist_kernel(
     const int32_t* __restrict__ keys, int32_t* __restrict__ H, int64_t N, int rounds, int NB,
-    int shift, int mask, int kmax, int nbits) {
+    int shift, int mask, int kmax, int nbits, int by_block) {
     constexpr int kSortThreads = kSortWaves * 64, kBatches = kSubTile / kSortThreads;
     extern __shared__ int lds[];
     int* hist = lds;
@@ -133,11 +134,12 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_hist_kernel(
         for (int j = 0; j < kBatches; ++j) k[j] = kn[j];
     }
     __syncthreads();
-    int32_t* out = H + (size_t)b * NB * nb + blk;
+    int32_t* out = H + (size_t)b * NB * nb + (by_block ? (size_t)blk * NB : (size_t)blk);
+    const size_t step = by_block ? 1 : nb;
     for (int i = tid; i < NB; i += kSortThreads) {
         int c = 0;
         for (int q = 0; q < copies; ++q) c += hist[q * NB + i];
-        out[(size_t)i * nb] = c;
+        out[(size_t)i * step] = c;
     }
 }
 
@@ -191,7 +193,7 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
     const int32_t* __restrict__ H, const int32_t* __restrict__ tot,
     int32_t* __restrict__ vals_out, int32_t* __restrict__ keys_out,
     int32_t* __restrict__ seg_off, int32_t* __restrict__ item_off, int64_t N, int rounds,
-    int NB, int shift, int mask, int kmax, int nbits, int R, int staged, int solo) {
+    int NB, int shift, int mask, int kmax, int nbits, int R, int staged, int solo, int by_block) {
     constexpr int kSortThreads = kSortWaves * 64, kBatches = kSubTile / kSortThreads;
     extern __shared__ int lds[];
     int* off = lds;                    // [NB]
@@ -208,7 +210,7 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
     vals_out += (size_t)b * N;
     if (keys_out) keys_out += (size_t)b * N;
     tot += (size_t)b * NB;
-    H += (size_t)b * NB * nb + blk;
+    H += (size_t)b * NB * nb + (by_block ? 0 : blk);
 
     // first round's keys are requested before the offset scans below need them
     int k[kBatches];
@@ -221,10 +223,32 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
     // apart): requested now, needed only after the counting pass
     constexpr int kHPer = 2048 / kSortThreads;
     int hcol[kHPer];
+    if (kSortWaves == 8 && by_block) {
+        // Few sort workgroups: no scan kernel has run; each workgroup adds up the counts of the earlier
+        // ones (where its own keys start inside the bins) and of all of them (the bin totals,
+        // kept in off[] until they are scanned) for itself.
 #pragma unroll
-    for (int q = 0; q < kHPer; ++q) {
-        const int i = tid + q * kSortThreads;
-        hcol[q] = (!solo && i < NB) ? H[(size_t)i * nb] : 0;
+        for (int q = 0; q < kHPer; ++q) {
+            const int i = tid + q * kSortThreads;
+            hcol[q] = 0;
+            if (i < NB) {
+                int before = 0, all = 0;
+#pragma unroll 8
+                for (int o = 0; o < nb; ++o) {
+                    const int c = H[(size_t)o * NB + i];
+                    all += c;
+                    before += o < blk ? c : 0;
+                }
+                hcol[q] = before;
+                wcnt[i] = all;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < kHPer; ++q) {
+            const int i = tid + q * kSortThreads;
+            hcol[q] = (!solo && i < NB) ? H[(size_t)i * nb] : 0;
+        }
     }
 
     // Bin totals -> off[] (exclusive scan: where each bin starts in the output), plus the
@@ -233,6 +257,7 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
     // counting pass -- no histogram or scan kernel runs then.
     auto offsets_from_totals = [&]() {
         auto total_of = [&](int i) -> int {
+            if (kSortWaves == 8 && by_block) return wcnt[i];   // (written by the thread that reads it)
             if (!solo) return tot[i];
             int t = 0;
             for (int w = 0; w < kSortWaves; ++w) t += wcnt[w * NB + i];
@@ -257,9 +282,10 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
             if (tid == 0) so[NB] = total;
         }
     };
+    if (kSortWaves == 8 && by_block) offsets_from_totals();   // ends with a barrier after its last use of wcnt
     for (int i = tid; i < kSortWaves * NB; i += kSortThreads) wcnt[i] = 0;
     __syncthreads();
-    if (!solo) offsets_from_totals();
+    if (!solo && !by_block) offsets_from_totals();
 
     int* mine = wcnt + wave * NB;
     const uint64_t lt = lanemask_lt();
@@ -501,16 +527,22 @@ static fk_status sort_pass(const Geometry& g, const Workspace& w, const int32_t*
     const bool wide = NB > 1024;       // 8 waves of counters would not fit in LDS
     // one workgroup per instance: the scatter kernel counts for itself
     const int solo = g.sort_blocks == 1 ? 1 : 0;
+    // Few workgroups and bins: the scatter kernel adds the histograms up itself, which saves the scan
+    // kernel's launch while a workgroup has no more than 2^15 counts to read (fk_update, 3 x 70001
+    // points, K = 333: 38.1 -> 36.0 us; 10^5 points, K = 64: 28.1 -> 26.1; at 2^16 counts, 2^18 points, K =
+    // 1024, it loses: 42.0 -> 44.2).
+    const int by_block = !solo && !wide && (int64_t)g.sort_blocks * NB <= 32768 ? 1 : 0;
     if (!solo) {
         const size_t hist_lds = (size_t)NB * (NB <= 64 ? 16 : 1) * sizeof(int);
         if (wide)
             hipLaunchKernelGGL(sort_hist_kernel<4>, grid, dim3(256), hist_lds, s, keys, H, g.N,
-                               rounds, NB, shift, mask, g.K - 1, nbits);
+                               rounds, NB, shift, mask, g.K - 1, nbits, by_block);
         else
             hipLaunchKernelGGL(sort_hist_kernel<8>, grid, dim3(512), hist_lds, s, keys, H, g.N,
-                               rounds, NB, shift, mask, g.K - 1, nbits);
+                               rounds, NB, shift, mask, g.K - 1, nbits, by_block);
         FK_HIP(hipGetLastError());
-        if (g.sort_blocks > 512)
+        if (by_block) {
+        } else if (g.sort_blocks > 512)
             hipLaunchKernelGGL(sort_binscan_kernel<256>, dim3((unsigned)NB, g.B), dim3(256), 0, s, H,
                                tot, g.sort_blocks, NB);
         else
@@ -536,11 +568,11 @@ static fk_status sort_pass(const Geometry& g, const Workspace& w, const int32_t*
     if (wide)
         hipLaunchKernelGGL(sort_scatter_kernel<4>, grid, dim3(256), lds, s, keys, vals_in, H, tot,
                            vals_out, keys_out, seg_off, item_off, g.N, rounds, NB, shift, mask,
-                           g.K - 1, nbits, g.rows_per_item, staged, solo);
+                           g.K - 1, nbits, g.rows_per_item, staged, solo, by_block);
     else
         hipLaunchKernelGGL(sort_scatter_kernel<8>, grid, dim3(512), lds, s, keys, vals_in, H, tot,
                            vals_out, keys_out, seg_off, item_off, g.N, rounds, NB, shift, mask,
-                           g.K - 1, nbits, g.rows_per_item, staged, solo);
+                           g.K - 1, nbits, g.rows_per_item, staged, solo, by_block);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }

@@ -67,6 +67,11 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
     for (int cb = 0; cb < ncb; ++cb) {
         const int col = cb * 64 * EPL + (lane & (LPR - 1)) * EPL;
         const bool active = col < d;
+        // this lane's piece of a row, or where that would cross the row's end the one that ends
+        // there; of the sums only those at its own columns are kept (from len on nobody reads them)
+        const int first = min(col, len - EPL);
+        const char* mine = X + first * (16 / EPL);
+        const int row_bytes = len * (16 / EPL);
         float acc[EPL];
 #pragma unroll
         for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
@@ -84,11 +89,7 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
                     const int idx = __shfl(myidx, rr & 63);
                     ok[u] = active && rr < nrows;
                     v[u] = uintx4{0u, 0u, 0u, 0u};
-                    if (ok[u]) {
-                        const char* row = X + (size_t)idx * len * (16 / EPL);
-                        if constexpr (EPL == 8) v[u] = raw_piece16((const uint16_t*)row, col, len);
-                        else v[u] = __builtin_bit_cast(uintx4, raw_piece32((const float*)row, col, len));
-                    }
+                    if (ok[u]) v[u] = *(const uintx4_any*)(mine + (int64_t)idx * row_bytes);
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -105,17 +106,6 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
                 }
             }
         }
-        // a lane whose piece crosses the row's end has summed the piece that ends there: move the
-        // sums down to their columns (a piece that starts past the end has none)
-        if (len & 7) {
-            const int past = col + EPL - len;
-#pragma unroll
-            for (int step = 0; step < EPL; ++step)
-                if (step < past) {
-#pragma unroll
-                    for (int e = 0; e < EPL; ++e) acc[e] = e + 1 < EPL ? acc[e + 1] : 0.f;
-                }
-        }
         // add the row slots of the wave together (fixed butterfly order)
         for (int o = LPR; o < 64; o <<= 1) {
 #pragma unroll
@@ -123,13 +113,20 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
         }
         if (slot == 0 && active) {
             if (WPI == 1) {
-                float* out = partial + ((size_t)b * max_items + item) * d + col;
+                float* out = partial + ((size_t)b * max_items + item) * d + first;
+                if (first == col) {
 #pragma unroll
-                for (int e = 0; e < EPL; e += 4)
-                    *(floatx4*)(out + e) = floatx4{acc[e], acc[e + 1], acc[e + 2], acc[e + 3]};
+                    for (int e = 0; e < EPL; e += 4)
+                        *(floatx4*)(out + e) = floatx4{acc[e], acc[e + 1], acc[e + 2], acc[e + 3]};
+                } else {
+#pragma unroll
+                    for (int e = 0; e < EPL; ++e)
+                        if (first + e >= col) out[e] = acc[e];
+                }
             } else {
 #pragma unroll
-                for (int e = 0; e < EPL; ++e) wsum[wave][col + e] = acc[e];
+                for (int e = 0; e < EPL; ++e)
+                    if (first + e >= col) wsum[wave][first + e] = acc[e];
             }
         }
     }
@@ -202,7 +199,15 @@ __global__ __launch_bounds__(1024) void finalize_kernel(
         }
         acc = ((a8[0] + a8[1]) + (a8[2] + a8[3])) + ((a8[4] + a8[5]) + (a8[6] + a8[7]));
     }
-    *(floatx4*)&red[slot * dpow + col] = acc;
+    // rows of one wave first (fixed butterfly order), then the waves' sums through LDS: with a row
+    // of 64 features 16 partial sums are added one after the other at the end instead of 64
+    for (int o = LR; o < 64; o <<= 1) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o);
+    }
+    const int sums_left = LR < 64 ? (int)blockDim.x >> 6 : slots;
+    if (LR >= 64) *(floatx4*)&red[slot * dpow + col] = acc;
+    else if ((tid & 63) < LR) *(floatx4*)&red[(tid >> 6) * dpow + col] = acc;
     __syncthreads();
     const int T = (int)blockDim.x;
     int n = n_prev;
@@ -213,7 +218,7 @@ __global__ __launch_bounds__(1024) void finalize_kernel(
     }
     for (int j = tid; j < d; j += T) {
         float s = 0.f;
-        for (int q = 0; q < slots; ++q) s += red[q * dpow + j];   // fixed order
+        for (int q = 0; q < sums_left; ++q) s += red[q * dpow + j];   // fixed order
         const size_t o = ((size_t)b * K + k) * d + j;
         if (accumulate) s += sums[o];
         if (sums) sums[o] = s;
