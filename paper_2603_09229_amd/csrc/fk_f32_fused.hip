@@ -4,17 +4,22 @@
 // each; here it is two.  (For more points the one-point-per-thread assignment kernel followed by
 // the sort-inverse update is faster: this kernel gives every wave all 64 points of a batch.)
 //
-// The table of sums is K x d floats; all of C fits LDS.  A workgroup of four waves walks
-// 64-point batches: every wave holds the 64 points (one per lane, features in registers) and
-// measures them against a quarter of the centroid rows by direct differences in fp32, exactly
-// as the stand-alone fp32 assignment kernels do (so the assignments are bit-identical to
-// theirs); the four candidates of a point are merged through LDS (smaller distance, then
-// lower index).  Cluster k belongs to wave k % 4: that wave alone adds the batch's points of its
-// clusters, in index order, to the cluster's row of a K x d table in LDS (lane = feature; LDS
-// executes a wave's operations in order, so consecutive points of one cluster need no wait
-// beyond the data dependency).  One owner per cluster row and a fixed order: no atomics,
-// reproducible sums.  Every workgroup leaves one partial table and one count per cluster; the
-// ordinary merge/normalise kernel adds them in workgroup order.
+// The table of sums is K x d floats.  A workgroup of eight or sixteen waves walks 64-point batches, which it
+// copies to LDS in whole lines one batch ahead: every wave then holds the 64 points (one per lane,
+// features in registers) and measures them against its share of the centroid rows by direct
+// differences in fp32, exactly as the stand-alone fp32 assignment kernels do (so the assignments
+// are bit-identical to theirs); the centroid rows are wave-uniform and come through the scalar
+// cache straight into the instructions.  The waves' candidates of a point are merged through LDS
+// (smaller distance, then lower index).  Cluster k belongs to wave k % WAVES: that wave alone adds the
+// batch's points of its clusters, in index order, to the cluster's row of a K x d table in LDS
+// (lane = feature; LDS executes a wave's operations in order, so consecutive points of one cluster
+// need no wait beyond the data dependency).  One owner per cluster row and a fixed order: no
+// atomics, reproducible sums.  Every workgroup leaves one partial table and one count per cluster;
+// the ordinary merge/normalise kernel adds them in workgroup order.
+//
+// What bounds it at one batch per compute unit (N = 16384): a chain of latencies -- points to LDS,
+// 2 x 64 vector instructions per centroid, hand-over, adds.  An iteration takes 18 us with it (d = K =
+// 64; 28 with four waves that each read all points from memory and the centroids from LDS).
 #include <algorithm>
 
 #include "fk_common.h"
@@ -24,20 +29,29 @@ namespace fk {
 
 constexpr int kF32FusedMaxK = 64;
 
+// LDS, in floats: points [64][DMAX + 4] (four floats of padding: the lanes' 16-byte reads of 64 rows
+// then spread over all banks) | table [kF32FusedMaxK][DMAX] | candidates 2 x [WAVES][64] | counts
+template <int DMAX, int WAVES>
+constexpr size_t f32_fused_lds() {
+    return ((size_t)64 * (DMAX + 4) + kF32FusedMaxK * DMAX + 2 * WAVES * 64 + kF32FusedMaxK) * 4;
+}
+
 // Grid (G, B): workgroup g handles the 64-point batches g, g + G, ...
 // partial: [B][K][G][d] floats, wg_counts: [B][K][G].
-template <int DMAX>
-__global__ __launch_bounds__(256) void f32_update_kernel(
+template <int DMAX, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void f32_update_kernel(
     const float* __restrict__ X, const float* __restrict__ C, int32_t* __restrict__ assign,
     float* __restrict__ partial, int32_t* __restrict__ wg_counts, int64_t N, int d, int len, int K) {
+    constexpr int kThreads = WAVES * 64;
     constexpr int NR = DMAX > 64 ? 2 : 1;              // table elements per cluster and lane
+    constexpr int LD = DMAX + 4;                       // row stride of the batch in LDS
+    constexpr int kPieces = 64 * DMAX / 4 / kThreads;  // 16-byte pieces of a batch per thread
     extern __shared__ float lds_f32[];
-    float* sc = lds_f32;                               // [K][DMAX], zero beyond d
-    float* tab = sc + kF32FusedMaxK * DMAX;            // [K][DMAX] sums
-    float* xs = tab + kF32FusedMaxK * DMAX;            // [64][d]: the batch as stored
-    float* cand_d = xs + 64 * DMAX;                    // [4][64]
-    int* cand_k = (int*)(cand_d + 256);                // [4][64]
-    int* tcnt = cand_k + 256;                          // [K] counts
+    float* xs = lds_f32;
+    float* tab = xs + 64 * LD;
+    float* cand_d = tab + kF32FusedMaxK * DMAX;
+    int* cand_k = (int*)(cand_d + WAVES * 64);
+    int* tcnt = cand_k + WAVES * 64;
 
     const int b = blockIdx.y, G = gridDim.x, wg = blockIdx.x;
     X += (size_t)b * N * len;
@@ -47,85 +61,92 @@ __global__ __launch_bounds__(256) void f32_update_kernel(
     const int q = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     const int64_t nbatches = (N + 63) / 64;
-    // own point's features of a batch: lane = point (every wave holds all 64 points)
-    float x[DMAX];
-    auto load_x = [&](int64_t t) {
-        const int64_t i = t * 64 + lane;
+    // this thread's pieces of a batch: consecutive threads take consecutive pieces of a row
+    floatx4 ahead[kPieces];
+    auto request = [&](int64_t t) {
 #pragma unroll
-        for (int j = 0; j < DMAX; j += 4) {
-            floatx4 v = {0.f, 0.f, 0.f, 0.f};
-            if (i < N && j < len) v = raw_piece32(X + (size_t)i * len, j, len);
-            x[j] = v[0]; x[j + 1] = v[1]; x[j + 2] = v[2]; x[j + 3] = v[3];
+        for (int i = 0; i < kPieces; ++i) {
+            const int o = tid + i * kThreads, r = o / (DMAX / 4), j = (o % (DMAX / 4)) * 4;
+            ahead[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+            if (t * 64 + r < N && j < len) ahead[i] = raw_piece32(X + (size_t)(t * 64 + r) * len, j, len);
         }
-        settle_row32<DMAX>(x, len);
     };
-    load_x(wg);                                        // in flight while the centroids are staged
-
-    for (int o = tid; o < K * DMAX; o += 256) {
-        const int r = o / DMAX, j = o % DMAX;
-        sc[o] = j < len ? C[(size_t)r * len + j] : 0.f;
-        tab[o] = 0.f;
-    }
+    request(wg);
+    for (int o = tid; o < K * DMAX; o += kThreads) tab[o] = 0.f;
     if (tid < kF32FusedMaxK) tcnt[tid] = 0;
 
     for (int64_t t = wg; t < nbatches; t += G) {
         const int64_t base = t * 64;
         const int rows = (int)min((int64_t)64, N - base);
-        // the previous batch's readers of xs / cand are done (first pass: sc is complete)
-        __syncthreads();
-        {
-            const int per_row = d / 4;                 // d is a multiple of 8
-            const int nvec = rows * per_row;
-            if (len == d) {
-                const floatx4* src = (const floatx4*)(X + (size_t)base * d);
-                for (int o = tid; o < nvec; o += 256) ((floatx4*)xs)[o] = src[o];
-            } else {
-                for (int o = tid; o < nvec; o += 256) {
-                    const int r = o / per_row;
-                    ((floatx4*)xs)[o] = row_piece32(X + (size_t)(base + r) * len, (o - r * per_row) * 4, len);
-                }
+        __syncthreads();                               // the previous batch's readers are done
+        if (len & 3) {
+#pragma unroll
+            for (int i = 0; i < kPieces; ++i) {
+                const int j = (tid + i * kThreads) % (DMAX / 4) * 4;
+                if (j < len) ahead[i] = settle32(ahead[i], j, len);
             }
         }
-        const int64_t i = base + lane;
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            const int o = tid + i * kThreads;
+            *(floatx4*)(xs + o / (DMAX / 4) * LD + o % (DMAX / 4) * 4) = ahead[i];
+        }
+        __syncthreads();
+        if (t + G < nbatches) request(t + G);          // lands while this batch is processed
+        float x[DMAX];                                 // lane = point
+#pragma unroll
+        for (int j = 0; j < DMAX; j += 4) {
+            const floatx4 v = *(const floatx4*)(xs + lane * LD + j);
+            x[j] = v[0]; x[j + 1] = v[1]; x[j + 2] = v[2]; x[j + 3] = v[3];
+        }
         float m = INFINITY;
         int a = 0x7FFFFFFF;
-        // rows q, q + 4, ... ascending with strict '<'; two rows at a time so that the two
+        // rows q, q + WAVES, ... ascending with strict '<'; two rows at a time so that the two
         // dependent chains of adds overlap (each row's own sum keeps its order)
-        for (int r = q; r < K; r += 8) {
-            const int r1 = r + 4 < K ? r + 4 : r;      // past the end: row r again (loses the '<')
+        for (int r = q; r < K; r += 2 * WAVES) {
+            const int r1 = r + WAVES < K ? r + WAVES : r;   // past the end: row r again (loses the '<')
+            const float* c0 = C + (size_t)r * len;
+            const float* c1 = C + (size_t)r1 * len;
             float D0 = 0.f, D1 = 0.f;
 #pragma unroll
-            for (int j = 0; j < DMAX; j += 4) {
-                const floatx4 c0 = *(const floatx4*)&sc[r * DMAX + j];
-                const floatx4 c1 = *(const floatx4*)&sc[r1 * DMAX + j];
-                const float e0 = x[j] - c0[0], e1 = x[j + 1] - c0[1];
-                const float e2 = x[j + 2] - c0[2], e3 = x[j + 3] - c0[3];
-                const float f0 = x[j] - c1[0], f1 = x[j + 1] - c1[1];
-                const float f2 = x[j + 2] - c1[2], f3 = x[j + 3] - c1[3];
-                D0 += e0 * e0; D1 += f0 * f0; D0 += e1 * e1; D1 += f1 * f1;
-                D0 += e2 * e2; D1 += f2 * f2; D0 += e3 * e3; D1 += f3 * f3;
+            for (int j = 0; j < DMAX; j += 16) {
+                if (j + 16 <= len) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const float u = x[j + e] - c0[j + e], v = x[j + e] - c1[j + e];
+                        D0 = fmaf(u, u, D0);
+                        D1 = fmaf(v, v, D1);
+                    }
+                } else if (j < len) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {     // past the end both are zero
+                        const float u = x[j + e] - (j + e < len ? c0[j + e] : 0.f), v = x[j + e] - (j + e < len ? c1[j + e] : 0.f);
+                        D0 = fmaf(u, u, D0);
+                        D1 = fmaf(v, v, D1);
+                    }
+                }
             }
             if (D0 < m) { m = D0; a = r; }
             if (D1 < m) { m = D1; a = r1; }
         }
         cand_d[q * 64 + lane] = m;
         cand_k[q * 64 + lane] = a;
-        __syncthreads();                               // candidates and the batch copy are in LDS
+        __syncthreads();
         // every wave merges for itself: lane = point
         float bm = cand_d[lane];
         int bk = cand_k[lane];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) {
+        for (int w = 1; w < WAVES; ++w) {
             const float dm = cand_d[w * 64 + lane];
             const int dk = cand_k[w * 64 + lane];
             if (dm < bm || (dm == bm && dk < bk)) { bm = dm; bk = dk; }
         }
         bk = min(bk, K - 1);   // only reachable with non-finite input; keeps the index in range
         const bool valid = lane < rows;
-        if (q == 0 && valid) assign[i] = bk;
+        if (q == 0 && valid) assign[base + lane] = bk;
 
         // the batch's points of this wave's clusters, in index order
-        uint64_t mine = __ballot(valid && (bk & 3) == q);
+        uint64_t mine = __ballot(valid && (bk & (WAVES - 1)) == q);
         while (mine) {
             const int p = __builtin_ctzll(mine);
             mine &= mine - 1;
@@ -134,15 +155,14 @@ __global__ __launch_bounds__(256) void f32_update_kernel(
 #pragma unroll
             for (int u = 0; u < NR; ++u) {
                 const int j = lane + 64 * u;
-                if (j < d) trow[j] += xs[p * d + j];
+                if (j < d) trow[j] += xs[p * LD + j];
             }
             if (lane == 0) tcnt[k] += 1;
         }
-        if (t + G < nbatches) load_x(t + G);           // lands behind the next barrier and copy
     }
 
     // the owner of a row wrote it: no barrier needed before reading it back
-    for (int k = q; k < K; k += 4) {
+    for (int k = q; k < K; k += WAVES) {
         float* row = partial + (((size_t)b * K + k) * G + wg) * d;
 #pragma unroll
         for (int u = 0; u < NR; ++u) {
@@ -156,25 +176,25 @@ __global__ __launch_bounds__(256) void f32_update_kernel(
 // ------------------------------------------------------------------------------------
 bool f32_update_enabled(const Geometry& g) { return g.f32_grid_cap > 0 && fused_update_allowed(); }
 
-template <int DMAX>
+template <int DMAX, int WAVES>
 static fk_status launch_f32_update_t(const Geometry& g, const Workspace& w, const float* X,
                                      const float* C, int32_t* assign, int* grid_out,
                                      hipStream_t s) {
-    auto kern = f32_update_kernel<DMAX>;
-    const size_t lds = ((size_t)2 * kF32FusedMaxK * DMAX + 64 * DMAX + 512 + kF32FusedMaxK) * 4;
+    auto kern = f32_update_kernel<DMAX, WAVES>;
+    const size_t lds = f32_fused_lds<DMAX, WAVES>();
     // set / queried once per kernel and device: the launch path stays free of runtime queries afterwards
     static PerDeviceInt per_cu;
     if (per_cu.get() == 0) {
         FK_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         int q = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&q, kern, 256, lds) != hipSuccess || q < 1) q = 1;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&q, kern, WAVES * 64, lds) != hipSuccess || q < 1) q = 1;
         per_cu.set(q);
     }
     int64_t G = cdiv((int64_t)device_cu_count() * per_cu.get(), g.B);
     G = std::min<int64_t>(G, g.f32_grid_cap);
     G = std::min<int64_t>(G, cdiv(g.N, 64));
     G = std::max<int64_t>(G, 1);
-    dim3 grid((unsigned)G, g.B), block(256);
+    dim3 grid((unsigned)G, g.B), block(WAVES * 64);
     hipLaunchKernelGGL(kern, grid, block, lds, s, X, C, assign, w.partial, w.wg_counts, g.N, g.d, g.len, g.K);
     FK_HIP(hipGetLastError());
     *grid_out = (int)G;
@@ -184,13 +204,17 @@ static fk_status launch_f32_update_t(const Geometry& g, const Workspace& w, cons
 fk_status launch_f32_update(const Geometry& g, const Workspace& w, const void* X,
                             const float* C_f32, int32_t* assign, int* grid_out, hipStream_t s) {
     if (g.f32_grid_cap <= 0) {
-        set_error("fused fp32 update: shape not eligible (needs fp32 storage, K <= 64, d <= 128, B*N <= 2^17)");
+        set_error("fused fp32 update: shape not eligible (fp32 storage, K <= 64, d <= 128, few points)");
         return FK_EUNSUPPORTED;
     }
     const float* Xf = (const float*)X;
-    if (g.d <= 32) return launch_f32_update_t<32>(g, w, Xf, C_f32, assign, grid_out, s);
-    if (g.d <= 64) return launch_f32_update_t<64>(g, w, Xf, C_f32, assign, grid_out, s);
-    return launch_f32_update_t<128>(g, w, Xf, C_f32, assign, grid_out, s);
+    if (g.d <= 32) return launch_f32_update_t<32, 8>(g, w, Xf, C_f32, assign, grid_out, s);
+    if (g.d > 64) return launch_f32_update_t<128, 8>(g, w, Xf, C_f32, assign, grid_out, s);
+    // up to one batch per compute unit: sixteen waves finish it sooner (N = 16384, d = K = 64: 18.1 us per
+    // iteration against 20.0); beyond that two workgroups of eight overlap (N = 2^17: 49 against 61)
+    if (cdiv(g.N, 64) * g.B <= device_cu_count())
+        return launch_f32_update_t<64, 16>(g, w, Xf, C_f32, assign, grid_out, s);
+    return launch_f32_update_t<64, 8>(g, w, Xf, C_f32, assign, grid_out, s);
 }
 
 }  // namespace fk
