@@ -172,7 +172,8 @@ fk_status fk_lloyd_iter(const void* X, float* C_f32, void* C_lp, int32_t* assign
  *              memory included, is refused with FK_EINVAL).  Chunks of `chunk_rows` rows are
  *              copied with hipMemcpyAsync on a side stream owned by the call into two
  *              device buffers carved from dev_ws while the previous chunk is assigned and
- *              reduced on `stream`.
+ *              reduced on `stream`.  Odd iterations take the chunks in reverse order and reuse the
+ *              two that are still in the buffers.
  *   C_f32      device in/out, [K,d] float.  The centroids are frozen during an iteration:
  *              sums and counts accumulate over the chunks, one normalisation per iteration
  *              (same result as the in-core path up to fp32 summation order).
