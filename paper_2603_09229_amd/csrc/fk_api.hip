@@ -79,12 +79,15 @@ bool make_geometry(int B, int64_t N, int d_user, int K, fk_dtype t, Geometry* g)
     if ((int64_t)B * N >= ((int64_t)1 << 31)) return false;
     if (B > 65535) return false;                 // instances are the y dimension of every launch
     g->B = B; g->N = N; g->d = d; g->K = K; g->t = t;
-    g->dchunks = d <= 32 ? 2 : (d <= 64 ? 4 : (d <= 128 ? 8 : (d <= 256 ? 16 : 32)));
+    // The kernels are compiled for these numbers of 16-feature chunks, and multiply whole ones: 10, 12,
+    // 14, 16, 20, 24 and 32 for rows beyond 128 (131072 points, K = 1000: d = 300 with 20 chunks 89 us, with
+    // 32 193; 28 chunks do not pay, d = 448: 138 against 132), powers of two below, where the
+    // one-pass updates need them.
+    const int c = (d + 15) / 16;
+    g->dchunks = c <= 2 ? 2 : c <= 4 ? 4 : c <= 8 ? 8 : c <= 16 ? (c + 1) / 2 * 2 : c <= 24 ? (c + 3) / 4 * 4 : 32;
     if (t == FK_F32) {
-        // the filtered fp32 assignment is compiled for widths of every chunk up to 8, every second
-        // up to 16, every fourth up to 32
-        const int c = (d + 15) / 16;
-        g->dchunks = c <= 8 ? c : c <= 16 ? (c + 1) / 2 * 2 : (c + 3) / 4 * 4;
+        // the filtered fp32 assignment is compiled for every number up to 8, and for 28
+        g->dchunks = c <= 8 ? c : c > 24 && c <= 28 ? 28 : g->dchunks;
     }
     g->ktiles = (int)cdiv(K, 32);
     int nbmax;
@@ -602,11 +605,13 @@ fk_status fk_assign_static(const void* X, const void* C, int32_t* assign, float*
     hipStream_t s = (hipStream_t)stream;
     if (t == FK_F32) return launch_assign(g, X, C, nullptr, assign, min_dist, s);   // no scratch at all
     // (the size limit holds for every shape, whether or not its kernel needs the scratch)
-    const size_t frag_bytes = (size_t)B * g.ktiles * g.dchunks * 64 * 16;
+    // (counted in the chunks of the header's table, of which the layout takes no more)
+    const int c = g.d <= 32 ? 2 : g.d <= 64 ? 4 : g.d <= 128 ? 8 : g.d <= 256 ? 16 : 32;
+    const size_t frag_bytes = (size_t)B * g.ktiles * c * 64 * 16;
     const size_t bias_bytes = (size_t)B * g.ktiles * 32 * 4;
     if (frag_bytes > kStaticFragBytes || bias_bytes > kStaticBiasBytes) {
         set_error("%s: centroids too large for the static scratch: B*ceil(K/32)*%d KiB = %zu bytes, limit %zu",
-                  fn, g.dchunks, frag_bytes, kStaticFragBytes);
+                  fn, c, frag_bytes, kStaticFragBytes);
         return FK_EWORKSPACE;
     }
     if (assign_few_takes_rows(g)) return launch_assign_rows(g, X, C, assign, min_dist, s);

@@ -337,19 +337,19 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_kernel(
 }
 
 // ------------------------------------------------------------------------------------
-// Wide features (128 < d <= 512; DCH = 16 or 32 chunks of 16).  Same sweep as above with one
-// 32-point tile per wave, so that a point's features still fit the register file (4*DCH
-// VGPRs), and LDS stages of 16 chunks: a whole centroid tile per stage for DCH = 16, half a
-// tile for DCH = 32 (the MFMA chain of a tile then runs across two stages).
+// Wide features (128 < d <= 512; DCH = 10, 12, 14, 16, 20, 24 or 32 chunks of 16).  Same sweep as above with
+// one 32-point tile per wave, so that a point's features still fit the register file (4*DCH
+// VGPRs), and LDS stages of up to 16 chunks: a whole centroid tile per stage up to DCH = 16, half a
+// tile beyond (the MFMA chain of a tile then runs across two stages).
 template <bool BF, int DCH, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void assign_mfma_wide_kernel(
     const uint16_t* __restrict__ X, const uintx4* __restrict__ c_frag,
     const float* __restrict__ c_bias, int32_t* __restrict__ assign,
     float* __restrict__ min_dist, int64_t N, int d, int len, int K, int ktiles) {
-    constexpr int SC = 16;                  // chunks (1 KiB pieces) per stage
-    constexpr int SPT = DCH / SC;           // stages per centroid tile
+    constexpr int SPT = DCH <= 16 ? 1 : 2;  // stages per centroid tile
+    constexpr int SC = DCH / SPT;           // chunks (1 KiB pieces) per stage
     constexpr int kThreads = WAVES * 64;
-    static_assert(DCH % SC == 0 && SC % WAVES == 0 && kThreads >= 32, "stage geometry");
+    static_assert(DCH % SC == 0 && kThreads >= 32, "stage geometry");
     __shared__ uintx4 sfrag[2][SC * 64];
     __shared__ float sbias[2][32];
 
@@ -367,9 +367,9 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_wide_kernel(
 
     auto fetch = [&](int st, int buf) -> float {
 #pragma unroll
-        for (int q = 0; q < SC / WAVES; ++q) {
+        for (int q = 0; q < (SC + WAVES - 1) / WAVES; ++q) {
             const int pc = q * WAVES + wave;                       // wave-uniform
-            copy16_to_lds(c_frag + ((size_t)(st * SC + pc) * 64 + lane), &sfrag[buf][pc * 64]);
+            if (SC % WAVES == 0 || pc < SC) copy16_to_lds(c_frag + ((size_t)(st * SC + pc) * 64 + lane), &sfrag[buf][pc * 64]);
         }
         float bv = kPadBias;
         if (tid < 32) bv = c_bias[(st / SPT) * 32 + tid];
@@ -1110,7 +1110,7 @@ static FewForm choose_few(const Geometry& g, bool have_rows) {
     }
     if (t <= 2 * U) {
         if (dch > 16) return c >= 8 ? kFewOne : kFewNone;
-        if (dch == 16) return c >= 32 ? kFewTwo8 : c >= 2 ? kFewOne : kFewNone;
+        if (dch > 8) return c >= 32 ? kFewTwo8 : c >= 2 ? kFewOne : kFewNone;
         if (c < (dch == 2 ? 16 : 8)) return kFewNone;
         return c >= 32 ? kFewTwo16 : kFewTwo8;
     }
@@ -1145,7 +1145,8 @@ static fk_status launch_few(const Geometry& g, FewForm form, const void* X, cons
                             int32_t* assign, float* min_dist, hipStream_t s) {
     // as many waves as 160 KiB of LDS hold a tile of rows each for; 8 where registers are the limit
     constexpr int kRowsWaves = DCH <= 8 ? 16 : DCH <= 16 ? 8 : 3, kWaves = DCH <= 8 ? 16 : 8;
-    if (form == kFewRows) return launch_few_w<BF, DCH, kRowsWaves, false, 1>(g, X, C, nullptr, assign, min_dist, s);
+    if constexpr (DCH <= 8 || DCH == 16 || DCH == 32)
+        if (form == kFewRows) return launch_few_w<BF, DCH, kRowsWaves, false, 1>(g, X, C, nullptr, assign, min_dist, s);
     if constexpr (DCH <= 16) {
         if (form == kFewTwo8) return launch_few_w<BF, DCH, 8, true, 2>(g, X, C, bias, assign, min_dist, s);
         if (form == kFewTwo16) return launch_few_w<BF, DCH, kWaves, true, 2>(g, X, C, bias, assign, min_dist, s);
@@ -1160,7 +1161,10 @@ fk_status launch_assign_rows(const Geometry& g, const void* X, const void* C, in
     case DCH:                                                                                    \
         return bf ? launch_few<true, DCH>(g, kFewRows, X, C, nullptr, assign, min_dist, s)       \
                   : launch_few<false, DCH>(g, kFewRows, X, C, nullptr, assign, min_dist, s)
-    switch (g.dchunks) { FK_FEW(2); FK_FEW(4); FK_FEW(8); FK_FEW(16); FK_FEW(32); }
+    // (rows have no layout: any kernel that is wide enough will do)
+    switch (g.dchunks <= 8 ? g.dchunks : g.dchunks <= 16 ? 16 : 32) {
+        FK_FEW(2); FK_FEW(4); FK_FEW(8); FK_FEW(16); FK_FEW(32);
+    }
 #undef FK_FEW
     set_error("assign: no kernel for %d feature chunks", g.dchunks);
     return FK_EUNSUPPORTED;
@@ -1232,8 +1236,9 @@ static fk_status launch_mfma_d(const Geometry& g, const void* X, const void* fra
         case 2: return launch_mfma<BF, 2>(g, X, frag, bias, assign, min_dist, s);
         case 4: return launch_mfma<BF, 4>(g, X, frag, bias, assign, min_dist, s);
         case 8: return launch_mfma<BF, 8>(g, X, frag, bias, assign, min_dist, s);
-        case 16: return launch_mfma_wide<BF, 16>(g, X, frag, bias, assign, min_dist, s);
-        case 32: return launch_mfma_wide<BF, 32>(g, X, frag, bias, assign, min_dist, s);
+#define FK_WIDE(DCH) case DCH: return launch_mfma_wide<BF, DCH>(g, X, frag, bias, assign, min_dist, s)
+        FK_WIDE(10); FK_WIDE(12); FK_WIDE(14); FK_WIDE(16); FK_WIDE(20); FK_WIDE(24); FK_WIDE(32);
+#undef FK_WIDE
     }
     set_error("assign: no kernel for %d feature chunks", g.dchunks);
     return FK_EUNSUPPORTED;

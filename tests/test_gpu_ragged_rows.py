@@ -41,3 +41,21 @@ def test_ragged_rows_equal_zero_padded_rows(dtype, B, N, d, K):
         finally:
             fk.fk_set_option("fused_update", -1)
         assert torch.equal(u[0], v[0]) and torch.equal(u[1], v[1]) and torch.equal(c, cp[..., :d]) and torch.equal(u[2], v[2][..., :d])
+
+
+@pytest.mark.parametrize("N", [500, 9000, 140000])
+@pytest.mark.parametrize("d", [130, 160, 180, 192, 210, 224, 250, 300, 320, 370, 400])
+def test_every_compiled_width_equals_zero_padded_rows(d, N):
+    """Rows between 128 and 512 features take kernels for 10, 12, 14, 16, 20, 24 or 32 chunks of 16: the chunks
+    that a wider kernel multiplies on top are zeros and change no bit."""
+    g = torch.Generator().manual_seed(N + d)
+    X, C = (3 * torch.randn((1, n, d), generator=g).half().to(DEV) for n in (N, 400))
+    wide = [F.pad(t, (0, 512 - d)) for t in (X, C)]
+    for u, v in zip(fk.fk_assign(X, C, min_dist=True), fk.fk_assign(*wide, min_dist=True)):
+        assert torch.equal(u, v)
+    c, cw = X[:, :400].float().contiguous(), wide[0][:, :400].float().contiguous()
+    u, v = fk.fk_lloyd_iter(X, c, 1), fk.fk_lloyd_iter(wide[0], cw, 1)
+    assert torch.equal(u[0], v[0]) and torch.equal(u[1], v[1])
+    # how a wave splits a segment's rows depends on the row width: the same n terms in two orders, each
+    # good to n 2^-24 of their largest
+    assert ((c - cw[..., :d]).abs() <= 2 * u[1].amax() * 2.0 ** -24 * X.abs().amax().float()).all()
