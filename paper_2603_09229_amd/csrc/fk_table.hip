@@ -38,7 +38,9 @@ typedef short shortx4 __attribute__((ext_vector_type(4)));
 // BF: bf16 (else fp16).  DCH: feature chunks of 16 per point (2, 4 or 8).
 // Dynamic LDS: centroid fragments [ktiles][DCH][64] x 16 B | batch rows [256][d/8] x 16 B |
 // bias [ktiles][32] floats | cluster ids [256] ints | per-wave point lists [8][256 + 32] ints.
-template <bool BF, int DCH>
+// RAGGED: rows whose length is no multiple of 8, read as they are stored (the code that settles their
+// last pieces costs the others 1% when it is only skipped).
+template <bool BF, int DCH, bool RAGGED>
 __global__ __launch_bounds__(512) void table_update_kernel(
     const uint16_t* __restrict__ X, const uintx4* __restrict__ c_frag,
     const float* __restrict__ c_bias, int32_t* __restrict__ assign, float* __restrict__ partial,
@@ -78,7 +80,7 @@ __global__ __launch_bounds__(512) void table_update_kernel(
 #pragma unroll
         for (int i = 0; i < DCH; ++i) {
             const int64_t point = min(batch * kRows + i * kRowsPerRound + my_row0, N - 1);
-            if (piece_live) xn[i] = raw_piece16(X + (size_t)point * len, my_piece * 8, len);
+            if (piece_live) xn[i] = RAGGED ? raw_piece16(X + (size_t)point * len, my_piece * 8, len) : *(const uintx4*)(X + (size_t)point * d + my_piece * 8);
         }
     };
 
@@ -108,7 +110,7 @@ __global__ __launch_bounds__(512) void table_update_kernel(
         // 1. the prefetched rows go to LDS, swizzled so that the 16 lanes that share a piece
         //    index hit 16 different bank groups
         if (piece_live) {
-            if (len & 7) {
+            if constexpr (RAGGED) {
 #pragma unroll
                 for (int i = 0; i < DCH; ++i) xn[i] = settle16(xn[i], my_piece * 8, len);
             }
@@ -278,10 +280,10 @@ __global__ __launch_bounds__(512) void table_update_kernel(
 // ------------------------------------------------------------------------------------
 bool table_update_enabled(const Geometry& g) { return g.table_grid_cap > 0 && fused_update_allowed(); }
 
-template <bool BF, int DCH>
-static fk_status launch_table_update_t(const Geometry& g, const Workspace& w, const void* X,
+template <bool BF, int DCH, bool RAGGED>
+static fk_status launch_table_update_r(const Geometry& g, const Workspace& w, const void* X,
                                        int32_t* assign, int* grid_out, hipStream_t s) {
-    auto kern = table_update_kernel<BF, DCH>;
+    auto kern = table_update_kernel<BF, DCH, RAGGED>;
     const size_t lds = (size_t)g.ktiles * DCH * 1024 + (size_t)256 * g.d * 2 + (size_t)g.ktiles * 128 +
                        256 * 4 + 8 * (256 + 32) * 4;
     static PerDeviceInt attr_set;
@@ -303,6 +305,13 @@ static fk_status launch_table_update_t(const Geometry& g, const Workspace& w, co
     FK_HIP(hipGetLastError());
     *grid_out = (int)G;
     return FK_OK;
+}
+
+template <bool BF, int DCH>
+static fk_status launch_table_update_t(const Geometry& g, const Workspace& w, const void* X, int32_t* assign,
+                                       int* grid_out, hipStream_t s) {
+    return g.len == g.d ? launch_table_update_r<BF, DCH, false>(g, w, X, assign, grid_out, s)
+                        : launch_table_update_r<BF, DCH, true>(g, w, X, assign, grid_out, s);
 }
 
 fk_status launch_table_update(const Geometry& g, const Workspace& w, const void* X, int32_t* assign,
