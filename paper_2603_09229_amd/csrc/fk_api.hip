@@ -90,6 +90,7 @@ bool make_geometry(int B, int64_t N, int d_user, int K, fk_dtype t, Geometry* g)
         g->dchunks = c <= 8 ? c : c > 24 && c <= 28 ? 28 : g->dchunks;
     }
     g->ktiles = (int)cdiv(K, 32);
+    g->one_pass = fused_update_allowed();
     int nbmax;
     if (K <= 2048) {
         g->sort_passes = 1;
@@ -348,7 +349,8 @@ static fk_status run_stream_update(const Geometry& g, const Workspace& w, const 
 }
 
 // Whether fk_update / fk_lloyd_iter copy the rows into zero-padded ones for this call (see
-// needs_padded_rows; the one-pass update for few clusters may be switched off).
+// needs_padded_rows; the one-pass update for few clusters may be switched off).  Every later choice
+// of the call rests on the same g.one_pass.
 static bool rows_are_padded(const Geometry& g) {
     return g.d != g.d_user && (g.d_user < 8 || fused_update_enabled(g));
 }

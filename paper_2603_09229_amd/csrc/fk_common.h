@@ -72,6 +72,10 @@ struct Geometry {
     fk_dtype t;
     int dchunks;      // ceil(d / 16)
     int ktiles;       // ceil(K / 32)
+    bool one_pass;    // the one-pass updates may be taken: the process-wide option as it stood when this
+                      // was filled in.  A call asks it once: whether rows are padded and which kernel
+                      // reads them must follow from one answer (the kernel for few clusters reads rows
+                      // of width d, past the end of X where they were not padded)
     // counting sort
     int sort_bits;    // bits of a cluster id, ceil(log2 K), >= 1
     int sort_passes;  // 1 when K <= 2048, else 2
@@ -198,7 +202,7 @@ fk_status launch_finalize(const Geometry& g, const Workspace& w, const int32_t* 
 fk_status launch_stream_update(const Geometry& g, const Workspace& w, const void* X,
                                int32_t* assign, bool compute_assign, int* grid_out,
                                hipStream_t s);
-bool fused_update_enabled(const Geometry& g);
+inline bool fused_update_enabled(const Geometry& g) { return g.fused_grid_cap > 0 && g.one_pass; }
 void set_fused_update_option(int v);       // 0 = never, otherwise whenever the shape allows
 bool fused_update_allowed();               // the option above is not 0
 
@@ -207,14 +211,14 @@ bool fused_update_allowed();               // the option above is not 0
 // leaves w.partial / w.wg_counts as launch_stream_update does.
 fk_status launch_table_update(const Geometry& g, const Workspace& w, const void* X,
                               int32_t* assign, int* grid_out, hipStream_t s);
-bool table_update_enabled(const Geometry& g);
+inline bool table_update_enabled(const Geometry& g) { return g.table_grid_cap > 0 && g.one_pass; }
 
 // Small fp32 problems, up to 64 clusters: assignment and sums in one pass over X (see
 // fk_f32_fused.hip).  C_f32 [B,K,d] are the centroids to assign against.  Computes and writes the
 // assignment; leaves w.partial / w.wg_counts as launch_stream_update does.
 fk_status launch_f32_update(const Geometry& g, const Workspace& w, const void* X,
                             const float* C_f32, int32_t* assign, int* grid_out, hipStream_t s);
-bool f32_update_enabled(const Geometry& g);
+inline bool f32_update_enabled(const Geometry& g) { return g.f32_grid_cap > 0 && g.one_pass; }
 
 // Row re-layout for widths that are not a multiple of 8: dst[r][j] = j < d_src ? src[r][j] : 0
 // for j < d_dst (padding, d_dst > d_src) or dst[r][j] = src[r][j] for j < d_dst (un-padding,

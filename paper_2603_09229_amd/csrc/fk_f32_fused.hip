@@ -174,8 +174,6 @@ __global__ __launch_bounds__(WAVES * 64) void f32_update_kernel(
 }
 
 // ------------------------------------------------------------------------------------
-bool f32_update_enabled(const Geometry& g) { return g.f32_grid_cap > 0 && fused_update_allowed(); }
-
 template <int DMAX, int WAVES>
 static fk_status launch_f32_update_t(const Geometry& g, const Workspace& w, const float* X,
                                      const float* C, int32_t* assign, int* grid_out,

@@ -286,8 +286,6 @@ void set_fused_update_option(int v) { g_fused_option.store(v, std::memory_order_
 
 bool fused_update_allowed() { return g_fused_option.load(std::memory_order_relaxed) != 0; }
 
-bool fused_update_enabled(const Geometry& g) { return g.fused_grid_cap > 0 && fused_update_allowed(); }
-
 template <bool BF, int DCH, bool ASSIGN>
 static fk_status launch_stream_update_t(const Geometry& g, const Workspace& w, const void* X,
                                         int32_t* assign, int* grid_out, hipStream_t s) {

@@ -278,8 +278,6 @@ __global__ __launch_bounds__(512) void table_update_kernel(
 }
 
 // ------------------------------------------------------------------------------------
-bool table_update_enabled(const Geometry& g) { return g.table_grid_cap > 0 && fused_update_allowed(); }
-
 template <bool BF, int DCH, bool RAGGED>
 static fk_status launch_table_update_r(const Geometry& g, const Workspace& w, const void* X,
                                        int32_t* assign, int* grid_out, hipStream_t s) {
