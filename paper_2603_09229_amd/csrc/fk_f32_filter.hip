@@ -510,19 +510,19 @@ __global__ __launch_bounds__(256) void f32_distance_kernel(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ assign,
     float* __restrict__ min_dist, int64_t N, int len, int K) {
     const int b = blockIdx.y, l = threadIdx.x & 15;
-    const int64_t i = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4);
-    if (i >= N) return;
-    const float* x = X + ((size_t)b * N + i) * len;
-    const float* c = C + ((size_t)b * K + assign[(size_t)b * N + i]) * len;
-    float s = 0.f;
-    for (int j = l * 4; j < len; j += 64) {
-        const floatx4 u = row_piece32(x, j, len), v = row_piece32(c, j, len);
+    for (int64_t i = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4); i < N; i += (int64_t)gridDim.x * 16) {
+        const float* x = X + ((size_t)b * N + i) * len;
+        const float* c = C + ((size_t)b * K + assign[(size_t)b * N + i]) * len;
+        float s = 0.f;
+        for (int j = l * 4; j < len; j += 64) {
+            const floatx4 u = row_piece32(x, j, len), v = row_piece32(c, j, len);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { const float t = u[e] - v[e]; s = fmaf(t, t, s); }
+            for (int e = 0; e < 4; ++e) { const float t = u[e] - v[e]; s = fmaf(t, t, s); }
+        }
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o);   // (the 16 lanes of a point leave together)
+        if (l == 0) min_dist[(size_t)b * N + i] = s;
     }
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o);
-    if (l == 0) min_dist[(size_t)b * N + i] = s;
 }
 
 // ------------------------------------------------------------------------------------
@@ -541,6 +541,8 @@ void set_f32_filter_option(int v) { g_filter_option.store(v, std::memory_order_r
 bool f32_filter_enabled(const Geometry& g) {
     const int opt = g_filter_option.load(std::memory_order_relaxed);
     if (g.t != FK_F32 || opt == 0) return false;
+    // two threads per point, and a launch dimension holds fewer than 2^32
+    if (cdiv(g.N, 256) * 512 > (int64_t)UINT32_MAX) return false;
     if (opt > 0) return true;
     const int64_t points = (int64_t)g.B * g.N;
     if (g.d > 128) return g.K > 16 || points <= ((int64_t)1 << 16);
@@ -584,7 +586,7 @@ fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* 
                        w.f32_list_len, assign, g.N, g.d, g.len, g.K, f32_direct_is_split(g) ? g.K - 1 : 0);
     FK_HIP(hipGetLastError());
     if (min_dist) {
-        hipLaunchKernelGGL(f32_distance_kernel, dim3((unsigned)cdiv(g.N, 16), g.B), dim3(256), 0, s, X, C, assign,
+        hipLaunchKernelGGL(f32_distance_kernel, dim3((unsigned)f32_distance_blocks(g.N), g.B), dim3(256), 0, s, X, C, assign,
                            min_dist, g.N, g.len, g.K);
         FK_HIP(hipGetLastError());
     }

@@ -26,8 +26,25 @@ static int option_is_read_once() {
     return fk_set_option("fused_update", -1) == FK_OK ? 0 : 1;
 }
 
+// A launch dimension holds fewer than 2^32 threads.
+static int launches_fit() {
+    for (int64_t N : {(int64_t)1, (int64_t)16, (int64_t)17, (int64_t)1 << 24, ((int64_t)1 << 28) - 16, (int64_t)1 << 28, ((int64_t)1 << 31) - 1}) {
+        CHECK(fk::f32_distance_blocks(N) >= 1 && fk::f32_distance_blocks(N) * 256 <= UINT32_MAX);
+        CHECK(N > ((int64_t)1 << 24) || fk::f32_distance_blocks(N) * 16 >= N);   // one group each where that fits
+    }
+    for (int option : {-1, 1})
+        for (int64_t below : {1, 255, 256, 257}) {
+            fk::Geometry g;
+            CHECK(fk_set_option("assign_f32_filter", option) == FK_OK);
+            CHECK(fk::make_geometry(1, ((int64_t)1 << 31) - below, 8, 64, FK_F32, &g));
+            CHECK(fk::f32_filter_enabled(g) == (below >= 256));
+            CHECK(!fk::f32_filter_enabled(g) || fk::cdiv(g.N, 256) * 512 <= UINT32_MAX);
+        }
+    return fk_set_option("assign_f32_filter", -1) == FK_OK ? 0 : 1;
+}
+
 int main() {
-    if (option_is_read_once()) return 1;
+    if (option_is_read_once() || launches_fit()) return 1;
     printf("host decisions ok\n");
     return 0;
 }

@@ -59,6 +59,18 @@ def test_filter_gives_the_direct_answer(both, kind, B, N, d, K):
     assert ((m1 - m0).abs()[fine] <= d * 2.0 ** -23 * m0[fine] + 1e-37).all()
 
 
+def test_distances_of_more_points_than_one_launch_dimension_has_threads_for(both):
+    """2^28 points at 16 threads a point are 2^32 threads: the distance pass takes several groups each."""
+    N = (1 << 28) + 5
+    g = torch.Generator(device=DEV).manual_seed(3)
+    X = torch.empty((1, N, 8), device=DEV).normal_(generator=g)
+    C = X[:, :24].clone()
+    (a1, m1), (a0, m0) = both(X, C)
+    assert torch.equal(a1, a0)
+    m1 -= m0
+    assert (m1.abs_() <= m0.mul_(8 * 2.0 ** -23).add_(1e-37)).all()
+
+
 def test_filtered_iterations_equal_direct_ones():
     g = torch.Generator().manual_seed(5)
     X = (torch.randn((2, 20011, 100), generator=g) + 3 * torch.randn((2, 1, 100), generator=g)).to(DEV)
