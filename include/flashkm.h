@@ -172,17 +172,19 @@ fk_status fk_lloyd_iter(const void* X, float* C_f32, void* C_lp, int32_t* assign
  *              memory included, is refused with FK_EINVAL).  Chunks of `chunk_rows` rows are
  *              copied with hipMemcpyAsync on a side stream owned by the call into two
  *              device buffers carved from dev_ws while the previous chunk is assigned and
- *              reduced on `stream`.  Odd iterations take the chunks in reverse order and reuse the
- *              two that are still in the buffers.
+ *              reduced on `stream`.  An iteration after the first reuses the two chunks that are still
+ *              in the buffers.
  *   C_f32      device in/out, [K,d] float.  The centroids are frozen during an iteration:
  *              sums and counts accumulate over the chunks, one normalisation per iteration
- *              (same result as the in-core path up to fp32 summation order).
+ *              (same result as the in-core path up to fp32 summation order, and a call of n
+ *              iterations gives the bits of n calls of one with the same chunk_rows).
  *   assign     device out or NULL, [N] int32 (last iteration)
  *   counts     device out, [K] int32
  *   chunk_rows rows per chunk; 0 = the largest that fits dev_ws_bytes
  *   dev_ws     device, dev_ws_bytes bytes: the whole device footprint of the call besides
  *              C_f32 / assign / counts.  fk_ooc_workspace_bytes gives the size needed for a
- *              given chunk_rows.
+ *              given chunk_rows.  (With up to 2*K*(d+1)*4 bytes less, rounded up, the call is still
+ *              served, but every iteration copies every chunk.)
  * Blocks the calling thread until all iterations are done.
  */
 fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_t* counts,

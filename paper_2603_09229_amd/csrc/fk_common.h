@@ -190,6 +190,9 @@ struct FinalizeArgs {
     int32_t* counts;     // [B,K]
     float* sums;         // [B,K,d] (needed when accumulate || !normalise)
     bool accumulate;     // add onto sums / counts already there
+    const float* late_sums = nullptr;      // [late][B,K,d], [late][B,K]: parts to add after these ones,
+    const int32_t* late_counts = nullptr;  // one after the other
+    int late = 0;
     bool normalise;      // divide and write centroids
 };
 // With wg_counts (few-cluster path) cluster k owns partial rows [k*G, (k+1)*G) and the counts

@@ -5,13 +5,15 @@
 // and segment reduction on the other buffer.  Events order the two streams:
 //   ready[i]  copy into buffer i finished      (compute waits)
 //   freed[i]  compute on buffer i finished     (the next copy into i waits)
-// Every other iteration takes the chunks in the opposite order: it starts with the two that are
-// still in the buffers, which saves two copies per iteration after the first (all of them with at
-// most two chunks).  The call is bound by its copies below about K = 3000 (57 GB/s from the host: 8
-// chunks of 2^18 x 128 fp16, K = 1024, two iterations: 19.5 ms with 16 copies, 17.3 with 14).
+// An iteration after the first starts with the two chunks that are still in the buffers, which saves
+// two copies per iteration (all of them with at most two chunks).  The call is bound by its copies
+// below about K = 3000 (57 GB/s from the host: 8 chunks of 2^18 x 128 fp16, K = 1024, two
+// iterations: 19.5 ms with 16 copies, 17.3 with 14).
 // The centroids are frozen for the whole iteration; per-chunk sums and counts are added
 // onto running totals and normalised once after the last chunk, so the result is the
-// in-core one up to fp32 summation order.
+// in-core one up to fp32 summation order.  They are added in the order of the chunks whatever the
+// order in which the chunks are taken -- those of the chunks taken early wait in two arrays of their
+// own until their turn -- so that a call of n iterations gives the bits of n calls of one.
 #include "fk_common.h"
 
 namespace fk {
@@ -20,7 +22,10 @@ struct OocLayout {
     size_t chunk_bytes;   // one chunk buffer
     size_t core_bytes;    // in-core workspace for one chunk
     size_t assign_bytes;  // per-chunk assignment buffer (used when the caller keeps none)
-    size_t total;
+    size_t total;         // what the call cannot do without
+    size_t late_sum_bytes, late_count_bytes;   // sums and counts of a chunk taken early
+    size_t with_late;     // ... with room for two of them: the size that is asked for.  In less room the
+                          // chunks are taken in order and copied in every iteration
 };
 
 static bool ooc_layout(int64_t chunk_rows, int d, int K, fk_dtype t, OocLayout* L, Geometry* g) {
@@ -31,6 +36,9 @@ static bool ooc_layout(int64_t chunk_rows, int d, int K, fk_dtype t, OocLayout* 
     L->core_bytes = align_up(carve(*g, nullptr, false).bytes, 256);
     L->assign_bytes = align_up((size_t)chunk_rows * 4, 256);
     L->total = 2 * L->chunk_bytes + L->core_bytes + L->assign_bytes;
+    L->late_sum_bytes = (size_t)K * g->d * 4;
+    L->late_count_bytes = (size_t)K * 4;
+    L->with_late = L->total + align_up(2 * L->late_sum_bytes, 256) + align_up(2 * L->late_count_bytes, 256);
     return true;
 }
 
@@ -44,7 +52,7 @@ size_t fk_ooc_workspace_bytes(int64_t chunk_rows, int d, int K, fk_dtype t) {
     OocLayout L;
     Geometry g;
     if (chunk_rows < 1 || !ooc_layout(chunk_rows, d, K, t, &L, &g)) return 0;
-    return L.total;
+    return L.with_late;
 }
 
 fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_t* counts,
@@ -87,13 +95,18 @@ fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_
     if (chunk_rows == 0) {
         // largest multiple of 1024 rows (or all of N) whose footprint fits
         const int64_t unit = 1024;
-        int64_t lo = 0, hi = cdiv(N, unit);
-        while (lo < hi) {
-            const int64_t mid = (lo + hi + 1) / 2;
-            const int64_t rows = mid * unit < N ? mid * unit : N;
-            if (ooc_layout(rows, d, K, t, &L, &gfull) && L.total <= dev_ws_bytes) lo = mid;
-            else hi = mid - 1;
-        }
+        auto largest = [&](bool late) {
+            int64_t lo = 0, hi = cdiv(N, unit);
+            while (lo < hi) {
+                const int64_t mid = (lo + hi + 1) / 2;
+                const int64_t rows = mid * unit < N ? mid * unit : N;
+                if (ooc_layout(rows, d, K, t, &L, &gfull) && (late ? L.with_late : L.total) <= dev_ws_bytes) lo = mid;
+                else hi = mid - 1;
+            }
+            return lo;
+        };
+        int64_t lo = largest(true);
+        if (lo == 0) lo = largest(false);
         if (lo == 0) {
             set_error("fk_lloyd_ooc: dev_ws of %zu bytes cannot hold even a 1024-row chunk", dev_ws_bytes);
             return FK_EWORKSPACE;
@@ -117,6 +130,9 @@ fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_
     void* core = base + 2 * L.chunk_bytes;
     int32_t* chunk_assign = (int32_t*)(base + 2 * L.chunk_bytes + L.core_bytes);
     const Workspace wfull = carve(gfull, core, false);
+    const bool early = L.with_late <= dev_ws_bytes;
+    float* const late_sums = (float*)(base + L.total);
+    int32_t* const late_counts = (int32_t*)(base + L.total + align_up(2 * L.late_sum_bytes, 256));
     const size_t row_bytes = (size_t)d * elem_size(t);                 // a row on the host
     const size_t dev_row_bytes = (size_t)gfull.d * elem_size(t);       // a padded row in a chunk buffer
     // Rows arrive as they are stored and the kernels read them so: a pitched copy moves a row at a
@@ -173,8 +189,16 @@ fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_
     for (int it = 0; it < iters; ++it) {
         OOC_TRY(launch_round_centroids(gfull, C_f32, t == FK_F32 ? nullptr : wfull.c_lp,
                                        wfull.c_frag, wfull.c_bias, cs));
+        // the chunks [first, first + count) are in the buffers and taken before their turn, the one whose
+        // buffer chunk 0 goes to (the even one) first
+        int64_t first = 0, count = 0;
+        if (early && it > 0 && nchunks > 2) {
+            first = held[0] < held[1] ? held[0] : held[1];
+            count = first > 0 && held[0] + held[1] == 2 * first + 1 ? 2 : 0;
+        }
         for (int64_t at = 0; at < nchunks; ++at) {
-            const int64_t c = (it & 1) ? nchunks - 1 - at : at;
+            const bool waits = at < count;       // its sums wait for their turn
+            const int64_t c = waits ? held[at] : at - count < first || count == 0 ? at - count : at;
             const int bi = (int)(c & 1);
             const int64_t r0 = c * chunk_rows;
             const int64_t rows = (N - r0) < chunk_rows ? (N - r0) : chunk_rows;
@@ -212,10 +236,15 @@ fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_
             fa.C_out_lp = nullptr;
             fa.c_frag = nullptr;
             fa.c_bias = nullptr;
-            fa.counts = counts;
-            fa.sums = wfull.sums;
-            fa.accumulate = at > 0;
+            fa.counts = waits ? late_counts + (c - first) * K : counts;
+            fa.sums = waits ? late_sums + (c - first) * K * gfull.d : wfull.sums;
+            fa.accumulate = !waits && c > 0;
             fa.normalise = (at + 1 == nchunks);
+            if (count > 0 && c == first - 1) {
+                fa.late_sums = late_sums;
+                fa.late_counts = late_counts;
+                fa.late = (int)count;
+            }
             OOC_TRY(launch_finalize(g, w, w.seg_off, w.item_off, fa, cs));
             OOC_HIP(hipEventRecord(freed[bi], cs));
             used[bi] = true;

@@ -152,7 +152,8 @@ __global__ __launch_bounds__(1024) void finalize_kernel(
     uint16_t* __restrict__ C_lp_out, float* __restrict__ C_lp_f32_out,
     uint16_t* __restrict__ c_frag, float* __restrict__ c_bias, int32_t* __restrict__ counts,
     float* __restrict__ sums, int d, int len, int K, int64_t max_items, int ktiles, int dch,
-    int accumulate, int normalise, int bf, const int32_t* __restrict__ wg_counts, int G) {
+    int accumulate, int normalise, int bf, const int32_t* __restrict__ wg_counts, int G,
+    const float* __restrict__ late_sums, const int32_t* __restrict__ late_counts, int late) {
     // dynamic LDS: 4 floats per thread for the row sums, then d floats for the squared entries
     // (a fixed worst-case array would cap the small workgroups of many-cluster shapes at a
     // few per CU)
@@ -216,11 +217,13 @@ __global__ __launch_bounds__(1024) void finalize_kernel(
     } else {
         n += seg_off[k + 1] - seg_off[k];
     }
+    for (int q = 0; q < late; ++q) n += late_counts[((size_t)q * gridDim.y + b) * K + k];
     for (int j = tid; j < d; j += T) {
         float s = 0.f;
         for (int q = 0; q < sums_left; ++q) s += red[q * dpow + j];   // fixed order
         const size_t o = ((size_t)b * K + k) * d + j;
         if (accumulate) s += sums[o];
+        for (int q = 0; q < late; ++q) s += late_sums[(size_t)q * gridDim.y * K * d + o];
         if (sums) sums[o] = s;
         if (normalise) {
             // the caller's rows have no padding; past their end everything is zero
@@ -310,7 +313,8 @@ fk_status launch_finalize(const Geometry& g, const Workspace& w, const int32_t* 
     hipLaunchKernelGGL(finalize_kernel, dim3(g.K, g.B), dim3(threads), lds, s, w.partial, seg_off,
                        item_off, a.C_prev_f32, a.C_out_f32, lp16, lp32, frag, a.c_bias, a.counts,
                        a.sums, g.d, g.len, g.K, g.max_items, g.ktiles, g.dchunks, a.accumulate ? 1 : 0,
-                       a.normalise ? 1 : 0, g.t == FK_BF16 ? 1 : 0, wg_counts, wg_per_cluster);
+                       a.normalise ? 1 : 0, g.t == FK_BF16 ? 1 : 0, wg_counts, wg_per_cluster,
+                       a.late_sums, a.late_counts, a.late);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }
