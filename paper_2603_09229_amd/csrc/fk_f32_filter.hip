@@ -505,7 +505,8 @@ __global__ __launch_bounds__(512, 4) void assign_f32_list_kernel(
         list_by_thread<DMAX == 0 ? 32 : DMAX>(X, C, list, len, assign, d, row_len, K, none, xs);
 }
 
-// min_dist[i] = |x_i - c_a(i)|^2 by direct differences: 16 lanes a point, whole rows per load
+// min_dist[i] = |x_i - c_a(i)|^2 by direct differences: 16 lanes a point, whole rows per load.  Infinity
+// where it is not finite, as in the direct kernels, whose minimum starts there.
 __global__ __launch_bounds__(256) void f32_distance_kernel(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ assign,
     float* __restrict__ min_dist, int64_t N, int len, int K) {
@@ -521,7 +522,7 @@ __global__ __launch_bounds__(256) void f32_distance_kernel(
         }
 #pragma unroll
         for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o);   // (the 16 lanes of a point leave together)
-        if (l == 0) min_dist[(size_t)b * N + i] = s;
+        if (l == 0) min_dist[(size_t)b * N + i] = s < INFINITY ? s : INFINITY;
     }
 }
 

@@ -59,6 +59,23 @@ def test_filter_gives_the_direct_answer(both, kind, B, N, d, K):
     assert ((m1 - m0).abs()[fine] <= d * 2.0 ** -23 * m0[fine] + 1e-37).all()
 
 
+@pytest.mark.parametrize("N,d,K", [(3001, 64, 100), (1000, 96, 257), (700, 256, 97), (263000, 24, 40)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
+def test_what_is_not_finite_is_answered_as_by_the_direct_kernels(both, N, d, K, bad):
+    g = torch.Generator().manual_seed(N + d)
+    X = torch.randn((1, N, d), generator=g)
+    C = X[:, :K].clone()
+    X[0, N // 2, d // 2] = bad
+    C[0, 3, d - 1] = bad
+    C[0, K // 2] = bad
+    for x, c in ((X, X[:, :K]), (X, C), (C, C), (C, torch.full_like(C, bad))):
+        (a1, m1), (a0, m0) = both(x.to(DEV), c.contiguous().to(DEV))
+        assert torch.equal(a1, a0)
+        assert not m1.isnan().any() and torch.equal(m1.isinf(), m0.isinf())
+        fine = m0.isfinite()
+        assert ((m1 - m0).abs()[fine] <= d * 2.0 ** -23 * m0[fine] + 1e-37).all()
+
+
 def test_distances_of_more_points_than_one_launch_dimension_has_threads_for(both):
     """2^28 points at 16 threads a point are 2^32 threads: the distance pass takes several groups each."""
     N = (1 << 28) + 5
