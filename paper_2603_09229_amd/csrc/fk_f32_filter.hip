@@ -68,7 +68,9 @@ __device__ __forceinline__ void split8(const float (&v)[8], uintx4& hi, uintx4& 
 // the order  head, tail of chunk 0;  head, tail of chunk 1;  ...;  bias,  where the bias piece
 // holds u-bias -|c'|^2/2 + kappa |c'|^2 as three bf16 values (24 bits) in its first features, to
 // be multiplied by ones.  A row whose norm overflows gets zeros and a bias that always wins, with
-// c2 = inf, so that no point is ever certain of it; rows past K one that never wins.
+// c2 = inf, so that no point is ever certain of it; rows past K one that never wins.  Rows with a NaN
+// or an infinity get that too -- no distance to them is below infinity, where the direct form's minimum
+// starts -- and stay out of the mean: one such centroid would leave every point open.
 // Tile 0 also leaves the shift m and clears the instance's list length.
 // A few microseconds of dependent loads: the rows of the mean are asked for eight at a time and
 // the own rows before the mean is needed.
@@ -108,7 +110,7 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
 #pragma unroll
                 for (int i = 0; i < 8; ++i) v[i] = C[(size_t)((int64_t)min(i0 + i, rows - 1) * K / rows) * len + tid];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) s += i0 + i < rows ? v[i] : 0.f;
+                for (int i = 0; i < 8; ++i) s += i0 + i < rows && fabsf(v[i]) < INFINITY ? v[i] : 0.f;
             }
         s /= (float)rows;
         m[tid] = s;
@@ -122,29 +124,35 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
         const int l = g & 63, k = kt * 32 + (l & 31), j0 = (g >> 6) * 16 + (l >> 5) * 8;
         if (g < 64 * dch) {
             double ss = 0.0;
+            bool odd = false;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
+                odd |= !(fabsf(own[i][e]) < INFINITY);
                 own[i][e] = k < K && j0 < d ? own[i][e] - m[j0 + e] : 0.f;
                 ss += (double)own[i][e] * (double)own[i][e];
             }
-            part[l & 31][(g >> 6) * 2 + (l >> 5)] = ss;
+            part[l & 31][(g >> 6) * 2 + (l >> 5)] = odd ? -1.0 : ss;
         }
     }
     __syncthreads();
     if (tid < 64) {
         const int r = tid & 31, h = tid >> 5, k = kt * 32 + r;
         double n2 = 0.0;
-        for (int q = 0; q < 2 * dch; ++q) n2 += part[r][q];
-        const bool fine = n2 < 1e38;                         // false for NaN too
+        bool never = k >= K;
+        for (int q = 0; q < 2 * dch; ++q) {
+            never |= part[r][q] < 0.0;
+            n2 += part[r][q];
+        }
+        const bool fine = !never && n2 < 1e38;               // false for NaN too
         uint16_t p[3] = {kNever, 0, 0};
-        if (k < K && fine) {
+        if (fine) {
             double left = (-0.5 + (double)filter_kappa(width)) * n2;
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
                 p[q] = float_to_lp((float)left, true);
                 left -= (double)lp_to_float(p[q], true);
             }
-        } else if (k < K) {
+        } else if (!never) {
             p[0] = kAlways;
         }
         uintx4 v = {0u, 0u, 0u, 0u};
@@ -152,7 +160,7 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
             v[0] = (uint32_t)p[0] | ((uint32_t)p[1] << 16);
             v[1] = p[2];
             fits[r] = fine;
-            c2[((size_t)b * ktiles + kt) * 32 + r] = k < K ? (fine ? (float)(n2 * 1.000001) : INFINITY) : 0.f;
+            c2[((size_t)b * ktiles + kt) * 32 + r] = fine ? (float)(n2 * 1.000001) : never ? 0.f : INFINITY;
         }
         frag[2 * dch * 64 + tid] = v;
     }
