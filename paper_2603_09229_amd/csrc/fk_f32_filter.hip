@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
     float* __restrict__ shift, int32_t* __restrict__ list_len, int d, int len, int K, int ktiles, int dch) {
     __shared__ float m[512];
     __shared__ double part[32][65];
-    __shared__ int fits[32];
+    __shared__ int fits[32], odd_row[32];
     const int b = blockIdx.y, kt = blockIdx.x, tid = threadIdx.x;
     const int width = dch * 16;
     C += (size_t)b * K * len;
@@ -116,6 +116,7 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
         m[tid] = s;
         if (kt == 0) shift[(size_t)b * width + tid] = s;
     }
+    if (tid < 32) odd_row[tid] = 0;
     if (kt == 0 && tid == 0) list_len[b] = 0;
     __syncthreads();
 #pragma unroll
@@ -131,18 +132,16 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
                 own[i][e] = k < K && j0 < d ? own[i][e] - m[j0 + e] : 0.f;
                 ss += (double)own[i][e] * (double)own[i][e];
             }
-            part[l & 31][(g >> 6) * 2 + (l >> 5)] = odd ? -1.0 : ss;
+            part[l & 31][(g >> 6) * 2 + (l >> 5)] = ss;
+            if (odd) odd_row[l & 31] = 1;
         }
     }
     __syncthreads();
     if (tid < 64) {
         const int r = tid & 31, h = tid >> 5, k = kt * 32 + r;
         double n2 = 0.0;
-        bool never = k >= K;
-        for (int q = 0; q < 2 * dch; ++q) {
-            never |= part[r][q] < 0.0;
-            n2 += part[r][q];
-        }
+        for (int q = 0; q < 2 * dch; ++q) n2 += part[r][q];
+        const bool never = k >= K || odd_row[r] != 0;
         const bool fine = !never && n2 < 1e38;               // false for NaN too
         uint16_t p[3] = {kNever, 0, 0};
         if (fine) {
