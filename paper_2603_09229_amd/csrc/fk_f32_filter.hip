@@ -17,9 +17,11 @@
 //   xl.cl and the two remainders of the splits           <= 3 2^-18 |x||c|      <= 1.5 2^-18 S
 //   every one of the D + 16 additions of the chain xh.ch + bias, at most 2^-23 of a partial sum
 //   that is at most |x||c| (1 + 2^-7), plus |c|^2/2 in the last 16  <= (0.51 D + 20) 2^-23 S
+//   (measured: 16 of them, one MFMA, are off by at most 1.8 2^-23 of the sum of the magnitudes of
+//   their terms, and 7.5 2^-23 of the largest, over terms up to 2^46 apart, with and without signs)
 //   the 2 D additions of the small products, partial sums <= 2^-7 |x||c|       <= 0.01 D 2^-23 S
 //   adding the two accumulators, bias to 24 bits, rounding of x - m and c - m  <= 4 2^-23 S
-//   the four low bits of a score that carry its slot                          <= 1.01 2^-19 S
+//   the four low bits of a score that carry its slot           <= 15 2^-23 S = 0.94 2^-19 S
 // together kappa S with kappa = 2^-17 + (0.53 D + 24) 2^-23 (the first and last lines are below
 // 2^-17).  The |c'_k|^2 part of it is added to the score of k through its bias, so the scores
 // kept are upper bounds less kappa |x'|^2, and centroid 1 is certain when
@@ -338,13 +340,25 @@ __global__ __launch_bounds__(WAVES * 64) void assign_f32_filter_kernel(
     const bool certain = m1 - m2 > room + theta + 1e-30f;
     const bool mine = h == 0 && point < N;
     if (mine && certain) assign[point] = k;
+    // A place on the list for the whole workgroup at once: additions to one address take 10 ns each, and
+    // with many open points one per wave cost more than the sweep (2^20 points, all open: 330 us).
+    // (The last stage has been read; LDS of its own would cost a workgroup per compute unit at DCH = 2.)
+    int* opened = (int*)&stage[0][0];
+    int* list_at = opened + WAVES;
     const uint64_t open = __ballot(mine && !certain);
-    if (open) {
-        int base = 0;
-        if (lane == __builtin_ctzll(open)) base = atomicAdd(list_len + b, __popcll(open));
-        base = __shfl(base, __builtin_ctzll(open));
-        if (mine && !certain) list[base + __popcll(open & ((1ull << lane) - 1ull))] = (int32_t)point;
+    if (lane == 0) opened[wave] = __popcll(open);
+    __syncthreads();
+    int before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        const int c = opened[w];
+        before += w < wave ? c : 0;
+        all += c;
     }
+    if (all == 0) return;
+    if (tid == 0) *list_at = atomicAdd(list_len + b, all);
+    __syncthreads();
+    if (mine && !certain) list[*list_at + before + __popcll(open & ((1ull << lane) - 1ull))] = (int32_t)point;
 }
 
 // The points on the list against all centroids by direct differences: ascending features, one
@@ -355,10 +369,18 @@ __global__ __launch_bounds__(WAVES * 64) void assign_f32_filter_kernel(
 // are too few, take points of their own (`teams` of 8 / teams waves each).  With P = 2 a short
 // list is spread thin and over in the time that a few rows take to arrive (5 to 20 us); with P =
 // 8 a long one is bound by the two vector instructions per term, as the direct kernels are.
-//   Long lists of short rows against few centroids, where that form spends its time on reading
+//   Long lists of rows of up to 64 features, where that form spends its time on reading centroid
 // rows: one point per thread with its features in registers, centroid tiles through LDS.
 //   What open points cost is then about the direct kernel's time for them on top of the filter's.
-constexpr int kListFloats = 4096;                      // points held by a workgroup x row width
+// Every centroid twice, so that all points are open, fk_assign against the direct kernels alone: 2^20 points,
+// d = K = 64: 292 us, 222 (one addition to the list's length per wave: 610); d = 64, K = 256: 924, 814
+// (in the first form: 1896); d = 128, K = 64: 950, 656 (4 teams: 1350); 300000 points, d = 96, K = 400:
+// 1238, 1149; 65536, d = 256, K = 512: 696, 1323.
+
+// Points held by a workgroup x row width, in floats.  Wide rows: enough that with few centroids as few
+// waves as possible are without a share of them.
+template <int DMAX>
+constexpr int list_floats() { return DMAX == 0 ? 15360 : 4096; }
 
 template <int P>
 __device__ __forceinline__ void list_points(
@@ -493,7 +515,7 @@ __global__ __launch_bounds__(512, 4) void assign_f32_list_kernel(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list,
     const int32_t* __restrict__ list_len, int32_t* __restrict__ assign, int64_t N, int d, int row_len,
     int K, int none) {
-    __shared__ __align__(16) float xs[kListFloats];
+    __shared__ __align__(16) float xs[list_floats<DMAX>()];
     __shared__ float cand_d[8][8];
     __shared__ int cand_k[8][8];
     const int b = blockIdx.y;
@@ -502,11 +524,13 @@ __global__ __launch_bounds__(512, 4) void assign_f32_list_kernel(
     C += (size_t)b * K * row_len;
     assign += (size_t)b * N;
     list += (size_t)b * N;
-    int teams = K <= 64 ? 8 : K <= 128 ? 4 : K <= 256 ? 2 : 1;
-    while (teams * 8 * d > kListFloats) teams >>= 1;         // d <= 512: ends at 1 or more
-    if (len <= 2 * teams * (int)gridDim.x)
-        list_points<2>(X, C, list, len, assign, d, row_len, K, none, teams, xs, cand_d, cand_k);
-    else if (DMAX == 0 || K > 128 || len < 256 * (int)gridDim.x)
+    const int most = K <= 64 ? 8 : K <= 128 ? 4 : K <= 256 ? 2 : 1;
+    int thin = most, teams = most;                           // both end at 1 or more (d <= 512)
+    while (thin * 8 * d > 4096) thin >>= 1;                  // (short lists: as wide a spread)
+    while (teams * 8 * d > list_floats<DMAX>()) teams >>= 1;
+    if (len <= 2 * thin * (int)gridDim.x)
+        list_points<2>(X, C, list, len, assign, d, row_len, K, none, thin, xs, cand_d, cand_k);
+    else if (DMAX == 0 || len < 256 * (int)gridDim.x)
         list_points<8>(X, C, list, len, assign, d, row_len, K, none, teams, xs, cand_d, cand_k);
     else
         list_by_thread<DMAX == 0 ? 32 : DMAX>(X, C, list, len, assign, d, row_len, K, none, xs);

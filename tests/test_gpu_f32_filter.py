@@ -41,12 +41,20 @@ def _data(kind, B, N, d, K, seed):
     C = torch.stack([X[b, pick[b]] for b in range(B)])
     if kind == "twins":             # every centroid twice
         C = torch.cat([C[:, : (K + 1) // 2]] * 2, 1)[:, :K]
+    elif kind == "triples":
+        C = torch.cat([C[:, : (K + 2) // 3]] * 3, 1)[:, :K]
+    elif kind == "border":          # between two centroids, 2^-4 .. 2^-28 of their distance off the middle
+        C[:, 1::2] = C[:, : K // 2 * 2 : 2] + 0.1 * torch.randn(C[:, 1::2].shape, generator=g)
+        of = torch.randint(0, max(1, K // 2), (B, N, 1), generator=g).expand(B, N, d) * 2
+        u, v = C.gather(1, of), C.gather(1, (of + 1).clamp(max=K - 1))
+        off = torch.exp2(-4 - 24 * torch.rand((B, N, 1), generator=g)) * (torch.randint(0, 2, (B, N, 1), generator=g) * 2 - 1)
+        X = (u + v) * 0.5 + off * (v - u)
     elif kind == "outlier":         # one centroid far away, the first
         C[:, 0] = 1e6
     return X.to(DEV), C.contiguous().to(DEV)
 
 
-@pytest.mark.parametrize("kind", ["gauss", "mixture", "far", "whole", "large", "small", "twins", "outlier"])
+@pytest.mark.parametrize("kind", ["gauss", "mixture", "far", "whole", "large", "small", "twins", "triples", "border", "outlier"])
 @pytest.mark.parametrize("B,N,d,K", [(1, 3001, 64, 100), (2, 517, 8, 33), (1, 1000, 96, 257), (1, 4100, 128, 64),
                                      (1, 700, 256, 97), (1, 300, 512, 70), (3, 130, 32, 1), (1, 333, 392, 31)])
 def test_filter_gives_the_direct_answer(both, kind, B, N, d, K):
@@ -57,6 +65,18 @@ def test_filter_gives_the_direct_answer(both, kind, B, N, d, K):
     fine = torch.isfinite(m0)
     assert torch.equal(fine, torch.isfinite(m1))
     assert ((m1 - m0).abs()[fine] <= d * 2.0 ** -23 * m0[fine] + 1e-37).all()
+
+
+@pytest.mark.parametrize("kind,B,N,d,K", [
+    # many open points: a thread each (rows of up to 32 and 64, few and many centroids), P = 8 with one team and
+    # with as many as there is room for; more points than four waves take
+    ("twins", 1, 140000, 32, 64), ("twins", 1, 140000, 60, 100), ("triples", 1, 133000, 48, 300), ("twins", 1, 3000, 64, 300),
+    ("twins", 1, 9001, 500, 100), ("twins", 1, 20001, 128, 64), ("mixture", 1, (1 << 19) + 5, 40, 30), ("border", 1, (1 << 19) + 5, 100, 50),
+])
+def test_filter_gives_the_direct_answer_for_many_points(both, kind, B, N, d, K):
+    (a1, m1), (a0, m0) = both(*_data(kind, B, N, d, K, seed=N + d + K))
+    assert torch.equal(a1, a0)
+    assert ((m1 - m0).abs() <= d * 2.0 ** -23 * m0 + 1e-37).all()
 
 
 @pytest.mark.parametrize("N,d,K", [(3001, 64, 100), (1000, 96, 257), (700, 256, 97), (263000, 24, 40)])
