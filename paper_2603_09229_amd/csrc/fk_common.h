@@ -173,6 +173,20 @@ fk_status launch_assign_rows(const Geometry& g, const void* X, const void* C, in
 fk_status launch_sort_inverse(const Geometry& g, const Workspace& w, const int32_t* assign,
                               int32_t* sorted_idx, int32_t* seg_off, int32_t* item_off,
                               hipStream_t s);
+// Whether the scatter kernel adds the workgroups' histograms up itself instead of a scan kernel doing it.  It
+// saves the launch and costs a thread per bin one read of every workgroup's count, one after the other.
+// fk_sort_inverse, us with the scan and without:
+//   64 bins, workgroups  8: 15.6 12.7   32: 15.6 13.8   48: 15.6 14.2   64: 15.7 14.9   512: 21.8 36.0
+//   16 bins             64: 13.8 13.6   80: 13.9 14.4
+// Where the workgroups come in several rounds each of them pays, and few bins gain least:
+//   16 bins, 16 instances of 48: 19.8 18.8, of 64: 26.9 27.4; 64 of 24: 34.7 32.6, of 48: 63.5 65.7
+//   256 bins, 64 instances of 48: 80.2 76.2, 300 of 32: 243 230, of 48: 409 411
+// Many bins times many workgroups: 1000 bins, 32: 18.6 17.7; 2^16 counts 42.0 44.2 (fk_update).
+inline bool sort_scatter_scans(int instances, int blocks, int bins) {
+    const int64_t all = (int64_t)instances * blocks;
+    const int most = all <= 512 ? 64 : all <= 1024 || bins >= 256 ? 48 : 24;
+    return blocks > 1 && blocks <= most && bins <= 1024 && blocks * bins <= 32768;
+}
 // Largest bin count for which the scatter stages its tile through LDS (-1 = the built-in 1024).
 void set_sort_stage_bins(int v);
 // Per-item segment sums of gathered rows -> w.partial.

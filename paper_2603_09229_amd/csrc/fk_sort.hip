@@ -185,15 +185,18 @@ __global__ __launch_bounds__(256) void sort_binscan_kernel(int32_t* __restrict__
 
 // Stable scatter.  Waves walk their keys in input order, so equal keys keep their order.
 //   vals_in == NULL: values are the key positions (first pass).
+//   kScans: see sort_scatter_scans; rounds is 1.  An instantiation of its own: the code costs the others 2%
+//   when it is only skipped, and without the form of several rounds it needs fewer registers (72; with 84
+//   a compute unit holds a workgroup less: 64 instances of 24 workgroups, 64 bins, 44.4 us against 37.8).
 //   keys_out may be NULL.  seg_off / item_off are written by workgroup 0 when non-NULL
 //   (single-pass sort: bins are cluster ids, so the bin offsets are the segment table).
-template <int kSortWaves>
+template <int kSortWaves, bool kScans>
 __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
     const int32_t* __restrict__ keys, const int32_t* __restrict__ vals_in,
     const int32_t* __restrict__ H, const int32_t* __restrict__ tot,
     int32_t* __restrict__ vals_out, int32_t* __restrict__ keys_out,
     int32_t* __restrict__ seg_off, int32_t* __restrict__ item_off, int64_t N, int rounds,
-    int NB, int shift, int mask, int kmax, int nbits, int R, int staged, int solo, int by_block) {
+    int NB, int shift, int mask, int kmax, int nbits, int R, int staged, int solo) {
     constexpr int kSortThreads = kSortWaves * 64, kBatches = kSubTile / kSortThreads;
     extern __shared__ int lds[];
     int* off = lds;                    // [NB]
@@ -210,7 +213,7 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
     vals_out += (size_t)b * N;
     if (keys_out) keys_out += (size_t)b * N;
     tot += (size_t)b * NB;
-    H += (size_t)b * NB * nb + (by_block ? 0 : blk);
+    H += (size_t)b * NB * nb + (kScans ? 0 : blk);
 
     // first round's keys are requested before the offset scans below need them
     int k[kBatches];
@@ -223,10 +226,10 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
     // apart): requested now, needed only after the counting pass
     constexpr int kHPer = 2048 / kSortThreads;
     int hcol[kHPer];
-    if (kSortWaves == 8 && by_block) {
+    if constexpr (kScans) {
         // Few sort workgroups: no scan kernel has run; each workgroup adds up the counts of the earlier
         // ones (where its own keys start inside the bins) and of all of them (the bin totals,
-        // kept in off[] until they are scanned) for itself.
+        // kept in the first wave's counters until they are scanned) for itself.
 #pragma unroll
         for (int q = 0; q < kHPer; ++q) {
             const int i = tid + q * kSortThreads;
@@ -257,7 +260,7 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
     // counting pass -- no histogram or scan kernel runs then.
     auto offsets_from_totals = [&]() {
         auto total_of = [&](int i) -> int {
-            if (kSortWaves == 8 && by_block) return wcnt[i];   // (written by the thread that reads it)
+            if constexpr (kScans) return wcnt[i];   // (written by the thread that reads it)
             if (!solo) return tot[i];
             int t = 0;
             for (int w = 0; w < kSortWaves; ++w) t += wcnt[w * NB + i];
@@ -282,17 +285,17 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
             if (tid == 0) so[NB] = total;
         }
     };
-    if (kSortWaves == 8 && by_block) offsets_from_totals();   // ends with a barrier after its last use of wcnt
+    if constexpr (kScans) offsets_from_totals();   // ends with a barrier after its last use of wcnt
     for (int i = tid; i < kSortWaves * NB; i += kSortThreads) wcnt[i] = 0;
     __syncthreads();
-    if (!solo && !by_block) offsets_from_totals();
+    if (!kScans && !solo) offsets_from_totals();
 
     int* mine = wcnt + wave * NB;
     const uint64_t lt = lanemask_lt();
     // info[j] = rank among equal digits of the batch | (size of that group << 8)
     int info[kBatches];
 
-    if (rounds == 1) {
+    if (kScans || rounds == 1) {
         // Keys, ranks and each key's position inside its wave's run of the digit stay in
         // registers between the two passes.  Pass 1: every lane reads the wave's running count
         // of its digit, then the first lane of each group of equal digits adds the group's
@@ -312,7 +315,7 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
             __builtin_amdgcn_wave_barrier();
         }
         __syncthreads();
-        if (solo) offsets_from_totals();
+        if (!kScans && solo) offsets_from_totals();
         int v[kBatches];
         if (vals_in) {
 #pragma unroll
@@ -416,7 +419,7 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
         rank_round(true);
     }
     __syncthreads();
-    if (solo) offsets_from_totals();
+    if (!kScans && solo) offsets_from_totals();
     // counts -> start positions: global bin offset + earlier workgroups + earlier waves
 #pragma unroll
     for (int q = 0; q < kHPer; ++q) {
@@ -527,11 +530,7 @@ static fk_status sort_pass(const Geometry& g, const Workspace& w, const int32_t*
     const bool wide = NB > 1024;       // 8 waves of counters would not fit in LDS
     // one workgroup per instance: the scatter kernel counts for itself
     const int solo = g.sort_blocks == 1 ? 1 : 0;
-    // Few workgroups and bins: the scatter kernel adds the histograms up itself, which saves the scan
-    // kernel's launch while a workgroup has no more than 2^15 counts to read (fk_update, 3 x 70001
-    // points, K = 333: 38.1 -> 36.0 us; 10^5 points, K = 64: 28.1 -> 26.1; at 2^16 counts, 2^18 points, K =
-    // 1024, it loses: 42.0 -> 44.2).
-    const int by_block = !solo && !wide && (int64_t)g.sort_blocks * NB <= 32768 ? 1 : 0;
+    const int by_block = rounds == 1 && sort_scatter_scans(g.B, g.sort_blocks, NB) ? 1 : 0;
     if (!solo) {
         const size_t hist_lds = (size_t)NB * (NB <= 64 ? 16 : 1) * sizeof(int);
         if (wide)
@@ -541,11 +540,10 @@ static fk_status sort_pass(const Geometry& g, const Workspace& w, const int32_t*
             hipLaunchKernelGGL(sort_hist_kernel<8>, grid, dim3(512), hist_lds, s, keys, H, g.N,
                                rounds, NB, shift, mask, g.K - 1, nbits, by_block);
         FK_HIP(hipGetLastError());
-        if (by_block) {
-        } else if (g.sort_blocks > 512)
+        if (!by_block && g.sort_blocks > 512)
             hipLaunchKernelGGL(sort_binscan_kernel<256>, dim3((unsigned)NB, g.B), dim3(256), 0, s, H,
                                tot, g.sort_blocks, NB);
-        else
+        else if (!by_block)
             hipLaunchKernelGGL(sort_binscan_kernel<64>, dim3((unsigned)cdiv(NB, 4), g.B), dim3(256), 0,
                                s, H, tot, g.sort_blocks, NB);
         FK_HIP(hipGetLastError());
@@ -557,22 +555,17 @@ static fk_status sort_pass(const Geometry& g, const Workspace& w, const int32_t*
     // 2x on the 64..256-bin passes of the two-pass sort.
     const int staged = rounds == 1 && NB >= 32 && NB <= g_stage_max_bins.load(std::memory_order_relaxed) ? 1 : 0;
     const size_t lds = (size_t)(NB + 40 + waves * NB + (staged ? NB + 2 * kSubTile : 0)) * sizeof(int);
+    auto kern = wide ? sort_scatter_kernel<4, false> : by_block ? sort_scatter_kernel<8, true> : sort_scatter_kernel<8, false>;
     if (lds > 64 * 1024) {
-        static PerDeviceInt attr_set[2];
-        if (!attr_set[wide].get()) {
-            FK_HIP(hipFuncSetAttribute(wide ? (const void*)sort_scatter_kernel<4> : (const void*)sort_scatter_kernel<8>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
-            attr_set[wide].set(1);
+        static PerDeviceInt attr_set[3];
+        PerDeviceInt& set = attr_set[wide ? 0 : 1 + by_block];
+        if (!set.get()) {
+            FK_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024));
+            set.set(1);
         }
     }
-    if (wide)
-        hipLaunchKernelGGL(sort_scatter_kernel<4>, grid, dim3(256), lds, s, keys, vals_in, H, tot,
-                           vals_out, keys_out, seg_off, item_off, g.N, rounds, NB, shift, mask,
-                           g.K - 1, nbits, g.rows_per_item, staged, solo, by_block);
-    else
-        hipLaunchKernelGGL(sort_scatter_kernel<8>, grid, dim3(512), lds, s, keys, vals_in, H, tot,
-                           vals_out, keys_out, seg_off, item_off, g.N, rounds, NB, shift, mask,
-                           g.K - 1, nbits, g.rows_per_item, staged, solo, by_block);
+    hipLaunchKernelGGL(kern, grid, dim3(waves * 64), lds, s, keys, vals_in, H, tot, vals_out, keys_out, seg_off, item_off,
+                       g.N, rounds, NB, shift, mask, g.K - 1, nbits, g.rows_per_item, staged, solo);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }

@@ -43,8 +43,20 @@ static int launches_fit() {
     return fk_set_option("assign_f32_filter", -1) == FK_OK ? 0 : 1;
 }
 
+// The scatter reads one count per workgroup and bin, in a row: only ever few of them, whatever the bins.
+static int few_counts_in_a_row() {
+    for (int instances : {1, 3, 64, 65535})
+        for (int bins : {1, 2, 8, 64, 256, 1000, 1024, 1025, 2048})
+            for (int blocks : {1, 2, 18, 32, 48, 64, 65, 128, 512, 4096, 65536}) {
+                const bool scans = fk::sort_scatter_scans(instances, blocks, bins);
+                CHECK(!scans || (blocks <= 64 && (int64_t)blocks * bins <= 32768));
+                CHECK(scans || blocks < 2 || blocks > (instances > 3 ? 18 : 32) || bins > 1000);   // ... and all of those that gain
+            }
+    return 0;
+}
+
 int main() {
-    if (option_is_read_once() || launches_fit()) return 1;
+    if (option_is_read_once() || launches_fit() || few_counts_in_a_row()) return 1;
     printf("host decisions ok\n");
     return 0;
 }
