@@ -142,10 +142,12 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
 // One workgroup (256 threads, or 1024 when clusters have many items) per cluster: s_k = sum
 // of the cluster's item rows in a fixed
 // order, n_k = seg_off[k+1] - seg_off[k].  Optionally added onto sums/counts already stored
-// (chunked mode), optionally normalised into centroids (Algorithm 3, last loop; an empty
-// cluster keeps its previous centroid).  When c_frag is given, the rounded centroid is also
+// (chunked mode; kLate: followed by the parts that have waited for their turn), optionally
+// normalised into centroids (Algorithm 3, last loop; an empty cluster keeps its previous
+// centroid).  When c_frag is given, the rounded centroid is also
 // written in MFMA fragment order together with its score bias -||c||^2/2, so the next
 // assignment needs no separate re-layout pass.
+template <bool kLate>
 __global__ __launch_bounds__(1024) void finalize_kernel(
     const float* __restrict__ partial, const int32_t* __restrict__ seg_off,
     const int32_t* __restrict__ item_off, const float* C_prev, float* C_out,
@@ -217,13 +219,15 @@ __global__ __launch_bounds__(1024) void finalize_kernel(
     } else {
         n += seg_off[k + 1] - seg_off[k];
     }
-    for (int q = 0; q < late; ++q) n += late_counts[((size_t)q * gridDim.y + b) * K + k];
+    if constexpr (kLate)
+        for (int q = 0; q < late; ++q) n += late_counts[((size_t)q * gridDim.y + b) * K + k];
     for (int j = tid; j < d; j += T) {
         float s = 0.f;
         for (int q = 0; q < sums_left; ++q) s += red[q * dpow + j];   // fixed order
         const size_t o = ((size_t)b * K + k) * d + j;
         if (accumulate) s += sums[o];
-        for (int q = 0; q < late; ++q) s += late_sums[(size_t)q * gridDim.y * K * d + o];
+        if constexpr (kLate)
+            for (int q = 0; q < late; ++q) s += late_sums[(size_t)q * gridDim.y * K * d + o];
         if (sums) sums[o] = s;
         if (normalise) {
             // the caller's rows have no padding; past their end everything is zero
@@ -310,7 +314,8 @@ fk_status launch_finalize(const Geometry& g, const Workspace& w, const int32_t* 
     int threads = g.max_items / g.K > 64 ? 1024 : 256;
     if (g.d <= 128 && (g.max_items / g.K <= 4 || (g.max_items / g.K <= 8 && (int64_t)g.K * g.B >= 4096))) threads = 64;
     const size_t lds = ((size_t)4 * threads + g.d) * sizeof(float);
-    hipLaunchKernelGGL(finalize_kernel, dim3(g.K, g.B), dim3(threads), lds, s, w.partial, seg_off,
+    auto kern = a.late > 0 ? finalize_kernel<true> : finalize_kernel<false>;
+    hipLaunchKernelGGL(kern, dim3(g.K, g.B), dim3(threads), lds, s, w.partial, seg_off,
                        item_off, a.C_prev_f32, a.C_out_f32, lp16, lp32, frag, a.c_bias, a.counts,
                        a.sums, g.d, g.len, g.K, g.max_items, g.ktiles, g.dchunks, a.accumulate ? 1 : 0,
                        a.normalise ? 1 : 0, g.t == FK_BF16 ? 1 : 0, wg_counts, wg_per_cluster,
