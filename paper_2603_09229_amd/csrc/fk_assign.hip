@@ -93,8 +93,9 @@ fk_status launch_prepare_centroids(const Geometry& g, const void* C_lp, void* c_
 }
 
 // dst[r][j] = j < d_src ? src[r][j] : 0 for j < d_dst: pads rows with zeros (d_dst > d_src) or
-// drops the padding again (d_dst < d_src).  VEC elements per thread: padding rows of 8 elements or
-// more to a multiple of 8 is bound by memory and takes 16 bytes at a time; what is left is small.
+// drops the padding again (d_dst < d_src).  VEC elements per thread: padding is bound by memory and
+// writes 16 bytes at a time (26 million rows of 7 fp32 values: 285 us with one value per thread); what
+// is left is small.
 template <typename T, int VEC>
 __global__ __launch_bounds__(256) void copy_rows_kernel(const T* __restrict__ src, T* __restrict__ dst,
                                                         int64_t rows, int d_src, int d_dst) {
@@ -103,18 +104,24 @@ __global__ __launch_bounds__(256) void copy_rows_kernel(const T* __restrict__ sr
     for (int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x; o < total; o += (int64_t)gridDim.x * 256) {
         const int64_t r = total < ((int64_t)1 << 32) ? (int64_t)((uint32_t)o / (uint32_t)per_row) : o / per_row;
         const int j = (int)(o - r * per_row) * VEC;
-        if constexpr (VEC == 8)
-            *(uintx4*)(dst + r * d_dst + j) = row_piece16((const uint16_t*)src + r * d_src, j, d_src);
+        if (VEC > 1 && d_src < 8) {
+            typedef T Piece __attribute__((ext_vector_type(VEC > 1 ? VEC : 2)));
+            Piece v;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) v[e] = j + e < d_src ? src[r * d_src + j + e] : T(0);
+            *(Piece*)(dst + o * VEC) = v;
+        } else if constexpr (VEC == 8)
+            *(uintx4*)(dst + o * VEC) = row_piece16((const uint16_t*)src + r * d_src, j, d_src);
         else if constexpr (VEC == 4)
-            *(floatx4*)(dst + r * d_dst + j) = row_piece32((const float*)src + r * d_src, j, d_src);
+            *(floatx4*)(dst + o * VEC) = row_piece32((const float*)src + r * d_src, j, d_src);
         else
-            dst[r * d_dst + j] = j < d_src ? src[r * d_src + j] : T(0);
+            dst[o] = j < d_src ? src[r * d_src + j] : T(0);
     }
 }
 
 fk_status launch_copy_rows(const void* src, void* dst, int64_t rows, int d_src, int d_dst,
                            int elem, hipStream_t s) {
-    const bool whole = d_src >= 8 && d_dst > d_src && d_dst % 8 == 0;
+    const bool whole = d_dst > d_src && d_dst % 8 == 0;
     const int64_t total = rows * (whole ? d_dst * elem / 16 : d_dst);
     const dim3 grid((unsigned)std::min<int64_t>(cdiv(total, 256), (int64_t)1 << 20)), block(256);
     if (elem == 2 && whole)
