@@ -1084,10 +1084,13 @@ bool assign_uses_stream_kernel(const Geometry& g) {
 // Few points: which form of the few-point kernel, if any.  With t tiles of 32 points, U compute
 // units and c centroid tiles (all times per fk_assign call, layout launch included, against the
 // sweeping kernel):
-//   t <= U, rows: any few centroids (1000 points, d = 128: K = 256 5.4 against 9.0 us, K = 1024 10.1
-//     against 22.0; d = 512, K = 64: 8.6 against 14.5).  Where a wave would walk through several
-//     tiles of rows the copies in fragment order are read faster (d = 256, K = 1024: 15.8 against
-//     17.7; d = 512, K = 256: 12.2 against 18.2).
+//   t <= U, rows: any few centroids (1000 points, d = 128: K = 256 5.8 against 9.4 us, K = 1024 10.5
+//     against 22.5; d = 256, K = 256: 7.4 against 16.7).  Where a wave would walk through several
+//     tiles of rows, or three waves share four (d > 256), the copies in fragment order are read
+//     faster (d = 256, K = 1024: 15.8 against 17.7; d = 512, K = 100: rows 16.8, fragments 12.1,
+//     sweeping 17.9).  Few tiles of wide rows leave most waves without work, which only pays where the
+//     sweeping kernel has many rows to read (d = 512, K = 5: one point 10.2 against 7.4, 300 points
+//     10.5 against 13.5; fragments, d = 136, K = 40: 7.4 against 7.1, d = 192: 8.1 against 8.7).
 //   more: 64 points per workgroup, so that each A operand serves two products, while there are
 //     centroids enough for the waves (16384 points, d = 128: K = 256 7.4 against 9.7, K = 4096 24.7
 //     against 74; 32768: K = 1024 14.1 against 22.9, but d = 32, K = 256: 6.6 against 5.7).
@@ -1110,14 +1113,23 @@ static FewForm choose_few(const Geometry& g, bool have_rows) {
         return kFewNone;
     const int64_t t = cdiv(g.N, 32) * g.B, U = device_cu_count();
     const int dch = g.dchunks, c = g.ktiles;
+    const bool points = g.N > 128;           // below that the sweeping kernel reads fewer rows
     if (t <= U) {
-        if (have_rows && c <= (dch <= 8 ? 32 : dch <= 16 ? 16 : 4)) return kFewRows;
-        if (dch <= 8 && c <= 8) return kFewNone;
-        return dch == 8 && c > 32 ? kFewTwo16 : kFewOne;
+        if (dch <= 8) {
+            if (have_rows && c <= 32) return kFewRows;
+            return c <= 8 ? kFewNone : dch == 8 && c > 32 ? kFewTwo16 : kFewOne;
+        }
+        if (dch <= 16) {
+            if (have_rows && c <= 16) return kFewRows;
+            return c >= 4 || (points && (dch * c >= 24 || dch == 16)) ? kFewOne : kFewNone;
+        }
+        if (c >= 4) return kFewOne;
+        if (have_rows) return c == 3 || points ? kFewRows : kFewNone;
+        return points && (c >= 2 || dch > 24) ? kFewOne : kFewNone;
     }
     if (t <= 2 * U) {
         if (dch > 16) return c >= 8 ? kFewOne : kFewNone;
-        if (dch > 8) return c >= 32 ? kFewTwo8 : c >= 2 ? kFewOne : kFewNone;
+        if (dch > 8) return c >= 32 ? kFewTwo8 : dch * c >= 24 && c >= 2 ? kFewOne : kFewNone;
         if (c < (dch == 2 ? 16 : 8)) return kFewNone;
         return c >= 32 ? kFewTwo16 : kFewTwo8;
     }
