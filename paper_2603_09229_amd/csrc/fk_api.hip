@@ -124,9 +124,11 @@ bool make_geometry(int B, int64_t N, int d_user, int K, fk_dtype t, Geometry* g)
     // the four waves of a workgroup (at most ~4096 + K partial rows to merge afterwards)
     int64_t R = 256;
     // ... fewer where the items would not fill the chip: a wave of 256 rows is one long chain of loads
-    // (fk_update, 2^18 points, d = 300, K = 500: 64.6 us with 256 rows per item, 59 with 64; 10^5 points,
-    // K = 64: 32.4 and 28.1)
-    while (R > 32 && B * (N / R + K) < 3000) R /= 2;
+    // (fk_update, 2^18 points, d = 300, K = 500: 62.1 us with 256 rows per item, 55.8 with 128; 20000
+    // points, d = 512, K = 34: 49.7 and, with 32, 27.8).  Beyond two waves per SIMD that gives nothing and
+    // the partial rows cost: 342180 points, d = 512, K = 34: 93.6 with 256, 90.8 with 128, 98.9 with 64;
+    // 600000, d = 96 in fp32, K = 400: 58.8 with 256, 60.8 with 128.
+    while (R > 32 && B * (N / R + K) < 2000) R /= 2;
     g->waves_per_item = 1;
     if (N > ((int64_t)1 << 22)) { R = cdiv(N, 4096); g->waves_per_item = 4; }
     g->rows_per_item = (int)R;
