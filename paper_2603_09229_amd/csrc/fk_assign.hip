@@ -28,11 +28,12 @@ namespace fk {
 // ROUNDED values, i.e. from exactly what the MFMA multiplies.  Rows >= K get a huge negative
 // finite bias: it must survive having its low mantissa bits overwritten (-inf would turn
 // into a NaN pattern) and still lose against every real score.
-template <bool SRC_F32>
+template <bool SRC_F32, bool RAGGED>
 __global__ __launch_bounds__(512) void centroid_layout_kernel(
     const void* __restrict__ src, uint16_t* __restrict__ C_lp, uint16_t* __restrict__ c_frag,
-    float* __restrict__ c_bias, int d, int len, int K, int ktiles, int dch, int bf) {
+    float* __restrict__ c_bias, int d, int K, int ktiles, int dch, int bf, int row_len) {
     __shared__ float part[32][65];
+    const int len = RAGGED ? row_len : d;
     const int b = blockIdx.y, kt = blockIdx.x;
     for (int g = threadIdx.x; g < 64 * dch; g += blockDim.x) {
         const int l = g & 63, s = g >> 6, r = l & 31, h = l >> 5;
@@ -45,7 +46,7 @@ __global__ __launch_bounds__(512) void centroid_layout_kernel(
         if (live) {
             const size_t o = ((size_t)b * K + k) * len;
             if (SRC_F32) {
-                const floatx4 lo = row_piece32((const float*)src + o, j0, len), hi = row_piece32((const float*)src + o, j0 + 4, len);
+                const floatx4 lo = row_piece32<RAGGED>((const float*)src + o, j0, len), hi = row_piece32<RAGGED>((const float*)src + o, j0 + 4, len);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     v[e] = float_to_lp(lo[e], bf);
@@ -54,10 +55,10 @@ __global__ __launch_bounds__(512) void centroid_layout_kernel(
                 if (C_lp) {
 #pragma unroll
                     for (int e = 0; e < 8; ++e)
-                        if (j0 + e < len) C_lp[o + j0 + e] = v[e];
+                        if (!RAGGED || j0 + e < len) C_lp[o + j0 + e] = v[e];
                 }
             } else {
-                const uintx4 p = row_piece16((const uint16_t*)src + o, j0, len);
+                const uintx4 p = row_piece16<RAGGED>((const uint16_t*)src + o, j0, len);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v[e] = (uint16_t)(p[e >> 1] >> (16 * (e & 1)));
             }
@@ -85,9 +86,10 @@ __global__ __launch_bounds__(512) void centroid_layout_kernel(
 fk_status launch_prepare_centroids(const Geometry& g, const void* C_lp, void* c_frag,
                                    float* c_bias, hipStream_t s) {
     dim3 grid(g.ktiles, g.B), block(std::min(512, 64 * g.dchunks));
-    hipLaunchKernelGGL(centroid_layout_kernel<false>, grid, block, 0, s, C_lp, (uint16_t*)nullptr,
-                       (uint16_t*)c_frag, c_bias, g.d, g.len, g.K, g.ktiles, g.dchunks,
-                       g.t == FK_BF16 ? 1 : 0);
+    auto kern = g.len == g.d ? centroid_layout_kernel<false, false> : centroid_layout_kernel<false, true>;
+    hipLaunchKernelGGL(kern, grid, block, 0, s, C_lp, (uint16_t*)nullptr,
+                       (uint16_t*)c_frag, c_bias, g.d, g.K, g.ktiles, g.dchunks,
+                       g.t == FK_BF16 ? 1 : 0, g.len);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }
@@ -153,9 +155,10 @@ fk_status launch_round_centroids(const Geometry& g, const float* C_f32, void* C_
         return FK_OK;
     }
     dim3 grid(g.ktiles, g.B), block(std::min(512, 64 * g.dchunks));
-    hipLaunchKernelGGL(centroid_layout_kernel<true>, grid, block, 0, s, (const void*)C_f32,
-                       (uint16_t*)C_lp, (uint16_t*)c_frag, c_bias, g.d, g.len, g.K, g.ktiles, g.dchunks,
-                       g.t == FK_BF16 ? 1 : 0);
+    auto kern = g.len == g.d ? centroid_layout_kernel<true, false> : centroid_layout_kernel<true, true>;
+    hipLaunchKernelGGL(kern, grid, block, 0, s, (const void*)C_f32,
+                       (uint16_t*)C_lp, (uint16_t*)c_frag, c_bias, g.d, g.K, g.ktiles, g.dchunks,
+                       g.t == FK_BF16 ? 1 : 0, g.len);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }
@@ -181,11 +184,12 @@ __device__ __forceinline__ void copy16_to_lds(const uintx4* gsrc, uintx4* lds_ba
 // Ties between scores equal after truncation: the earlier centroid tile wins; inside a tile
 // the lower row wins for scores >= 0 (the usual case for a winner: x.c > ||c||^2/2), the
 // higher row among the lane's 16 for negative ones.
-template <bool BF, int DCH, int P, int WAVES, int ST>
+template <bool BF, int DCH, int P, int WAVES, int ST, bool RAGGED>
 __global__ __launch_bounds__(WAVES * 64) void assign_mfma_kernel(
     const uint16_t* __restrict__ X, const uintx4* __restrict__ c_frag,
     const float* __restrict__ c_bias, int32_t* __restrict__ assign,
-    float* __restrict__ min_dist, int64_t N, int d, int len, int K, int ktiles) {
+    float* __restrict__ min_dist, int64_t N, int d, int K, int ktiles, int row_len) {
+    const int len = RAGGED ? row_len : d;
     constexpr int kThreads = WAVES * 64;
     constexpr int kStageVec = ST * DCH * 64;            // 16-byte vectors per stage
     constexpr int kPieces = ST * DCH;                   // 1 KiB pieces per stage
@@ -236,11 +240,11 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_kernel(
         for (int s = 0; s < DCH; ++s) {
             const int j0 = s * 16 + h * 8;
             uintx4 v = {0u, 0u, 0u, 0u};
-            if (point < N && j0 < d) v = raw_piece16(X + (size_t)point * len, j0, len);
+            if (point < N && j0 < d) v = raw_piece16<RAGGED>(X + (size_t)point * len, j0, len);
             xf[pt][s] = v;
         }
     }
-    if (len & 7) {
+    if (RAGGED && (len & 7)) {
 #pragma unroll
         for (int s = 0; s < DCH; ++s)
             if (s == len >> 4)                               // the chunk that the row ends in
@@ -820,10 +824,12 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_few_kernel(
 // ------------------------------------------------------------------------------------
 // fp32: one point per thread, features in registers, centroid tiles of TK rows in LDS,
 // D_ik by direct differences in fp32; ascending k with strict '<'.
-template <int DMAX, int TK, int THREADS>
+// RAGGED (here and below): rows whose length is no multiple of 8, read as they are stored.
+template <int DMAX, int TK, int THREADS, bool RAGGED>
 __global__ __launch_bounds__(THREADS) void assign_f32_kernel(
     const float* __restrict__ X, const float* __restrict__ C, int32_t* __restrict__ assign,
-    float* __restrict__ min_dist, int64_t N, int d, int len, int K) {
+    float* __restrict__ min_dist, int64_t N, int d, int K, int row_len) {
+    const int len = RAGGED ? row_len : d;
     __shared__ float sc[TK][DMAX];
     const int b = blockIdx.y;
     X += (size_t)b * N * len;
@@ -832,13 +838,7 @@ __global__ __launch_bounds__(THREADS) void assign_f32_kernel(
     if (min_dist) min_dist += (size_t)b * N;
     const int64_t i = (int64_t)blockIdx.x * THREADS + threadIdx.x;
     float x[DMAX];
-#pragma unroll
-    for (int j = 0; j < DMAX; j += 4) {
-        floatx4 v = {0.f, 0.f, 0.f, 0.f};
-        if (i < N && j < len) v = raw_piece32(X + (size_t)i * len, j, len);
-        x[j] = v[0]; x[j + 1] = v[1]; x[j + 2] = v[2]; x[j + 3] = v[3];
-    }
-    settle_row32<DMAX>(x, len);
+    load_row32<DMAX, RAGGED>(x, X + (size_t)i * len, len, i < N);
     float m = INFINITY;
     int a = 0;
     for (int k0 = 0; k0 < K; k0 += TK) {
@@ -870,9 +870,11 @@ __global__ __launch_bounds__(THREADS) void assign_f32_kernel(
 // fp32 with wide features (128 < d <= 512): the point no longer fits in registers, so each
 // thread keeps 16 running distances (one per row of the LDS centroid tile) and walks its own
 // row of X in blocks of 32 features, once per centroid tile (the re-reads come from cache).
+template <bool RAGGED>
 __global__ __launch_bounds__(256) void assign_f32_wide_kernel(
     const float* __restrict__ X, const float* __restrict__ C, int32_t* __restrict__ assign,
-    float* __restrict__ min_dist, int64_t N, int d, int len, int K) {
+    float* __restrict__ min_dist, int64_t N, int d, int K, int row_len) {
+    const int len = RAGGED ? row_len : d;
     constexpr int TK = 16;
     extern __shared__ float sc_dyn[];                  // [TK][d]
     const int b = blockIdx.y;
@@ -895,10 +897,16 @@ __global__ __launch_bounds__(256) void assign_f32_wide_kernel(
 #pragma unroll
         for (int r = 0; r < TK; ++r) D[r] = 0.f;
         for (int j0 = 0; j0 < d; j0 += 8) {             // d is a multiple of 8
-            floatx4 xa = raw_piece32(xrow, j0, len), xb = raw_piece32(xrow, j0 + 4, len);
-            if (j0 + 8 > len) {
-                xa = settle32(xa, j0, len);
-                xb = settle32(xb, j0 + 4, len);
+            floatx4 xa, xb;
+            if (!RAGGED) {
+                xa = *(const floatx4*)(xrow + j0);
+                xb = *(const floatx4*)(xrow + j0 + 4);
+            } else if (j0 + 8 <= len) {
+                xa = *(const floatx4_any*)(xrow + j0);
+                xb = *(const floatx4_any*)(xrow + j0 + 4);
+            } else {
+                xa = row_piece32(xrow, j0, len);
+                xb = row_piece32(xrow, j0 + 4, len);
             }
 #pragma unroll
             for (int r = 0; r < TK; ++r) {
@@ -927,10 +935,11 @@ __global__ __launch_bounds__(256) void assign_f32_wide_kernel(
 // tile between them (8 rows each), then the four candidates of a point are merged through
 // LDS (smaller distance first, lower index on equal distances).  Four times the parallelism
 // of the one-thread-per-point kernel when there are too few points to fill the chip.
-template <int DMAX>
+template <int DMAX, bool RAGGED>
 __global__ __launch_bounds__(256) void assign_f32_split_kernel(
     const float* __restrict__ X, const float* __restrict__ C, int32_t* __restrict__ assign,
-    float* __restrict__ min_dist, int64_t N, int d, int len, int K) {
+    float* __restrict__ min_dist, int64_t N, int d, int K, int row_len) {
+    const int len = RAGGED ? row_len : d;
     constexpr int TK = 32;
     __shared__ float sc[TK][DMAX];
     __shared__ float cand_d[4][64];
@@ -943,13 +952,7 @@ __global__ __launch_bounds__(256) void assign_f32_split_kernel(
     const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
     const int64_t i = (int64_t)blockIdx.x * 64 + lane;
     float x[DMAX];
-#pragma unroll
-    for (int j = 0; j < DMAX; j += 4) {
-        floatx4 v = {0.f, 0.f, 0.f, 0.f};
-        if (i < N && j < len) v = raw_piece32(X + (size_t)i * len, j, len);
-        x[j] = v[0]; x[j + 1] = v[1]; x[j + 2] = v[2]; x[j + 3] = v[3];
-    }
-    settle_row32<DMAX>(x, len);
+    load_row32<DMAX, RAGGED>(x, X + (size_t)i * len, len, i < N);
     float m = INFINITY;
     int a = 0x7FFFFFFF;
     for (int k0 = 0; k0 < K; k0 += TK) {
@@ -998,9 +1001,10 @@ static fk_status launch_mfma_v(const Geometry& g, const void* X, const void* fra
     constexpr int ST = (16 / DCH) < 8 ? (16 / DCH) : 8;   // up to 16 KiB of fragments per stage
     const int64_t per_wg = (int64_t)P * 32 * WAVES;
     dim3 grid((unsigned)cdiv(g.N, per_wg), g.B), block(WAVES * 64);
-    hipLaunchKernelGGL((assign_mfma_kernel<BF, DCH, P, WAVES, ST>), grid, block, 0, s,
+    auto kern = g.len == g.d ? assign_mfma_kernel<BF, DCH, P, WAVES, ST, false> : assign_mfma_kernel<BF, DCH, P, WAVES, ST, true>;
+    hipLaunchKernelGGL(kern, grid, block, 0, s,
                        (const uint16_t*)X, (const uintx4*)frag, bias, assign, min_dist, g.N,
-                       g.d, g.len, g.K, g.ktiles);
+                       g.d, g.K, g.ktiles, g.len);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }
@@ -1272,8 +1276,9 @@ fk_status launch_assign(const Geometry& g, const void* X, const void* C_or_frag,
     const float* Cf = (const float*)C_or_frag;
     if (w && f32_filter_enabled(g)) return launch_f32_filter(g, *w, Xf, Cf, assign, min_dist, s);
     if (g.d > 128) {
-        hipLaunchKernelGGL(assign_f32_wide_kernel, dim3((unsigned)cdiv(g.N, 256), g.B), dim3(256),
-                           (size_t)16 * g.d * sizeof(float), s, Xf, Cf, assign, min_dist, g.N, g.d, g.len, g.K);
+        auto kern = g.len == g.d ? assign_f32_wide_kernel<false> : assign_f32_wide_kernel<true>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)cdiv(g.N, 256), g.B), dim3(256), (size_t)16 * g.d * sizeof(float), s,
+                           Xf, Cf, assign, min_dist, g.N, g.d, g.K, g.len);
         FK_HIP(hipGetLastError());
         return FK_OK;
     }
@@ -1281,14 +1286,11 @@ fk_status launch_assign(const Geometry& g, const void* X, const void* C_or_frag,
     // over the chip
     const bool small = f32_direct_is_split(g);
     dim3 grid((unsigned)cdiv(g.N, small ? 64 : 256), g.B), block(256);
-#define FK_F32_LAUNCH(DM)                                                                         \
-    do {                                                                                          \
-        if (small)                                                                                \
-            hipLaunchKernelGGL((assign_f32_split_kernel<DM>), grid, block, 0, s, Xf, Cf, assign,  \
-                               min_dist, g.N, g.d, g.len, g.K);                                          \
-        else                                                                                      \
-            hipLaunchKernelGGL((assign_f32_kernel<DM, 32, 256>), grid, block, 0, s, Xf, Cf, assign, \
-                               min_dist, g.N, g.d, g.len, g.K);                                          \
+#define FK_F32_LAUNCH(DM)                                                                          \
+    do {                                                                                           \
+        auto kern = g.len == g.d ? (small ? assign_f32_split_kernel<DM, false> : assign_f32_kernel<DM, 32, 256, false>)  \
+                                 : (small ? assign_f32_split_kernel<DM, true> : assign_f32_kernel<DM, 32, 256, true>);   \
+        hipLaunchKernelGGL(kern, grid, block, 0, s, Xf, Cf, assign, min_dist, g.N, g.d, g.K, g.len);  \
     } while (0)
     if (g.d <= 32) FK_F32_LAUNCH(32);
     else if (g.d <= 64) FK_F32_LAUNCH(64);

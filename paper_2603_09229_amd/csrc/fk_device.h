@@ -54,8 +54,12 @@ __device__ __forceinline__ floatx16 mfma32(uintx4 a, uintx4 b, floatx16 c) {
 // raw_* reads the piece that would cross the row's end so that it ends there, settle* then moves
 // its elements down to where they belong and fills up with zeros.  The two are apart so that a
 // kernel can issue all its loads first and settle them under one test of len, which keeps rows
-// that need none of it on straight-line code.
+// that need none of it on straight-line code.  RAGGED = false: len is a multiple of 8 and the rows
+// are 16-byte aligned; the plain load, whose offset goes into the instruction (assign_f32_split_kernel,
+// 217895 points, d = 128, K = 18: 92 us with it, 108 with the test at every load).
+template <bool RAGGED = true>
 __device__ __forceinline__ uintx4 raw_piece16(const uint16_t* __restrict__ row, int j, int len) {
+    if constexpr (!RAGGED) return *(const uintx4*)(row + j);
     return *(const uintx4_any*)(row + min(j, len - 8));
 }
 
@@ -66,13 +70,16 @@ __device__ __forceinline__ uintx4 settle16(uintx4 v, int j, int len) {
     return j + 8 > len ? uintx4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)c, (uint32_t)(c >> 32)} : v;
 }
 
+template <bool RAGGED = true>
 __device__ __forceinline__ uintx4 row_piece16(const uint16_t* __restrict__ row, int j, int len) {
-    uintx4 v = raw_piece16(row, j, len);
-    if (len & 7) v = settle16(v, j, len);
+    uintx4 v = raw_piece16<RAGGED>(row, j, len);
+    if (RAGGED && (len & 7)) v = settle16(v, j, len);
     return v;
 }
 
+template <bool RAGGED = true>
 __device__ __forceinline__ floatx4 raw_piece32(const float* __restrict__ row, int j, int len) {
+    if constexpr (!RAGGED) return *(const floatx4*)(row + j);
     return *(const floatx4_any*)(row + min(j, len - 4));
 }
 
@@ -84,20 +91,30 @@ __device__ __forceinline__ floatx4 settle32(floatx4 v, int j, int len) {
          : past == 3 ? floatx4{v[3], 0.f, 0.f, 0.f} : floatx4{0.f, 0.f, 0.f, 0.f};
 }
 
+template <bool RAGGED = true>
 __device__ __forceinline__ floatx4 row_piece32(const float* __restrict__ row, int j, int len) {
-    floatx4 v = raw_piece32(row, j, len);
-    if (len & 7) v = settle32(v, j, len);
+    floatx4 v = raw_piece32<RAGGED>(row, j, len);
+    if (RAGGED && (len & 7)) v = settle32(v, j, len);
     return v;
 }
 
-// a whole row in registers, read piece by piece with raw_piece32
-template <int DMAX>
-__device__ __forceinline__ void settle_row32(float (&x)[DMAX], int len) {
-    if (len & 3) {
+// A whole row in registers, zeros past its end.  RAGGED: the pieces inside the row by plain loads at any
+// element's address, the one that crosses its end once more from len - 4 and moved into place: a
+// test of len at every load cost 15% of the direct kernels' time (see raw_piece16).
+template <int DMAX, bool RAGGED>
+__device__ __forceinline__ void load_row32(float (&x)[DMAX], const float* __restrict__ row, int len, bool live) {
 #pragma unroll
-        for (int j = 0; j < DMAX; j += 4)
+    for (int j = 0; j < DMAX; j += 4) {
+        floatx4 v = {0.f, 0.f, 0.f, 0.f};
+        if (live && (RAGGED ? j + 4 <= len : j < len)) v = RAGGED ? (floatx4)*(const floatx4_any*)(row + j) : *(const floatx4*)(row + j);
+        x[j] = v[0]; x[j + 1] = v[1]; x[j + 2] = v[2]; x[j + 3] = v[3];
+    }
+    if (RAGGED && (len & 3) && live) {
+        const floatx4 last = *(const floatx4_any*)(row + len - 4);
+#pragma unroll
+        for (int j = 4; j < DMAX; j += 4)
             if (j == (len & ~3)) {
-                const floatx4 v = settle32(floatx4{x[j], x[j + 1], x[j + 2], x[j + 3]}, j, len);
+                const floatx4 v = settle32(last, j, len);
                 x[j] = v[0]; x[j + 1] = v[1]; x[j + 2] = v[2]; x[j + 3] = v[3];
             }
     }

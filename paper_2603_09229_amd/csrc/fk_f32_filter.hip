@@ -476,13 +476,7 @@ __device__ __forceinline__ void list_by_thread(
         const int64_t at = g + threadIdx.x;
         const int own = list[min(at, (int64_t)len - 1)];
         float x[DMAX];
-#pragma unroll
-        for (int j = 0; j < DMAX; j += 4) {
-            floatx4 v = {0.f, 0.f, 0.f, 0.f};
-            if (j < row_len) v = raw_piece32(X + (size_t)own * row_len, j, row_len);
-            x[j] = v[0]; x[j + 1] = v[1]; x[j + 2] = v[2]; x[j + 3] = v[3];
-        }
-        settle_row32<DMAX>(x, row_len);
+        load_row32<DMAX, true>(x, X + (size_t)own * row_len, row_len, true);
         float m = INFINITY;
         int a = none;
         for (int k0 = 0; k0 < K; k0 += TK) {

@@ -39,12 +39,15 @@ __device__ __forceinline__ int find_cluster(const int32_t* __restrict__ item_off
 // lanes span a row, so a wave reads 64 >> lpr_log2 rows per load instruction.  With WPI = 4
 // wave w takes the 64-row batches w, w+4, ... of the item and the four wave sums are added in
 // wave order through LDS.
-template <int EPL, bool BF, int WPI>
+// RAGGED: rows whose length is no multiple of 8, read as they are stored (skipped at run time, that code costs
+// the others 3%: 342180 points, d = 512, K = 34: 68.3 -> 70.4 us).
+template <int EPL, bool BF, int WPI, bool RAGGED>
 __global__ __launch_bounds__(256) void segment_reduce_kernel(
     const void* __restrict__ Xv, const int32_t* __restrict__ sorted_idx,
     const int32_t* __restrict__ seg_off, const int32_t* __restrict__ item_off,
-    float* __restrict__ partial, int64_t N, int d, int len, int K, int R, int64_t max_items,
-    int lpr_log2) {
+    float* __restrict__ partial, int64_t N, int d, int K, int R, int64_t max_items,
+    int lpr_log2, int row_len) {
+    const int len = RAGGED ? row_len : d;
     __shared__ float wsum[WPI == 4 ? 4 : 1][WPI == 4 ? 512 : 1];
     const int b = blockIdx.y;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -69,7 +72,7 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
         const bool active = col < d;
         // this lane's piece of a row, or where that would cross the row's end the one that ends
         // there; of the sums only those at its own columns are kept (from len on nobody reads them)
-        const int first = min(col, len - EPL);
+        const int first = RAGGED ? min(col, len - EPL) : col;
         const char* mine = X + first * (16 / EPL);
         const int row_bytes = len * (16 / EPL);
         float acc[EPL];
@@ -89,7 +92,10 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
                     const int idx = __shfl(myidx, rr & 63);
                     ok[u] = active && rr < nrows;
                     v[u] = uintx4{0u, 0u, 0u, 0u};
-                    if (ok[u]) v[u] = *(const uintx4_any*)(mine + (int64_t)idx * row_bytes);
+                    if (ok[u]) {
+                        const char* at = mine + (int64_t)idx * row_bytes;
+                        v[u] = RAGGED ? (uintx4)*(const uintx4_any*)at : *(const uintx4*)at;
+                    }
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
@@ -114,7 +120,7 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
         if (slot == 0 && active) {
             if (WPI == 1) {
                 float* out = partial + ((size_t)b * max_items + item) * d + first;
-                if (first == col) {
+                if (!RAGGED || first == col) {
 #pragma unroll
                     for (int e = 0; e < EPL; e += 4)
                         *(floatx4*)(out + e) = floatx4{acc[e], acc[e + 1], acc[e + 2], acc[e + 3]};
@@ -126,7 +132,7 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
             } else {
 #pragma unroll
                 for (int e = 0; e < EPL; ++e)
-                    if (first + e >= col) wsum[wave][first + e] = acc[e];
+                    if (!RAGGED || first + e >= col) wsum[wave][first + e] = acc[e];
             }
         }
     }
@@ -147,18 +153,20 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
 // centroid).  When c_frag is given, the rounded centroid is also
 // written in MFMA fragment order together with its score bias -||c||^2/2, so the next
 // assignment needs no separate re-layout pass.
-template <bool kLate>
+template <bool kLate, bool RAGGED>
 __global__ __launch_bounds__(1024) void finalize_kernel(
     const float* __restrict__ partial, const int32_t* __restrict__ seg_off,
     const int32_t* __restrict__ item_off, const float* C_prev, float* C_out,
     uint16_t* __restrict__ C_lp_out, float* __restrict__ C_lp_f32_out,
     uint16_t* __restrict__ c_frag, float* __restrict__ c_bias, int32_t* __restrict__ counts,
-    float* __restrict__ sums, int d, int len, int K, int64_t max_items, int ktiles, int dch,
+    float* __restrict__ sums, int d, int K, int64_t max_items, int ktiles, int dch,
     int accumulate, int normalise, int bf, const int32_t* __restrict__ wg_counts, int G,
-    const float* __restrict__ late_sums, const int32_t* __restrict__ late_counts, int late) {
+    const float* __restrict__ late_sums, const int32_t* __restrict__ late_counts, int late,
+    int row_len) {
     // dynamic LDS: 4 floats per thread for the row sums, then d floats for the squared entries
     // (a fixed worst-case array would cap the small workgroups of many-cluster shapes at a
     // few per CU)
+    const int len = RAGGED ? row_len : d;
     extern __shared__ float fin_lds[];
     float* red = fin_lds;
     float* nrm = fin_lds + 4 * blockDim.x;
@@ -236,9 +244,9 @@ __global__ __launch_bounds__(1024) void finalize_kernel(
         if (normalise) {
             // the caller's rows have no padding; past their end everything is zero
             const size_t at = ((size_t)b * K + k) * len + j;
-            const float c = j >= len ? 0.f : n > 0 ? (float)((double)s / (double)n) : C_prev[at];
+            const float c = RAGGED && j >= len ? 0.f : n > 0 ? (float)((double)s / (double)n) : C_prev[at];
             const uint16_t lp = float_to_lp(c, bf);
-            if (j < len) {
+            if (!RAGGED || j < len) {
                 C_out[at] = c;
                 if (C_lp_out) C_lp_out[at] = lp;
                 if (C_lp_f32_out) C_lp_f32_out[at] = c;
@@ -288,14 +296,10 @@ fk_status launch_segment_reduce(const Geometry& g, const Workspace& w, const voi
     dim3 grid((unsigned)(wide ? g.max_items : cdiv(g.max_items, 4)), g.B), block(256);
 #define FK_REDUCE(EPL, BF)                                                                        \
     do {                                                                                          \
-        if (wide)                                                                                 \
-            hipLaunchKernelGGL((segment_reduce_kernel<EPL, BF, 4>), grid, block, 0, s, X,         \
-                               sorted_idx, seg_off, item_off, w.partial, g.N, g.d, g.len, g.K,    \
-                               g.rows_per_item, g.max_items, lpr_log2);                           \
-        else                                                                                      \
-            hipLaunchKernelGGL((segment_reduce_kernel<EPL, BF, 1>), grid, block, 0, s, X,         \
-                               sorted_idx, seg_off, item_off, w.partial, g.N, g.d, g.len, g.K,    \
-                               g.rows_per_item, g.max_items, lpr_log2);                           \
+        auto kern = g.len == g.d ? (wide ? segment_reduce_kernel<EPL, BF, 4, false> : segment_reduce_kernel<EPL, BF, 1, false>)  \
+                                 : (wide ? segment_reduce_kernel<EPL, BF, 4, true> : segment_reduce_kernel<EPL, BF, 1, true>);   \
+        hipLaunchKernelGGL(kern, grid, block, 0, s, X, sorted_idx, seg_off, item_off, w.partial, g.N, g.d, g.K,     \
+                           g.rows_per_item, g.max_items, lpr_log2, g.len);                               \
     } while (0)
     if (g.t == FK_F32) FK_REDUCE(4, false);
     else if (g.t == FK_F16) FK_REDUCE(8, false);
@@ -318,12 +322,13 @@ fk_status launch_finalize(const Geometry& g, const Workspace& w, const int32_t* 
     int threads = g.max_items / g.K > 64 ? 1024 : 256;
     if (g.d <= 128 && (g.max_items / g.K <= 4 || (g.max_items / g.K <= 8 && (int64_t)g.K * g.B >= 4096))) threads = 64;
     const size_t lds = ((size_t)4 * threads + g.d) * sizeof(float);
-    auto kern = a.late > 0 ? finalize_kernel<true> : finalize_kernel<false>;
+    auto kern = g.len == g.d ? (a.late > 0 ? finalize_kernel<true, false> : finalize_kernel<false, false>)
+                             : (a.late > 0 ? finalize_kernel<true, true> : finalize_kernel<false, true>);
     hipLaunchKernelGGL(kern, dim3(g.K, g.B), dim3(threads), lds, s, w.partial, seg_off,
                        item_off, a.C_prev_f32, a.C_out_f32, lp16, lp32, frag, a.c_bias, a.counts,
-                       a.sums, g.d, g.len, g.K, g.max_items, g.ktiles, g.dchunks, a.accumulate ? 1 : 0,
+                       a.sums, g.d, g.K, g.max_items, g.ktiles, g.dchunks, a.accumulate ? 1 : 0,
                        a.normalise ? 1 : 0, g.t == FK_BF16 ? 1 : 0, wg_counts, wg_per_cluster,
-                       a.late_sums, a.late_counts, a.late);
+                       a.late_sums, a.late_counts, a.late, g.len);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }
