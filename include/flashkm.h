@@ -219,7 +219,8 @@ fk_status fk_standard_update(const void* X, const int32_t* assign, const float* 
  * Section 4.3: a configuration is derived from the machine and the problem shape, with no
  * tuning run).  fk_plan writes a one-line description of what the in-core entry points would
  * launch for this shape into buf (host memory, NUL-terminated, truncated to buf_bytes):
- * assign kernel and tile shape, sort passes and tiling, reduction granularity, workspace.
+ * assign kernel and tile shape, sort passes and tiling, reduction granularity, workspace, and which
+ * rows are copied into padded ones first.
  * Host-only.  fk_set_option changes a choice for every later call of this process, so that the
  * choices can be checked against the alternatives (value -1 = back to the rule of the shape):
  *   "assign_variant" v   tile shape v in 0..3 of the sweeping assign kernel

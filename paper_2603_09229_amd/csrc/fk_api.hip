@@ -494,6 +494,7 @@ int fk_plan(int B, int64_t N, int d, int K, fk_dtype t, char* buf, size_t buf_by
         return FK_EUNSUPPORTED;
     }
     char assign[96];
+    if (d >= 8) g.len = d;                       // as fk_assign has it
     if (f32_filter_enabled(g))
         snprintf(assign, sizeof(assign), "f32_filter(chunks=%d)", g.dchunks);
     else if (t == FK_F32)
@@ -534,9 +535,11 @@ int fk_plan(int B, int64_t N, int d, int K, fk_dtype t, char* buf, size_t buf_by
                  g.waves_per_item == 4 ? "workgroup_per_item" : "wave_per_item", g.rows_per_item,
                  (long long)g.max_items, carve(g, nullptr).bytes);
     }
-    if (g.d != g.d_user) {
+    if (rows_are_padded(g)) {
         const size_t n = strlen(buf);
-        if (n + 1 < buf_bytes) snprintf(buf + n, buf_bytes - n, " rows_padded=%d->%d", g.d_user, g.d);
+        if (n + 1 < buf_bytes)
+            snprintf(buf + n, buf_bytes - n, " rows_padded=%d->%d%s", g.d_user, g.d,
+                     g.d_user < 8 ? "" : "(fk_lloyd_iter and fk_update; fk_assign reads them as they are)");
     }
     {
         const DeviceInfo& di = device_info();

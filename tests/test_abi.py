@@ -109,7 +109,15 @@ def test_plan_describes_the_choice_per_shape():
     assert "f32_update" not in fk.fk_plan(1, 16384, 64, 64, f32)
     fk.fk_set_option("fused_update", -1)
     assert fk.fk_plan(1, 100, 600, 3, f16) == "unsupported"
-    assert "rows_padded=12->16" in fk.fk_plan(1, 100, 12, 40, f16)
+    # rows are read as they are stored, except for fewer than 8 elements and in the few-cluster update
+    assert "rows_padded" not in fk.fk_plan(1, 100, 12, 40, f16)
+    assert "rows_padded=12->16(fk_lloyd_iter and fk_update;" in fk.fk_plan(1, 100, 12, 16, f16)
+    assert fk.fk_plan(1, 100, 5, 40, f16).count("rows_padded=5->8 ") == 1
+    assert "mfma_stream" in fk.fk_plan(1, 1 << 24, 64, 48, f16)
+    assert "mfma_stream" not in fk.fk_plan(1, 1 << 24, 60, 48, f16)        # copies whole pieces: not from ragged rows
+    fk.fk_set_option("fused_update", 0)
+    assert "rows_padded" not in fk.fk_plan(1, 100, 12, 16, f16)
+    fk.fk_set_option("fused_update", -1)
     fk.fk_set_option("assign_variant", 1)
     assert "variant=1" in fk.fk_plan(1, 1 << 20, 128, 1024, f16)
     fk.fk_set_option("assign_variant", -1)
