@@ -191,8 +191,8 @@ Workspace carve(const Geometry& g, void* base, bool padded_x) {
     w.partial = (float*)take((size_t)g.B * std::max((size_t)g.max_items, fused_rows) * g.d * 4);
     if (fused_rows > 0) w.wg_counts = (int32_t*)take((size_t)g.B * fused_rows * 4);
     w.sums = (float*)take(BKd * 4);
-    if (g.d != g.d_user) {
-        if (padded_x && needs_padded_rows(g)) w.x_pad = take(BN * g.d * elem_size(g.t));
+    if (needs_padded_rows(g)) {
+        if (padded_x) w.x_pad = take(BN * g.d * elem_size(g.t));
         w.c_pad_f32 = (float*)take(BKd * 4);
         w.c_pad_lp = take(BKd * elem_size(g.t));
     }

@@ -70,7 +70,7 @@ struct Geometry {
                       // read the caller's rows (row_piece16 / row_piece32), d after the rows have
                       // been copied into zero-padded ones (zeros change no distance and no mean)
     fk_dtype t;
-    int dchunks;      // ceil(d / 16)
+    int dchunks;      // 16-feature chunks of the assignment kernel: ceil(d / 16) or the next number it is compiled for
     int ktiles;       // ceil(K / 32)
     bool one_pass;    // the one-pass updates may be taken: the process-wide option as it stood when this
                       // was filled in.  A call asks it once: whether rows are padded and which kernel
@@ -117,8 +117,8 @@ struct Workspace {
     float* f32_shift;    // [B,dchunks*16] shift of the filtered fp32 assignment (fk_f32_filter.hip)
     int32_t* f32_list_len; // [B] points it has left open (the points themselves: sorted_idx)
     void* x_pad;         // [B,N,d] zero-padded copy of X            (only when needs_padded_rows)
-    float* c_pad_f32;    // [B,K,d] zero-padded fp32 centroids       (only when d != d_user)
-    void* c_pad_lp;      // [B,K,d] zero-padded centroids, dtype t   (only when d != d_user)
+    float* c_pad_f32;    // [B,K,d] zero-padded fp32 centroids       (likewise)
+    void* c_pad_lp;      // [B,K,d] zero-padded centroids, dtype t   (likewise)
     size_t bytes;        // total bytes carved
 };
 

@@ -37,6 +37,8 @@ def test_workspace_sizes_are_sane():
     assert fk.fk_workspace_bytes(1, 1000, 64, 10, f32) % 256 == 0
     # a width that is not a multiple of 8 is served through a zero-padded copy: room for it
     assert fk.fk_workspace_bytes(1, 1000, 12, 4, f16) >= fk.fk_workspace_bytes(1, 1000, 16, 4, f16) + 1000 * 16 * 2
+    # ... and none for the centroids of shapes whose rows are read as they are stored
+    assert fk.fk_workspace_bytes(1, 1000, 500, 60000, f16) <= fk.fk_workspace_bytes(1, 1000, 504, 60000, f16)
     assert fk.fk_ooc_workspace_bytes(1 << 16, 100, 16, f16) >= 2 * (1 << 16) * 104 * 2   # chunk rows padded to 104
     for bad in [(0, 10, 64, 4), (1, 0, 64, 4), (1, 10, 0, 4), (1, 10, 520, 4), (1, 10, 64, 0),
                 (1, 10, 64, 65537), (3, 1 << 30, 64, 4), (65536, 4, 64, 4)]:
