@@ -39,7 +39,7 @@ typedef short shortx4 __attribute__((ext_vector_type(4)));
 // Dynamic LDS: centroid fragments [ktiles][DCH][64] x 16 B | batch rows [256][d/8] x 16 B |
 // bias [ktiles][32] floats | cluster ids [256] ints | per-wave point lists [8][256 + 32] ints.
 // RAGGED: rows whose length is no multiple of 8, read as they are stored (the code that settles their
-// last pieces costs the others 1% when it is only skipped).
+// last pieces costs the others 0.4% when it is only skipped).
 template <bool BF, int DCH, bool RAGGED>
 __global__ __launch_bounds__(512) void table_update_kernel(
     const uint16_t* __restrict__ X, const uintx4* __restrict__ c_frag,
