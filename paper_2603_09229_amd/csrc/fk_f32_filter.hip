@@ -370,7 +370,9 @@ __global__ __launch_bounds__(WAVES * 64) void assign_f32_filter_kernel(
 // list is spread thin and over in the time that a few rows take to arrive (5 to 20 us); with P =
 // 8 a long one is bound by the two vector instructions per term, as the direct kernels are.
 //   Long lists of rows of up to 64 features, where that form spends its time on reading centroid
-// rows: one point per thread with its features in registers, centroid tiles through LDS.
+// rows: one point per thread with its features in registers, centroid tiles through LDS.  (Not rows of
+// up to 16 against many centroids: it multiplies 32 features.  7 x 294694 points, d = 8, K = 14868: 60.1 ms
+// against 34.4.)
 //   What open points cost is then about the direct kernel's time for them on top of the filter's.
 // Every centroid twice, so that all points are open, fk_assign against the direct kernels alone: 2^20 points,
 // d = K = 64: 292 us, 222 (one addition to the list's length per wave: 610); d = 64, K = 256: 924, 814
@@ -476,7 +478,7 @@ __device__ __forceinline__ void list_by_thread(
         const int64_t at = g + threadIdx.x;
         const int own = list[min(at, (int64_t)len - 1)];
         float x[DMAX];
-        load_row32<DMAX, true>(x, X + (size_t)own * row_len, row_len, true);
+        load_row32<DMAX>(x, X + (size_t)own * row_len, row_len, true);
         float m = INFINITY;
         int a = none;
         for (int k0 = 0; k0 < K; k0 += TK) {
