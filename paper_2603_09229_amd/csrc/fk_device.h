@@ -98,23 +98,30 @@ __device__ __forceinline__ floatx4 row_piece32(const float* __restrict__ row, in
     return v;
 }
 
-// A whole row in registers, zeros past its end.  RAGGED: the pieces inside the row by plain loads at any
-// element's address, the one that crosses its end once more from len - 4 and moved into place: a
-// test of len at every load cost 15% of the direct kernels' time (see raw_piece16).
-template <int DMAX, bool RAGGED>
+// A whole ragged row in registers, zeros past its end: the pieces inside the row by plain loads at any
+// element's address, the one that crosses its end from len - 4 and moved into place.  A test of len at
+// every load instead is slower for DMAX = 32 and 128 (500000 points, d = 29, K = 9 58 us against 22; 10^6, d =
+// 100, K = 12 296 against 219), and the faster form for 64 (300000 points, d = 43, K = 20 34.4 against 37.4;
+// d = 60 the same).
+template <int DMAX>
 __device__ __forceinline__ void load_row32(float (&x)[DMAX], const float* __restrict__ row, int len, bool live) {
+    floatx4 last = {0.f, 0.f, 0.f, 0.f};
+    if (DMAX != 64 && (len & 3) && live) last = *(const floatx4_any*)(row + len - 4);
 #pragma unroll
     for (int j = 0; j < DMAX; j += 4) {
         floatx4 v = {0.f, 0.f, 0.f, 0.f};
-        if (live && (RAGGED ? j + 4 <= len : j < len)) v = RAGGED ? (floatx4)*(const floatx4_any*)(row + j) : *(const floatx4*)(row + j);
+        if constexpr (DMAX == 64) {
+            if (live && j < len) v = raw_piece32(row, j, len);
+        } else {
+            if (live && j + 4 <= len) v = *(const floatx4_any*)(row + j);
+        }
         x[j] = v[0]; x[j + 1] = v[1]; x[j + 2] = v[2]; x[j + 3] = v[3];
     }
-    if (RAGGED && (len & 3) && live) {
-        const floatx4 last = *(const floatx4_any*)(row + len - 4);
+    if (len & 3) {
 #pragma unroll
         for (int j = 4; j < DMAX; j += 4)
             if (j == (len & ~3)) {
-                const floatx4 v = settle32(last, j, len);
+                const floatx4 v = settle32(DMAX == 64 ? floatx4{x[j], x[j + 1], x[j + 2], x[j + 3]} : last, j, len);
                 x[j] = v[0]; x[j + 1] = v[1]; x[j + 2] = v[2]; x[j + 3] = v[3];
             }
     }
