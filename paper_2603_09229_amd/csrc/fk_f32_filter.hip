@@ -526,7 +526,7 @@ __global__ __launch_bounds__(512, 4) void assign_f32_list_kernel(
     while (teams * 8 * d > list_floats<DMAX>()) teams >>= 1;
     if (len <= 2 * thin * (int)gridDim.x)
         list_points<2>(X, C, list, len, assign, d, row_len, K, none, thin, xs, cand_d, cand_k);
-    else if (DMAX == 0 || len < 256 * (int)gridDim.x)
+    else if (DMAX == 0 || len < 256 * (int)gridDim.x || (K > 128 && d <= 16))
         list_points<8>(X, C, list, len, assign, d, row_len, K, none, teams, xs, cand_d, cand_k);
     else
         list_by_thread<DMAX == 0 ? 32 : DMAX>(X, C, list, len, assign, d, row_len, K, none, xs);
