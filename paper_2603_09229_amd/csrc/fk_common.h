@@ -150,9 +150,12 @@ fk_status launch_assign(const Geometry& g, const void* X, const void* C_or_frag,
 fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* X, const float* C,
                             int32_t* assign, float* min_dist, hipStream_t s);
 bool f32_filter_enabled(const Geometry& g);
-// Workgroups of 256 threads of its distance pass, 16 points at a time each.  A launch dimension holds fewer
-// than 2^32 threads, which one group per workgroup reaches at 2^28 points.
-inline int64_t f32_distance_blocks(int64_t N) { const int64_t groups = cdiv(N, 16), most = (int64_t)1 << 20; return groups < most ? groups : most; }
+// Workgroups of 256 threads of its distance pass, `lanes` threads a point.  A launch dimension holds fewer
+// than 2^32 threads, which one point per group of 16 lanes reaches at 2^28 points.
+inline int64_t f32_distance_blocks(int64_t N, int lanes) {
+    const int64_t groups = cdiv(N, 256 / lanes), most = (int64_t)1 << 20;
+    return groups < most ? groups : most;
+}
 // direct kernels, d <= 128: the four waves of a workgroup share a centroid tile (few points)
 inline bool f32_direct_is_split(const Geometry& g) { return g.d <= 128 && (int64_t)g.B * g.N < ((int64_t)1 << 18); }
 void set_f32_filter_option(int v);         // -1 = by shape, 0 = never, 1 = always

@@ -532,23 +532,27 @@ __global__ __launch_bounds__(512, 4) void assign_f32_list_kernel(
         list_by_thread<DMAX == 0 ? 32 : DMAX>(X, C, list, len, assign, d, row_len, K, none, xs);
 }
 
-// min_dist[i] = |x_i - c_a(i)|^2 by direct differences: 16 lanes a point, whole rows per load.  Infinity
-// where it is not finite, as in the direct kernels, whose minimum starts there.
+// min_dist[i] = |x_i - c_a(i)|^2 by direct differences: LANES (4, 8 or 16) lanes a point, enough for a whole
+// row per load where it has up to 64 features.  Infinity where it is not finite, as in the direct
+// kernels, whose minimum starts there.  (The lanes' sums meet in a butterfly: lanes without a piece add
+// zero, so that their number changes no bit.)
+template <int LANES>
 __global__ __launch_bounds__(256) void f32_distance_kernel(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ assign,
     float* __restrict__ min_dist, int64_t N, int len, int K) {
-    const int b = blockIdx.y, l = threadIdx.x & 15;
-    for (int64_t i = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4); i < N; i += (int64_t)gridDim.x * 16) {
+    const int b = blockIdx.y, l = threadIdx.x & (LANES - 1);
+    constexpr int kPoints = 256 / LANES;
+    for (int64_t i = (int64_t)blockIdx.x * kPoints + threadIdx.x / LANES; i < N; i += (int64_t)gridDim.x * kPoints) {
         const float* x = X + ((size_t)b * N + i) * len;
         const float* c = C + ((size_t)b * K + assign[(size_t)b * N + i]) * len;
         float s = 0.f;
-        for (int j = l * 4; j < len; j += 64) {
+        for (int j = l * 4; j < len; j += 4 * LANES) {
             const floatx4 u = row_piece32(x, j, len), v = row_piece32(c, j, len);
 #pragma unroll
             for (int e = 0; e < 4; ++e) { const float t = u[e] - v[e]; s = fmaf(t, t, s); }
         }
 #pragma unroll
-        for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o);   // (the 16 lanes of a point leave together)
+        for (int o = LANES / 2; o > 0; o >>= 1) s += __shfl_xor(s, o);   // (the lanes of a point leave together)
         if (l == 0) min_dist[(size_t)b * N + i] = s < INFINITY ? s : INFINITY;
     }
 }
@@ -618,7 +622,9 @@ fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* 
                        w.f32_list_len, assign, g.N, g.d, g.len, g.K, f32_direct_is_split(g) ? g.K - 1 : 0);
     FK_HIP(hipGetLastError());
     if (min_dist) {
-        hipLaunchKernelGGL(f32_distance_kernel, dim3((unsigned)f32_distance_blocks(g.N), g.B), dim3(256), 0, s, X, C, assign,
+        const int lanes = g.d <= 16 ? 4 : g.d <= 32 ? 8 : 16;
+        auto kern = lanes == 4 ? f32_distance_kernel<4> : lanes == 8 ? f32_distance_kernel<8> : f32_distance_kernel<16>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)f32_distance_blocks(g.N, lanes), g.B), dim3(256), 0, s, X, C, assign,
                            min_dist, g.N, g.len, g.K);
         FK_HIP(hipGetLastError());
     }

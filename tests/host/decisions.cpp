@@ -28,10 +28,12 @@ static int option_is_read_once() {
 
 // A launch dimension holds fewer than 2^32 threads.
 static int launches_fit() {
-    for (int64_t N : {(int64_t)1, (int64_t)16, (int64_t)17, (int64_t)1 << 24, ((int64_t)1 << 28) - 16, (int64_t)1 << 28, ((int64_t)1 << 31) - 1}) {
-        CHECK(fk::f32_distance_blocks(N) >= 1 && fk::f32_distance_blocks(N) * 256 <= UINT32_MAX);
-        CHECK(N > ((int64_t)1 << 24) || fk::f32_distance_blocks(N) * 16 >= N);   // one group each where that fits
-    }
+    for (int lanes : {4, 8, 16})
+        for (int64_t N : {(int64_t)1, (int64_t)16, (int64_t)17, (int64_t)1 << 24, ((int64_t)1 << 28) - 16, (int64_t)1 << 28, ((int64_t)1 << 31) - 1}) {
+            const int64_t blocks = fk::f32_distance_blocks(N, lanes);
+            CHECK(blocks >= 1 && blocks * 256 <= UINT32_MAX);
+            CHECK(N > ((int64_t)1 << 24) || blocks * (256 / lanes) >= N);   // one group each where that fits
+        }
     for (int option : {-1, 1})
         for (int64_t below : {1, 255, 256, 257}) {
             fk::Geometry g;
