@@ -128,7 +128,12 @@ bool make_geometry(int B, int64_t N, int d_user, int K, fk_dtype t, Geometry* g)
     // points, d = 512, K = 34: 49.7 and, with 32, 27.8).  Beyond two waves per SIMD that gives nothing and
     // the partial rows cost: 342180 points, d = 512, K = 34: 93.6 with 256, 90.8 with 128, 98.9 with 64;
     // 600000, d = 96 in fp32, K = 400: 58.8 with 256, 60.8 with 128.
-    while (R > 32 && B * (N / R + K) < 2000) R /= 2;
+    // (One workgroup merges a cluster's items, 32768 values at a time: with few clusters of wide rows more
+    // than two such rounds cost more than the shorter chains give.  35655 points, d = 512, K = 1: 43 us with 256 rows per
+    // item, 58 with 32, reduction and merge.)
+    int64_t row = 4;
+    while (row < d) row <<= 1;
+    while (R > 32 && B * (N / R + K) < 2000 && N / (R / 2) * row <= (int64_t)K * 65536) R /= 2;
     g->waves_per_item = 1;
     if (N > ((int64_t)1 << 22)) { R = cdiv(N, 4096); g->waves_per_item = 4; }
     g->rows_per_item = (int)R;
