@@ -147,8 +147,8 @@ bool make_geometry(int B, int64_t N, int d_user, int K, fk_dtype t, Geometry* g)
     if (t != FK_F32 && K > 32 && K <= 256 && d <= 128)
         g->table_grid_cap = (int)std::min<int64_t>(B >= 256 ? 1 : 256 / B, cdiv(N, 256));
     // small fp32 problems (at most 2^17 points in all, where the iteration is bound by its
-    // number of launches; d = K = 64: 18 against 38 us per iteration at 2^14 points, 50 against 56 at
-    // 2^17; d = 128, K = 64: 31 against 47 at 2^14, 64 against 56 at 2^16): 64-point batches, up to 2048
+    // number of launches; d = K = 64: 16.5 against 38 us per iteration at 2^14 points, 47 against 56 at
+    // 2^17; d = 128, K = 64: 30 against 47 at 2^14, 66 against 56 at 2^16): 64-point batches, up to 2048
     // workgroups in all
     g->f32_grid_cap = 0;
     if (t == FK_F32 && K <= 64 && d <= 128 && (int64_t)B * N <= ((int64_t)1 << 17))

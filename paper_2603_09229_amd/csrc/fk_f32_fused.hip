@@ -4,7 +4,7 @@
 // each; here it is two.  (For more points the one-point-per-thread assignment kernel followed by
 // the sort-inverse update is faster: this kernel gives every wave all 64 points of a batch.)
 //
-// The table of sums is K x d floats.  A workgroup of eight or sixteen waves walks 64-point batches, which it
+// The table of sums is K x d floats.  A workgroup of four to sixteen waves walks 64-point batches, which it
 // copies to LDS in whole lines one batch ahead: every wave then holds the 64 points (one per lane,
 // features in registers) and measures them against its share of the centroid rows by direct
 // differences in fp32, exactly as the stand-alone fp32 assignment kernels do (so the assignments
@@ -18,7 +18,7 @@
 // the ordinary merge/normalise kernel adds them in workgroup order.
 //
 // What bounds it at one batch per compute unit (N = 16384): a chain of latencies -- points to LDS,
-// 2 x 64 vector instructions per centroid, hand-over, adds.  An iteration takes 18 us with it (d = K =
+// 2 x 64 vector instructions per centroid, hand-over, adds.  An iteration takes 16.5 us with it (d = K =
 // 64; 28 with four waves that each read all points from memory and the centroids from LDS).
 #include <algorithm>
 
@@ -38,7 +38,8 @@ constexpr size_t f32_fused_lds() {
 
 // Grid (G, B): workgroup g handles the 64-point batches g, g + G, ...
 // partial: [B][K][G][d] floats, wg_counts: [B][K][G].
-template <int DMAX, int WAVES>
+// TAIL: rows whose length is no multiple of 16 (a test at every piece of a row cost all others 5 to 14%).
+template <int DMAX, int WAVES, bool TAIL>
 __global__ __launch_bounds__(WAVES * 64) void f32_update_kernel(
     const float* __restrict__ X, const float* __restrict__ C, int32_t* __restrict__ assign,
     float* __restrict__ partial, int32_t* __restrict__ wg_counts, int64_t N, int d, int len, int K) {
@@ -111,19 +112,35 @@ __global__ __launch_bounds__(WAVES * 64) void f32_update_kernel(
 #pragma unroll
             for (int j = 0; j < DMAX; j += 16) {
                 if (j + 16 <= len) {
+                    float p[16], q1[16];
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) { p[e] = c0[j + e]; q1[e] = c1[j + e]; }
+                    __builtin_amdgcn_sched_barrier(0);      // both rows asked for before the first wait
 #pragma unroll
                     for (int e = 0; e < 16; ++e) {
-                        const float u = x[j + e] - c0[j + e], v = x[j + e] - c1[j + e];
+                        const float u = x[j + e] - p[e], v = x[j + e] - q1[e];
                         D0 = fmaf(u, u, D0);
                         D1 = fmaf(v, v, D1);
                     }
-                } else if (j < len) {
+                }
+            }
+            if constexpr (TAIL) {
+                // the last len % 16 features, from LDS: once in the code, wherever the row ends
+                int j = len & ~15;
+                const float* xt = xs + lane * LD;
+                if (len & 8) {
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) {     // past the end both are zero
-                        const float u = x[j + e] - (j + e < len ? c0[j + e] : 0.f), v = x[j + e] - (j + e < len ? c1[j + e] : 0.f);
+                    for (int e = 0; e < 8; ++e) {
+                        const float t = xt[j + e], u = t - c0[j + e], v = t - c1[j + e];
                         D0 = fmaf(u, u, D0);
                         D1 = fmaf(v, v, D1);
                     }
+                    j += 8;
+                }
+                for (; j < len; ++j) {
+                    const float t = xt[j], u = t - c0[j], v = t - c1[j];
+                    D0 = fmaf(u, u, D0);
+                    D1 = fmaf(v, v, D1);
                 }
             }
             if (D0 < m) { m = D0; a = r; }
@@ -174,11 +191,11 @@ __global__ __launch_bounds__(WAVES * 64) void f32_update_kernel(
 }
 
 // ------------------------------------------------------------------------------------
-template <int DMAX, int WAVES>
-static fk_status launch_f32_update_t(const Geometry& g, const Workspace& w, const float* X,
+template <int DMAX, int WAVES, bool TAIL>
+static fk_status launch_f32_update_r(const Geometry& g, const Workspace& w, const float* X,
                                      const float* C, int32_t* assign, int* grid_out,
                                      hipStream_t s) {
-    auto kern = f32_update_kernel<DMAX, WAVES>;
+    auto kern = f32_update_kernel<DMAX, WAVES, TAIL>;
     const size_t lds = f32_fused_lds<DMAX, WAVES>();
     // set / queried once per kernel and device: the launch path stays free of runtime queries afterwards
     static PerDeviceInt per_cu;
@@ -188,15 +205,25 @@ static fk_status launch_f32_update_t(const Geometry& g, const Workspace& w, cons
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&q, kern, WAVES * 64, lds) != hipSuccess || q < 1) q = 1;
         per_cu.set(q);
     }
-    int64_t G = cdiv((int64_t)device_cu_count() * per_cu.get(), g.B);
+    // (a fourth workgroup of eight waves only adds tables to merge: N = 60000, d = 32, K = 64, six iterations:
+    // 150 us with, 135 without)
+    int64_t G = cdiv((int64_t)device_cu_count() * (WAVES == 4 ? per_cu.get() : std::min(per_cu.get(), 3)), g.B);
     G = std::min<int64_t>(G, g.f32_grid_cap);
     G = std::min<int64_t>(G, cdiv(g.N, 64));
     G = std::max<int64_t>(G, 1);
+    G = cdiv(cdiv(g.N, 64), cdiv(cdiv(g.N, 64), G));   // no more tables than as many rounds need: 7 x 13000, d = 128, K = 64 636 -> 518
     dim3 grid((unsigned)G, g.B), block(WAVES * 64);
     hipLaunchKernelGGL(kern, grid, block, lds, s, X, C, assign, w.partial, w.wg_counts, g.N, g.d, g.len, g.K);
     FK_HIP(hipGetLastError());
     *grid_out = (int)G;
     return FK_OK;
+}
+
+template <int DMAX, int WAVES>
+static fk_status launch_f32_update_t(const Geometry& g, const Workspace& w, const float* X, const float* C, int32_t* assign,
+                                     int* grid_out, hipStream_t s) {
+    return g.len % 16 == 0 ? launch_f32_update_r<DMAX, WAVES, false>(g, w, X, C, assign, grid_out, s)
+                           : launch_f32_update_r<DMAX, WAVES, true>(g, w, X, C, assign, grid_out, s);
 }
 
 fk_status launch_f32_update(const Geometry& g, const Workspace& w, const void* X,
@@ -206,12 +233,23 @@ fk_status launch_f32_update(const Geometry& g, const Workspace& w, const void* X
         return FK_EUNSUPPORTED;
     }
     const float* Xf = (const float*)X;
-    if (g.d <= 32) return launch_f32_update_t<32, 8>(g, w, Xf, C_f32, assign, grid_out, s);
-    if (g.d > 64) return launch_f32_update_t<128, 8>(g, w, Xf, C_f32, assign, grid_out, s);
-    // up to one batch per compute unit: sixteen waves finish it sooner (N = 16384, d = K = 64: 18.1 us per
-    // iteration against 20.0); beyond that two workgroups of eight overlap (N = 2^17: 49 against 61)
-    if (cdiv(g.N, 64) * g.B <= device_cu_count())
-        return launch_f32_update_t<64, 16>(g, w, Xf, C_f32, assign, grid_out, s);
+    // Waves per workgroup.  Few clusters leave more waves without rows, and smaller workgroups are more of
+    // them, each with its own chain of additions (six iterations, us, 4 / 8 / 16 waves, before the rows came
+    // in pairs of loads):
+    //   N = 16384, d = 64:    K = 4 86 / 91 / 99, K = 8 88 / 82 / 91, K = 32 122 / 97 / 95, K = 64 164 / 124 / 111
+    //   N = 2^17,  d = 64:    K = 8 165 / 185, K = 16 185 / 185, K = 64 300 / 284
+    //   N = 2^17,  d = 128:   K = 8 285 / 351, K = 16 335 / 356, K = 64 630 / 659;  N = 60000: K = 64 407 / 391
+    //   N = 7 x 13000, d = 128: K = 8 254 / 417, K = 64 638 / 792
+    const bool once = cdiv(g.N, 64) * g.B <= device_cu_count();      // up to one batch per compute unit
+    const bool four = g.K <= 4 || (!once && (g.K <= 8 || g.d > 64));
+    if (g.d <= 32)
+        return four ? launch_f32_update_t<32, 4>(g, w, Xf, C_f32, assign, grid_out, s)
+                    : launch_f32_update_t<32, 8>(g, w, Xf, C_f32, assign, grid_out, s);
+    if (g.d > 64)
+        return four ? launch_f32_update_t<128, 4>(g, w, Xf, C_f32, assign, grid_out, s)
+                    : launch_f32_update_t<128, 8>(g, w, Xf, C_f32, assign, grid_out, s);
+    if (four) return launch_f32_update_t<64, 4>(g, w, Xf, C_f32, assign, grid_out, s);
+    if (once && g.K > 16) return launch_f32_update_t<64, 16>(g, w, Xf, C_f32, assign, grid_out, s);
     return launch_f32_update_t<64, 8>(g, w, Xf, C_f32, assign, grid_out, s);
 }
 
