@@ -235,6 +235,8 @@ fk_status fk_standard_update(const void* X, const int32_t* assign, const float* 
  *   "sort_min_rounds" r  sort workgroups own at least r sub-tiles of 4096 keys (the rule gives
  *                        one up to 2^24 keys); changes fk_workspace_bytes, so set it before sizing
  *   "fused_update"   0   do not take the sort-free one-pass updates below
+ *   "gather_update"  n   0 = never take the sort-free update of small instances below, 1..64 = always, in
+ *                        that many parts; changes fk_workspace_bytes, so set it before sizing
  *   "timer_repeat"   r   measurement only: while the stage timer runs, the assignment (or fused)
  *                        kernel and the segment reduction are each launched r times back to back
  *                        inside their interval (same outputs rewritten), so that interval /
@@ -255,6 +257,9 @@ fk_status fk_standard_update(const void* X, const int32_t* assign, const float* 
  * cluster's row of the table of sums owned by one wave): at this size the iteration is bound by
  * its number of launches.  Same assignments and counts as the general path, sums up to fp32
  * summation order, bit-reproducible; fk_update alone keeps the sort-inverse path.
+ * Small instances (B*K*N <= 2^23 and a few MiB of points; any type): an update that none of the passes
+ * above takes is one launch without a sort, or two: every workgroup reads all assignments and adds the
+ * rows of one cluster.  Same counts as the sorted path, sums up to fp32 summation order, bit-reproducible.
  * All of these passes need room for one partial table per workgroup, which fk_workspace_bytes
  * includes.
  */

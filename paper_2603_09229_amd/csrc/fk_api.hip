@@ -70,6 +70,27 @@ static int ceil_log2(int v) {
 
 static std::atomic<int> g_sort_min_rounds{0};   // fk_set_option("sort_min_rounds")
 
+static std::atomic<int> g_gather_option{-1};    // fk_set_option("gather_update")
+void set_gather_update_option(int v) { g_gather_option.store(v, std::memory_order_relaxed); }
+
+// fk_update, us, sorted / this: 1340 points, d = 128, K = 72 17.4 / 5.9; 8192, d = 128, K = 1000 23.6 / 9.5 (points of
+// Zipf sizes 29.9 / 11.7); 16384, d = 128, K = 480 23.0 / 13.3 (38.8 / 16.9); fp32 250000, d = 32, K = 20 27.7 / 14.6.
+// Every cluster's workgroup reads all keys, and thousands of workgroups pay for themselves one after the
+// other: 5 instances of 3556, K = 448 21.1 / 22.4; 32768, K = 1024 24.6 / 23.5; 70001 x 3, K = 333 34.3 / 43.4.  A
+// workgroup adds its rows at 40-80 GB/s, so that it may have to add 2 MiB or 16384 rows at most even
+// if all points are in one cluster, and with few clusters, which leave the chip idle, parts of 512 KiB (15991 points,
+// d = 256, K = 15, Zipf sizes: one part 35.8, eight 13.9, sorted 32.8).  All points in one cluster: 16384, d = 128, K = 480 92 / 38;
+// 8000 fp32, d = 512, K = 100 63 / 56; 2010 fp32, d = 256, K = 467 24.0 / 26.7.
+int choose_gather_parts(int B, int64_t N, int d, int K, fk_dtype t) {
+    const int v = g_gather_option.load(std::memory_order_relaxed);
+    if (v >= 0) return N <= ((int64_t)1 << 30) ? v : 0;
+    const int64_t bytes = N * d * (int64_t)elem_size(t), clusters = (int64_t)B * K;
+    int64_t G = std::max(cdiv(bytes, (int64_t)2 << 20), cdiv(N, 16384));
+    if (G > 16 || clusters * G > 1024 || clusters * N > ((int64_t)8 << 20)) return 0;
+    if (clusters < 128) G = std::max(G, std::min<int64_t>(cdiv(bytes, (int64_t)512 << 10), 8));
+    return (int)G;
+}
+
 bool make_geometry(int B, int64_t N, int d_user, int K, fk_dtype t, Geometry* g) {
     if (B < 1 || N < 1 || K < 1 || K > 65536 || d_user < 1 || d_user > 512) return false;
     const int d = (d_user + 7) / 8 * 8;
@@ -153,6 +174,7 @@ bool make_geometry(int B, int64_t N, int d_user, int K, fk_dtype t, Geometry* g)
     g->f32_grid_cap = 0;
     if (t == FK_F32 && K <= 64 && d <= 128 && (int64_t)B * N <= ((int64_t)1 << 17))
         g->f32_grid_cap = (int)std::min<int64_t>(B >= 2048 ? 1 : 2048 / B, cdiv(N, 64));
+    g->gather_parts = choose_gather_parts(B, N, d, K, t);
     return true;
 }
 
@@ -192,7 +214,7 @@ Workspace carve(const Geometry& g, void* base, bool padded_x) {
         w.f32_list_len = (int32_t*)take((size_t)g.B * 4);
     }
     w.c_bias = (float*)take((size_t)g.B * g.ktiles * 32 * 4);
-    const size_t fused_rows = (size_t)g.K * std::max({g.fused_grid_cap, g.table_grid_cap, g.f32_grid_cap});
+    const size_t fused_rows = (size_t)g.K * std::max({g.fused_grid_cap, g.table_grid_cap, g.f32_grid_cap, g.gather_parts});
     w.partial = (float*)take((size_t)g.B * std::max((size_t)g.max_items, fused_rows) * g.d * 4);
     if (fused_rows > 0) w.wg_counts = (int32_t*)take((size_t)g.B * fused_rows * 4);
     w.sums = (float*)take(BKd * 4);
@@ -362,13 +384,25 @@ static bool rows_are_padded(const Geometry& g) {
     return g.d != g.d_user && (g.d_user < 8 || fused_update_enabled(g));
 }
 
-// update = sort-inverse + segment reduce + merge/normalise, all into the carved workspace
+// update = sort-inverse + segment reduce + merge/normalise, all into the carved workspace; small
+// instances without the sort
 static fk_status run_update(const Geometry& g, const Workspace& w, const void* X,
                             const int32_t* assign, const FinalizeArgs& fa, hipStream_t s) {
     if (fused_update_enabled(g)) return run_stream_update(g, w, X, (int32_t*)assign, false, fa, s);
+    const int rep = timer_repeat();
+    if (g.gather_parts > 0) {
+        for (int r = 0; r < rep; ++r) FK_TRY(launch_gather_update(g, w, X, assign, fa, s));
+        timer_mark(s, kStageReduce, rep);
+        if (gather_needs_merge(g, fa)) {
+            Geometry gm = g;
+            gm.max_items = (int64_t)g.K * g.gather_parts;
+            FK_TRY(launch_finalize(gm, w, nullptr, nullptr, fa, s, w.wg_counts, g.gather_parts));
+            timer_mark(s, kStageFinalize);
+        }
+        return FK_OK;
+    }
     FK_TRY(launch_sort_inverse(g, w, assign, w.sorted_idx, w.seg_off, w.item_off, s));
     timer_mark(s, kStageSort);
-    const int rep = timer_repeat();
     for (int r = 0; r < rep; ++r)
         FK_TRY(launch_segment_reduce(g, w, X, w.sorted_idx, w.seg_off, w.item_off, s));
     timer_mark(s, kStageReduce, rep);
@@ -484,6 +518,10 @@ int fk_set_option(const char* name, int value) {
         set_fused_update_option(value);
         return FK_OK;
     }
+    if (name && strcmp(name, "gather_update") == 0 && value >= -1 && value <= 64) {
+        set_gather_update_option(value);
+        return FK_OK;
+    }
     set_error("fk_set_option: unknown option or value out of range");
     return FK_EINVAL;
 }
@@ -532,6 +570,10 @@ int fk_plan(int B, int64_t N, int d, int K, fk_dtype t, char* buf, size_t buf_by
                  "per iteration, no sort; at most %d workgroups per instance) fk_assign alone=%s "
                  "fk_update alone=sort-inverse workspace=%zu",
                  g.f32_grid_cap, assign, carve(g, nullptr).bytes);
+    } else if (g.gather_parts > 0) {
+        snprintf(buf, buf_bytes,
+                 "assign=%s ktiles=%d update=gather(parts=%d, no sort) max_items=%lld workspace=%zu", assign, g.ktiles,
+                 g.gather_parts, (long long)g.max_items, carve(g, nullptr).bytes);
     } else {
         snprintf(buf, buf_bytes,
                  "assign=%s ktiles=%d sort=%dpass(tile=%d,blocks=%d) reduce=%s(rows_per_item=%d) "

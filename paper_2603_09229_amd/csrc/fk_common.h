@@ -95,6 +95,9 @@ struct Geometry {
     // one-pass assignment + sums for small fp32 problems (K <= 64, d <= 128, at most 2^17 points
     // in all; see fk_f32_fused.hip): most workgroups per instance, 0 when not eligible
     int f32_grid_cap;
+    // small instances: the update without a sort (see gather_update_kernel in fk_update.hip): into how many
+    // parts an instance is cut, 0 when the shape is not eligible
+    int gather_parts;
 };
 
 // Carved device workspace (all pointers 256-byte aligned inside the caller's buffer).
@@ -217,6 +220,16 @@ struct FinalizeArgs {
 fk_status launch_finalize(const Geometry& g, const Workspace& w, const int32_t* seg_off,
                           const int32_t* item_off, const FinalizeArgs& a, hipStream_t s,
                           const int32_t* wg_counts = nullptr, int wg_per_cluster = 0);
+
+// Small instances (g.gather_parts > 0): every workgroup reads all assignments of its part of the instance and adds the rows
+// of one cluster.  Writes what launch_finalize does; where gather_needs_merge, w.partial / w.wg_counts as
+// launch_stream_update with wg_per_cluster = g.gather_parts instead.
+fk_status launch_gather_update(const Geometry& g, const Workspace& w, const void* X, const int32_t* assign,
+                               const FinalizeArgs& a, hipStream_t s);
+// (parts that wait for their turn are added by the merge kernel)
+inline bool gather_needs_merge(const Geometry& g, const FinalizeArgs& a) { return g.gather_parts > 1 || a.late > 0; }
+int choose_gather_parts(int B, int64_t N, int d, int K, fk_dtype t);
+void set_gather_update_option(int v);      // -1 = by shape, 0 = never, 1..64 = always, in that many parts
 
 // Few clusters: stream X once, add every 32-point batch into per-workgroup K x d tables with a
 // one-hot MFMA (no sort, no gather); with compute_assign the assignment is computed (and

@@ -228,8 +228,6 @@ fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_
                 OOC_TRY(launch_assign(g, xbuf[bi], C_f32, nullptr, a, nullptr, cs, &w));
             else
                 OOC_TRY(launch_assign(g, xbuf[bi], w.c_frag, w.c_bias, a, nullptr, cs));
-            OOC_TRY(launch_sort_inverse(g, w, a, w.sorted_idx, w.seg_off, w.item_off, cs));
-            OOC_TRY(launch_segment_reduce(g, w, xbuf[bi], w.sorted_idx, w.seg_off, w.item_off, cs));
             FinalizeArgs fa;
             fa.C_prev_f32 = C_f32;
             fa.C_out_f32 = C_f32;
@@ -245,7 +243,16 @@ fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_
                 fa.late_counts = late_counts;
                 fa.late = (int)count;
             }
-            OOC_TRY(launch_finalize(g, w, w.seg_off, w.item_off, fa, cs));
+            if (g.gather_parts > 0) {
+                OOC_TRY(launch_gather_update(g, w, xbuf[bi], a, fa, cs));
+                g.max_items = (int64_t)K * g.gather_parts;
+                if (gather_needs_merge(g, fa))
+                    OOC_TRY(launch_finalize(g, w, nullptr, nullptr, fa, cs, w.wg_counts, g.gather_parts));
+            } else {
+                OOC_TRY(launch_sort_inverse(g, w, a, w.sorted_idx, w.seg_off, w.item_off, cs));
+                OOC_TRY(launch_segment_reduce(g, w, xbuf[bi], w.sorted_idx, w.seg_off, w.item_off, cs));
+                OOC_TRY(launch_finalize(g, w, w.seg_off, w.item_off, fa, cs));
+            }
             OOC_HIP(hipEventRecord(freed[bi], cs));
             used[bi] = true;
         }

@@ -145,28 +145,90 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
     }
 }
 
-// One workgroup (256 threads, or 1024 when clusters have many items) per cluster: s_k = sum
-// of the cluster's item rows in a fixed
-// order, n_k = seg_off[k+1] - seg_off[k].  Optionally added onto sums/counts already stored
+// Where a cluster's mean goes, and what is added to its sum on the way.
+struct EmitTo {
+    const float* C_prev;
+    float* C_out;
+    uint16_t* C_lp_out;
+    float* C_lp_f32_out;
+    uint16_t* c_frag;
+    float* c_bias;
+    int32_t* counts;
+    float* sums;
+    const float* late_sums;
+    const int32_t* late_counts;
+    int d, K, B, ktiles, dch, accumulate, normalise, bf, late, row_len;
+};
+
+// The end of an update, by the whole workgroup: cluster k of instance b has n points (late ones not among
+// them yet), sum_of(j) is the sum of their feature j.  Optionally added onto sums/counts already stored
 // (chunked mode; kLate: followed by the parts that have waited for their turn), optionally
 // normalised into centroids (Algorithm 3, last loop; an empty cluster keeps its previous
 // centroid).  When c_frag is given, the rounded centroid is also
 // written in MFMA fragment order together with its score bias -||c||^2/2, so the next
-// assignment needs no separate re-layout pass.
+// assignment needs no separate re-layout pass.  nrm: d floats of LDS.
+template <bool kLate, bool RAGGED, class Sum>
+__device__ __forceinline__ void emit_centroid(const EmitTo& to, int b, int k, int n, float* nrm, Sum sum_of) {
+    const int tid = threadIdx.x, d = to.d, K = to.K, T = (int)blockDim.x;
+    const int len = RAGGED ? to.row_len : d;
+    if constexpr (kLate)
+        for (int q = 0; q < to.late; ++q) n += to.late_counts[((size_t)q * to.B + b) * K + k];
+    for (int j = tid; j < d; j += T) {
+        float s = sum_of(j);
+        const size_t o = ((size_t)b * K + k) * d + j;
+        if (to.accumulate) s += to.sums[o];
+        if constexpr (kLate)
+            for (int q = 0; q < to.late; ++q) s += to.late_sums[(size_t)q * to.B * K * d + o];
+        if (to.sums) to.sums[o] = s;
+        if (to.normalise) {
+            // the caller's rows have no padding; past their end everything is zero
+            const size_t at = ((size_t)b * K + k) * len + j;
+            const float c = RAGGED && j >= len ? 0.f : n > 0 ? (float)((double)s / (double)n) : to.C_prev[at];
+            const uint16_t lp = float_to_lp(c, to.bf);
+            if (!RAGGED || j < len) {
+                to.C_out[at] = c;
+                if (to.C_lp_out) to.C_lp_out[at] = lp;
+                if (to.C_lp_f32_out) to.C_lp_f32_out[at] = c;
+            }
+            if (to.c_frag) {
+                // fragment order: tile k/32, chunk j/16, lane (j%16)/8*32 + k%32, element j%8
+                const size_t pos = ((((size_t)b * to.ktiles + (k >> 5)) * to.dch + (j >> 4)) * 64 +
+                                    (((j >> 3) & 1) << 5) + (k & 31)) * 8 + (j & 7);
+                to.c_frag[pos] = lp;
+                const float f = lp_to_float(lp, to.bf);
+                nrm[j] = __fmul_rn(f, f);
+            }
+        }
+    }
+    if (tid == 0) to.counts[(size_t)b * K + k] = n;
+    if (to.normalise && to.c_frag) {
+        __syncthreads();
+        // same association as the stand-alone layout kernel: groups of 8 features first (one
+        // thread per group; the first wave holds them all, d <= 512), then the groups in order
+        if (tid < 64) {
+            float ss = 0.f;
+            if (tid * 8 < d) {
+                for (int e = 0; e < 8; ++e) ss = __fadd_rn(ss, nrm[tid * 8 + e]);
+            }
+            float n2 = 0.f;
+            for (int g0 = 0; g0 * 8 < d; ++g0)
+                n2 = __fadd_rn(n2, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(ss), g0)));
+            if (tid == 0) to.c_bias[((size_t)b * to.ktiles) * 32 + k] = -0.5f * n2;
+        }
+    }
+}
+
+// One workgroup (256 threads, or 1024 when clusters have many items) per cluster: s_k = sum
+// of the cluster's item rows in a fixed order, n_k = seg_off[k+1] - seg_off[k]; then emit_centroid.
 template <bool kLate, bool RAGGED>
 __global__ __launch_bounds__(1024) void finalize_kernel(
     const float* __restrict__ partial, const int32_t* __restrict__ seg_off,
-    const int32_t* __restrict__ item_off, const float* C_prev, float* C_out,
-    uint16_t* __restrict__ C_lp_out, float* __restrict__ C_lp_f32_out,
-    uint16_t* __restrict__ c_frag, float* __restrict__ c_bias, int32_t* __restrict__ counts,
-    float* __restrict__ sums, int d, int K, int64_t max_items, int ktiles, int dch,
-    int accumulate, int normalise, int bf, const int32_t* __restrict__ wg_counts, int G,
-    const float* __restrict__ late_sums, const int32_t* __restrict__ late_counts, int late,
-    int row_len) {
+    const int32_t* __restrict__ item_off, EmitTo to, int64_t max_items,
+    const int32_t* __restrict__ wg_counts, int G) {
     // dynamic LDS: 4 floats per thread for the row sums, then d floats for the squared entries
     // (a fixed worst-case array would cap the small workgroups of many-cluster shapes at a
     // few per CU)
-    const int len = RAGGED ? row_len : d;
+    const int d = to.d, K = to.K;
     extern __shared__ float fin_lds[];
     float* red = fin_lds;
     float* nrm = fin_lds + 4 * blockDim.x;
@@ -193,7 +255,7 @@ __global__ __launch_bounds__(1024) void finalize_kernel(
         i1 = item_off[k + 1];
     }
     // read the running count before anyone overwrites it (barrier below)
-    const int n_prev = accumulate ? counts[(size_t)b * K + k] : 0;
+    const int n_prev = to.accumulate ? to.counts[(size_t)b * K + k] : 0;
     const float* P = partial + (size_t)b * max_items * d;
     // eight rows in flight per thread; the eight running sums are added in a fixed order
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -224,59 +286,203 @@ __global__ __launch_bounds__(1024) void finalize_kernel(
     if (!by_wave) *(floatx4*)&red[slot * dpow + col] = acc;
     else if ((tid & 63) < LR) *(floatx4*)&red[(tid >> 6) * dpow + col] = acc;
     __syncthreads();
-    const int T = (int)blockDim.x;
     int n = n_prev;
     if (wg_counts) {
         for (int q = 0; q < ((int)blockDim.x + 63) / 64; ++q) n += cred[q];
     } else {
         n += seg_off[k + 1] - seg_off[k];
     }
-    if constexpr (kLate)
-        for (int q = 0; q < late; ++q) n += late_counts[((size_t)q * gridDim.y + b) * K + k];
-    for (int j = tid; j < d; j += T) {
+    emit_centroid<kLate, RAGGED>(to, b, k, n, nrm, [&](int j) {
         float s = 0.f;
         for (int q = 0; q < sums_left; ++q) s += red[q * dpow + j];   // fixed order
-        const size_t o = ((size_t)b * K + k) * d + j;
-        if (accumulate) s += sums[o];
-        if constexpr (kLate)
-            for (int q = 0; q < late; ++q) s += late_sums[(size_t)q * gridDim.y * K * d + o];
-        if (sums) sums[o] = s;
-        if (normalise) {
-            // the caller's rows have no padding; past their end everything is zero
-            const size_t at = ((size_t)b * K + k) * len + j;
-            const float c = RAGGED && j >= len ? 0.f : n > 0 ? (float)((double)s / (double)n) : C_prev[at];
-            const uint16_t lp = float_to_lp(c, bf);
-            if (!RAGGED || j < len) {
-                C_out[at] = c;
-                if (C_lp_out) C_lp_out[at] = lp;
-                if (C_lp_f32_out) C_lp_f32_out[at] = c;
+        return s;
+    });
+}
+
+// ------------------------------------------------------------------------------------
+// Small instances (choose_gather_parts): the whole update, or all of it but the merge, in one launch and without a sort.  A workgroup
+// owns one cluster (or, with G parts, the points of one cluster in a G-th of the instance), reads every
+// assignment of its part, keeps the indices of its own points and adds their rows.  Every workgroup reads
+// all assignments, K*N in all, which come from L2; what it saves are the four to seven dependent
+// launches of the sort, each bound by latency at this size.
+// Wave w takes the 256-key blocks w, w + WAVES, ...; its matches collect in a list of its own in LDS and are
+// added 64 rows at a time, with the row pieces per lane of segment_reduce_kernel.  Which wave adds a
+// row and in which place follows from the assignments alone: fixed order, no atomics.
+template <int EPL, bool BF, bool RAGGED, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void gather_update_kernel(
+    const void* __restrict__ Xv, const int32_t* __restrict__ keys, EmitTo to,
+    float* __restrict__ partial, int32_t* __restrict__ wg_counts, int64_t N, int G, int merged, int lpr_log2) {
+    constexpr int kBlocks = EPL == 4 ? 2 : 1;      // column blocks of 64 lanes x 16 bytes in the widest row
+    constexpr int kAhead = 4;                      // key loads in flight per wave
+    constexpr int kList = 64 + 256;                // fewer than 64 waiting + one block's matches
+    typedef int32_t intx4_any __attribute__((ext_vector_type(4), aligned(4)));
+    extern __shared__ float gather_lds[];          // [WAVES][dpow] row sums | [d] squared entries
+    __shared__ int list[WAVES][kList];
+    __shared__ int pool[WAVES * 64];
+    __shared__ int left[WAVES], cred[WAVES];
+    const int d = to.d, K = to.K, len = RAGGED ? to.row_len : d;
+    const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int k = blockIdx.x / G, part = blockIdx.x - k * G;
+    const int64_t share = (N + G - 1) / G;
+    const int lo = (int)min(N, part * share), hi = (int)min(N, lo + share);
+    keys += (size_t)b * N;
+    const int n_prev = to.accumulate ? to.counts[(size_t)b * K + k] : 0;
+    // ids out of range belong to the first and the last cluster
+    const int32_t k_lo = k == 0 ? INT32_MIN : k, k_hi = k == K - 1 ? INT32_MAX : k;
+    const uint32_t span = (uint32_t)k_hi - (uint32_t)k_lo;
+
+    const int LPR = 1 << lpr_log2, S = 64 >> lpr_log2, slot = lane >> lpr_log2;
+    const int row_bytes = len * (16 / EPL);
+    const char* X = (const char*)Xv + (size_t)b * N * row_bytes;
+    float acc[kBlocks][EPL];
+#pragma unroll
+    for (int cb = 0; cb < kBlocks; ++cb)
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[cb][e] = 0.f;
+    int* mylist = list[wave];
+    int held = 0, own = 0;
+
+    auto add_rows = [&](const int* rows, int count) {
+        constexpr int U = 8;
+#pragma unroll
+        for (int cb = 0; cb < kBlocks; ++cb) {
+            const int col = cb * 64 * EPL + (lane & (LPR - 1)) * EPL;
+            if (cb > 0 && cb * 64 * EPL >= d) break;
+            const bool active = col < d;
+            // where a lane's piece would cross the row's end: the one that ends there (see segment_reduce_kernel)
+            const char* mine = X + (RAGGED ? min(col, len - EPL) : col) * (16 / EPL);
+            for (int q = 0; q < count; q += S * U) {
+                uintx4 v[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int rr = q + u * S + slot;
+                    v[u] = uintx4{0u, 0u, 0u, 0u};
+                    if (active && rr < count) {
+                        const char* at = mine + (int64_t)rows[rr] * row_bytes;
+                        v[u] = RAGGED ? (uintx4)*(const uintx4_any*)at : *(const uintx4*)at;
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if constexpr (EPL == 4) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[cb][e] += __uint_as_float(v[u][e]);
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            acc[cb][2 * e] += lp_to_float((uint16_t)(v[u][e] & 0xFFFFu), BF);
+                            acc[cb][2 * e + 1] += lp_to_float((uint16_t)(v[u][e] >> 16), BF);
+                        }
+                    }
+                }
             }
-            if (c_frag) {
-                // fragment order: tile k/32, chunk j/16, lane (j%16)/8*32 + k%32, element j%8
-                const size_t pos = ((((size_t)b * ktiles + (k >> 5)) * dch + (j >> 4)) * 64 +
-                                    (((j >> 3) & 1) << 5) + (k & 31)) * 8 + (j & 7);
-                c_frag[pos] = lp;
-                const float f = lp_to_float(lp, bf);
-                nrm[j] = __fmul_rn(f, f);
+        }
+    };
+
+    const uint64_t lt = (1ull << lane) - 1ull;
+    // one block's matches (of every key, or only of those before hi) go on the list
+    auto take = [&](const intx4_any& kv, int at, bool whole) {
+        uint64_t mm[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mm[e] = __ballot((uint32_t)kv[e] - (uint32_t)k_lo <= span && (whole || at + e < hi));
+        if ((mm[0] | mm[1] | mm[2] | mm[3]) == 0) return;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if ((mm[e] >> lane) & 1) mylist[held + __popcll(mm[e] & lt)] = at + e;
+            held += __popcll(mm[e]);
+        }
+        __builtin_amdgcn_wave_barrier();
+        while (held >= 64) {
+            held -= 64;
+            own += 64;
+            add_rows(mylist + held, 64);
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    constexpr int kStride = WAVES * 256;
+    int base = lo + wave * 256;
+    for (; base + (kAhead - 1) * kStride + 256 <= hi; base += kAhead * kStride) {
+        intx4_any kv[kAhead];
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) kv[a] = *(const intx4_any*)(keys + (base + a * kStride + lane * 4));
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) take(kv[a], base + a * kStride + lane * 4, true);
+    }
+    if (base < hi) {
+        intx4_any kv[kAhead];
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) {
+            const int at = base + a * kStride + lane * 4;
+            kv[a] = intx4_any{0, 0, 0, 0};
+            if (at + 4 <= hi) {
+                kv[a] = *(const intx4_any*)(keys + at);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (at + e < hi) kv[a][e] = keys[at + e];
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a)
+            if (base + a * kStride < hi) take(kv[a], base + a * kStride + lane * 4, false);
+    }
+    // what is left, fewer than 64 rows a wave, is shared out again in whole batches of loads: most clusters
+    // here have a few rows in all, and the waves without any are done
+    if (lane == 0) { left[wave] = held; cred[wave] = own + held; }
+    __syncthreads();
+    int n = n_prev, rest = 0, before = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        n += cred[w];
+        before += w < wave ? left[w] : 0;
+        rest += left[w];
+    }
+    if (lane < held) pool[before + lane] = mylist[lane];
+    __syncthreads();
+    const int batch = 8 * S, mine0 = wave * batch;
+    bool busy = own > 0;
+    for (int q = mine0; q < rest; q += WAVES * batch) {
+        busy = true;
+        add_rows(pool + q, min(batch, rest - q));
+    }
+
+    int dpow = 4;
+    while (dpow < d) dpow <<= 1;
+    float* red = gather_lds;
+    float* nrm = red + WAVES * dpow;
+    if (busy) {
+#pragma unroll
+        for (int cb = 0; cb < kBlocks; ++cb) {
+            if (cb > 0 && cb * 64 * EPL >= d) break;
+            const int col = cb * 64 * EPL + (lane & (LPR - 1)) * EPL;
+            const int first = RAGGED ? min(col, len - EPL) : col;
+            for (int o = LPR; o < 64; o <<= 1) {
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) acc[cb][e] += __shfl_xor(acc[cb][e], o);
+            }
+            if (slot == 0 && col < d) {
+#pragma unroll
+                for (int e = 0; e < EPL; ++e)
+                    if (!RAGGED || first + e >= col) red[wave * dpow + first + e] = acc[cb][e];
             }
         }
     }
-    if (tid == 0) counts[(size_t)b * K + k] = n;
-    if (normalise && c_frag) {
-        __syncthreads();
-        // same association as the stand-alone layout kernel: groups of 8 features first (one
-        // thread per group; the first wave holds them all, d <= 512), then the groups in order
-        if (tid < 64) {
-            float ss = 0.f;
-            if (tid * 8 < d) {
-                for (int e = 0; e < 8; ++e) ss = __fadd_rn(ss, nrm[tid * 8 + e]);
-            }
-            float n2 = 0.f;
-            for (int g0 = 0; g0 * 8 < d; ++g0)
-                n2 = __fadd_rn(n2, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(ss), g0)));
-            if (tid == 0) c_bias[((size_t)b * ktiles) * 32 + k] = -0.5f * n2;
-        }
+    if (lane == 0) left[wave] = busy ? 1 : 0;      // (read by everyone before the last barrier)
+    __syncthreads();
+    auto sum_of = [&](int j) {
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w)
+            if (left[w]) s += red[w * dpow + j];
+        return s;
+    };
+    if (merged) {                                  // a row and a count for the merge kernel
+        const size_t row = ((size_t)b * K + k) * G + part;
+        for (int j = tid; j < d; j += WAVES * 64) partial[row * d + j] = sum_of(j);
+        if (tid == 0) wg_counts[row] = n - n_prev;
+        return;
     }
+    emit_centroid<false, RAGGED>(to, b, k, n, nrm, sum_of);
 }
 
 // ------------------------------------------------------------------------------------
@@ -309,13 +515,58 @@ fk_status launch_segment_reduce(const Geometry& g, const Workspace& w, const voi
     return FK_OK;
 }
 
+static EmitTo emit_args(const Geometry& g, const FinalizeArgs& a) {
+    EmitTo to;
+    to.C_prev = a.C_prev_f32;
+    to.C_out = a.C_out_f32;
+    to.C_lp_out = g.t == FK_F32 ? nullptr : (uint16_t*)a.C_out_lp;
+    to.C_lp_f32_out = g.t != FK_F32 || a.C_out_lp == a.C_out_f32 ? nullptr : (float*)a.C_out_lp;
+    to.c_frag = g.t == FK_F32 ? nullptr : (uint16_t*)a.c_frag;
+    to.c_bias = a.c_bias;
+    to.counts = a.counts;
+    to.sums = a.sums;
+    to.late_sums = a.late_sums;
+    to.late_counts = a.late_counts;
+    to.d = g.d; to.K = g.K; to.B = g.B; to.ktiles = g.ktiles; to.dch = g.dchunks;
+    to.accumulate = a.accumulate ? 1 : 0;
+    to.normalise = a.normalise ? 1 : 0;
+    to.bf = g.t == FK_BF16 ? 1 : 0;
+    to.late = a.late;
+    to.row_len = g.len;
+    return to;
+}
+
+template <int EPL, bool BF, int WAVES>
+static fk_status launch_gather_w(const Geometry& g, const Workspace& w, const void* X, const int32_t* assign,
+                                 const EmitTo& to, int G, bool merged, hipStream_t s) {
+    const int lpr_log2 = std::min(6, ceil_log2((int)cdiv(g.d, EPL)));
+    int dpow = 4;
+    while (dpow < g.d) dpow <<= 1;
+    const size_t lds = ((size_t)WAVES * dpow + g.d) * sizeof(float);      // at most 16 x 512 + 512 floats
+    auto kern = g.len == g.d ? gather_update_kernel<EPL, BF, false, WAVES> : gather_update_kernel<EPL, BF, true, WAVES>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)g.K * G), g.B), dim3(WAVES * 64), lds, s, X, assign, to, w.partial,
+                       w.wg_counts, g.N, G, merged ? 1 : 0, lpr_log2);
+    FK_HIP(hipGetLastError());
+    return FK_OK;
+}
+
+fk_status launch_gather_update(const Geometry& g, const Workspace& w, const void* X, const int32_t* assign,
+                               const FinalizeArgs& a, hipStream_t s) {
+    const int G = g.gather_parts;
+    const bool merged = gather_needs_merge(g, a);
+    const EmitTo to = emit_args(g, a);
+    // sixteen waves where a compute unit has one workgroup (it is then bound by its loads in flight: 15991 points,
+    // d = 256, K = 15, Zipf sizes 17.3 -> 15.0 us), four where many workgroups have little to read
+    const int64_t workgroups = (int64_t)g.B * g.K * G;
+    const bool large = workgroups <= 256, medium = workgroups <= 512 || cdiv(g.N, G) > 1024;
+    if (g.t == FK_F32) return (large ? launch_gather_w<4, false, 16> : medium ? launch_gather_w<4, false, 8> : launch_gather_w<4, false, 4>)(g, w, X, assign, to, G, merged, s);
+    if (g.t == FK_F16) return (large ? launch_gather_w<8, false, 16> : medium ? launch_gather_w<8, false, 8> : launch_gather_w<8, false, 4>)(g, w, X, assign, to, G, merged, s);
+    return (large ? launch_gather_w<8, true, 16> : medium ? launch_gather_w<8, true, 8> : launch_gather_w<8, true, 4>)(g, w, X, assign, to, G, merged, s);
+}
+
 fk_status launch_finalize(const Geometry& g, const Workspace& w, const int32_t* seg_off,
                           const int32_t* item_off, const FinalizeArgs& a, hipStream_t s,
                           const int32_t* wg_counts, int wg_per_cluster) {
-    uint16_t* lp16 = g.t == FK_F32 ? nullptr : (uint16_t*)a.C_out_lp;
-    float* lp32 = g.t == FK_F32 ? (float*)a.C_out_lp : nullptr;
-    if (lp32 == a.C_out_f32) lp32 = nullptr;
-    uint16_t* frag = g.t == FK_F32 ? nullptr : (uint16_t*)a.c_frag;
     // few clusters with many partial rows each: more rows in flight per workgroup
     // ... and many clusters with few rows each (up to 4, or up to 8 when there are thousands of
     // clusters to spread over the chip): the smallest workgroup that still has a thread per feature
@@ -324,11 +575,8 @@ fk_status launch_finalize(const Geometry& g, const Workspace& w, const int32_t* 
     const size_t lds = ((size_t)4 * threads + g.d) * sizeof(float);
     auto kern = g.len == g.d ? (a.late > 0 ? finalize_kernel<true, false> : finalize_kernel<false, false>)
                              : (a.late > 0 ? finalize_kernel<true, true> : finalize_kernel<false, true>);
-    hipLaunchKernelGGL(kern, dim3(g.K, g.B), dim3(threads), lds, s, w.partial, seg_off,
-                       item_off, a.C_prev_f32, a.C_out_f32, lp16, lp32, frag, a.c_bias, a.counts,
-                       a.sums, g.d, g.K, g.max_items, g.ktiles, g.dchunks, a.accumulate ? 1 : 0,
-                       a.normalise ? 1 : 0, g.t == FK_BF16 ? 1 : 0, wg_counts, wg_per_cluster,
-                       a.late_sums, a.late_counts, a.late, g.len);
+    hipLaunchKernelGGL(kern, dim3(g.K, g.B), dim3(threads), lds, s, w.partial, seg_off, item_off, emit_args(g, a),
+                       g.max_items, wg_counts, wg_per_cluster);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }

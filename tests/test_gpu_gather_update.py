@@ -1,0 +1,83 @@
+"""The update of small instances without a sort (gather_update_kernel in csrc/fk_update.hip): counts of the sorted path and
+means of the 64-bit sums, over parts, waves per workgroup, widths, ids out of range and one cluster with everything."""
+import pytest
+import torch
+
+from paper_2603_09229_amd import binding as fk
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("B,N,d,K", [
+    (1, 1, 8, 1), (2, 63, 9, 3), (3, 255, 16, 5), (1, 257, 5, 40), (1, 1025, 33, 300), (2, 4097, 100, 70), (1, 5000, 255, 2),
+    (1, 6001, 256, 17), (1, 3000, 260, 600), (1, 2500, 511, 33), (1, 2049, 512, 1), (5, 1111, 64, 200), (1, 16384, 24, 130),
+])
+def test_gathered_update(dtype, B, N, d, K):
+    g = torch.Generator(device=DEV).manual_seed(N + d + K)
+    X = torch.randn((B, N, d), generator=g, device=DEV).to(dtype)
+    C0 = torch.randn((B, K, d), generator=g, device=DEV)
+    skewed = (K * torch.rand((B, N), generator=g, device=DEV) ** 4).int() - 1      # -1 and K belong to the first and the last
+    for label in (skewed, torch.full_like(skewed, K // 2), skewed + 2):
+        at = label.clamp(0, K - 1).long()
+        n = torch.stack([torch.bincount(a, minlength=K) for a in at])
+        x = X.double().cpu()
+        total = torch.zeros((B, K, d), dtype=torch.float64).scatter_add_(1, at.cpu()[..., None].expand(B, N, d), x).to(DEV)
+        size = torch.zeros((B, K, d), dtype=torch.float64).scatter_add_(1, at.cpu()[..., None].expand(B, N, d), x.abs()).to(DEV)
+        want = torch.where(n[..., None] > 0, total / n.clamp(min=1)[..., None], C0.double())
+        # n additions of 2^-24 of the magnitudes' sum each at most, divided by n, and the rounded mean
+        bound = 2.0 ** -24 * (size + want.abs())
+        try:
+            for parts in (-1, 1, 2, 7):
+                fk.fk_set_option("fused_update", 0)
+                fk.fk_set_option("gather_update", parts)
+                assert parts < 0 or f"gather(parts={parts}," in fk.fk_plan(B, N, d, K, dtype)
+                C, lp, m = fk.fk_update(X, label, C0)
+                assert torch.equal(m.long(), n)
+                assert ((C.double() - want).abs() <= bound).all()
+                assert torch.equal(lp, C.to(dtype))
+                again = fk.fk_update(X, label, C0)
+                assert torch.equal(C, again[0]) and torch.equal(lp, again[1])
+                if B == 1 and parts > 0:
+                    # inside a fit: the next assignment reads the fragments and biases written here
+                    D = C0.clone()
+                    a, c, _ = fk.fk_lloyd_iter(X, D, 2)
+                    fk.fk_set_option("gather_update", 0)
+                    E = C0.clone()
+                    b, e, _ = fk.fk_lloyd_iter(X, E, 1)
+                    fk.fk_set_option("gather_update", parts)
+                    F = C0.clone()
+                    f, h, _ = fk.fk_lloyd_iter(X, F, 1)
+                    assert torch.equal(b, f) and torch.equal(e, h)
+                    h, _, _ = fk.fk_lloyd_iter(X, F, 1)
+                    assert torch.equal(a, h) and torch.equal(D, F)
+        finally:
+            fk.fk_set_option("gather_update", -1)
+            fk.fk_set_option("fused_update", -1)
+
+
+@pytest.mark.parametrize("parts", [1, 3])
+@pytest.mark.parametrize("dtype,N,d,K,chunk", [(torch.float16, 6001, 72, 50, 2001), (torch.bfloat16, 7100, 20, 33, 1024), (torch.float32, 4100, 3, 10, 1000)])
+def test_out_of_core_chunks(dtype, N, d, K, chunk, parts):
+    g = torch.Generator().manual_seed(N)
+    centre = 8 * torch.randn((K, d), generator=g)
+    lab = torch.cat([torch.arange(K), torch.randint(0, K, (N - K,), generator=g)])
+    X = (centre[lab] + 0.3 * torch.randn((N, d), generator=g)).to(dtype).pin_memory()
+    got = []
+    try:
+        for v in (0, parts):
+            fk.fk_set_option("gather_update", v)
+            ws = torch.empty(fk.fk_ooc_workspace_bytes(chunk, d, K, dtype), dtype=torch.uint8, device=DEV)
+            C, D = (X[:K].float().to(DEV).contiguous() for _ in range(2))
+            a, n = fk.fk_lloyd_ooc(X, C, 3, dev_ws=ws, chunk_rows=chunk)
+            for _ in range(3):
+                fk.fk_lloyd_ooc(X, D, 1, dev_ws=ws, chunk_rows=chunk)
+            assert torch.equal(C, D)             # chunks that wait for their turn (merged) and those that do not
+            got.append((a, n, C))
+    finally:
+        fk.fk_set_option("gather_update", -1)
+    (a, n, C), (b, m, D) = got
+    assert torch.equal(a, b) and torch.equal(n, m)
+    # the same n terms in two orders: n 2^-24 of their largest each, divided by n
+    assert ((C - D).abs() <= 2 * 2.0 ** -24 * n.amax() * X.float().abs().max()).all()
