@@ -19,55 +19,98 @@ namespace {
 
 __device__ __forceinline__ int clamp_key(int k, int kmax) { return min(max(k, 0), kmax); }
 
-// Lanes of the wave whose `digit` equals this lane's, among lanes in `valid`.
-__device__ __forceinline__ uint64_t match_digit(int digit, int nbits, uint64_t valid) {
-    uint64_t peers = valid;
-    // digits have at most 11 bits; unrolled, each step guarded by a wave-uniform test
+// For each of a wave's batches of 64 digits, the lanes with the same digit as this one, among the valid
+// ones: bit by bit, each bit of all batches before the next, so that a step is one ballot and two three-input
+// operations a batch and the batches do not wait for each other (bit by bit inside a batch, with a test of
+// the number of bits at each: 6900 of the scatter's 25000 cycles at 300000 keys, K = 400).
+template <int kBatches>
+__device__ __forceinline__ void match_digits(const int (&digit)[kBatches], int nbits, uint32_t (&lo)[kBatches],
+                                             uint32_t (&hi)[kBatches]) {
+    for (int b = 0; b < nbits; ++b) {
 #pragma unroll
-    for (int b = 0; b < 11; ++b) {
-        if (b < nbits) {
-            const bool bit = (digit >> b) & 1;
-            const uint64_t bal = __ballot(bit);
-            peers &= bit ? bal : ~bal;
+        for (int j = 0; j < kBatches; ++j) {
+            const int set = __builtin_amdgcn_sbfe(digit[j], b, 1);       // all ones where the bit is set
+            const uint64_t bal = __ballot(set != 0);
+            lo[j] &= ~((uint32_t)bal ^ (uint32_t)set);
+            hi[j] &= ~((uint32_t)(bal >> 32) ^ (uint32_t)set);
         }
     }
-    return peers;
 }
 
-__device__ __forceinline__ uint64_t lanemask_lt() {
-    return (1ull << (threadIdx.x & 63)) - 1ull;
+__device__ __forceinline__ int lanes_below(uint32_t lo, uint32_t hi) {
+    return __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0));
+}
+
+// Inclusive scan over the wave in six register moves (row shifts, then the rows' last lanes to those after).
+__device__ __forceinline__ int wave_inclusive_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);
+    return x;
 }
 
 // In-place exclusive scan of v[0..n) in LDS by the whole workgroup; returns the total.
-// `scratch` holds at least 33 ints.  Ends with a barrier.
+// `scratch` holds at least one int per wave.  Ends with a barrier.
 __device__ int block_exclusive_scan(int* v, int n, int* scratch) {
     const int T = blockDim.x, tid = threadIdx.x;
     const int per = (n + T - 1) / T;
     const int lo = min(n, tid * per), hi = min(n, lo + per);
     int sum = 0;
     for (int i = lo; i < hi; ++i) sum += v[i];
-    // inclusive scan of the per-thread sums inside each wave
-    int inc = sum;
-    const int lane = tid & 63, wave = tid >> 6;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(inc, o);
-        if (lane >= o) inc += t;
-    }
+    const int inc = wave_inclusive_scan(sum), lane = tid & 63, wave = tid >> 6;
     if (lane == 63) scratch[wave] = inc;
     __syncthreads();
-    if (tid == 0) {
-        int run = 0;
-        const int nw = (T + 63) >> 6;
-        for (int w = 0; w < nw; ++w) { const int t = scratch[w]; scratch[w] = run; run += t; }
-        scratch[32] = run;
+    const int nw = (T + 63) >> 6;
+    int before = 0, total = 0;
+    for (int w = 0; w < nw; ++w) {
+        const int t = scratch[w];
+        before += w < wave ? t : 0;
+        total += t;
     }
-    __syncthreads();
-    int run = scratch[wave] + inc - sum;
+    int run = before + inc - sum;
     for (int i = lo; i < hi; ++i) { const int t = v[i]; v[i] = run; run += t; }
-    const int total = scratch[32];
     __syncthreads();
     return total;
+}
+
+// The same for the bin totals, by the sort's first workgroup with the tables that follow from them: seg_off[0..n] as the
+// scan itself, item_off[0..n] (where not NULL) as the exclusive scan of ceil(v / R).
+__device__ void block_scan_tables(int* v, int n, int* scratch, int R, int32_t* seg_off, int32_t* item_off) {
+    const int T = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int per = (n + T - 1) / T;
+    const int lo = min(n, tid * per), hi = min(n, lo + per);
+    int sum = 0, items = 0;
+    for (int i = lo; i < hi; ++i) {
+        sum += v[i];
+        items += (v[i] + R - 1) / R;
+    }
+    const int inc = wave_inclusive_scan(sum), inc_items = wave_inclusive_scan(items);
+    if (lane == 63) { scratch[wave] = inc; scratch[16 + wave] = inc_items; }
+    __syncthreads();
+    int run = inc - sum, run_items = inc_items - items, total = 0, total_items = 0;
+    for (int w = 0; w < (T + 63) >> 6; ++w) {
+        const int t = scratch[w], ti = scratch[16 + w];
+        run += w < wave ? t : 0;
+        run_items += w < wave ? ti : 0;
+        total += t;
+        total_items += ti;
+    }
+    for (int i = lo; i < hi; ++i) {
+        const int t = v[i];
+        v[i] = run;
+        seg_off[i] = run;
+        if (item_off) item_off[i] = run_items;
+        run += t;
+        run_items += (t + R - 1) / R;
+    }
+    if (tid == 0) {
+        seg_off[n] = total;
+        if (item_off) item_off[n] = total_items;
+    }
+    __syncthreads();
 }
 
 }  // namespace
@@ -159,12 +202,7 @@ __global__ __launch_bounds__(256) void sort_binscan_kernel(int32_t* __restrict__
     const int lo = live ? min(nb, t * per) : 0, hi = live ? min(nb, lo + per) : 0;
     int sum = 0;
     for (int i = lo; i < hi; ++i) sum += row[i];
-    int inc = sum;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int v = __shfl_up(inc, o);
-        if (lane >= o) inc += v;
-    }
+    const int inc = wave_inclusive_scan(sum);
     int base = 0, total = inc;                             // total valid in lane 63
     if (TPB == 256) {
         if (lane == 63) wsum[wave] = inc;
@@ -186,12 +224,16 @@ __global__ __launch_bounds__(256) void sort_binscan_kernel(int32_t* __restrict__
 // Stable scatter.  Waves walk their keys in input order, so equal keys keep their order.
 //   vals_in == NULL: values are the key positions (first pass).
 //   kScans: see sort_scatter_scans; rounds is 1.  An instantiation of its own: the code costs the others 2%
-//   when it is only skipped, and without the form of several rounds it needs fewer registers (72; with 84
-//   a compute unit holds a workgroup less: 64 instances of 24 workgroups, 64 bins, 44.4 us against 37.8).
+//   when it is only skipped.  Both of eight waves are held to 80 registers (three workgroups on a compute unit: with two,
+//   64 instances of 24 workgroups, 64 bins took 44.4 us instead of 37.8).
+// Bound by its chain of latencies: keys and tables, ranks, two scans, LDS, stores.  300000 keys, K = 400 11.7 -> 9.1
+// us, 2^20, K = 1024 15.5 -> 13.0, 2^23 in two passes of 64 bins 84.7 -> 73.6, since the tables are requested with the
+// keys, the ranks found bit by bit for all batches at once (2.9 us of the first), the scans in register moves, both
+// tables of the first workgroup in one scan, and each loop over LDS reads before it writes.
 //   keys_out may be NULL.  seg_off / item_off are written by workgroup 0 when non-NULL
 //   (single-pass sort: bins are cluster ids, so the bin offsets are the segment table).
 template <int kSortWaves, bool kScans>
-__global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
+__global__ __launch_bounds__(kSortWaves * 64, kSortWaves == 8 ? 6 : 3) void sort_scatter_kernel(
     const int32_t* __restrict__ keys, const int32_t* __restrict__ vals_in,
     const int32_t* __restrict__ H, const int32_t* __restrict__ tot,
     int32_t* __restrict__ vals_out, int32_t* __restrict__ keys_out,
@@ -215,83 +257,82 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
     tot += (size_t)b * NB;
     H += (size_t)b * NB * nb + (kScans ? 0 : blk);
 
-    // first round's keys are requested before the offset scans below need them
-    int k[kBatches];
-    // a wave owns `rounds` consecutive batches-of-8 (contiguous in the input, so that wave order
+    // The first round's keys and the tables are requested before anything waits for them.  A wave owns
+    // `rounds` consecutive batches-of-8 (contiguous in the input, so that wave order
     // is input order and the sort stays stable with several rounds)
+    int k[kBatches];
     const int64_t base0 = (int64_t)blk * rounds * kSubTile + (int64_t)wave * rounds * (kBatches * 64);
     constexpr int kRoundStep = kBatches * 64;
-    load_round(keys, base0, N, lane, kmax, k);
+#pragma unroll
+    for (int j = 0; j < kBatches; ++j) {
+        const int64_t i = base0 + j * 64 + lane;
+        k[j] = i < N ? keys[i] : 0;
+    }
     // this workgroup's column of the scanned histogram table (one entry per bin, a cache line
-    // apart): requested now, needed only after the counting pass
-    constexpr int kHPer = 2048 / kSortThreads;
-    int hcol[kHPer];
+    // apart), needed only after the counting pass, and the bin totals
+    constexpr int kHPer = (kSortWaves == 8 ? 1024 : 2048) / kSortThreads;      // (eight waves: at most 1024 bins)
+    int hcol[kHPer], bin_total[kHPer];
     if constexpr (kScans) {
         // Few sort workgroups: no scan kernel has run; each workgroup adds up the counts of the earlier
-        // ones (where its own keys start inside the bins) and of all of them (the bin totals,
-        // kept in the first wave's counters until they are scanned) for itself.
+        // ones (where its own keys start inside the bins) and of all of them (the bin totals) for itself.
 #pragma unroll
         for (int q = 0; q < kHPer; ++q) {
             const int i = tid + q * kSortThreads;
-            hcol[q] = 0;
+            int before = 0, all = 0;
             if (i < NB) {
-                int before = 0, all = 0;
 #pragma unroll 8
                 for (int o = 0; o < nb; ++o) {
                     const int c = H[(size_t)o * NB + i];
                     all += c;
                     before += o < blk ? c : 0;
                 }
-                hcol[q] = before;
-                wcnt[i] = all;
             }
+            hcol[q] = before;
+            bin_total[q] = all;
         }
     } else {
 #pragma unroll
         for (int q = 0; q < kHPer; ++q) {
             const int i = tid + q * kSortThreads;
-            hcol[q] = (!solo && i < NB) ? H[(size_t)i * nb] : 0;
+            const bool live = !solo && i < NB;
+            hcol[q] = live ? H[(size_t)i * nb] : 0;
+            bin_total[q] = live ? tot[i] : 0;
         }
     }
+    for (int i = tid; i < kSortWaves * NB; i += kSortThreads) wcnt[i] = 0;
 
     // Bin totals -> off[] (exclusive scan: where each bin starts in the output), plus the
     // segment and item tables when asked for.  The totals come from the scan kernel, or, when
     // one workgroup sorts the whole instance (solo), from its own per-wave counts after the
     // counting pass -- no histogram or scan kernel runs then.
     auto offsets_from_totals = [&]() {
-        auto total_of = [&](int i) -> int {
-            if constexpr (kScans) return wcnt[i];   // (written by the thread that reads it)
-            if (!solo) return tot[i];
-            int t = 0;
-            for (int w = 0; w < kSortWaves; ++w) t += wcnt[w * NB + i];
-            return t;
-        };
-        if (item_off && blk == 0) {
-            // exclusive scan of ceil(n_k / R): where each cluster's items start
-            for (int i = tid; i < NB; i += kSortThreads) off[i] = (total_of(i) + R - 1) / R;
-            __syncthreads();
-            const int items = block_exclusive_scan(off, NB, scratch);
-            int32_t* io = item_off + (size_t)b * (NB + 1);
-            for (int i = tid; i < NB; i += kSortThreads) io[i] = off[i];
-            if (tid == 0) io[NB] = items;
-            __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kHPer; ++q) {
+            const int i = tid + q * kSortThreads;
+            if (i < NB) {
+                int t = bin_total[q];
+                if (!kScans && solo) {
+#pragma unroll
+                    for (int w = 0; w < kSortWaves; ++w) t += wcnt[w * NB + i];
+                }
+                off[i] = t;
+            }
         }
-        for (int i = tid; i < NB; i += kSortThreads) off[i] = total_of(i);
         __syncthreads();
-        const int total = block_exclusive_scan(off, NB, scratch);
-        if (seg_off && blk == 0) {
-            int32_t* so = seg_off + (size_t)b * (NB + 1);
-            for (int i = tid; i < NB; i += kSortThreads) so[i] = off[i];
-            if (tid == 0) so[NB] = total;
-        }
+        if (seg_off && blk == 0)
+            block_scan_tables(off, NB, scratch, R, seg_off + (size_t)b * (NB + 1), item_off ? item_off + (size_t)b * (NB + 1) : nullptr);
+        else
+            (void)block_exclusive_scan(off, NB, scratch);
     };
-    if constexpr (kScans) offsets_from_totals();   // ends with a barrier after its last use of wcnt
-    for (int i = tid; i < kSortWaves * NB; i += kSortThreads) wcnt[i] = 0;
-    __syncthreads();
-    if (!kScans && !solo) offsets_from_totals();
+    if (kScans || !solo) offsets_from_totals();
+    else __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kBatches; ++j) {
+        const int64_t i = base0 + j * 64 + lane;
+        k[j] = i < N ? clamp_key(k[j], kmax) : -1;
+    }
 
     int* mine = wcnt + wave * NB;
-    const uint64_t lt = lanemask_lt();
     // info[j] = rank among equal digits of the batch | (size of that group << 8)
     int info[kBatches];
 
@@ -301,17 +342,22 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
         // of its digit, then the first lane of each group of equal digits adds the group's
         // size; LDS executes a wave's operations in order, so the eight batches need no wait
         // between them.
-        int pre[kBatches];
+        int pre[kBatches], digit[kBatches];
+        uint32_t lo[kBatches], hi[kBatches];
 #pragma unroll
         for (int j = 0; j < kBatches; ++j) {
-            const bool valid = k[j] >= 0;
-            const int digit = valid ? (k[j] >> shift) & mask : 0;
-            const uint64_t peers = match_digit(digit, nbits, __ballot(valid));
-            const int rank = __popcll(peers & lt), cnt = __popcll(peers);
-            info[j] = rank;
-            pre[j] = valid ? mine[digit] : 0;
+            const uint64_t valid = __ballot(k[j] >= 0);
+            digit[j] = k[j] >= 0 ? (k[j] >> shift) & mask : 0;
+            lo[j] = (uint32_t)valid;
+            hi[j] = (uint32_t)(valid >> 32);
+        }
+        match_digits(digit, nbits, lo, hi);
+#pragma unroll
+        for (int j = 0; j < kBatches; ++j) {
+            info[j] = lanes_below(lo[j], hi[j]);
+            pre[j] = k[j] >= 0 ? mine[digit[j]] : 0;
             __builtin_amdgcn_wave_barrier();
-            if (valid && rank == 0) atomicAdd(&mine[digit], cnt);
+            if (k[j] >= 0 && info[j] == 0) atomicAdd(&mine[digit[j]], __popc(lo[j]) + __popc(hi[j]));
             __builtin_amdgcn_wave_barrier();
         }
         __syncthreads();
@@ -329,11 +375,13 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
             // written by consecutive threads, so that a store instruction covers a few
             // contiguous runs instead of 64 scattered words.
             for (int i = tid; i < NB; i += kSortThreads) {
-                int run = 0;
+                int run = 0, t[kSortWaves];
+#pragma unroll
+                for (int w = 0; w < kSortWaves; ++w) t[w] = wcnt[w * NB + i];
+#pragma unroll
                 for (int w = 0; w < kSortWaves; ++w) {
-                    const int t = wcnt[w * NB + i];
                     wcnt[w * NB + i] = run;           // where wave w's run starts inside the bin's
-                    run += t;
+                    run += t[w];
                 }
                 gdel[i] = run;                        // the tile's count of bin i
             }
@@ -359,11 +407,21 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
             __syncthreads();
             const int64_t tile0 = (int64_t)blk * kSubTile;
             const int live = (int)min((int64_t)kSubTile, N - tile0);
-            for (int i = tid; i < live; i += kSortThreads) {
-                const int key = skey[i];
-                const int pos = i + gdel[(key >> shift) & mask];
-                vals_out[pos] = sval[i];
-                if (keys_out) keys_out[pos] = key;
+            int pos[kBatches];
+#pragma unroll
+            for (int j = 0; j < kBatches; ++j) {
+                const int i = tid + j * kSortThreads;
+                k[j] = i < live ? skey[i] : 0;
+                info[j] = i < live ? sval[i] : 0;
+            }
+#pragma unroll
+            for (int j = 0; j < kBatches; ++j) pos[j] = tid + j * kSortThreads + gdel[(k[j] >> shift) & mask];
+#pragma unroll
+            for (int j = 0; j < kBatches; ++j) {
+                if (tid + j * kSortThreads < live) {
+                    vals_out[pos[j]] = info[j];
+                    if (keys_out) keys_out[pos[j]] = k[j];
+                }
             }
             return;
         }
@@ -372,11 +430,13 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
         for (int q = 0; q < kHPer; ++q) {
             const int i = tid + q * kSortThreads;
             if (i < NB) {
-                int run = off[i] + hcol[q];
+                int run = off[i] + hcol[q], t[kSortWaves];
+#pragma unroll
+                for (int w = 0; w < kSortWaves; ++w) t[w] = wcnt[w * NB + i];
+#pragma unroll
                 for (int w = 0; w < kSortWaves; ++w) {
-                    const int t = wcnt[w * NB + i];
                     wcnt[w * NB + i] = run;
-                    run += t;
+                    run += t[w];
                 }
             }
         }
@@ -399,14 +459,21 @@ __global__ __launch_bounds__(kSortWaves * 64) void sort_scatter_kernel(
     // More than one round per workgroup (beyond 16M keys per instance): ranks are recomputed
     // in the second pass and the wave's cursors advance batch by batch.
     auto rank_round = [&](bool count) {
+        int digit[kBatches];
+        uint32_t lo[kBatches], hi[kBatches];
 #pragma unroll
         for (int j = 0; j < kBatches; ++j) {
-            const bool valid = k[j] >= 0;
-            const int digit = valid ? (k[j] >> shift) & mask : 0;
-            const uint64_t peers = match_digit(digit, nbits, __ballot(valid));
-            const int rank = __popcll(peers & lt), cnt = __popcll(peers);
+            const uint64_t valid = __ballot(k[j] >= 0);
+            digit[j] = k[j] >= 0 ? (k[j] >> shift) & mask : 0;
+            lo[j] = (uint32_t)valid;
+            hi[j] = (uint32_t)(valid >> 32);
+        }
+        match_digits(digit, nbits, lo, hi);
+#pragma unroll
+        for (int j = 0; j < kBatches; ++j) {
+            const int rank = lanes_below(lo[j], hi[j]), cnt = __popc(lo[j]) + __popc(hi[j]);
             info[j] = rank | (cnt << 8);
-            if (count && valid && rank == 0) mine[digit] += cnt;
+            if (count && k[j] >= 0 && rank == 0) mine[digit[j]] += cnt;
             __builtin_amdgcn_wave_barrier();
         }
     };
