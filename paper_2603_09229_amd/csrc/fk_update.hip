@@ -16,6 +16,16 @@ namespace fk {
 
 namespace {
 
+// Points per item of a cluster of n, a multiple of R; the item table has room for ceil(n / R) of them.  A wave
+// adds an item's points and one workgroup merges the cluster's items, `balance` rows in the time of one point: beyond
+// sqrt(balance n) items the merge costs more than their shorter chains give.  fk_update with clusters of Zipf
+// sizes, us, items of R points / this: 154912 points, d = 80, K = 649 108 / 54; 2^23, d = 128, K = 4096 726 / 628 (the merge
+// alone 194 before); fp32 88476, d = 104, K = 660 76 / 54.
+__device__ __forceinline__ int item_length(int n, int R, float balance) {
+    const int items = (n + R - 1) / R, most = max(64, (int)sqrtf(balance * (float)n));
+    return items <= most ? R : (items + most - 1) / most * R;
+}
+
 // Largest k in [0,K) with item_off[k] <= item, found by the whole wave 64 probes at a
 // time.  Requires item < item_off[K]; the cluster found is then non-empty.
 __device__ __forceinline__ int find_cluster(const int32_t* __restrict__ item_off, int K,
@@ -46,7 +56,7 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
     const void* __restrict__ Xv, const int32_t* __restrict__ sorted_idx,
     const int32_t* __restrict__ seg_off, const int32_t* __restrict__ item_off,
     float* __restrict__ partial, int64_t N, int d, int K, int R, int64_t max_items,
-    int lpr_log2, int row_len) {
+    int lpr_log2, int row_len, float balance) {
     const int len = RAGGED ? row_len : d;
     __shared__ float wsum[WPI == 4 ? 4 : 1][WPI == 4 ? 512 : 1];
     const int b = blockIdx.y;
@@ -58,9 +68,10 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
     sorted_idx += (size_t)b * N;
     if (item >= item_off[K]) return;   // uniform over the waves that share an item
     const int k = find_cluster(item_off, K, (int)item, lane);
-    const int piece = (int)item - item_off[k];
-    const int start = seg_off[k] + piece * R;
-    const int end = min(seg_off[k + 1], start + R);
+    const int first_pos = seg_off[k], n = seg_off[k + 1] - first_pos, length = item_length(n, R, balance);
+    const int64_t offset = (int64_t)((int)item - item_off[k]) * length;
+    if (offset >= n) return;           // (uniform likewise)
+    const int start = first_pos + (int)offset, end = first_pos + (int)min((int64_t)n, offset + length);
 
     const int LPR = 1 << lpr_log2, S = 64 >> lpr_log2;
     const int slot = lane >> lpr_log2;
@@ -223,7 +234,7 @@ __device__ __forceinline__ void emit_centroid(const EmitTo& to, int b, int k, in
 template <bool kLate, bool RAGGED>
 __global__ __launch_bounds__(1024) void finalize_kernel(
     const float* __restrict__ partial, const int32_t* __restrict__ seg_off,
-    const int32_t* __restrict__ item_off, EmitTo to, int64_t max_items,
+    const int32_t* __restrict__ item_off, EmitTo to, int R, float balance, int64_t max_items,
     const int32_t* __restrict__ wg_counts, int G) {
     // dynamic LDS: 4 floats per thread for the row sums, then d floats for the squared entries
     // (a fixed worst-case array would cap the small workgroups of many-cluster shapes at a
@@ -252,7 +263,8 @@ __global__ __launch_bounds__(1024) void finalize_kernel(
         seg_off += (size_t)b * (K + 1);
         item_off += (size_t)b * (K + 1);
         i0 = item_off[k];
-        i1 = item_off[k + 1];
+        const int n = seg_off[k + 1] - seg_off[k], length = item_length(n, R, balance);
+        i1 = i0 + (n + length - 1) / length;
     }
     // read the running count before anyone overwrites it (barrier below)
     const int n_prev = to.accumulate ? to.counts[(size_t)b * K + k] : 0;
@@ -492,6 +504,22 @@ static int ceil_log2(int v) {
     return b;
 }
 
+// Threads of a merge workgroup.
+static int merge_threads(const Geometry& g) {
+    // few clusters with many partial rows each: more rows in flight per workgroup
+    // ... and many clusters with few rows each (up to 4, or up to 8 when there are thousands of
+    // clusters to spread over the chip): the smallest workgroup that still has a thread per feature
+    int threads = g.max_items / g.K > 64 ? 1024 : 256;
+    if (g.d <= 128 && (g.max_items / g.K <= 4 || (g.max_items / g.K <= 8 && (int64_t)g.K * g.B >= 4096))) threads = 64;
+    return threads;
+}
+
+// Rows of four features per thread that a merge workgroup adds at a time, by the rows of 16 bytes per lane that
+// the waves of an item do (see item_length).
+static float item_balance(const Geometry& g) {
+    return (float)merge_threads(g) / (g.t == FK_F32 ? 64.f : 128.f) / (float)g.waves_per_item;
+}
+
 fk_status launch_segment_reduce(const Geometry& g, const Workspace& w, const void* X,
                                 const int32_t* sorted_idx, const int32_t* seg_off,
                                 const int32_t* item_off, hipStream_t s) {
@@ -505,7 +533,7 @@ fk_status launch_segment_reduce(const Geometry& g, const Workspace& w, const voi
         auto kern = g.len == g.d ? (wide ? segment_reduce_kernel<EPL, BF, 4, false> : segment_reduce_kernel<EPL, BF, 1, false>)  \
                                  : (wide ? segment_reduce_kernel<EPL, BF, 4, true> : segment_reduce_kernel<EPL, BF, 1, true>);   \
         hipLaunchKernelGGL(kern, grid, block, 0, s, X, sorted_idx, seg_off, item_off, w.partial, g.N, g.d, g.K,     \
-                           g.rows_per_item, g.max_items, lpr_log2, g.len);                               \
+                           g.rows_per_item, g.max_items, lpr_log2, g.len, item_balance(g));                               \
     } while (0)
     if (g.t == FK_F32) FK_REDUCE(4, false);
     else if (g.t == FK_F16) FK_REDUCE(8, false);
@@ -567,16 +595,12 @@ fk_status launch_gather_update(const Geometry& g, const Workspace& w, const void
 fk_status launch_finalize(const Geometry& g, const Workspace& w, const int32_t* seg_off,
                           const int32_t* item_off, const FinalizeArgs& a, hipStream_t s,
                           const int32_t* wg_counts, int wg_per_cluster) {
-    // few clusters with many partial rows each: more rows in flight per workgroup
-    // ... and many clusters with few rows each (up to 4, or up to 8 when there are thousands of
-    // clusters to spread over the chip): the smallest workgroup that still has a thread per feature
-    int threads = g.max_items / g.K > 64 ? 1024 : 256;
-    if (g.d <= 128 && (g.max_items / g.K <= 4 || (g.max_items / g.K <= 8 && (int64_t)g.K * g.B >= 4096))) threads = 64;
+    const int threads = merge_threads(g);
     const size_t lds = ((size_t)4 * threads + g.d) * sizeof(float);
     auto kern = g.len == g.d ? (a.late > 0 ? finalize_kernel<true, false> : finalize_kernel<false, false>)
                              : (a.late > 0 ? finalize_kernel<true, true> : finalize_kernel<false, true>);
     hipLaunchKernelGGL(kern, dim3(g.K, g.B), dim3(threads), lds, s, w.partial, seg_off, item_off, emit_args(g, a),
-                       g.max_items, wg_counts, wg_per_cluster);
+                       g.rows_per_item, item_balance(g), g.max_items, wg_counts, wg_per_cluster);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }
