@@ -32,6 +32,7 @@
 // What bounds it: the matrix pipe (3 MFMA per 32 points x 32 centroids x 16 features, 6 N K D
 // flop) from about 64 centroids up, below that reading X.
 #include <algorithm>
+#include <type_traits>
 
 #include "fk_common.h"
 #include "fk_device.h"
@@ -187,8 +188,13 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
 // double-buffered LDS stage of eight chunks that is filled by direct copies; a lane holds 16
 // centroid rows of one point.  The head product and the two small products have accumulators of
 // their own, which keeps the rounding of the small ones small and gives two independent chains.
+// Waves per SIMD that the registers are held to: what the kernel has without reading ahead.
+constexpr int filter_occupancy(int dch, int waves) {
+    return waves == 8 || dch <= 3 || dch == 7 ? 1 : dch <= 6 ? 4 : dch <= 12 ? 3 : dch <= 16 ? 2 : 1;
+}
+
 template <int DCH, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void assign_f32_filter_kernel(
+__global__ __launch_bounds__(WAVES * 64, filter_occupancy(DCH, WAVES)) void assign_f32_filter_kernel(
     const float* __restrict__ X, const uintx4* __restrict__ frag, const float* __restrict__ c2,
     const float* __restrict__ shift, int32_t* __restrict__ assign, int32_t* __restrict__ list,
     int32_t* __restrict__ list_len, int64_t N, int d, int len, int K, int ktiles) {
@@ -198,7 +204,15 @@ __global__ __launch_bounds__(WAVES * 64) void assign_f32_filter_kernel(
     constexpr int SC = DCH / SPT;                            // chunks of a tile in one stage
     constexpr int kPieces = SPT > 1 ? 2 * SC + 1 : ST * kTile;   // pieces per stage, at most
     static_assert(SC * SPT == DCH, "whole chunks per stage");
-    __shared__ uintx4 stage[2][kPieces * 64];
+    // Four waves: two objects, and code for each, since with one array every operand read waits for the copy in
+    // flight into the other half; and the operands of a chunk are read while the one before is multiplied (a wave alone on
+    // its SIMD otherwise waits as long for LDS as it multiplies).  Sweep, us: 50000 points, d = 512, K = 1000 225 -> 196; 5000,
+    // d = 333, K = 5000 393 -> 337; 300000, d = 96, K = 400 81.4 -> 80.0 (78.0 of 79.5 in a fit); 1317, d = 512, K = 293 44.9
+    // -> 40.5.  Eight waves have no registers left for either (2^20 points, d = 128, K = 64 127 us, 162 with two objects, 180
+    // with both), nor have three chunks at their five waves a SIMD (58.1, 59.0) and seven at four (93, 108).
+    constexpr bool kApart = WAVES == 4 && DCH != 3 && DCH != 7;
+    __shared__ uintx4 even[(kApart ? 1 : 2) * kPieces * 64], other_half[kApart ? kPieces * 64 : 1];
+    uintx4* const odd = kApart ? other_half : even + kPieces * 64;
 
     const int b = blockIdx.y;
     X += (size_t)b * N * len;
@@ -212,7 +226,7 @@ __global__ __launch_bounds__(WAVES * 64) void assign_f32_filter_kernel(
     const int64_t point = ((int64_t)blockIdx.x * WAVES + wave) * 32 + n;
     const int nst = SPT > 1 ? ktiles * SPT : (ktiles + ST - 1) / ST;
 
-    auto fetch = [&](int st, int buf) {
+    auto fetch = [&](int st, uintx4* to) {
         const int first = SPT > 1 ? (st / SPT) * kTile + (st % SPT) * 2 * SC : st * kPieces;
         const int count = SPT > 1 ? (st % SPT == SPT - 1 ? 2 * SC + 1 : 2 * SC) : min(kPieces, ktiles * kTile - first);
 #pragma unroll
@@ -221,10 +235,10 @@ __global__ __launch_bounds__(WAVES * 64) void assign_f32_filter_kernel(
             if (pc < count)
                 __builtin_amdgcn_global_load_lds(
                     (const __attribute__((address_space(1))) void*)(frag + (size_t)(first + pc) * 64 + lane),
-                    (__attribute__((address_space(3))) void*)&stage[buf][pc * 64], 16, 0, 0);
+                    (__attribute__((address_space(3))) void*)(to + pc * 64), 16, 0, 0);
         }
     };
-    fetch(0, 0);
+    fetch(0, even);
 
     uintx4 xh[DCH], xl[DCH];
     float x2 = 0.f;
@@ -279,11 +293,27 @@ __global__ __launch_bounds__(WAVES * 64) void assign_f32_filter_kernel(
     __syncthreads();
 
     floatx16 big, small;
-    auto chunk = [&](const uintx4* at, int s) {              // head and tail of chunk s at `at`
-        const uintx4 ah = at[lane], al = at[64 + lane];
-        small = mfma32<true>(ah, xl[s], small);
-        big = mfma32<true>(ah, xh[s], big);
-        small = mfma32<true>(al, xh[s], small);
+    // `chunks` chunks from `at` on, which are the point's from s0 on
+    auto products = [&](const uintx4* at, int s0, auto chunks) {
+        constexpr int kChunks = decltype(chunks)::value;
+        uintx4 ah, al, nh = at[lane], nl = at[64 + lane];
+        if constexpr (kApart) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);          // two LDS reads
+#pragma unroll
+        for (int s = 0; s < kChunks; ++s) {
+            if (kApart || s == 0) { ah = nh; al = nl; }
+            if (kApart && s + 1 < kChunks) {
+                nh = at[(2 * s + 2) * 64 + lane];
+                nl = at[(2 * s + 3) * 64 + lane];
+                __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+            } else if (!kApart && s > 0) {
+                ah = at[2 * s * 64 + lane];
+                al = at[(2 * s + 1) * 64 + lane];
+            }
+            small = mfma32<true>(ah, xl[s0 + s], small);
+            big = mfma32<true>(ah, xh[s0 + s], big);
+            small = mfma32<true>(al, xh[s0 + s], small);
+            if constexpr (kApart) __builtin_amdgcn_sched_group_barrier(0x8, 3, 0);        // three MFMAs
+        }
     };
     auto fold = [&](const uintx4* bias, int tile) {
         big = mfma32<true>(bias[lane], ones, big);
@@ -296,30 +326,39 @@ __global__ __launch_bounds__(WAVES * 64) void assign_f32_filter_kernel(
         }
         btile = m1 != before ? tile : btile;
     };
-    for (int st0 = 0; st0 < nst; st0 += SPT) {
-#pragma unroll
-        for (int part = 0; part < SPT; ++part) {
-            const int st = st0 + part, buf = st & 1;
-            if (st + 1 < nst) fetch(st + 1, buf ^ 1);        // lands during the sweep
-            if constexpr (SPT > 1) {
-                if (part == 0) { big = floatx16{}; small = floatx16{}; }
-#pragma unroll
-                for (int s = 0; s < SC; ++s) chunk(&stage[buf][2 * s * 64], part * SC + s);
-                if (part == SPT - 1) fold(&stage[buf][2 * SC * 64], st / SPT);
-            } else {
-                const int nt = min(ST, ktiles - st * ST);
-                for (int tt = 0; tt < nt; ++tt) {
-                    const uintx4* tile = &stage[buf][tt * kTile * 64];
-                    big = floatx16{};
-                    small = floatx16{};
-#pragma unroll
-                    for (int s = 0; s < DCH; ++s) chunk(tile + 2 * s * 64, s);
-                    fold(tile + 2 * DCH * 64, st * ST + tt);
-                }
+    // stage st, whose pieces are in `now`; the next one's land in `then` meanwhile
+    auto sweep = [&](int st, int part, const uintx4* now, uintx4* then) {
+        if (st + 1 < nst) fetch(st + 1, then);
+        if constexpr (SPT > 1) {
+            if (part == 0) { big = floatx16{}; small = floatx16{}; }
+            products(now, part * SC, std::integral_constant<int, SC>());
+            if (part == SPT - 1) fold(now + 2 * SC * 64, st / SPT);
+        } else {
+            const int nt = min(ST, ktiles - st * ST);
+            for (int tt = 0; tt < nt; ++tt) {
+                const uintx4* tile = now + tt * kTile * 64;
+                big = floatx16{};
+                small = floatx16{};
+                products(tile, 0, std::integral_constant<int, DCH>());
+                fold(tile + 2 * DCH * 64, st * ST + tt);
             }
-            if (st + 1 < nst) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
         }
+        if (st + 1 < nst) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    };
+    if constexpr (kApart) {
+        static_assert(SPT == 1 || SPT % 2 == 0, "a tile starts in `even`");
+        constexpr int kStep = SPT > 1 ? SPT : 2;
+        for (int st0 = 0; st0 < nst; st0 += kStep) {
+#pragma unroll
+            for (int i = 0; i < kStep; i += 2) {
+                sweep(st0 + i, i, even, odd);
+                if (SPT > 1 || st0 + i + 1 < nst) sweep(st0 + i + 1, i + 1, odd, even);
+            }
+        }
+    } else {
+        static_assert(kApart || SPT == 1, "whole tiles");
+        for (int st = 0; st < nst; ++st) sweep(st, 0, even + (st & 1) * kPieces * 64, even + ((st & 1) ^ 1) * kPieces * 64);
     }
 
     // the two lanes of a point meet
@@ -343,7 +382,7 @@ __global__ __launch_bounds__(WAVES * 64) void assign_f32_filter_kernel(
     // A place on the list for the whole workgroup at once: additions to one address take 10 ns each, and
     // with many open points one per wave cost more than the sweep (2^20 points, all open: 330 us).
     // (The last stage has been read; LDS of its own would cost a workgroup per compute unit at DCH = 2.)
-    int* opened = (int*)&stage[0][0];
+    int* opened = (int*)&even[0];
     int* list_at = opened + WAVES;
     const uint64_t open = __ballot(mine && !certain);
     if (lane == 0) opened[wave] = __popcll(open);
