@@ -73,14 +73,14 @@ static std::atomic<int> g_sort_min_rounds{0};   // fk_set_option("sort_min_round
 static std::atomic<int> g_gather_option{-1};    // fk_set_option("gather_update")
 void set_gather_update_option(int v) { g_gather_option.store(v, std::memory_order_relaxed); }
 
-// fk_update, us, sorted / this: 1340 points, d = 128, K = 72 17.4 / 5.9; 8192, d = 128, K = 1000 23.6 / 9.5 (points of
-// Zipf sizes 29.9 / 11.7); 16384, d = 128, K = 480 23.0 / 13.3 (38.8 / 16.9); fp32 250000, d = 32, K = 20 27.7 / 14.6.
+// fk_update, us, sorted / this: 1340 points, d = 128, K = 72 14.8 / 6.7; 8192, d = 128, K = 1000 21.0 / 9.7 (points of
+// Zipf sizes 27.4 / 11.8); 16384, d = 128, K = 480 20.7 / 14.7 (28.9 / 17.5); fp32 250000, d = 32, K = 20 25.8 / 15.2.
 // Every cluster's workgroup reads all keys, and thousands of workgroups pay for themselves one after the
 // other: 5 instances of 3556, K = 448 21.1 / 22.4; 32768, K = 1024 24.6 / 23.5; 70001 x 3, K = 333 34.3 / 43.4.  A
 // workgroup adds its rows at 40-80 GB/s, so that it may have to add 2 MiB or 16384 rows at most even
 // if all points are in one cluster, and with few clusters, which leave the chip idle, parts of 512 KiB (15991 points,
-// d = 256, K = 15, Zipf sizes: one part 35.8, eight 13.9, sorted 32.8).  All points in one cluster: 16384, d = 128, K = 480 92 / 38;
-// 8000 fp32, d = 512, K = 100 63 / 56; 2010 fp32, d = 256, K = 467 24.0 / 26.7.
+// d = 256, K = 15, Zipf sizes: one part 35.8, eight 15.5, sorted 25.7).  All points in one cluster: 16384, d = 128, K = 480
+// 39 / 38; 15991, d = 256, K = 15 32 / 24; 8000 fp32, d = 512, K = 100 48 / 55; fp32 250000, d = 32, K = 20 29 / 41.
 int choose_gather_parts(int B, int64_t N, int d, int K, fk_dtype t) {
     const int v = g_gather_option.load(std::memory_order_relaxed);
     if (v >= 0) return N <= ((int64_t)1 << 30) ? v : 0;
