@@ -250,13 +250,13 @@ fk_status fk_standard_update(const void* X, const int32_t* assign, const float* 
  * pass over X per iteration: a persistent workgroup per compute unit keeps the K x d table of sums
  * in the accumulators of its eight waves (32 clusters each) and adds the points it has just
  * assigned, compacted per wave, with a one-hot MFMA.  Same assignments and counts as the general
- * path, sums up to fp32 summation order, bit-reproducible.  fk_update alone keeps the
- * sort-inverse path for these shapes.
+ * path, sums up to fp32 summation order, bit-reproducible.  fk_update alone sorts or, where the
+ * instance is small (see below), gathers.
  * Small fp32 problems (FK_F32, K <= 64, d <= 128, B*N <= 2^17): fk_lloyd_iter likewise takes one
  * pass per iteration (64-point batches, distances by the same fp32 differences as fk_assign, each
  * cluster's row of the table of sums owned by one wave): at this size the iteration is bound by
  * its number of launches.  Same assignments and counts as the general path, sums up to fp32
- * summation order, bit-reproducible; fk_update alone keeps the sort-inverse path.
+ * summation order, bit-reproducible; fk_update alone sorts or gathers, as above.
  * Small instances (B*K*N <= 2^23 and a few MiB of points; any type): an update that none of the passes
  * above takes is one launch without a sort, or two: every workgroup reads all assignments and adds the
  * rows of one cluster.  Same counts as the sorted path, sums up to fp32 summation order, bit-reproducible.

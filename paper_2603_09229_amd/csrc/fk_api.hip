@@ -553,12 +553,14 @@ int fk_plan(int B, int64_t N, int d, int K, fk_dtype t, char* buf, size_t buf_by
         const int v = choose_assign_variant(g);
         snprintf(assign, sizeof(assign), "mfma_sweep(variant=%d,points_per_wg=%d)", v, pts[v]);
     }
+    char update[48] = "sort-inverse";            // fk_update of a shape whose iteration is one pass
+    if (g.gather_parts > 0) snprintf(update, sizeof(update), "gather(parts=%d, no sort)", g.gather_parts);
     if (table_update_enabled(g)) {
         snprintf(buf, buf_bytes,
                  "assign+update=table_update(K x d table in the registers of a workgroup, X read once "
                  "per iteration, no sort; at most %d workgroups per instance) fk_assign alone=%s "
-                 "fk_update alone=sort-inverse workspace=%zu",
-                 g.table_grid_cap, assign, carve(g, nullptr).bytes);
+                 "fk_update alone=%s workspace=%zu",
+                 g.table_grid_cap, assign, update, carve(g, nullptr).bytes);
     } else if (fused_update_enabled(g)) {
         snprintf(buf, buf_bytes,
                  "assign+update=stream_update(one-hot MFMA, X read once per iteration, no sort; "
@@ -568,8 +570,8 @@ int fk_plan(int B, int64_t N, int d, int K, fk_dtype t, char* buf, size_t buf_by
         snprintf(buf, buf_bytes,
                  "assign+update=f32_update(K x d table in the registers of a workgroup, X read once "
                  "per iteration, no sort; at most %d workgroups per instance) fk_assign alone=%s "
-                 "fk_update alone=sort-inverse workspace=%zu",
-                 g.f32_grid_cap, assign, carve(g, nullptr).bytes);
+                 "fk_update alone=%s workspace=%zu",
+                 g.f32_grid_cap, assign, update, carve(g, nullptr).bytes);
     } else if (g.gather_parts > 0) {
         snprintf(buf, buf_bytes,
                  "assign=%s ktiles=%d update=gather(parts=%d, no sort) max_items=%lld workspace=%zu", assign, g.ktiles,

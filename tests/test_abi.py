@@ -125,3 +125,20 @@ def test_plan_describes_the_choice_per_shape():
     fk.fk_set_option("assign_variant", -1)
     with pytest.raises(fk.FlashKMError):
         fk.fk_set_option("assign_variant", 9)
+
+
+@pytest.mark.parametrize("B,N,d,K,dtype,gathers", [
+    (1, 1340, 128, 72, torch.bfloat16, True), (1, 200000, 128, 200, torch.bfloat16, False), (1, 16384, 64, 64, torch.float32, True),
+    (4, 32768, 128, 64, torch.float32, False),
+])
+def test_plan_names_the_update_that_fk_update_takes(B, N, d, K, dtype, gathers):
+    """Shapes of the one-pass iterations: fk_update alone goes by the size, with a sort or without."""
+    try:
+        for option in (-1, 0):
+            fk.fk_set_option("gather_update", option)
+            plan = fk.fk_plan(B, N, d, K, dtype)
+            assert "assign+update=" in plan
+            assert ("fk_update alone=gather(parts=" in plan) == (gathers and option != 0)
+            assert ("fk_update alone=sort-inverse" in plan) == (not gathers or option == 0)
+    finally:
+        fk.fk_set_option("gather_update", -1)
