@@ -270,6 +270,8 @@ int fk_set_option(const char* name, int value);
  * Measurement aid (not a step of the method): while started, fk_lloyd_iter and fk_update
  * record a HIP event on their stream after each stage of every iteration -- assignment
  * kernel, sort-inverse, segment reduction, merge/normalise (with the centroid re-layout).
+ * One-pass iterations are booked under assignment, their merge under merge; an update without a sort under
+ * segment reduction, which then ends with what the merge does, or is followed by it where there are parts.
  * fk_stage_timer_stop waits for the last event and returns, per stage in that order,
  * the summed elapsed milliseconds and the number of kernel launches timed (one per interval
  * unless "timer_repeat" is set) in stage_ms[4] / stage_launches[4] (host arrays); its return value is the number of events recorded, or -1

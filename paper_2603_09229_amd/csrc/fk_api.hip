@@ -468,9 +468,10 @@ int fk_stage_timer_stop(double* stage_ms, int* stage_launches) {
     if (hipEventSynchronize(g_timer.pool[g_timer.used - 1]) != hipSuccess) return -1;
     for (size_t i = 1; i < g_timer.used; ++i) {
         int st = g_timer.stage[i];
-        // the gap between one iteration's last mark and the next iteration's opening mark
+        // the gap between one iteration's last mark (the merge or, in an update without a sort that has
+        // no parts to merge, the reduction) and the next iteration's opening mark
         // is the centroid re-layout: booked under the merge/normalise stage
-        const bool relayout = st < 0 && g_timer.stage[i - 1] == kStageFinalize;
+        const bool relayout = st < 0 && (g_timer.stage[i - 1] == kStageFinalize || g_timer.stage[i - 1] == kStageReduce);
         if (st < 0 && !relayout) continue;
         float ms = 0.f;
         if (hipEventElapsedTime(&ms, g_timer.pool[i - 1], g_timer.pool[i]) != hipSuccess) return -1;

@@ -81,3 +81,23 @@ def test_out_of_core_chunks(dtype, N, d, K, chunk, parts):
     assert torch.equal(a, b) and torch.equal(n, m)
     # the same n terms in two orders: n 2^-24 of their largest each, divided by n
     assert ((C - D).abs() <= 2 * 2.0 ** -24 * n.amax() * X.float().abs().max()).all()
+
+
+@pytest.mark.parametrize("parts", [1, 2])
+def test_stage_timer_books_all_of_an_update_without_a_sort(parts):
+    """The launch under the reduction, the merge of parts under the merge, and there too, with parts and without,
+    what is enqueued between two updates: the re-layout of the centroids that the next call starts from."""
+    g = torch.Generator(device=DEV).manual_seed(3)
+    X = torch.randn((1, 3000, 128), generator=g, device=DEV).half()
+    C = X[:, :300].float().contiguous()
+    try:
+        fk.fk_set_option("gather_update", parts)
+        fk.fk_lloyd_iter(X, C, 1)
+        fk.fk_stage_timer_start()
+        for _ in range(2):
+            fk.fk_lloyd_iter(X, C, 2)
+        st = fk.fk_stage_timer_stop()
+    finally:
+        fk.fk_set_option("gather_update", -1)
+    assert {k: n for k, (_, n) in st.items()} == {"assign": 4, "sort": 0, "reduce": 4, "finalize": 4 if parts > 1 else 0}
+    assert st["assign"][0] > 0 and st["reduce"][0] > 0 and st["finalize"][0] > 0 and st["sort"][0] == 0
