@@ -374,18 +374,21 @@ __global__ __launch_bounds__(WAVES * 64) void gather_update_kernel(
                         v[u] = RAGGED ? (uintx4)*(const uintx4_any*)at : *(const uintx4*)at;
                     }
                 }
+                // the loads of a batch in pairs first: a wave may add hundreds of rows, and with every row in one chain
+                // a lane's sum was twice as far off as the sorted update's, whose items are shorter
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if constexpr (EPL == 4) {
+                for (int e = 0; e < EPL; ++e) {
+                    float t[U];
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[cb][e] += __uint_as_float(v[u][e]);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            acc[cb][2 * e] += lp_to_float((uint16_t)(v[u][e] & 0xFFFFu), BF);
-                            acc[cb][2 * e + 1] += lp_to_float((uint16_t)(v[u][e] >> 16), BF);
-                        }
+                    for (int u = 0; u < U; ++u) {
+                        if constexpr (EPL == 4) t[u] = __uint_as_float(v[u][e]);
+                        else t[u] = lp_to_float((uint16_t)(e & 1 ? v[u][e / 2] >> 16 : v[u][e / 2] & 0xFFFFu), BF);
                     }
+#pragma unroll
+                    for (int half = U / 2; half > 0; half /= 2)
+#pragma unroll
+                        for (int u = 0; u < half; ++u) t[u] += t[u + half];
+                    acc[cb][e] += t[0];
                 }
             }
         }
@@ -482,11 +485,14 @@ __global__ __launch_bounds__(WAVES * 64) void gather_update_kernel(
     if (lane == 0) left[wave] = busy ? 1 : 0;      // (read by everyone before the last barrier)
     __syncthreads();
     auto sum_of = [&](int j) {
-        float s = 0.f;
+        float t[WAVES];                            // (in pairs: a few additions to the largest sums, not one per wave)
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w)
-            if (left[w]) s += red[w * dpow + j];
-        return s;
+        for (int w = 0; w < WAVES; ++w) t[w] = left[w] ? red[w * dpow + j] : 0.f;
+#pragma unroll
+        for (int half = WAVES / 2; half > 0; half /= 2)
+#pragma unroll
+            for (int w = 0; w < half; ++w) t[w] += t[w + half];
+        return t[0];
     };
     if (merged) {                                  // a row and a count for the merge kernel
         const size_t row = ((size_t)b * K + k) * G + part;

@@ -101,3 +101,23 @@ def test_stage_timer_books_all_of_an_update_without_a_sort(parts):
         fk.fk_set_option("gather_update", -1)
     assert {k: n for k, (_, n) in st.items()} == {"assign": 4, "sort": 0, "reduce": 4, "finalize": 4 if parts > 1 else 0}
     assert st["assign"][0] > 0 and st["reduce"][0] > 0 and st["finalize"][0] > 0 and st["sort"][0] == 0
+
+
+@pytest.mark.parametrize("dtype,N,d,K", [(torch.float32, 8000, 512, 100), (torch.bfloat16, 8192, 128, 1000), (torch.float16, 5000, 256, 300)])
+def test_no_long_chain_of_additions(dtype, N, d, K):
+    """Every column holds one 1 and otherwise 2^-24, which an addition to the 1 loses whole: the sum is off by as many of
+    them as follow the 1 in its chain.  No term passes through more than 64 additions, in batches and on to the mean,
+    with the sort (items of 32 rows, their merge) or without."""
+    X = torch.full((1, N, d), 2.0 ** -24, dtype=dtype, device=DEV)
+    X[0, torch.arange(d, device=DEV) * 997 % N, torch.arange(d, device=DEV)] = 1.0     # any place in a chain
+    label = torch.full((1, N), K // 2, dtype=torch.int32, device=DEV)
+    total = 1 + (N - 1) * 2.0 ** -24
+    for parts in (-1, 0):
+        try:
+            fk.fk_set_option("gather_update", parts)
+            assert ("gather" in fk.fk_plan(1, N, d, K, dtype)) == (parts != 0)
+            C, _, _ = fk.fk_update(X, label, torch.zeros((1, K, d), device=DEV))
+        finally:
+            fk.fk_set_option("gather_update", -1)
+        # ... each good to 2^-24 of the whole, and the rounding of the mean
+        assert (C[0, K // 2].double() * N - total).abs().max() <= (64 + 1) * 2.0 ** -24 * total
