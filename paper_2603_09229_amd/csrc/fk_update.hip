@@ -42,6 +42,28 @@ __device__ __forceinline__ int find_cluster(const int32_t* __restrict__ item_off
     return lo;
 }
 
+// Adds the rows' pieces of a batch of loads to the lane's sums, in pairs first: a large cluster's items are hundreds of
+// rows long, and so are a wave's shares of one in gather_update_kernel.  With every row a link of one chain the means of
+// 300000 points in one cluster (fp32, d = 96, K = 400: items of 384 rows) were 2.6e-7 off, with items of 128 2.1e-7; in pairs
+// 1.5e-7, in the same time.
+template <int EPL, bool BF, int U>
+__device__ __forceinline__ void add_in_pairs(const uintx4 (&v)[U], float (&acc)[EPL]) {
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) {
+        float t[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if constexpr (EPL == 4) t[u] = __uint_as_float(v[u][e]);
+            else t[u] = lp_to_float((uint16_t)(e & 1 ? v[u][e / 2] >> 16 : v[u][e / 2] & 0xFFFFu), BF);
+        }
+#pragma unroll
+        for (int half = U / 2; half > 0; half /= 2)
+#pragma unroll
+            for (int u = 0; u < half; ++u) t[u] += t[u + half];
+        acc[e] += t[0];
+    }
+}
+
 }  // namespace
 
 // WPI waves per item (1, or all 4 of the workgroup for the long items of few-cluster
@@ -108,19 +130,7 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
                         v[u] = RAGGED ? (uintx4)*(const uintx4_any*)at : *(const uintx4*)at;
                     }
                 }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (EPL == 4) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[e] += __uint_as_float(v[u][e]);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            acc[2 * e] += lp_to_float((uint16_t)(v[u][e] & 0xFFFFu), BF);
-                            acc[2 * e + 1] += lp_to_float((uint16_t)(v[u][e] >> 16), BF);
-                        }
-                    }
-                }
+                add_in_pairs<EPL, BF>(v, acc);
             }
         }
         // add the row slots of the wave together (fixed butterfly order)
@@ -374,22 +384,7 @@ __global__ __launch_bounds__(WAVES * 64) void gather_update_kernel(
                         v[u] = RAGGED ? (uintx4)*(const uintx4_any*)at : *(const uintx4*)at;
                     }
                 }
-                // the loads of a batch in pairs first: a wave may add hundreds of rows, and with every row in one chain
-                // a lane's sum was twice as far off as the sorted update's, whose items are shorter
-#pragma unroll
-                for (int e = 0; e < EPL; ++e) {
-                    float t[U];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        if constexpr (EPL == 4) t[u] = __uint_as_float(v[u][e]);
-                        else t[u] = lp_to_float((uint16_t)(e & 1 ? v[u][e / 2] >> 16 : v[u][e / 2] & 0xFFFFu), BF);
-                    }
-#pragma unroll
-                    for (int half = U / 2; half > 0; half /= 2)
-#pragma unroll
-                        for (int u = 0; u < half; ++u) t[u] += t[u + half];
-                    acc[cb][e] += t[0];
-                }
+                add_in_pairs<EPL, BF>(v, acc[cb]);
             }
         }
     };
