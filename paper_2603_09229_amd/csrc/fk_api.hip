@@ -73,21 +73,22 @@ static std::atomic<int> g_sort_min_rounds{0};   // fk_set_option("sort_min_round
 static std::atomic<int> g_gather_option{-1};    // fk_set_option("gather_update")
 void set_gather_update_option(int v) { g_gather_option.store(v, std::memory_order_relaxed); }
 
-// fk_update, us, sorted / this: 1340 points, d = 128, K = 72 14.8 / 6.7; 8192, d = 128, K = 1000 21.0 / 9.7 (points of
-// Zipf sizes 27.4 / 11.8); 16384, d = 128, K = 480 20.7 / 14.7 (28.9 / 17.5); fp32 250000, d = 32, K = 20 25.8 / 15.2.
+// fk_update, us, sorted / this: 1340 points, d = 128, K = 72 15.3 / 5.8; 8192, d = 128, K = 1000 22.2 / 10.1 (points of
+// Zipf sizes 29.3 / 10.1); 16384, d = 128, K = 480 21.4 / 14.1 (28.8 / 14.5); fp32 250000, d = 32, K = 20 26.7 / 14.5.
 // Every cluster's workgroup reads all keys, and thousands of workgroups pay for themselves one after the
-// other: 5 instances of 3556, K = 448 21.1 / 22.4; 32768, K = 1024 24.6 / 23.5; 70001 x 3, K = 333 34.3 / 43.4.  A
-// workgroup adds its rows at 40-80 GB/s, so that it may have to add 2 MiB or 16384 rows at most even
-// if all points are in one cluster, and with few clusters, which leave the chip idle, parts of 512 KiB (15991 points,
-// d = 256, K = 15, Zipf sizes: one part 35.8, eight 15.5, sorted 25.7).  All points in one cluster: 16384, d = 128, K = 480
-// 39 / 38; 15991, d = 256, K = 15 32 / 24; 8000 fp32, d = 512, K = 100 48 / 55; fp32 250000, d = 32, K = 20 29 / 41.
+// other: 5 instances of 3556, d = 128, K = 448 19.0 / 21.3; 32768, K = 1024 23 / 34; 70001 x 3, d = 100, K = 333 33 / 76.  A
+// workgroup adds its rows at about 100 GB/s, so that it may have to add 2 MiB or 16384 rows at most even
+// if all points are in one cluster, and with few clusters, which leave the chip idle, parts of 512 KiB (36850 fp32 points, d = 77,
+// K = 17: eight parts 11.7, Zipf sizes 15.9, all in one cluster 28.5; sixteen 10.8, 12.3, 21.0; sorted 20.2, 22.9, 25.4).
+// All points in one cluster: 16384, d = 128, K = 480 37 / 27; 8000 fp32, d = 512, K = 100 48 / 27; 250000 fp32, d = 32, K = 20 30 / 29;
+// 5 x 2000, d = 200, K = 200 20.8 / 21.9; 3 x 4000 fp32, d = 180, K = 120 25.5 / 27.2.
 int choose_gather_parts(int B, int64_t N, int d, int K, fk_dtype t) {
     const int v = g_gather_option.load(std::memory_order_relaxed);
-    if (v >= 0) return N <= ((int64_t)1 << 30) ? v : 0;
     const int64_t bytes = N * d * (int64_t)elem_size(t), clusters = (int64_t)B * K;
+    if (v >= 0) return N <= ((int64_t)1 << 30) && bytes < ((int64_t)1 << 32) ? v : 0;      // (offsets of 32 bits)
     int64_t G = std::max(cdiv(bytes, (int64_t)2 << 20), cdiv(N, 16384));
     if (G > 16 || clusters * G > 1024 || clusters * N > ((int64_t)8 << 20)) return 0;
-    if (clusters < 128) G = std::max(G, std::min<int64_t>(cdiv(bytes, (int64_t)512 << 10), 8));
+    if (clusters < 128) G = std::max(G, std::min<int64_t>(cdiv(bytes, (int64_t)512 << 10), clusters <= 32 ? 16 : 8));
     return (int)G;
 }
 

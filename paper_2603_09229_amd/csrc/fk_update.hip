@@ -328,19 +328,25 @@ __global__ __launch_bounds__(1024) void finalize_kernel(
 // all assignments, K*N in all, which come from L2; what it saves are the four to seven dependent
 // launches of the sort, each bound by latency at this size.
 // Wave w takes the 256-key blocks w, w + WAVES, ...; its matches collect in a list of its own in LDS and are
-// added 64 rows at a time, with the row pieces per lane of segment_reduce_kernel.  Which wave adds a
-// row and in which place follows from the assignments alone: fixed order, no atomics.
+// added a group of rows at a time, with the row pieces per lane of segment_reduce_kernel, where every wave has several
+// blocks, otherwise after all waves have shared them out evenly.  Which wave adds a row and in which place follows from
+// the assignments alone: fixed order, no atomics.
+// A compute unit's instructions bound a large cluster, so whole batches of rows are loaded without a test for each:
+// all points in one cluster, us, with tests and without: 2010 fp32, d = 256, K = 467 27.1 -> 18.9; 4096, d = 256, K = 500 33.2 ->
+// 20.8 (twice the loads in flight: 32.2).  Shares of few blocks: 1024 fp32, d = 512, K = 20, where one wave had a
+// block's 256 rows, 51.4 -> 12.7 with both.
 template <int EPL, bool BF, bool RAGGED, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void gather_update_kernel(
     const void* __restrict__ Xv, const int32_t* __restrict__ keys, EmitTo to,
     float* __restrict__ partial, int32_t* __restrict__ wg_counts, int64_t N, int G, int merged, int lpr_log2) {
     constexpr int kBlocks = EPL == 4 ? 2 : 1;      // column blocks of 64 lanes x 16 bytes in the widest row
     constexpr int kAhead = 4;                      // key loads in flight per wave
-    constexpr int kList = 64 + 256;                // fewer than 64 waiting + one block's matches
+    constexpr int kLoads = 8;                      // row loads in flight per lane
+    constexpr int kHold = 256, kList = kHold + 256; // waiting + one block's matches
     typedef int32_t intx4_any __attribute__((ext_vector_type(4), aligned(4)));
-    extern __shared__ float gather_lds[];          // [WAVES][dpow] row sums | [d] squared entries
     __shared__ int list[WAVES][kList];
-    __shared__ int pool[WAVES * 64];
+    __shared__ int pool[WAVES * kHold];
+    __shared__ float nrm[512];                     // squared entries
     __shared__ int left[WAVES], cred[WAVES];
     const int d = to.d, K = to.K, len = RAGGED ? to.row_len : d;
     const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -362,27 +368,34 @@ __global__ __launch_bounds__(WAVES * 64) void gather_update_kernel(
 #pragma unroll
         for (int e = 0; e < EPL; ++e) acc[cb][e] = 0.f;
     int* mylist = list[wave];
+    const int group = min(max(64, kLoads * S), kHold), hold = hi - lo >= 4 * WAVES * 256 ? group : kHold;
     int held = 0, own = 0;
 
     auto add_rows = [&](const int* rows, int count) {
-        constexpr int U = 8;
+        constexpr int U = kLoads;
 #pragma unroll
         for (int cb = 0; cb < kBlocks; ++cb) {
             const int col = cb * 64 * EPL + (lane & (LPR - 1)) * EPL;
             if (cb > 0 && cb * 64 * EPL >= d) break;
-            const bool active = col < d;
-            // where a lane's piece would cross the row's end: the one that ends there (see segment_reduce_kernel)
-            const char* mine = X + (RAGGED ? min(col, len - EPL) : col) * (16 / EPL);
-            for (int q = 0; q < count; q += S * U) {
-                uintx4 v[U];
+            // where a lane's piece would cross the row's end: the one that ends there (see segment_reduce_kernel); lanes
+            // beyond the row read it too, and nobody their sums
+            const uint32_t mine = min(col, len - EPL) * (16 / EPL);
+            auto piece = [&](int rr) -> uintx4 {
+                const char* at = X + (mine + (uint32_t)rows[rr] * (uint32_t)row_bytes);
+                return RAGGED ? (uintx4)*(const uintx4_any*)at : *(const uintx4*)at;
+            };
+            uintx4 v[U];
+            int q = slot;
+            for (; q - slot + S * U <= count; q += S * U) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[u] = piece(q + u * S);
+                add_in_pairs<EPL, BF>(v, acc[cb]);
+            }
+            if (q - slot < count) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const int rr = q + u * S + slot;
                     v[u] = uintx4{0u, 0u, 0u, 0u};
-                    if (active && rr < count) {
-                        const char* at = mine + (int64_t)rows[rr] * row_bytes;
-                        v[u] = RAGGED ? (uintx4)*(const uintx4_any*)at : *(const uintx4*)at;
-                    }
+                    if (q + u * S < count) v[u] = piece(q + u * S);
                 }
                 add_in_pairs<EPL, BF>(v, acc[cb]);
             }
@@ -402,10 +415,10 @@ __global__ __launch_bounds__(WAVES * 64) void gather_update_kernel(
             held += __popcll(mm[e]);
         }
         __builtin_amdgcn_wave_barrier();
-        while (held >= 64) {
-            held -= 64;
-            own += 64;
-            add_rows(mylist + held, 64);
+        while (held > hold) {
+            held -= group;
+            own += group;
+            add_rows(mylist + held, group);
         }
         __builtin_amdgcn_wave_barrier();
     };
@@ -436,8 +449,8 @@ __global__ __launch_bounds__(WAVES * 64) void gather_update_kernel(
         for (int a = 0; a < kAhead; ++a)
             if (base + a * kStride < hi) take(kv[a], base + a * kStride + lane * 4, false);
     }
-    // what is left, fewer than 64 rows a wave, is shared out again in whole batches of loads: most clusters
-    // here have a few rows in all, and the waves without any are done
+    // what is left is shared out again: a part of few blocks may have all its rows on one wave's list, and most
+    // clusters here have a few rows in all, which one wave adds in one batch while the others are done
     if (lane == 0) { left[wave] = held; cred[wave] = own + held; }
     __syncthreads();
     int n = n_prev, rest = 0, before = 0;
@@ -447,19 +460,15 @@ __global__ __launch_bounds__(WAVES * 64) void gather_update_kernel(
         before += w < wave ? left[w] : 0;
         rest += left[w];
     }
-    if (lane < held) pool[before + lane] = mylist[lane];
+    for (int i = lane; i < held; i += 64) pool[before + i] = mylist[i];
     __syncthreads();
-    const int batch = 8 * S, mine0 = wave * batch;
-    bool busy = own > 0;
-    for (int q = mine0; q < rest; q += WAVES * batch) {
-        busy = true;
-        add_rows(pool + q, min(batch, rest - q));
-    }
+    const int unit = 8 * S, each = ((rest + WAVES - 1) / WAVES + unit - 1) & -unit;       // (a power of two)
+    const int from = wave * each;
+    if (from < rest) add_rows(pool + from, min(each, rest - from));
+    const bool busy = own > 0 || from < rest;
 
-    int dpow = 4;
-    while (dpow < d) dpow <<= 1;
-    float* red = gather_lds;
-    float* nrm = red + WAVES * dpow;
+    constexpr int kRow = kList;                    // (no list is read any more)
+    float* red = (float*)&list[0][0];
     if (busy) {
 #pragma unroll
         for (int cb = 0; cb < kBlocks; ++cb) {
@@ -473,7 +482,7 @@ __global__ __launch_bounds__(WAVES * 64) void gather_update_kernel(
             if (slot == 0 && col < d) {
 #pragma unroll
                 for (int e = 0; e < EPL; ++e)
-                    if (!RAGGED || first + e >= col) red[wave * dpow + first + e] = acc[cb][e];
+                    if (!RAGGED || first + e >= col) red[wave * kRow + first + e] = acc[cb][e];
             }
         }
     }
@@ -482,7 +491,7 @@ __global__ __launch_bounds__(WAVES * 64) void gather_update_kernel(
     auto sum_of = [&](int j) {
         float t[WAVES];                            // (in pairs: a few additions to the largest sums, not one per wave)
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) t[w] = left[w] ? red[w * dpow + j] : 0.f;
+        for (int w = 0; w < WAVES; ++w) t[w] = left[w] ? red[w * kRow + j] : 0.f;
 #pragma unroll
         for (int half = WAVES / 2; half > 0; half /= 2)
 #pragma unroll
@@ -569,11 +578,8 @@ template <int EPL, bool BF, int WAVES>
 static fk_status launch_gather_w(const Geometry& g, const Workspace& w, const void* X, const int32_t* assign,
                                  const EmitTo& to, int G, bool merged, hipStream_t s) {
     const int lpr_log2 = std::min(6, ceil_log2((int)cdiv(g.d, EPL)));
-    int dpow = 4;
-    while (dpow < g.d) dpow <<= 1;
-    const size_t lds = ((size_t)WAVES * dpow + g.d) * sizeof(float);      // at most 16 x 512 + 512 floats
     auto kern = g.len == g.d ? gather_update_kernel<EPL, BF, false, WAVES> : gather_update_kernel<EPL, BF, true, WAVES>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)g.K * G), g.B), dim3(WAVES * 64), lds, s, X, assign, to, w.partial,
+    hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)g.K * G), g.B), dim3(WAVES * 64), 0, s, X, assign, to, w.partial,
                        w.wg_counts, g.N, G, merged ? 1 : 0, lpr_log2);
     FK_HIP(hipGetLastError());
     return FK_OK;
@@ -584,13 +590,13 @@ fk_status launch_gather_update(const Geometry& g, const Workspace& w, const void
     const int G = g.gather_parts;
     const bool merged = gather_needs_merge(g, a);
     const EmitTo to = emit_args(g, a);
-    // sixteen waves where a compute unit has one workgroup (it is then bound by its loads in flight: 15991 points,
-    // d = 256, K = 15, Zipf sizes 17.3 -> 15.0 us), four where many workgroups have little to read
+    // four waves where many workgroups have little to read (32 instances of 1000 points, d = 64, K = 32: 6.6 us, with eight 10.1;
+    // 1000, K = 900: 6.2, 9.4)
     const int64_t workgroups = (int64_t)g.B * g.K * G;
-    const bool large = workgroups <= 256, medium = workgroups <= 512 || cdiv(g.N, G) > 1024;
-    if (g.t == FK_F32) return (large ? launch_gather_w<4, false, 16> : medium ? launch_gather_w<4, false, 8> : launch_gather_w<4, false, 4>)(g, w, X, assign, to, G, merged, s);
-    if (g.t == FK_F16) return (large ? launch_gather_w<8, false, 16> : medium ? launch_gather_w<8, false, 8> : launch_gather_w<8, false, 4>)(g, w, X, assign, to, G, merged, s);
-    return (large ? launch_gather_w<8, true, 16> : medium ? launch_gather_w<8, true, 8> : launch_gather_w<8, true, 4>)(g, w, X, assign, to, G, merged, s);
+    const bool wide = workgroups <= 512 || cdiv(g.N, G) > 1024;
+    if (g.t == FK_F32) return (wide ? launch_gather_w<4, false, 8> : launch_gather_w<4, false, 4>)(g, w, X, assign, to, G, merged, s);
+    if (g.t == FK_F16) return (wide ? launch_gather_w<8, false, 8> : launch_gather_w<8, false, 4>)(g, w, X, assign, to, G, merged, s);
+    return (wide ? launch_gather_w<8, true, 8> : launch_gather_w<8, true, 4>)(g, w, X, assign, to, G, merged, s);
 }
 
 fk_status launch_finalize(const Geometry& g, const Workspace& w, const int32_t* seg_off,

@@ -121,3 +121,32 @@ def test_no_long_chain_of_additions(dtype, N, d, K):
             fk.fk_set_option("gather_update", -1)
         # ... each good to 2^-24 of the whole, and the rounding of the mean
         assert (C[0, K // 2].double() * N - total).abs().max() <= (64 + 1) * 2.0 ** -24 * total
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("N,d,K,parts", [
+    # four and eight waves; shares of one block of 256 keys a wave and around those from which waves add as they go;
+    # lists around 256 rows; whole and broken batches of rows, of 64 and more rows to a load
+    (256, 64, 3, 1), (257, 8, 3, 1), (513, 512, 5, 2), (1023, 100, 520, 1), (2048, 33, 600, 2), (4097, 256, 300, 1), (8191, 16, 300, 1), (8192, 40, 300, 1),
+    (8449, 9, 270, 1), (16383, 128, 40, 1), (16384, 24, 40, 1), (16641, 320, 7, 1), (40000, 32, 9, 2), (70001, 8, 2, 3),
+])
+def test_every_row_counts_once(dtype, N, d, K, parts):
+    """Small whole numbers: every partial sum is exact, so that a row lost or taken twice shows."""
+    g = torch.Generator(device=DEV).manual_seed(N + d)
+    X = torch.randint(-3, 4, (1, N, d), generator=g, device=DEV)
+    X[..., 0] = 1 + torch.arange(N, device=DEV) % 3
+    u = torch.rand((1, N), generator=g, device=DEV)
+    C0 = torch.randn((1, K, d), generator=g, device=DEV)
+    for label in ((K * u).int(), (K * u ** 4).int(), torch.full((1, N), K // 2, dtype=torch.int32, device=DEV), (K * (torch.arange(N, device=DEV)[None] // 64) // (N // 64 + 1)).int()):
+        label = label.clamp(max=K - 1)
+        total = torch.zeros((K, d), dtype=torch.int64).index_add_(0, label[0].long().cpu(), X[0].cpu())
+        n = torch.bincount(label[0].cpu(), minlength=K)
+        want = torch.where(n[:, None] > 0, (total.double() / n.clamp(min=1)[:, None]).float(), C0[0].cpu())
+        try:
+            fk.fk_set_option("fused_update", 0)
+            fk.fk_set_option("gather_update", parts)
+            C, _, m = fk.fk_update(X.to(dtype), label, C0)
+        finally:
+            fk.fk_set_option("gather_update", -1)
+            fk.fk_set_option("fused_update", -1)
+        assert torch.equal(m[0].cpu().long(), n) and torch.equal(C[0].cpu(), want)
