@@ -236,7 +236,8 @@ fk_status fk_standard_update(const void* X, const int32_t* assign, const float* 
  *                        one up to 2^24 keys); changes fk_workspace_bytes, so set it before sizing
  *   "fused_update"   0   do not take the sort-free one-pass updates below
  *   "gather_update"  n   0 = never take the sort-free update of small instances below, 1..64 = always, in
- *                        that many parts; changes fk_workspace_bytes, so set it before sizing
+ *                        that many parts (fewer in a workspace without room for them); changes
+ *                        fk_workspace_bytes, so set it before sizing
  *   "timer_repeat"   r   measurement only: while the stage timer runs, the assignment (or fused)
  *                        kernel and the segment reduction are each launched r times back to back
  *                        inside their interval (same outputs rewritten), so that interval /
@@ -261,7 +262,8 @@ fk_status fk_standard_update(const void* X, const int32_t* assign, const float* 
  * above takes is one launch without a sort, or two: every workgroup reads all assignments and adds the
  * rows of one cluster.  Same counts as the sorted path, sums up to fp32 summation order, bit-reproducible.
  * All of these passes need room for one partial table per workgroup, which fk_workspace_bytes
- * includes.
+ * includes (the last has one for every part of an instance, and makes do with fewer parts where ws is
+ * as large as sorting needs; means then differ in summation order).
  */
 int fk_plan(int B, int64_t N, int d, int K, fk_dtype t, char* buf, size_t buf_bytes);
 int fk_set_option(const char* name, int value);

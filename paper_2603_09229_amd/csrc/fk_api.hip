@@ -92,6 +92,15 @@ int choose_gather_parts(int B, int64_t N, int d, int K, fk_dtype t) {
     return (int)G;
 }
 
+// A workspace sized without regard to the parts (for more points, which are sorted, say) has room for as many of them
+// as there are items.
+bool limit_gather_parts(Geometry* g) {
+    const int most = (int)std::min<int64_t>(g->max_items / g->K, g->gather_parts);
+    if (most == g->gather_parts) return false;
+    g->gather_parts = most;                      // at least one: max_items is no less than K
+    return true;
+}
+
 bool make_geometry(int B, int64_t N, int d_user, int K, fk_dtype t, Geometry* g) {
     if (B < 1 || N < 1 || K < 1 || K > 65536 || d_user < 1 || d_user > 512) return false;
     const int d = (d_user + 7) / 8 * 8;
@@ -215,9 +224,12 @@ Workspace carve(const Geometry& g, void* base, bool padded_x) {
         w.f32_list_len = (int32_t*)take((size_t)g.B * 4);
     }
     w.c_bias = (float*)take((size_t)g.B * g.ktiles * 32 * 4);
-    const size_t fused_rows = (size_t)g.K * std::max({g.fused_grid_cap, g.table_grid_cap, g.f32_grid_cap, g.gather_parts});
-    w.partial = (float*)take((size_t)g.B * std::max((size_t)g.max_items, fused_rows) * g.d * 4);
+    const size_t fused_rows = (size_t)g.K * std::max({g.fused_grid_cap, g.table_grid_cap, g.f32_grid_cap});
+    const size_t gather_rows = (size_t)g.K * g.gather_parts;
+    w.partial = (float*)take((size_t)g.B * std::max({(size_t)g.max_items, fused_rows, gather_rows}) * g.d * 4);
     if (fused_rows > 0) w.wg_counts = (int32_t*)take((size_t)g.B * fused_rows * 4);
+    // (an update that gathers does not sort: the parts' counts take the place of the sort's totals)
+    w.gather_counts = gather_rows <= 2049 ? w.digit_off : (int32_t*)take((size_t)g.B * gather_rows * 4);
     w.sums = (float*)take(BKd * 4);
     if (needs_padded_rows(g)) {
         if (padded_x) w.x_pad = take(BN * g.d * elem_size(g.t));
@@ -332,7 +344,8 @@ static fk_status check_common(const char* fn, int B, int64_t N, int d, int K, fk
         set_error("%s: workspace pointer is NULL or not 256-byte aligned", fn);
         return FK_EINVAL;
     }
-    const size_t need = carve(*g, nullptr).bytes;
+    size_t need = carve(*g, nullptr).bytes;
+    if (ws_bytes < need && limit_gather_parts(g)) need = carve(*g, nullptr).bytes;
     if (ws_bytes < need) {
         set_error("%s: workspace too small: %zu bytes given, %zu needed", fn, ws_bytes, need);
         return FK_EWORKSPACE;
@@ -397,7 +410,7 @@ static fk_status run_update(const Geometry& g, const Workspace& w, const void* X
         if (gather_needs_merge(g, fa)) {
             Geometry gm = g;
             gm.max_items = (int64_t)g.K * g.gather_parts;
-            FK_TRY(launch_finalize(gm, w, nullptr, nullptr, fa, s, w.wg_counts, g.gather_parts));
+            FK_TRY(launch_finalize(gm, w, nullptr, nullptr, fa, s, w.gather_counts, g.gather_parts));
             timer_mark(s, kStageFinalize);
         }
         return FK_OK;

@@ -116,6 +116,7 @@ struct Workspace {
     int32_t* keys_sorted;// [B,N] sorted keys (two-pass sort only)
     float* partial;      // [B,max(max_items, K*(largest one-pass grid cap)),d] per-item segment sums
     int32_t* wg_counts;  // [B,K,grid cap] per-workgroup counts (one-pass updates only)
+    int32_t* gather_counts;  // [B,K,gather_parts] the same of an update without a sort
     float* sums;         // [B,K,d] accumulated sums (chunked mode)
     float* f32_shift;    // [B,dchunks*16] shift of the filtered fp32 assignment (fk_f32_filter.hip)
     int32_t* f32_list_len; // [B] points it has left open (the points themselves: sorted_idx)
@@ -222,12 +223,13 @@ fk_status launch_finalize(const Geometry& g, const Workspace& w, const int32_t* 
                           const int32_t* wg_counts = nullptr, int wg_per_cluster = 0);
 
 // Small instances (g.gather_parts > 0): every workgroup reads all assignments of its part of the instance and adds the rows
-// of one cluster.  Writes what launch_finalize does; where gather_needs_merge, w.partial / w.wg_counts as
+// of one cluster.  Writes what launch_finalize does; where gather_needs_merge, w.partial / w.gather_counts as
 // launch_stream_update with wg_per_cluster = g.gather_parts instead.
 fk_status launch_gather_update(const Geometry& g, const Workspace& w, const void* X, const int32_t* assign,
                                const FinalizeArgs& a, hipStream_t s);
 // (parts that wait for their turn are added by the merge kernel)
 inline bool gather_needs_merge(const Geometry& g, const FinalizeArgs& a) { return g.gather_parts > 1 || a.late > 0; }
+bool limit_gather_parts(Geometry* g);      // to the partial rows that the sorted update has room for; whether that changed them
 int choose_gather_parts(int B, int64_t N, int d, int K, fk_dtype t);
 void set_gather_update_option(int v);      // -1 = by shape, 0 = never, 1..64 = always, in that many parts
 

@@ -30,6 +30,7 @@ struct OocLayout {
 
 static bool ooc_layout(int64_t chunk_rows, int d, int K, fk_dtype t, OocLayout* L, Geometry* g) {
     if (!make_geometry(1, chunk_rows, d, K, t, g)) return false;
+    (void)limit_gather_parts(g);              // the chunks that fit a given dev_ws are those that sorting has room for
     // chunk buffers have room for rows of the kernels' width (a multiple of 8), which rows of fewer
     // than 8 elements need: they land in them through a pitched copy, the padding columns zeroed once
     L->chunk_bytes = align_up((size_t)chunk_rows * g->d * elem_size(t), 256);
@@ -247,7 +248,7 @@ fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_
                 OOC_TRY(launch_gather_update(g, w, xbuf[bi], a, fa, cs));
                 g.max_items = (int64_t)K * g.gather_parts;
                 if (gather_needs_merge(g, fa))
-                    OOC_TRY(launch_finalize(g, w, nullptr, nullptr, fa, cs, w.wg_counts, g.gather_parts));
+                    OOC_TRY(launch_finalize(g, w, nullptr, nullptr, fa, cs, w.gather_counts, g.gather_parts));
             } else {
                 OOC_TRY(launch_sort_inverse(g, w, a, w.sorted_idx, w.seg_off, w.item_off, cs));
                 OOC_TRY(launch_segment_reduce(g, w, xbuf[bi], w.sorted_idx, w.seg_off, w.item_off, cs));

@@ -580,7 +580,7 @@ static fk_status launch_gather_w(const Geometry& g, const Workspace& w, const vo
     const int lpr_log2 = std::min(6, ceil_log2((int)cdiv(g.d, EPL)));
     auto kern = g.len == g.d ? gather_update_kernel<EPL, BF, false, WAVES> : gather_update_kernel<EPL, BF, true, WAVES>;
     hipLaunchKernelGGL(kern, dim3((unsigned)((int64_t)g.K * G), g.B), dim3(WAVES * 64), 0, s, X, assign, to, w.partial,
-                       w.wg_counts, g.N, G, merged ? 1 : 0, lpr_log2);
+                       w.gather_counts, g.N, G, merged ? 1 : 0, lpr_log2);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }

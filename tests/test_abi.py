@@ -142,3 +142,25 @@ def test_plan_names_the_update_that_fk_update_takes(B, N, d, K, dtype, gathers):
             assert ("fk_update alone=sort-inverse" in plan) == (not gathers or option == 0)
     finally:
         fk.fk_set_option("gather_update", -1)
+
+
+@pytest.mark.parametrize("N,d,K,dtype", [
+    (16384, 512, 64, torch.float32), (1024, 512, 20, torch.float32), (8000, 512, 100, torch.float32), (8192, 128, 1000, torch.bfloat16),
+    (3740, 139, 11, torch.bfloat16), (20000, 128, 2, torch.float32),
+])
+def test_a_workspace_that_sorting_fits_is_large_enough(N, d, K, dtype):
+    """Small instances need no more than that; the room for more parts of them is asked for, not insisted on.  (Out of core none is
+    asked for, and the chunks that fit a given size are as long as those that are sorted.)"""
+    L = fk.lib()
+    sizes = []
+    try:
+        for option in (0, -1):
+            fk.fk_set_option("gather_update", option)
+            assert ("gather(parts=" in fk.fk_plan(1, N, d, K, dtype)) == (option != 0)
+            sizes.append((fk.fk_workspace_bytes(1, N, d, K, dtype), fk.fk_ooc_workspace_bytes(N, d, K, dtype)))
+    finally:
+        fk.fk_set_option("gather_update", -1)
+    assert sizes[0][1] == sizes[1][1] and sizes[0][0] <= sizes[1][0]
+    ws = ctypes.c_void_p(256)                    # never dereferenced: X is refused next
+    for room, status in ((sizes[0][0], 1), (sizes[0][0] - 1, 3)):
+        assert L.fk_update(None, ws, ws, ws, None, ws, 1, N, d, K, fk._DTYPE[dtype], ws, room, None) == status

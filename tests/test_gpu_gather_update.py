@@ -150,3 +150,21 @@ def test_every_row_counts_once(dtype, N, d, K, parts):
             fk.fk_set_option("gather_update", -1)
             fk.fk_set_option("fused_update", -1)
         assert torch.equal(m[0].cpu().long(), n) and torch.equal(C[0].cpu(), want)
+
+
+@pytest.mark.parametrize("N,d,K,dtype", [(16384, 512, 64, torch.float32), (1024, 512, 20, torch.float32), (8192, 128, 1000, torch.bfloat16)])
+def test_as_many_parts_as_the_workspace_has_room_for(N, d, K, dtype):
+    g = torch.Generator(device=DEV).manual_seed(N)
+    X = torch.randint(-3, 4, (1, N, d), generator=g, device=DEV).to(dtype)
+    label = (K * torch.rand((1, N), generator=g, device=DEV) ** 4).int()
+    C0 = torch.zeros((1, K, d), device=DEV)
+    want = fk.fk_update(X, label, C0)
+    try:
+        fk.fk_set_option("gather_update", 0)
+        room = fk.fk_workspace_bytes(1, N, d, K, dtype)
+    finally:
+        fk.fk_set_option("gather_update", -1)
+    ws = torch.full((room + 4096,), 0x55, dtype=torch.uint8, device=DEV)
+    got = fk.fk_update(X, label, C0, ws=ws[:room])
+    assert all(torch.equal(a, b) for a, b in zip(got, want))                      # sums of small whole numbers are exact
+    assert bool((ws[room:] == 0x55).all())
