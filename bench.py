@@ -103,6 +103,7 @@ def main() -> int:
         return clock_trace(torch, fk, dev)
     if args.general_update:
         fk.fk_set_option("fused_update", 0)
+        fk.fk_set_option("gather_update", 0)
     w = short[args.workload]
     steps = args.steps if args.steps is not None else w.iters
     if args.workload == "c5":
