@@ -19,12 +19,14 @@ def test_one_pass_equals_the_general_path(B, N, d, K):
     try:
         for v in (-1, 0):
             fk.fk_set_option("fused_update", v)
+            fk.fk_set_option("gather_update", v)
             assert ("f32_update" in fk.fk_plan(B, N, d, K, torch.float32)) == (v < 0)
             C = X[:, :K].clone()
             a, n, _ = fk.fk_lloyd_iter(X, C, 1)
             res.append((a, n, C))
     finally:
         fk.fk_set_option("fused_update", -1)
+        fk.fk_set_option("gather_update", -1)
     (a, n, C), (b, m, D) = res
     assert torch.equal(a, b) and torch.equal(n, m)
     # the same n terms in two orders: n 2^-24 of their largest each, divided by n

@@ -15,7 +15,8 @@ DEV = "cuda:0"
     (torch.float16, 8192, 128, 40, 1024), (torch.bfloat16, 7100, 20, 33, 1024), (torch.float32, 9000, 64, 25, 1000),
 ])
 @pytest.mark.parametrize("room", [True, False])
-def test_one_call_gives_the_bits_of_single_iterations(dtype, N, d, K, chunk, room):
+@pytest.mark.parametrize("gather", [-1, 0])
+def test_one_call_gives_the_bits_of_single_iterations(dtype, N, d, K, chunk, room, gather):
     g = torch.Generator().manual_seed(N + d)
     centre = 8 * torch.randn((K, d), generator=g)
     lab = torch.cat([torch.arange(K), torch.randint(0, K, (N - K,), generator=g)])
@@ -24,7 +25,11 @@ def test_one_call_gives_the_bits_of_single_iterations(dtype, N, d, K, chunk, roo
     need = fk.fk_ooc_workspace_bytes(chunk, d, K, dtype) - (0 if room else 256)
     ws = torch.empty(need, dtype=torch.uint8, device=DEV)
     C, D = (X[:K].float().to(DEV).contiguous() for _ in range(2))
-    a, n = fk.fk_lloyd_ooc(X, C, 4, dev_ws=ws, chunk_rows=chunk)
-    for _ in range(4):
-        b, m = fk.fk_lloyd_ooc(X, D, 1, dev_ws=ws, chunk_rows=chunk)
+    try:
+        fk.fk_set_option("gather_update", gather)          # (out of core that changes no size)
+        a, n = fk.fk_lloyd_ooc(X, C, 4, dev_ws=ws, chunk_rows=chunk)
+        for _ in range(4):
+            b, m = fk.fk_lloyd_ooc(X, D, 1, dev_ws=ws, chunk_rows=chunk)
+    finally:
+        fk.fk_set_option("gather_update", -1)
     assert torch.equal(a, b) and torch.equal(n, m) and torch.equal(C, D)

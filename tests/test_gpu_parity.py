@@ -243,8 +243,19 @@ UPDATE_CASES = [
 ]
 
 
+@pytest.fixture(params=[-1, 0], ids=["by_size", "sorted"])
+def gather_option(request):
+    """Small instances without a sort, as their size has it, or with one."""
+    fk.fk_set_option("gather_update", request.param)
+    yield request.param
+    fk.fk_set_option("gather_update", -1)
+
+
 @pytest.mark.parametrize("dtype,B,N,d,K,zipf", UPDATE_CASES)
-def test_update_matches_oracle(dtype, B, N, d, K, zipf):
+def test_update_matches_oracle(dtype, B, N, d, K, zipf, gather_option):
+    plan = fk.fk_plan(B, N, d, K, dtype)
+    if gather_option == 0:
+        assert "sort=" in plan or "fk_update alone=sort-inverse" in plan or "stream_update" in plan
     w, X, lab, C0 = _problem(dtype, B, N, d, K, seed=200 + N, zipf=zipf)
     a = lab.clone()
     if K > 4:
@@ -340,7 +351,7 @@ def test_lloyd_multi_iteration_call_equals_repeated_single_calls():
     (torch.float32, 9000, 5, 7, 4096),
     (torch.bfloat16, 10000, 3, 4, 0),
 ])
-def test_out_of_core_equals_in_core(dtype, N, d, K, chunk):
+def test_out_of_core_equals_in_core(dtype, N, d, K, chunk, gather_option):
     w, X, _, C0 = _problem(dtype, 1, N, d, K, seed=300 + N)
     Xpin = X[0].clone().pin_memory()
     rows = chunk if chunk else 12288
@@ -489,7 +500,7 @@ def test_results_do_not_depend_on_the_stream():
     assert torch.equal(Ca, Cb) and torch.equal(a1, a2) and torch.equal(n1, n2)
 
 
-def test_random_shapes_full_iteration():
+def test_random_shapes_full_iteration(gather_option):
     """Seeded sweep over odd shapes: every dtype, ragged N, K on both sides of the tile and
     stage boundaries, d every multiple of 8; one full iteration each against the oracle."""
     rng = np.random.default_rng(2024)
@@ -591,7 +602,7 @@ ODD_WIDTH_CASES = [
 
 
 @pytest.mark.parametrize("dtype,B,N,d,K", ODD_WIDTH_CASES)
-def test_any_row_width(dtype, B, N, d, K):
+def test_any_row_width(dtype, B, N, d, K, gather_option):
     w, X, lab, C0 = _problem(dtype, B, N, d, K, seed=600 + N + d)
     Xd = X.to(DEV)
     keep = Xd.clone()
@@ -628,8 +639,8 @@ def test_any_row_width(dtype, B, N, d, K):
 
 # ---------------------------------------------------------------------------------------
 # Few clusters (16-bit storage, K <= 32, d <= 128): the sort-free one-hot MFMA update, fused
-# with the assignment inside fk_lloyd_iter.  fk_set_option("fused_update", 0) sends the same
-# shape down the general sort-inverse path, so the two can be compared.
+# with the assignment inside fk_lloyd_iter.  fk_set_option "fused_update" 0 and "gather_update" 0 send the
+# same shape down the general sort-inverse path, so the two can be compared.
 FEW_CLUSTER_CASES = [
     # dtype, B, N, d, K, zipf
     (torch.float16, 1, 100000, 64, 16, 1.2),      # the skewed large-N / small-K recipe, scaled
@@ -648,8 +659,12 @@ FEW_CLUSTER_CASES = [
 
 @pytest.fixture
 def general_path_switch():
-    yield lambda on: fk.fk_set_option("fused_update", 0 if on else -1)
-    fk.fk_set_option("fused_update", -1)
+    def switch(on):
+        for name in ("fused_update", "gather_update"):
+            fk.fk_set_option(name, 0 if on else -1)
+
+    yield switch
+    switch(False)
 
 
 @pytest.mark.parametrize("dtype,B,N,d,K,zipf", FEW_CLUSTER_CASES)
@@ -660,7 +675,7 @@ def test_few_cluster_iteration_matches_oracle_and_general_path(dtype, B, N, d, K
     C_f = C0.to(DEV).clone()
     a_f, n_f, lp_f = fk.fk_lloyd_iter(Xd, C_f, 1)
     general_path_switch(True)
-    assert "stream_update" not in fk.fk_plan(B, N, d, K, dtype)
+    assert "sort=" in fk.fk_plan(B, N, d, K, dtype)
     C_s = C0.to(DEV).clone()
     a_s, n_s, lp_s = fk.fk_lloyd_iter(Xd, C_s, 1)
     general_path_switch(False)
@@ -729,7 +744,7 @@ def test_few_cluster_update_clamps_ids_like_the_sort_path(general_path_switch):
 
 # Up to 256 clusters (16-bit storage, 32 < K <= 256, d <= 128): assignment + table of sums in
 # one pass over X (table split over the registers of a persistent workgroup, compacted one-hot
-# MFMA).  fk_set_option("fused_update", 0) sends the same shape down the general path.
+# MFMA).  general_path_switch sends the same shape down the general path.
 TABLE_CASES = [
     # dtype, B, N, d, K, zipf
     (torch.bfloat16, 4, 32768, 128, 256, 0.0),    # the batched token-clustering recipe, 4 instances
@@ -753,7 +768,7 @@ def test_table_update_iteration_matches_oracle_and_general_path(dtype, B, N, d, 
     C_f = C0.to(DEV).clone()
     a_f, n_f, lp_f = fk.fk_lloyd_iter(Xd, C_f, 1)
     general_path_switch(True)
-    assert "table_update" not in fk.fk_plan(B, N, d, K, dtype)
+    assert "sort=" in fk.fk_plan(B, N, d, K, dtype)
     C_s = C0.to(DEV).clone()
     a_s, n_s, lp_s = fk.fk_lloyd_iter(Xd, C_s, 1)
     general_path_switch(False)
@@ -829,7 +844,7 @@ def test_f32_few_cluster_iteration_matches_oracle_and_general_path(B, N, d, K, z
     C_f = C0.to(DEV).clone()
     a_f, n_f, lp_f = fk.fk_lloyd_iter(Xd, C_f, 1)
     general_path_switch(True)
-    assert "f32_update" not in fk.fk_plan(B, N, d, K, dtype)
+    assert "sort=" in fk.fk_plan(B, N, d, K, dtype)
     C_s = C0.to(DEV).clone()
     a_s, n_s, lp_s = fk.fk_lloyd_iter(Xd, C_s, 1)
     general_path_switch(False)
@@ -883,10 +898,10 @@ def test_f32_few_cluster_all_points_in_one_cluster_and_empty_clusters():
 
 def test_kernel_choices_do_not_change_the_result():
     """Seeded sweep: every host-side kernel choice forced the other way (tile shape, streaming
-    assign, staged scatter, several sub-tiles per sort workgroup, sort-free update) must give the
+    assign, staged scatter, several sub-tiles per sort workgroup, sort-free updates) must give the
     same assignments and counts as the default rules, and centroids equal up to summation order."""
     rng = np.random.default_rng(77)
-    opts = ("assign_variant", "assign_stream", "sort_stage_bins", "sort_min_rounds", "fused_update")
+    opts = ("assign_variant", "assign_stream", "sort_stage_bins", "sort_min_rounds", "fused_update", "gather_update")
     for case in range(36):
         dtype = (torch.float16, torch.bfloat16)[case % 2]
         d = int(rng.choice([8, 24, 32, 64, 72, 128, 100, 200]))
@@ -901,7 +916,7 @@ def test_kernel_choices_do_not_change_the_result():
         a_d, n_d, _ = fk.fk_lloyd_iter(X, Cd, 2)
         forced = {"assign_variant": int(rng.integers(0, 4)), "assign_stream": int(rng.integers(0, 2)),
                   "sort_stage_bins": int(rng.choice([0, 2048])), "sort_min_rounds": int(rng.choice([1, 2, 3])),
-                  "fused_update": 0}
+                  "fused_update": 0, "gather_update": 0}
         try:
             for k, v in forced.items():
                 fk.fk_set_option(k, v)

@@ -31,15 +31,18 @@ def test_ragged_rows_equal_zero_padded_rows(dtype, B, N, d, K):
     Xp, Cp = F.pad(X, (0, pad)), F.pad(C, (0, pad))
     for u, v in zip(fk.fk_assign(X, C.to(dtype), min_dist=True), fk.fk_assign(Xp, Cp.to(dtype), min_dist=True)):
         assert torch.equal(u, v)
-    u, v = fk.fk_update(X, lab, C), fk.fk_update(Xp, lab, Cp)
-    assert torch.equal(u[0], v[0][..., :d]) and torch.equal(u[1], v[1][..., :d]) and torch.equal(u[2], v[2])
-    for fused in (-1, 0):
+    for fused, gather in ((-1, -1), (0, -1), (0, 0)):
         try:
             fk.fk_set_option("fused_update", fused)
+            fk.fk_set_option("gather_update", gather)
+            assert gather < 0 or "sort=" in fk.fk_plan(B, N, d, K, dtype)
+            p, q = fk.fk_update(X, lab, C), fk.fk_update(Xp, lab, Cp)
             c, cp = C.clone(), Cp.clone()
             u, v = fk.fk_lloyd_iter(X, c, 3), fk.fk_lloyd_iter(Xp, cp, 3)
         finally:
             fk.fk_set_option("fused_update", -1)
+            fk.fk_set_option("gather_update", -1)
+        assert torch.equal(p[0], q[0][..., :d]) and torch.equal(p[1], q[1][..., :d]) and torch.equal(p[2], q[2])
         assert torch.equal(u[0], v[0]) and torch.equal(u[1], v[1]) and torch.equal(c, cp[..., :d]) and torch.equal(u[2], v[2][..., :d])
 
 
