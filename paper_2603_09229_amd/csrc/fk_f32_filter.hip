@@ -188,9 +188,9 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
 // double-buffered LDS stage of eight chunks that is filled by direct copies; a lane holds 16
 // centroid rows of one point.  The head product and the two small products have accumulators of
 // their own, which keeps the rounding of the small ones small and gives two independent chains.
-// Waves per SIMD that the registers are held to: what the kernel has without reading ahead.
+// Waves per SIMD that the registers are held to: what the kernel has without reading ahead (none of these spills).
 constexpr int filter_occupancy(int dch, int waves) {
-    return waves == 8 || dch <= 3 || dch == 7 ? 1 : dch <= 6 ? 4 : dch <= 12 ? 3 : dch <= 16 ? 2 : 1;
+    return waves == 8 || dch <= 3 || dch == 7 || dch == 12 ? 1 : dch <= 6 ? 4 : dch <= 10 ? 3 : dch <= 16 ? 2 : 1;
 }
 
 template <int DCH, int WAVES>
@@ -206,11 +206,14 @@ __global__ __launch_bounds__(WAVES * 64, filter_occupancy(DCH, WAVES)) void assi
     static_assert(SC * SPT == DCH, "whole chunks per stage");
     // Four waves: two objects, and code for each, since with one array every operand read waits for the copy in
     // flight into the other half; and the operands of a chunk are read while the one before is multiplied (a wave alone on
-    // its SIMD otherwise waits as long for LDS as it multiplies).  Sweep, us: 50000 points, d = 512, K = 1000 225 -> 196; 5000,
-    // d = 333, K = 5000 393 -> 337; 300000, d = 96, K = 400 81.4 -> 80.0 (78.0 of 79.5 in a fit); 1317, d = 512, K = 293 44.9
-    // -> 40.5.  Eight waves have no registers left for either (2^20 points, d = 128, K = 64 127 us, 162 with two objects, 180
-    // with both), nor have three chunks at their five waves a SIMD (58.1, 59.0) and seven at four (93, 108).
-    constexpr bool kApart = WAVES == 4 && DCH != 3 && DCH != 7;
+    // its SIMD otherwise waits as long for LDS as it multiplies).  Sweep, us, medians of 300 launches: 50000 points, d = 512,
+    // K = 1000 251 -> 227; 5000, d = 333, K = 5000 393 -> 335; 300000, d = 96, K = 400 99.3 -> 97.8; 1317, d = 512, K = 293
+    // 43.9 -> 39.7.  Eight waves have no registers left for either (2^20 points, d = 128, K = 64 127 us, 162 with two objects,
+    // 180 with both), nor have three chunks at their five waves a SIMD (58.1, 59.0), seven at four (93, 108) and twelve at three:
+    // with 12 registers spilled fk_assign of 8000 points, d = 192, K = 2000 91.5 -> 96.7, 600000, K = 200 204 -> 213; with two waves
+    // 87.5 and 216.  Twelve chunks as they were need the order of reads and products kept (92.0 and 204; 96.7 without).
+    constexpr bool kApart = WAVES == 4 && DCH != 3 && DCH != 7 && DCH != 12;
+    constexpr bool kInTurn = kApart || SPT > 1;
     __shared__ uintx4 even[(kApart ? 1 : 2) * kPieces * 64], other_half[kApart ? kPieces * 64 : 1];
     uintx4* const odd = kApart ? other_half : even + kPieces * 64;
 
@@ -297,7 +300,7 @@ __global__ __launch_bounds__(WAVES * 64, filter_occupancy(DCH, WAVES)) void assi
     auto products = [&](const uintx4* at, int s0, auto chunks) {
         constexpr int kChunks = decltype(chunks)::value;
         uintx4 ah, al, nh = at[lane], nl = at[64 + lane];
-        if constexpr (kApart) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);          // two LDS reads
+        if constexpr (kInTurn) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);         // two LDS reads
 #pragma unroll
         for (int s = 0; s < kChunks; ++s) {
             if (kApart || s == 0) { ah = nh; al = nl; }
@@ -308,11 +311,12 @@ __global__ __launch_bounds__(WAVES * 64, filter_occupancy(DCH, WAVES)) void assi
             } else if (!kApart && s > 0) {
                 ah = at[2 * s * 64 + lane];
                 al = at[(2 * s + 1) * 64 + lane];
+                if constexpr (kInTurn) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
             }
             small = mfma32<true>(ah, xl[s0 + s], small);
             big = mfma32<true>(ah, xh[s0 + s], big);
             small = mfma32<true>(al, xh[s0 + s], small);
-            if constexpr (kApart) __builtin_amdgcn_sched_group_barrier(0x8, 3, 0);        // three MFMAs
+            if constexpr (kInTurn) __builtin_amdgcn_sched_group_barrier(0x8, 3, 0);       // three MFMAs
         }
     };
     auto fold = [&](const uintx4* bias, int tile) {
@@ -357,8 +361,13 @@ __global__ __launch_bounds__(WAVES * 64, filter_occupancy(DCH, WAVES)) void assi
             }
         }
     } else {
-        static_assert(kApart || SPT == 1, "whole tiles");
-        for (int st = 0; st < nst; ++st) sweep(st, 0, even + (st & 1) * kPieces * 64, even + ((st & 1) ^ 1) * kPieces * 64);
+        for (int st0 = 0; st0 < nst; st0 += SPT) {
+#pragma unroll
+            for (int part = 0; part < SPT; ++part) {
+                const int half = (SPT > 1 ? part : st0) & 1;
+                sweep(st0 + part, part, even + half * kPieces * 64, even + (half ^ 1) * kPieces * 64);
+            }
+        }
     }
 
     // the two lanes of a point meet

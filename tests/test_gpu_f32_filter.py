@@ -79,6 +79,16 @@ def test_filter_gives_the_direct_answer_for_many_points(both, kind, B, N, d, K):
     assert ((m1 - m0).abs() <= d * 2.0 ** -23 * m0 + 1e-37).all()
 
 
+@pytest.mark.parametrize("d", [7, 16, 32, 48, 61, 80, 96, 112, 128, 129, 160, 161, 192, 224, 256, 257, 320, 384, 448, 512])
+@pytest.mark.parametrize("K", [1, 32, 33, 65, 300])
+def test_every_number_of_chunks_with_few_and_many_tiles(both, d, K):
+    """One stage, an odd and an even number of them, whole and half tiles per stage."""
+    for kind in ("mixture", "whole"):
+        (a1, m1), (a0, m0) = both(*_data(kind, 1, 777, d, K, seed=d + K))
+        assert torch.equal(a1, a0)
+        assert ((m1 - m0).abs() <= d * 2.0 ** -23 * m0 + 1e-37).all()
+
+
 @pytest.mark.parametrize("N,d,K", [(3001, 64, 100), (1000, 96, 257), (700, 256, 97), (263000, 24, 40)])
 @pytest.mark.parametrize("bad", [float("nan"), float("inf"), -float("inf")])
 def test_what_is_not_finite_is_answered_as_by_the_direct_kernels(both, N, d, K, bad):
