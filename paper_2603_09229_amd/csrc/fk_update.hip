@@ -353,7 +353,15 @@ __global__ __launch_bounds__(WAVES * 64) void gather_update_kernel(
     __shared__ int left[WAVES], cred[WAVES];
     const int d = to.d, K = to.K, len = RAGGED ? to.row_len : d;
     const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int k = blockIdx.x / G, part = blockIdx.x - k * G;
+    // Workgroups go to the eight XCDs in turn.  With a multiple of eight of them in an instance a cluster that is large in all
+    // instances would be added by one XCD alone, so the clusters change places from instance to instance (from every 8 / apart
+    // to the next).  The middle one with all points, us, sorted / in place / moved: 50 instances of 4000 fp32 points, d = 64, K = 8
+    // 23 / 44 / 25; 32 x 8000, d = 128, K = 8 32 / 54 / 29; 128 x 1000 fp32, d = 256, K = 4 35 / 56 / 28; 4 x 4000 fp32, d = 256, K = 60
+    // 26 / 28 / 23.  Odd numbers spread by themselves, and moving cost 100 x 4000 fp32, d = 128, K = 3 36 -> 53.
+    const int turn = blockIdx.x / G, part = blockIdx.x - turn * G;
+    const int apart = min((int)gridDim.x & -(int)gridDim.x, 8);
+    int k = turn;
+    if (apart > 1 && b * apart > 7) k = (int)((uint32_t)(turn + (b * apart >> 3)) % (uint32_t)K);
     const int64_t share = (N + G - 1) / G;
     const int lo = (int)min(N, part * share), hi = (int)min(N, lo + share);
     keys += (size_t)b * N;

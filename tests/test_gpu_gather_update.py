@@ -168,3 +168,28 @@ def test_as_many_parts_as_the_workspace_has_room_for(N, d, K, dtype):
     got = fk.fk_update(X, label, C0, ws=ws[:room])
     assert all(torch.equal(a, b) for a, b in zip(got, want))                      # sums of small whole numbers are exact
     assert bool((ws[room:] == 0x55).all())
+
+
+@pytest.mark.parametrize("B,N,d,K,parts", [
+    # workgroups per instance odd, even, a multiple of four and of eight; more turns than clusters
+    (41, 300, 8, 3, 1), (23, 270, 24, 10, 1), (70, 300, 16, 4, 1), (19, 513, 12, 8, 1), (9, 1000, 32, 12, 2), (33, 260, 8, 1, 8), (5, 700, 100, 24, 3), (300, 64, 8, 16, 1),
+])
+def test_every_cluster_of_every_instance_has_its_turn(B, N, d, K, parts):
+    """Clusters change places among the workgroups from instance to instance.  Sums of small whole numbers are exact."""
+    g = torch.Generator(device=DEV).manual_seed(B + N)
+    X = torch.randint(-3, 4, (B, N, d), generator=g, device=DEV)
+    label = (K * torch.rand((B, N), generator=g, device=DEV) ** 3).int()
+    at = (label.long() + K * torch.arange(B, device=DEV)[:, None]).view(-1).cpu()
+    total = torch.zeros((B * K, d), dtype=torch.int64).index_add_(0, at, X.view(-1, d).cpu())
+    n = torch.bincount(at, minlength=B * K)
+    C0 = torch.randn((B, K, d), generator=g, device=DEV)
+    want = torch.where(n[:, None] > 0, (total.double() / n.clamp(min=1)[:, None]).float(), C0.view(-1, d).cpu())
+    try:
+        fk.fk_set_option("fused_update", 0)
+        fk.fk_set_option("gather_update", parts)
+        for dtype in (torch.float16, torch.float32):
+            C, _, m = fk.fk_update(X.to(dtype), label, C0)
+            assert torch.equal(m.view(-1).cpu().long(), n) and torch.equal(C.view(-1, d).cpu(), want)
+    finally:
+        fk.fk_set_option("gather_update", -1)
+        fk.fk_set_option("fused_update", -1)
