@@ -224,16 +224,18 @@ __global__ __launch_bounds__(256) void sort_binscan_kernel(int32_t* __restrict__
 // Stable scatter.  Waves walk their keys in input order, so equal keys keep their order.
 //   vals_in == NULL: values are the key positions (first pass).
 //   kScans: see sort_scatter_scans; rounds is 1.  An instantiation of its own: the code costs the others 2%
-//   when it is only skipped.  Both of eight waves are held to 80 registers (three workgroups on a compute unit: with two,
-//   64 instances of 24 workgroups, 64 bins took 44.4 us instead of 37.8).
+//   when it is only skipped.  Both of eight waves are held to 80 registers, of which they spill 4 and 2 (three workgroups on
+//   a compute unit; fk_sort_inverse, us, held / not: 2^23 keys, K = 4096 110 / 121, 2^22, K = 32 25.7 / 27.4, 2^25, K = 300 302 / 306;
+//   300000, K = 400 15.8 / 15.2, 70001, K = 333 13.3 / 12.9, where there are few workgroups).  That of four is not: held to three
+//   waves per SIMD 2^20 keys, K = 2000 took 39.4 instead of 39.1, 100000 23.3 instead of 22.7.
 // Bound by its chain of latencies: keys and tables, ranks, two scans, LDS, stores.  300000 keys, K = 400 11.7 -> 9.1
-// us, 2^20, K = 1024 15.5 -> 13.0, 2^23 in two passes of 64 bins 84.7 -> 73.6, since the tables are requested with the
+// us, 2^20, K = 1024 15.5 -> 13.0, 2^23 in two passes of 64 bins 84.7 -> 73.6, all together, since the tables are requested with the
 // keys, the ranks found bit by bit for all batches at once (2.9 us of the first), the scans in register moves, both
 // tables of the first workgroup in one scan, and each loop over LDS reads before it writes.
 //   keys_out may be NULL.  seg_off / item_off are written by workgroup 0 when non-NULL
 //   (single-pass sort: bins are cluster ids, so the bin offsets are the segment table).
 template <int kSortWaves, bool kScans>
-__global__ __launch_bounds__(kSortWaves * 64, kSortWaves == 8 ? 6 : 3) void sort_scatter_kernel(
+__global__ __launch_bounds__(kSortWaves * 64, kSortWaves == 8 ? 6 : 1) void sort_scatter_kernel(
     const int32_t* __restrict__ keys, const int32_t* __restrict__ vals_in,
     const int32_t* __restrict__ H, const int32_t* __restrict__ tot,
     int32_t* __restrict__ vals_out, int32_t* __restrict__ keys_out,
