@@ -258,9 +258,11 @@ fk_status fk_standard_update(const void* X, const int32_t* assign, const float* 
  * cluster's row of the table of sums owned by one wave): at this size the iteration is bound by
  * its number of launches.  Same assignments and counts as the general path, sums up to fp32
  * summation order, bit-reproducible; fk_update alone sorts or gathers, as above.
- * Small instances (B*K*N <= 2^23 and a few MiB of points; any type): an update that none of the passes
- * above takes is one launch without a sort, or two: every workgroup reads all assignments and adds the
- * rows of one cluster.  Same counts as the sorted path, sums up to fp32 summation order, bit-reproducible.
+ * Small instances (any type; at most 32 MiB of rows, counted in multiples of 8 features, and 2^18 points in an
+ * instance, which is cut into parts of 2 MiB or 2^14 points, 512 KiB where B*K < 128; B*K*N <= 2^23 and
+ * B*K*parts <= 1024): an update that none of the passes above takes is one launch without a sort, or two:
+ * every workgroup reads all assignments of its part and adds the rows of one cluster.  Same counts as the
+ * sorted path, sums up to fp32 summation order, bit-reproducible.
  * All of these passes need room for one partial table per workgroup, which fk_workspace_bytes
  * includes (the last has one for every part of an instance, and makes do with fewer parts where ws is
  * as large as sorting needs; means then differ in summation order).

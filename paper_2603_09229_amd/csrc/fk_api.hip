@@ -81,7 +81,8 @@ void set_gather_update_option(int v) { g_gather_option.store(v, std::memory_orde
 // if all points are in one cluster, and with few clusters, which leave the chip idle, parts of 512 KiB (36850 fp32 points, d = 77,
 // K = 17: eight parts 11.7, Zipf sizes 15.9, all in one cluster 28.5; sixteen 10.8, 12.3, 21.0; sorted 20.2, 22.9, 25.4).
 // All points in one cluster: 16384, d = 128, K = 480 37 / 27; 8000 fp32, d = 512, K = 100 48 / 27; 250000 fp32, d = 32, K = 20 30 / 29;
-// 5 x 2000, d = 200, K = 200 20.8 / 21.9; 3 x 4000 fp32, d = 180, K = 120 25.5 / 27.2.
+// 3 x 4000 fp32, d = 180, K = 120 25 / 24; 3740, d = 139, K = 11 19.8 / 20.6; slower still where every one of many instances has
+// one cluster: 16 x 8590 fp32, d = 111, K = 12 32 / 40, 16 x 16000, d = 64, K = 10 25 / 31 (Zipf sizes 31 / 24, 25 / 18).
 int choose_gather_parts(int B, int64_t N, int d, int K, fk_dtype t) {
     const int v = g_gather_option.load(std::memory_order_relaxed);
     const int64_t bytes = N * d * (int64_t)elem_size(t), clusters = (int64_t)B * K;
