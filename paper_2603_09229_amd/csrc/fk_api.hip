@@ -372,13 +372,13 @@ static fk_status check_common(const char* fn, int B, int64_t N, int d, int K, fk
 // few clusters: one streaming pass over X builds per-workgroup tables of sums (computing the
 // assignment on the way when asked to), then the usual merge/normalise
 static fk_status run_stream_update(const Geometry& g, const Workspace& w, const void* X,
-                                   int32_t* assign, bool compute_assign, const FinalizeArgs& fa,
+                                   int32_t* assign, bool compute_assign, bool keep_assign, const FinalizeArgs& fa,
                                    hipStream_t s) {
     int G = 0;
     const int rep = timer_repeat();
     for (int r = 0; r < rep; ++r) {
         if (g.fused_grid_cap > 0)
-            FK_TRY(launch_stream_update(g, w, X, assign, compute_assign, &G, s));
+            FK_TRY(launch_stream_update(g, w, X, assign, compute_assign, keep_assign, &G, s));
         else if (g.table_grid_cap > 0)
             FK_TRY(launch_table_update(g, w, X, assign, &G, s));    // always computes the assignment
         else
@@ -403,7 +403,7 @@ static bool rows_are_padded(const Geometry& g) {
 // instances without the sort
 static fk_status run_update(const Geometry& g, const Workspace& w, const void* X,
                             const int32_t* assign, const FinalizeArgs& fa, hipStream_t s) {
-    if (fused_update_enabled(g)) return run_stream_update(g, w, X, (int32_t*)assign, false, fa, s);
+    if (fused_update_enabled(g)) return run_stream_update(g, w, X, (int32_t*)assign, false, false, fa, s);
     const int rep = timer_repeat();
     if (g.gather_parts > 0) {
         for (int r = 0; r < rep; ++r) FK_TRY(launch_gather_update(g, w, X, assign, fa, s));
@@ -863,7 +863,7 @@ fk_status fk_lloyd_iter(const void* X, float* C_f32, void* C_lp, int32_t* assign
         fa.accumulate = false;
         fa.normalise = true;
         if (fused) {
-            FK_TRY(run_stream_update(g, w, X, assign, true, fa, s));
+            FK_TRY(run_stream_update(g, w, X, assign, true, it + 1 == iters, fa, s));
         } else {
             FK_TRY(run_update(g, w, X, assign, fa, s));
         }

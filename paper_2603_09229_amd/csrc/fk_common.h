@@ -234,11 +234,11 @@ int choose_gather_parts(int B, int64_t N, int d, int K, fk_dtype t);
 void set_gather_update_option(int v);      // -1 = by shape, 0 = never, 1..64 = always, in that many parts
 
 // Few clusters: stream X once, add every 32-point batch into per-workgroup K x d tables with a
-// one-hot MFMA (no sort, no gather); with compute_assign the assignment is computed (and
-// written) in the same pass, otherwise read.  Leaves w.partial / w.wg_counts ready for
+// one-hot MFMA (no sort, no gather); with compute_assign the assignment is computed (and, where
+// keep_assign says so, written) in the same pass, otherwise read.  Leaves w.partial / w.wg_counts ready for
 // launch_finalize with max_items = K * (*grid_out) and wg_per_cluster = *grid_out.
 fk_status launch_stream_update(const Geometry& g, const Workspace& w, const void* X,
-                               int32_t* assign, bool compute_assign, int* grid_out,
+                               int32_t* assign, bool compute_assign, bool keep_assign, int* grid_out,
                                hipStream_t s);
 inline bool fused_update_enabled(const Geometry& g) { return g.fused_grid_cap > 0 && g.one_pass; }
 void set_fused_update_option(int v);       // 0 = never, otherwise whenever the shape allows
