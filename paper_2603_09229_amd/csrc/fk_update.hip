@@ -76,7 +76,8 @@ __device__ __forceinline__ void add_in_pairs(const uintx4 (&v)[U], float (&acc)[
 // wave order through LDS.
 // RAGGED: rows whose length is no multiple of 8, read as they are stored (skipped at run time, that code costs
 // the others 3%: 342180 points, d = 512, K = 34: 68.3 -> 70.4 us).
-template <int EPL, bool BF, int WPI, bool RAGGED>
+// ONCE: loads that ask for no place in the caches, see reads_once.
+template <int EPL, bool BF, int WPI, bool RAGGED, bool ONCE>
 __global__ __launch_bounds__(256) void segment_reduce_kernel(
     const void* __restrict__ Xv, const int32_t* __restrict__ sorted_idx,
     const int32_t* __restrict__ seg_off, const int32_t* __restrict__ item_off,
@@ -130,7 +131,8 @@ __global__ __launch_bounds__(256) void segment_reduce_kernel(
                     v[u] = uintx4{0u, 0u, 0u, 0u};
                     if (ok[u]) {
                         const char* at = mine + (int64_t)idx * row_bytes;
-                        v[u] = RAGGED ? (uintx4)*(const uintx4_any*)at : *(const uintx4*)at;
+                        if constexpr (ONCE) v[u] = __builtin_nontemporal_load((const uintx4*)at);
+                        else v[u] = RAGGED ? (uintx4)*(const uintx4_any*)at : *(const uintx4*)at;
                     }
                 }
                 add_in_pairs<EPL, BF>(v, acc);
@@ -541,6 +543,17 @@ static float item_balance(const Geometry& g) {
     return (float)merge_threads(g) / (g.t == FK_F32 ? 64.f : 128.f) / (float)g.waves_per_item;
 }
 
+// Whether the reduction's loads carry the non-temporal hint: X larger than the last-level cache and rows of
+// at least a cache line.  What the caches hold of a smaller X the next pass over it finds there, and a line that two rows share would be
+// fetched twice.  us without and with the hint.  fk_update, fp16, K = 500, d = 128: 1.2 million points 84.0 81.3, 1.6 million 115.3 102.7;
+// 2^23, K = 4096 535 493 (the reduction 406 361); fp32 4 million, d = 128, K = 1000 434 398.  Rows of 192 bytes, 4 million 225 220; of 96
+// 324 331; of 64 241 250.  A smaller X, fits: 2^20, d = 128, K = 1024 (256 MiB) 1249 1280; fp32 300000, d = 96, K = 400 388 398;
+// ragged rows: 12 million, d = 17, K = 600 403 438.
+static bool reads_once(const Geometry& g) {
+    const int64_t row = (int64_t)g.d * elem_size(g.t);
+    return g.len == g.d && row >= 128 && (int64_t)g.B * g.N * row > device_info().llc_bytes;
+}
+
 fk_status launch_segment_reduce(const Geometry& g, const Workspace& w, const void* X,
                                 const int32_t* sorted_idx, const int32_t* seg_off,
                                 const int32_t* item_off, hipStream_t s) {
@@ -549,10 +562,12 @@ fk_status launch_segment_reduce(const Geometry& g, const Workspace& w, const voi
     if (lpr_log2 > 6) lpr_log2 = 6;          // wider rows go column block by column block
     const bool wide = g.waves_per_item == 4;
     dim3 grid((unsigned)(wide ? g.max_items : cdiv(g.max_items, 4)), g.B), block(256);
+    const bool once = reads_once(g);
+#define FK_REDUCE_W(EPL, BF, RAGGED, ONCE) (wide ? segment_reduce_kernel<EPL, BF, 4, RAGGED, ONCE> : segment_reduce_kernel<EPL, BF, 1, RAGGED, ONCE>)
 #define FK_REDUCE(EPL, BF)                                                                        \
     do {                                                                                          \
-        auto kern = g.len == g.d ? (wide ? segment_reduce_kernel<EPL, BF, 4, false> : segment_reduce_kernel<EPL, BF, 1, false>)  \
-                                 : (wide ? segment_reduce_kernel<EPL, BF, 4, true> : segment_reduce_kernel<EPL, BF, 1, true>);   \
+        auto kern = g.len != g.d ? FK_REDUCE_W(EPL, BF, true, false)                              \
+                  : once ? FK_REDUCE_W(EPL, BF, false, true) : FK_REDUCE_W(EPL, BF, false, false);  \
         hipLaunchKernelGGL(kern, grid, block, 0, s, X, sorted_idx, seg_off, item_off, w.partial, g.N, g.d, g.K,     \
                            g.rows_per_item, g.max_items, lpr_log2, g.len, item_balance(g));                               \
     } while (0)
@@ -560,6 +575,7 @@ fk_status launch_segment_reduce(const Geometry& g, const Workspace& w, const voi
     else if (g.t == FK_F16) FK_REDUCE(8, false);
     else FK_REDUCE(8, true);
 #undef FK_REDUCE
+#undef FK_REDUCE_W
     FK_HIP(hipGetLastError());
     return FK_OK;
 }
