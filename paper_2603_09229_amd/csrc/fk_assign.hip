@@ -492,6 +492,10 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_wide_kernel(
 // fragments are then read back from LDS.  The 16-byte pieces of a row are stored XOR-swizzled
 // by the row number so that those reads are free of bank conflicts.  Same scores, packing and
 // tie rules as the sweeping kernel above.
+// Copies and stores ask for no place in the caches, and with swizzled rows no more than two workgroups a unit run: 8430998 points,
+// d = 64, K = 12 204 us without either, 189 with such copies, 186 with two workgroups, 178 with the stores too (6.1 TB/s), 243 with
+// one workgroup; 2^24, d = 64, K = 64, distances 440 -> 428; 6 million, d = 56, K = 20 130 -> 117.  (The sweeping kernels' operand loads, 32 bytes of a line at a time, lose by the hint: 4 million, d = 128,
+// K = 200 317 -> 384.)
 template <bool BF, int DCH, int WAVES, int KT>
 __global__ __launch_bounds__(WAVES * 64) void assign_mfma_stream_kernel(
     const uint16_t* __restrict__ X, const uintx4* __restrict__ c_frag,
@@ -542,7 +546,7 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_stream_kernel(
             const int64_t point = min(batch * kRows + row, N - 1);
             __builtin_amdgcn_global_load_lds(
                 (const __attribute__((address_space(1))) void*)(X + (size_t)point * d + piece * 8),
-                (__attribute__((address_space(3))) void*)(buf + q * 64), 16, 0, 0);
+                (__attribute__((address_space(3))) void*)(buf + q * 64), 16, 0, 2);      // (2: the non-temporal hint)
         }
     };
 
@@ -633,8 +637,8 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_stream_kernel(
                 xnorm += __shfl_xor(xnorm, 32);
             }
             if (h == 0 && point < N) {
-                assign[point] = k;
-                if (min_dist) min_dist[point] = fmaxf(0.f, xnorm - 2.f * m);
+                __builtin_nontemporal_store(k, assign + point);
+                if (min_dist) __builtin_nontemporal_store(fmaxf(0.f, xnorm - 2.f * m), min_dist + point);
             }
         }
         // the next batch must have landed before it is read (wave-private buffers: no barrier)
@@ -1222,8 +1226,7 @@ static fk_status launch_mfma(const Geometry& g, const void* X, const void* frag,
     if (const FewForm few = choose_few(g, false); few != kFewNone)
         return launch_few<BF, DCH>(g, few, X, frag, bias, assign, min_dist, s);
     if (g.ktiles <= ST && assign_uses_stream_kernel(g)) {
-        // persistent waves: as many workgroups as fit the chip, each wave striding over
-        // 32-point batches
+        // persistent waves: two workgroups a compute unit, or as many as fit, each wave striding over 32-point batches
         constexpr int WAVES = 4;
         const size_t lds = (size_t)(WAVES * 3 * DCH * 64) * 16;
         const bool one_tile = g.ktiles == 1;
@@ -1239,7 +1242,8 @@ static fk_status launch_mfma(const Geometry& g, const void* X, const void* frag,
                 q = 1;
             per_cu_cache[one_tile].set(q);
         }
-        const int per_cu = per_cu_cache[one_tile].get();
+        // (rows that are not stored swizzled need the waves: 2 x 4 million, d = 40, K = 30 127 us, with two a unit 140)
+        const int per_cu = std::min(per_cu_cache[one_tile].get(), (g.d & (g.d - 1)) == 0 ? 2 : 8);
         const int64_t nbatches = cdiv(g.N, 32);
         int64_t wgs = (int64_t)device_cu_count() * per_cu;
         if (wgs > cdiv(nbatches, WAVES)) wgs = cdiv(nbatches, WAVES);
