@@ -829,7 +829,9 @@ __global__ __launch_bounds__(WAVES * 64) void assign_mfma_few_kernel(
 
 // ------------------------------------------------------------------------------------
 // fp32: one point per thread, features in registers, centroid tiles of TK rows in LDS,
-// D_ik by direct differences in fp32; ascending k with strict '<'.
+// D_ik by direct differences in fp32, ascending features, one fused multiply-add each (written out, here and below: of
+// D += e0 * e0; D += e1 * e1 the compiler rounds the second square and fuses the first, and two centroids at nearly the same distance are
+// then told apart otherwise than where the same sum is written as a chain); ascending k with strict '<'.
 // RAGGED (here and below): rows whose length is no multiple of 8, read as they are stored.
 template <int DMAX, int TK, int THREADS, bool RAGGED>
 __global__ __launch_bounds__(THREADS) void assign_f32_kernel(
@@ -871,7 +873,7 @@ __global__ __launch_bounds__(THREADS) void assign_f32_kernel(
                 const floatx4 c = *(const floatx4*)&sc[r][j];
                 const float e0 = x[j] - c[0], e1 = x[j + 1] - c[1];
                 const float e2 = x[j + 2] - c[2], e3 = x[j + 3] - c[3];
-                D += e0 * e0; D += e1 * e1; D += e2 * e2; D += e3 * e3;
+                D = fmaf(e3, e3, fmaf(e2, e2, fmaf(e1, e1, fmaf(e0, e0, D))));
             }
             if (D < m) { m = D; a = k0 + r; }
         }
@@ -931,8 +933,8 @@ __global__ __launch_bounds__(256) void assign_f32_wide_kernel(
                 const float e0 = xa[0] - ca[0], e1 = xa[1] - ca[1], e2 = xa[2] - ca[2], e3 = xa[3] - ca[3];
                 const float e4 = xb[0] - cb[0], e5 = xb[1] - cb[1], e6 = xb[2] - cb[2], e7 = xb[3] - cb[3];
                 float t = D[r];
-                t += e0 * e0; t += e1 * e1; t += e2 * e2; t += e3 * e3;
-                t += e4 * e4; t += e5 * e5; t += e6 * e6; t += e7 * e7;
+                t = fmaf(e3, e3, fmaf(e2, e2, fmaf(e1, e1, fmaf(e0, e0, t))));
+                t = fmaf(e7, e7, fmaf(e6, e6, fmaf(e5, e5, fmaf(e4, e4, t))));
                 D[r] = t;
             }
         }
@@ -996,7 +998,7 @@ __global__ __launch_bounds__(256) void assign_f32_split_kernel(
                 const floatx4 c = *(const floatx4*)&sc[r][j];
                 const float e0 = x[j] - c[0], e1 = x[j + 1] - c[1];
                 const float e2 = x[j + 2] - c[2], e3 = x[j + 3] - c[3];
-                D += e0 * e0; D += e1 * e1; D += e2 * e2; D += e3 * e3;
+                D = fmaf(e3, e3, fmaf(e2, e2, fmaf(e1, e1, fmaf(e0, e0, D))));
             }
             if (D < m) { m = D; a = k0 + r; }
         }
