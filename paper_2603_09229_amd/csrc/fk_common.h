@@ -154,7 +154,7 @@ fk_status launch_assign(const Geometry& g, const void* X, const void* C_or_frag,
 fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* X, const float* C,
                             int32_t* assign, float* min_dist, hipStream_t s);
 bool f32_filter_enabled(const Geometry& g);
-// Workgroups of 256 threads of its distance pass, `lanes` threads a point.  A launch dimension holds fewer
+// Half workgroups (of 256 threads) that measure distances, `lanes` threads a point.  A launch dimension holds fewer
 // than 2^32 threads, which one point per group of 16 lanes reaches at 2^28 points.
 inline int64_t f32_distance_blocks(int64_t N, int lanes) {
     const int64_t groups = cdiv(N, 256 / lanes), most = (int64_t)1 << 20;

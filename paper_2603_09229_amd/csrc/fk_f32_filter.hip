@@ -74,14 +74,17 @@ __device__ __forceinline__ void split8(const float (&v)[8], uintx4& hi, uintx4& 
 // c2 = inf, so that no point is ever certain of it; rows past K one that never wins.  Rows with a NaN
 // or an infinity get that too -- no distance to them is below infinity, where the direct form's minimum
 // starts -- and stay out of the mean: one such centroid would leave every point open.
-// Tile 0 also leaves the shift m and clears the instance's list length.
-// A few microseconds of dependent loads: the rows of the mean are asked for eight at a time and
-// the own rows before the mean is needed.
+// Tile 0 also leaves the shift m and clears the lengths of the instance's lists.
+// A few microseconds of dependent loads, and of instructions that no cache holds yet: the rows of the mean are asked for eight at a
+// time and the own rows before the mean is needed, and nothing is in the code that the shape has no use for (kGroups, RAGGED; d = 128, K = 211
+// 7.2 -> 5.5 us; with all 32 rows of the mean asked for at once 7.6).
 constexpr int kLayoutThreads = 512;
 
+template <int kGroups, bool RAGGED>
 __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
     const float* __restrict__ C, uintx4* __restrict__ frag, float* __restrict__ c2,
-    float* __restrict__ shift, int32_t* __restrict__ list_len, int d, int len, int K, int ktiles, int dch) {
+    float* __restrict__ shift, int32_t* __restrict__ list_len, int32_t* __restrict__ pair_len, int d, int row_len, int K, int ktiles, int dch) {
+    const int len = RAGGED ? row_len : d;
     __shared__ float m[512];
     __shared__ double part[32][65];
     __shared__ int fits[32], odd_row[32];
@@ -90,7 +93,6 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
     C += (size_t)b * K * len;
     frag += ((size_t)b * ktiles + kt) * (2 * dch + 1) * 64;
     // this thread's groups of eight features: group g = tid + i * threads is lane g % 64 of chunk g / 64
-    constexpr int kGroups = 64 * 32 / kLayoutThreads;
     float own[kGroups][8];
 #pragma unroll
     for (int i = 0; i < kGroups; ++i) {
@@ -99,7 +101,7 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
 #pragma unroll
         for (int e = 0; e < 8; ++e) own[i][e] = 0.f;
         if (g < 64 * dch && k < K && j0 < d) {
-            const floatx4 u = row_piece32(C + (size_t)k * len, j0, len), v = row_piece32(C + (size_t)k * len, j0 + 4, len);
+            const floatx4 u = row_piece32<RAGGED>(C + (size_t)k * len, j0, len), v = row_piece32<RAGGED>(C + (size_t)k * len, j0 + 4, len);
 #pragma unroll
             for (int e = 0; e < 4; ++e) { own[i][e] = u[e]; own[i][e + 4] = v[e]; }
         }
@@ -107,20 +109,22 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
     const int rows = min(K, 32);
     if (tid < width) {
         float s = 0.f;
-        if (tid < len)
+        if (tid < len) {
+#pragma unroll 1
             for (int i0 = 0; i0 < rows; i0 += 8) {
                 float v[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = C[(size_t)((int64_t)min(i0 + i, rows - 1) * K / rows) * len + tid];
+                for (int i = 0; i < 8; ++i) v[i] = C[(uint32_t)min(i0 + i, rows - 1) * (uint32_t)K / (uint32_t)rows * (uint32_t)len + tid];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) s += i0 + i < rows && fabsf(v[i]) < INFINITY ? v[i] : 0.f;
             }
+        }
         s /= (float)rows;
         m[tid] = s;
         if (kt == 0) shift[(size_t)b * width + tid] = s;
     }
     if (tid < 32) odd_row[tid] = 0;
-    if (kt == 0 && tid == 0) list_len[b] = 0;
+    if (kt == 0 && tid == 0) { list_len[b] = 0; pair_len[b] = 0; }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kGroups; ++i) {
@@ -140,31 +144,38 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
         }
     }
     __syncthreads();
-    if (tid < 64) {
-        const int r = tid & 31, h = tid >> 5, k = kt * 32 + r;
+    {
+        // sixteen lanes a row
+        const int r = tid >> 4, c = tid & 15, k = kt * 32 + r;
         double n2 = 0.0;
-        for (int q = 0; q < 2 * dch; ++q) n2 += part[r][q];
-        const bool never = k >= K || odd_row[r] != 0;
-        const bool fine = !never && n2 < 1e38;               // false for NaN too
-        uint16_t p[3] = {kNever, 0, 0};
-        if (fine) {
-            double left = (-0.5 + (double)filter_kappa(width)) * n2;
 #pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                p[q] = float_to_lp((float)left, true);
-                left -= (double)lp_to_float(p[q], true);
+        for (int q = 0; q < 4; ++q)
+            if (c + 16 * q < 2 * dch) n2 += part[r][c + 16 * q];
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
+        if (c < 2) {
+            const bool never = k >= K || odd_row[r] != 0;
+            const bool fine = !never && n2 < 1e38;           // false for NaN too
+            uint16_t p[3] = {kNever, 0, 0};
+            if (fine) {
+                double left = (-0.5 + (double)filter_kappa(width)) * n2;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    p[q] = float_to_lp((float)left, true);
+                    left -= (double)lp_to_float(p[q], true);
+                }
+            } else if (!never) {
+                p[0] = kAlways;
             }
-        } else if (!never) {
-            p[0] = kAlways;
+            uintx4 v = {0u, 0u, 0u, 0u};
+            if (c == 0) {
+                v[0] = (uint32_t)p[0] | ((uint32_t)p[1] << 16);
+                v[1] = p[2];
+                fits[r] = fine;
+                c2[((size_t)b * ktiles + kt) * 32 + r] = fine ? (float)(n2 * 1.000001) : never ? 0.f : INFINITY;
+            }
+            frag[2 * dch * 64 + c * 32 + r] = v;
         }
-        uintx4 v = {0u, 0u, 0u, 0u};
-        if (h == 0) {
-            v[0] = (uint32_t)p[0] | ((uint32_t)p[1] << 16);
-            v[1] = p[2];
-            fits[r] = fine;
-            c2[((size_t)b * ktiles + kt) * 32 + r] = fine ? (float)(n2 * 1.000001) : never ? 0.f : INFINITY;
-        }
-        frag[2 * dch * 64 + tid] = v;
     }
     __syncthreads();
 #pragma unroll
@@ -183,6 +194,86 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
     }
 }
 
+// What a lane keeps of its scores: the best and the second best (low 4 bits = 15 - slot) with their tiles and, where
+// THREE, the value of the third, so that a point that is open between two centroids only need not be measured against
+// all of them.
+// (Rows of more than 96 features: narrower ones are measured in full sooner than the sweep takes one more operation a score, 300000
+// points, d = 96, K = 400 399 us a fit for 386, 598071, d = 32, K = 75 312 for 287.)
+constexpr bool filter_keeps_three(int dch) { return dch >= 7; }
+
+template <bool THREE>
+struct TopScores {
+    float m1, m2, m3;
+    int t1, t2;                                              // tiles; after settle(): centroids
+
+    __device__ __forceinline__ void clear() { m1 = m2 = m3 = -INFINITY; t1 = t2 = 0; }
+    __device__ __forceinline__ void fold(const floatx16& big, const floatx16& small, int tile) {
+        const float before1 = m1, before2 = m2;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const float u = __uint_as_float((__float_as_uint(big[i] + small[i]) & 0xFFFFFFF0u) | (uint32_t)(15 - i));
+            if constexpr (THREE) m3 = __builtin_amdgcn_fmed3f(m2, m3, u);
+            m2 = __builtin_amdgcn_fmed3f(m1, m2, u);
+            m1 = __builtin_fmaxf(m1, u);
+        }
+        // (equal scores may be given the wrong tile: the third is then as good as the second, and the point measured in full)
+        if constexpr (THREE) t2 = m2 == before2 ? t2 : m2 == before1 && m1 != before1 ? t1 : tile;
+        t1 = m1 != before1 ? tile : t1;
+    }
+    __device__ __forceinline__ static int centroid(float m, int tile, int h) {
+        const int i = 15 - (int)(__float_as_uint(m) & 15u);
+        return tile * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
+    }
+    __device__ __forceinline__ void settle(int h) {
+        t1 = centroid(m1, t1, h);
+        if constexpr (THREE) t2 = centroid(m2, t2, h);
+    }
+    __device__ __forceinline__ void merge(const TopScores& o) {
+        if constexpr (THREE) m3 = __builtin_fmaxf(__builtin_fmaxf(m3, o.m3), __builtin_fmaxf(__builtin_fminf(m1, o.m2), __builtin_fminf(m2, o.m1)));
+        const bool other = o.m1 > m1;
+        const float low = other ? m1 : o.m1, next = other ? o.m2 : m2;
+        if constexpr (THREE) {
+            const int low_k = other ? t1 : o.t1, next_k = other ? o.t2 : t2;
+            t2 = low > next ? low_k : next_k;
+        }
+        m2 = __builtin_fmaxf(low, next);
+        t1 = other ? o.t1 : t1;
+        m1 = other ? o.m1 : m1;
+    }
+    __device__ __forceinline__ void merge_halves(int h) {    // the two lanes of a point meet
+        settle(h);
+        TopScores o;
+        o.clear();
+        o.m1 = __shfl_xor(m1, 32);
+        o.m2 = __shfl_xor(m2, 32);
+        o.t1 = __shfl_xor(t1, 32);
+        if constexpr (THREE) {
+            o.m3 = __shfl_xor(m3, 32);
+            o.t2 = __shfl_xor(t2, 32);
+        }
+        merge(o);
+    }
+    // 0: t1 it is; 1: t1 or t2; 2: open.  x2 = |x'|^2, c2 = |c'|^2 by centroid.
+    __device__ __forceinline__ int verdict(float x2, const float* __restrict__ c2, int width, int d, int K) {
+        t1 = min(t1, K - 1);
+        const float room = 2.02f * filter_kappa(width) * (x2 + c2[t1]);
+        // distance to the best one, from above (u_1 is s_1 + kappa |c'_1|^2 give or take room / 2)
+        const float near = fmaxf(0.f, x2 - 2.f * m1) + 3.f * room;
+        const float theta = (float)(d + 4) * 5.9604645e-08f * 1.1f * near;
+        if (m1 - m2 > room + theta + 1e-30f) return 0;
+        return THREE && m1 - m3 > room + theta + 1e-30f ? 1 : 2;
+    }
+};
+
+// Open points carry -1 where distances are wanted, whose place then holds the two centroids (see assign_f32_list_kernel).
+__device__ __forceinline__ void leave_verdict(int k1, int k2, int verdict, bool mine, int64_t point, int K, int32_t* __restrict__ assign,
+                                              int32_t* __restrict__ pair_at) {
+    if (!mine) return;
+    const int32_t both = (int32_t)((uint32_t)k1 | ((uint32_t)min(k2, K - 1) << 16));
+    if (pair_at && verdict == 1) pair_at[point] = both;
+    if (verdict == 0 || verdict == 1 || pair_at) assign[point] = verdict == 0 ? k1 : pair_at ? -1 : both;
+}
+
 // The sweep.  As in the 16-bit kernels a wave owns 32 points, whose features stay in registers as
 // B operands (heads and tails: 8 DCH registers per lane), and the centroid tiles pass through a
 // double-buffered LDS stage of eight chunks that is filled by direct copies; a lane holds 16
@@ -197,7 +288,7 @@ template <int DCH, int WAVES>
 __global__ __launch_bounds__(WAVES * 64, filter_occupancy(DCH, WAVES)) void assign_f32_filter_kernel(
     const float* __restrict__ X, const uintx4* __restrict__ frag, const float* __restrict__ c2,
     const float* __restrict__ shift, int32_t* __restrict__ assign, int32_t* __restrict__ list,
-    int32_t* __restrict__ list_len, int64_t N, int d, int len, int K, int ktiles) {
+    int32_t* __restrict__ list_len, int32_t* __restrict__ pair_len, int32_t* __restrict__ pair_at, int64_t N, int d, int len, int K, int ktiles) {
     constexpr int kTile = 2 * DCH + 1;                       // 1 KiB pieces per centroid tile
     constexpr int ST = DCH < 8 ? 8 / DCH : 1;                // tiles per stage ...
     constexpr int SPT = DCH <= 8 ? 1 : DCH <= 16 ? 2 : 4;    // ... or stages per tile
@@ -224,6 +315,7 @@ __global__ __launch_bounds__(WAVES * 64, filter_occupancy(DCH, WAVES)) void assi
     shift += (size_t)b * DCH * 16;
     assign += (size_t)b * N;
     list += (size_t)b * N;
+    if (pair_at) pair_at += (size_t)b * N;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 31, h = lane >> 5;
     const int64_t point = ((int64_t)blockIdx.x * WAVES + wave) * 32 + n;
@@ -290,8 +382,9 @@ __global__ __launch_bounds__(WAVES * 64, filter_occupancy(DCH, WAVES)) void assi
     // the ones that the bias piece is multiplied by
     const uintx4 ones = {h == 0 ? 0x3F803F80u : 0u, h == 0 ? 0x3F80u : 0u, 0u, 0u};
 
-    float m1 = -INFINITY, m2 = -INFINITY;                    // best and second best, low 4 bits = 15 - slot
-    int btile = 0;
+    constexpr bool kThree = filter_keeps_three(DCH);
+    TopScores<kThree> top;
+    top.clear();
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 
@@ -321,14 +414,7 @@ __global__ __launch_bounds__(WAVES * 64, filter_occupancy(DCH, WAVES)) void assi
     };
     auto fold = [&](const uintx4* bias, int tile) {
         big = mfma32<true>(bias[lane], ones, big);
-        const float before = m1;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const float u = __uint_as_float((__float_as_uint(big[i] + small[i]) & 0xFFFFFFF0u) | (uint32_t)(15 - i));
-            m2 = __builtin_amdgcn_fmed3f(m1, m2, u);
-            m1 = __builtin_fmaxf(m1, u);
-        }
-        btile = m1 != before ? tile : btile;
+        top.fold(big, small, tile);
     };
     // stage st, whose pieces are in `now`; the next one's land in `then` meanwhile
     auto sweep = [&](int st, int part, const uintx4* now, uintx4* then) {
@@ -370,43 +456,164 @@ __global__ __launch_bounds__(WAVES * 64, filter_occupancy(DCH, WAVES)) void assi
         }
     }
 
-    // the two lanes of a point meet
-    const int i = 15 - (int)(__float_as_uint(m1) & 15u);
-    int k = btile * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
-    const float o1 = __shfl_xor(m1, 32), o2 = __shfl_xor(m2, 32);
-    const int ok = __shfl_xor(k, 32);
+    top.merge_halves(h);
     x2 += __shfl_xor(x2, 32);
-    m2 = __builtin_fmaxf(__builtin_fmaxf(m2, o2), __builtin_fminf(m1, o1));
-    if (o1 > m1) { m1 = o1; k = ok; }
-    k = min(k, K - 1);
-    const float kappa = filter_kappa(DCH * 16);
-    const float n2 = c2[k];
-    const float room = 2.02f * kappa * (x2 + n2);
-    // distance to the best one, from above (u_1 is s_1 + kappa |c'_1|^2 give or take room / 2)
-    const float near = fmaxf(0.f, x2 - 2.f * m1) + 3.f * room;
-    const float theta = (float)(d + 4) * 5.9604645e-08f * 1.1f * near;
-    const bool certain = m1 - m2 > room + theta + 1e-30f;
+    const int verdict = top.verdict(x2, c2, DCH * 16, d, K);
     const bool mine = h == 0 && point < N;
-    if (mine && certain) assign[point] = k;
+    leave_verdict(top.t1, top.t2, verdict, mine, point, K, assign, pair_at);
     // A place on the list for the whole workgroup at once: additions to one address take 10 ns each, and
     // with many open points one per wave cost more than the sweep (2^20 points, all open: 330 us).
     // (The last stage has been read; LDS of its own would cost a workgroup per compute unit at DCH = 2.)
+    // Open points go on the list from its front, those open between two centroids from its end.
     int* opened = (int*)&even[0];
-    int* list_at = opened + WAVES;
-    const uint64_t open = __ballot(mine && !certain);
-    if (lane == 0) opened[wave] = __popcll(open);
+    int* list_at = opened + 2 * WAVES;
+    const uint64_t below = (1ull << lane) - 1ull;
+    const uint64_t open = __ballot(mine && verdict == 2), pair = kThree ? __ballot(mine && verdict == 1) : 0;
+    if (lane == 0) {
+        opened[wave] = __popcll(open);
+        if constexpr (kThree) opened[WAVES + wave] = __popcll(pair);
+    }
     __syncthreads();
-    int before = 0, all = 0;
+    int before = 0, all = 0, pairs_before = 0, pairs = 0;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) {
         const int c = opened[w];
         before += w < wave ? c : 0;
         all += c;
+        if constexpr (kThree) {
+            const int p = opened[WAVES + w];
+            pairs_before += w < wave ? p : 0;
+            pairs += p;
+        }
     }
-    if (all == 0) return;
-    if (tid == 0) *list_at = atomicAdd(list_len + b, all);
+    if (all + pairs == 0) return;
+    if (tid == 0 && all > 0) list_at[0] = atomicAdd(list_len + b, all);
+    if (kThree && tid == 1 && pairs > 0) list_at[1] = atomicAdd(pair_len + b, pairs);
     __syncthreads();
-    if (mine && !certain) list[*list_at + before + __popcll(open & ((1ull << lane) - 1ull))] = (int32_t)point;
+    if (mine && verdict == 2) list[list_at[0] + before + __popcll(open & below)] = (int32_t)point;
+    if (kThree && mine && verdict == 1) list[N - 1 - (list_at[1] + pairs_before + __popcll(pair & below))] = (int32_t)point;
+}
+
+// Few points: a workgroup of the sweep has 128 and walks through all centroids alone, so that a few thousand points keep
+// a few compute units busy.  Here it has 32, its waves share out the centroid tiles, and nothing but the points and the waves' best scores
+// passes through LDS: the operands of a tile come straight from memory (from L2, where all workgroups find them), half a tile or less
+// ahead of their use.  Same scores, same verdicts.  fk_assign, us, in the sweep / here: 2415 points, d = 128, K = 3561 116 / 37; 2 x 5764,
+// d = 415, K = 767 138 / 103; 8000, d = 512, K = 4000 551 / 309; an iteration of 2 x 3027, d = 242, K = 609 69 / 47.
+constexpr int few_ahead(int dch) { return dch % 4 == 0 ? 4 : dch % 3 == 0 ? 3 : dch % 5 == 0 ? 5 : dch % 7 == 0 ? 7 : dch % 2 == 0 ? 2 : 1; }
+constexpr int few_waves(int dch) { return 8; }
+
+template <int DCH>
+__global__ __launch_bounds__(few_waves(DCH) * 64, DCH <= 3 ? 4 : 2) void assign_f32_filter_few_kernel(
+    const float* __restrict__ X, const uintx4* __restrict__ frag, const float* __restrict__ c2,
+    const float* __restrict__ shift, int32_t* __restrict__ assign, int32_t* __restrict__ list,
+    int32_t* __restrict__ list_len, int32_t* __restrict__ pair_len, int32_t* __restrict__ pair_at, int64_t N, int d, int len, int K, int ktiles) {
+    constexpr int WAVES = few_waves(DCH), kTile = 2 * DCH + 1, GC = few_ahead(DCH), NG = DCH / GC;
+    constexpr bool kThree = filter_keeps_three(DCH);
+    constexpr bool kHeld = DCH <= 16 && DCH != 14;           // the points' operands stay in registers (14: they would spill)
+    // heads and tails of the 32 points, as B operands; at the end the waves' best scores
+    __shared__ uintx4 xs[2 * DCH * 64 > WAVES * 40 ? 2 * DCH * 64 : WAVES * 40];
+    __shared__ float sums[WAVES][32];
+    auto found = (TopScores<kThree>(*)[32])xs;
+    static_assert(sizeof(found[0]) * WAVES <= sizeof(xs), "room for the best scores");
+    const int b = blockIdx.y;
+    X += (size_t)b * N * len;
+    frag += (size_t)b * ktiles * kTile * 64;
+    c2 += (size_t)b * ktiles * 32;
+    shift += (size_t)b * DCH * 16;
+    assign += (size_t)b * N;
+    list += (size_t)b * N;
+    if (pair_at) pair_at += (size_t)b * N;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = lane & 31, h = lane >> 5;
+    const int64_t point = (int64_t)blockIdx.x * 32 + n;
+
+    // step: group of GC chunks of one of this wave's tiles
+    const int tiles = wave < ktiles ? (ktiles - wave + WAVES - 1) / WAVES : 0;
+    uintx4 ahead[2 * GC];
+    auto load = [&](int t, int g) {
+        const uintx4* at = frag + ((size_t)(wave + t * WAVES) * kTile + 2 * g * GC) * 64 + lane;
+#pragma unroll
+        for (int q = 0; q < 2 * GC; ++q) ahead[q] = at[q * 64];
+    };
+    if (tiles > 0) load(0, 0);
+    float x2 = 0.f;
+    const float* row = X + (size_t)min(point, N - 1) * len;
+    for (int s = wave; s < DCH; s += WAVES) {
+        const int j0 = s * 16 + h * 8;
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = 0.f;
+        if (point < N && j0 < d) {
+            const floatx4 a = row_piece32(row, j0, len), c = row_piece32(row, j0 + 4, len);
+            const floatx4 ma = *(const floatx4*)(shift + j0), mc = *(const floatx4*)(shift + j0 + 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { v[e] = a[e] - ma[e]; v[e + 4] = c[e] - mc[e]; }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x2 = fmaf(v[e], v[e], x2);
+        }
+        uintx4 hi, lo;
+        split8(v, hi, lo);
+        xs[2 * s * 64 + lane] = hi;
+        xs[(2 * s + 1) * 64 + lane] = lo;
+    }
+    x2 += __shfl_xor(x2, 32);
+    if (h == 0) sums[wave][n] = x2;
+    __syncthreads();
+    uintx4 xh[kHeld ? DCH : 1], xl[kHeld ? DCH : 1];
+    if constexpr (kHeld) {
+#pragma unroll
+        for (int s = 0; s < DCH; ++s) { xh[s] = xs[2 * s * 64 + lane]; xl[s] = xs[(2 * s + 1) * 64 + lane]; }
+    }
+    const uintx4 ones = {h == 0 ? 0x3F803F80u : 0u, h == 0 ? 0x3F80u : 0u, 0u, 0u};
+    TopScores<kThree> top;
+    top.clear();
+    for (int t = 0; t < tiles; ++t) {
+        const int tile = wave + t * WAVES;
+        const uintx4 bias = frag[((size_t)tile * kTile + 2 * DCH) * 64 + lane];
+        floatx16 big = floatx16{}, small = floatx16{};
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            uintx4 now[2 * GC];
+#pragma unroll
+            for (int q = 0; q < 2 * GC; ++q) now[q] = ahead[q];
+            if (!kHeld) asm volatile("" ::: "memory");    // (or they are all read before the loop)
+            if (g + 1 < NG) load(t, g + 1);
+            else if (t + 1 < tiles) load(t + 1, 0);
+#pragma unroll
+            for (int q = 0; q < GC; ++q) {
+                const int s = g * GC + q;
+                const uintx4 bh = kHeld ? xh[kHeld ? s : 0] : xs[2 * s * 64 + lane], bl = kHeld ? xl[kHeld ? s : 0] : xs[(2 * s + 1) * 64 + lane];
+                small = mfma32<true>(now[2 * q], bl, small);
+                big = mfma32<true>(now[2 * q], bh, big);
+                small = mfma32<true>(now[2 * q + 1], bh, small);
+            }
+        }
+        big = mfma32<true>(bias, ones, big);
+        top.fold(big, small, tile);
+    }
+    top.merge_halves(h);
+    __syncthreads();                                         // (the operands have been read)
+    if (h == 0) found[wave][n] = top;
+    __syncthreads();
+    if (wave != 0) return;
+    x2 = sums[0][n];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) {
+        x2 += sums[w][n];
+        if (w < ktiles) top.merge(found[w][n]);
+    }
+    const int verdict = top.verdict(x2, c2, DCH * 16, d, K);
+    const bool mine = h == 0 && point < N;
+    leave_verdict(top.t1, top.t2, verdict, mine, point, K, assign, pair_at);
+    const uint64_t below = (1ull << lane) - 1ull;
+    const uint64_t open = __ballot(mine && verdict == 2), pair = __ballot(mine && verdict == 1);
+    int at = 0, pair_from = 0;
+    if (lane == 0 && open) at = atomicAdd(list_len + b, __popcll(open));
+    if (lane == 0 && pair) pair_from = atomicAdd(pair_len + b, __popcll(pair));
+    at = __builtin_amdgcn_readfirstlane(at);
+    pair_from = __builtin_amdgcn_readfirstlane(pair_from);
+    if (mine && verdict == 2) list[at + __popcll(open & below)] = (int32_t)point;
+    if (mine && verdict == 1) list[N - 1 - (pair_from + __popcll(pair & below))] = (int32_t)point;
 }
 
 // The points on the list against all centroids by direct differences: ascending features, one
@@ -421,26 +628,139 @@ __global__ __launch_bounds__(WAVES * 64, filter_occupancy(DCH, WAVES)) void assi
 // rows: one point per thread with its features in registers, centroid tiles through LDS.  (Not rows of
 // up to 16 against many centroids: it multiplies 32 features.  7 x 294694 points, d = 8, K = 14868: 60.1 ms
 // against 34.4.)
+//   Points that are open between two centroids only, nineteen of twenty where the filter keeps three scores, are on a list of
+// their own and cost two rows each (list_pairs).  fk_assign of 65536 points, d = 256, K = 512, distances: 1837 such points and 42 others,
+// list and distances 44 -> 22 us.
 //   What open points cost is then about the direct kernel's time for them on top of the filter's.
 // Every centroid twice, so that all points are open, fk_assign against the direct kernels alone: 2^20 points,
 // d = K = 64: 292 us, 222 (one addition to the list's length per wave: 610); d = 64, K = 256: 924, 814
 // (in the first form: 1896); d = 128, K = 64: 950, 656 (4 teams: 1350); 300000 points, d = 96, K = 400:
 // 1238, 1149; 65536, d = 256, K = 512: 696, 1323.
 
+// |x - c|^2 by direct differences for every point whose distance is wanted: LANES (4, 8 or 16) lanes a point, enough for a whole
+// row per load where it has up to 64 features.  Infinity where it is not finite, as in the direct kernels, whose
+// minimum starts there.  (The lanes' sums meet in a butterfly: lanes without a piece add zero, so that their number changes no bit.)
+constexpr int distance_lanes(int len) { return len <= 16 ? 4 : len <= 32 ? 8 : 16; }
+
+template <int LANES, int U>
+__device__ __forceinline__ void row_distances(const float* const (&x)[U], const float* const (&c)[U], int len, int l, float (&s)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) s[u] = 0.f;
+    for (int j = l * 4; j < len; j += 4 * LANES) {
+        floatx4 v[U], w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) { v[u] = row_piece32(x[u], j, len); w[u] = row_piece32(c[u], j, len); }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { const float t = v[u][e] - w[u][e]; s[u] = fmaf(t, t, s[u]); }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+        for (int o = LANES / 2; o > 0; o >>= 1) s[u] += __shfl_xor(s[u], o);
+        s[u] = s[u] < INFINITY ? s[u] : INFINITY;
+    }
+}
+
+template <int DMAX>
+__device__ __forceinline__ float row_distance(const float* x, const float* c, int len) {
+    const float* const xs[1] = {x};
+    const float* const cs[1] = {c};
+    float s[1];
+    if (DMAX == 32 && len <= 16) row_distances<4, 1>(xs, cs, len, threadIdx.x & 3, s);
+    else if (DMAX == 32) row_distances<8, 1>(xs, cs, len, threadIdx.x & 7, s);
+    else row_distances<16, 1>(xs, cs, len, threadIdx.x & 15, s);
+    return s[0];
+}
+
+// Share `part` of `parts` of the points, by 512 threads, U points at a time a group of lanes; open points (-1) are left out.
+// fk_assign with distances, K = 200, us, one / two / four at a time: 400000 points, d = 64 97 / 86 / 81, d = 128 145 / 130 / 125; d = 256,
+// 65536, K = 512 84.6 / 85.9 / 86.6, 200000, K = 100 120 / 111 / 111.
+template <int LANES, int U>
+__device__ __forceinline__ void measure_points(const float* __restrict__ X, const float* __restrict__ C, const int32_t* assign,
+                                               float* min_dist, int64_t N, int len, int64_t part, int64_t parts) {
+    constexpr int each = 512 / LANES;
+    const int l = threadIdx.x & (LANES - 1);
+    for (int64_t i0 = part * (U * each) + threadIdx.x / LANES; i0 < N; i0 += parts * (U * each)) {
+        int k[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = min(i0 + u * each, N - 1);
+            k[u] = __hip_atomic_load(assign + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (i0 + u * each >= N) k[u] = -1;
+        }
+        const float *x[U], *c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            x[u] = X + (size_t)min(i0 + u * each, N - 1) * len;
+            c[u] = C + (size_t)max(k[u], 0) * len;
+        }
+        float s[U];
+        row_distances<LANES, U>(x, c, len, l, s);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (l == 0 && k[u] >= 0) min_dist[i0 + u * each] = s[u];
+    }
+}
+
 // Points held by a workgroup x row width, in floats.  Wide rows: enough that with few centroids as few
 // waves as possible are without a share of them.
 template <int DMAX>
 constexpr int list_floats() { return DMAX == 0 ? 15360 : 4096; }
 
-template <int P>
+// The end of a round of `held` points, P to a team of `size` waves: the lanes' best meet in the waves, the waves' in LDS.
+template <int DMAX, int P>
+__device__ __forceinline__ void list_merge(
+    const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list, int64_t g, int len,
+    int32_t* __restrict__ assign, float* __restrict__ min_dist, int row_len, int K, int none, int size, int held,
+    float (&best)[P], int (&at)[P], float (*cand_d)[8], int (*cand_k)[8]) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const float od = __shfl_xor(best[p], o);
+            const int ok = __shfl_xor(at[p], o);
+            if (od < best[p] || (od == best[p] && ok < at[p])) { best[p] = od; at[p] = ok; }
+        }
+        if (lane == 0) { cand_d[wave][p] = best[p]; cand_k[wave][p] = at[p]; }
+    }
+    __syncthreads();
+    if (tid < held && g + tid < len) {
+        const int p = tid % P, w0 = tid / P * size;
+        float bd = cand_d[w0][p];
+        int bk = cand_k[w0][p];
+        for (int w = w0 + 1; w < w0 + size; ++w) {
+            const float od = cand_d[w][p];
+            const int ok = cand_k[w][p];
+            if (od < bd || (od == bd && ok < bk)) { bd = od; bk = ok; }
+        }
+        bk = bk < K ? bk : none;
+        assign[list[g + tid]] = bk;
+        cand_k[w0][p] = bk;
+    }
+    __syncthreads();
+    if (min_dist) {
+        const int lanes = distance_lanes(row_len), l = tid & (lanes - 1);
+        for (int q = tid / lanes; q < held && g + q < len; q += 512 / lanes) {
+            const int own = list[g + q], k = cand_k[q / P * size][q % P];
+            const float D = row_distance<DMAX>(X + (size_t)own * row_len, C + (size_t)k * row_len, row_len);
+            if (l == 0) min_dist[own] = D;
+        }
+        __syncthreads();
+    }
+}
+
+template <int DMAX, int P>
 __device__ __forceinline__ void list_points(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list, int len,
-    int32_t* __restrict__ assign, int d, int row_len, int K, int none, int teams, float* xs, float (*cand_d)[8], int (*cand_k)[8]) {
+    int32_t* __restrict__ assign, float* __restrict__ min_dist, int d, int row_len, int K, int none, int teams, int G, float* xs, float (*cand_d)[8], int (*cand_k)[8]) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int size = 8 / teams, team = wave / size, part = wave - team * size;   // waves of a team share the centroids
     const int held = teams * P;
     const float* x = xs + team * P * d;
-    for (int64_t g = (int64_t)blockIdx.x * held; g < len; g += (int64_t)gridDim.x * held) {
+    for (int64_t g = (int64_t)blockIdx.x * held; g < len; g += (int64_t)G * held) {
         // one wave per row (past the end of the list: the last point again)
         for (int r = wave; r < held; r += 8) {
             const int own = list[min(g + r, (int64_t)len - 1)];
@@ -491,38 +811,103 @@ __device__ __forceinline__ void list_points(
                     if (D[p] < best[p]) { best[p] = D[p]; at[p] = k; }
             }
         }
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                const float od = __shfl_xor(best[p], o);
-                const int ok = __shfl_xor(at[p], o);
-                if (od < best[p] || (od == best[p] && ok < at[p])) { best[p] = od; at[p] = ok; }
-            }
-            if (lane == 0) { cand_d[wave][p] = best[p]; cand_k[wave][p] = at[p]; }
+        list_merge<DMAX, P>(X, C, list, g, len, assign, min_dist, row_len, K, none, size, held, best, at, cand_d, cand_k);
+    }
+}
+
+// Short lists of wide rows against many centroids: two points a team, lane = centroid row as in list_points, but the rows arrive 16
+// features at a time in whole pieces of 64 bytes, two steps ahead (four or six: slower), and pass through LDS.  Read by their own lanes a
+// step touches every line eight times, which a few workgroups alone feel: 11 points of d = 415 against 767 rows took 186 us,
+// here 50.  Up to 256 centroids a wave has one block of rows, and the shorter chain of list_points is as fast or faster (fk_assign,
+// us, this / that: 16000 points, d = 512, K = 230 60.6 / 55.2, d = 256, K = 100 36.2 / 34.3, d = 128, K = 200 27.7 / 29.2).
+template <int DMAX>
+__device__ __forceinline__ void list_few(
+    const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list, int len,
+    int32_t* __restrict__ assign, float* __restrict__ min_dist, int d, int row_len, int K, int none, int teams, int G, float* xs, float* tiles,
+    float (*cand_d)[8], int (*cand_k)[8]) {
+    constexpr int P = 2, kRow = 20;                          // (four floats of padding: 16 lanes' reads hit all banks)
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int size = 8 / teams, team = wave / size, part = wave - team * size;
+    const int held = teams * P, steps = (d + 15) / 16;
+    const int blocks = K > part * 64 ? (K - part * 64 + size * 64 - 1) / (size * 64) : 0, all = blocks * steps;
+    const float* x = xs + team * P * d;
+    float* tile = tiles + wave * 64 * kRow;
+    const int r0 = lane >> 2, j0 = (lane & 3) * 4;           // this lane's pieces: rows r0 + 16 q, features j0 .. j0 + 3
+    for (int64_t g = (int64_t)blockIdx.x * held; g < len; g += (int64_t)G * held) {
+        for (int r = wave; r < held; r += 8) {
+            const int own = list[min(g + r, (int64_t)len - 1)];
+            for (int j = lane * 4; j < d; j += 256) *(floatx4*)(xs + r * d + j) = row_piece32(X + (size_t)own * row_len, j, row_len);
         }
+        float best[P], D[P];
+        int at[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) { best[p] = INFINITY; at[p] = 0x7FFFFFFF; D[p] = 0.f; }
         __syncthreads();
-        if (tid < held && g + tid < len) {
-            const int p = tid % P, w0 = tid / P * size;
-            float bd = cand_d[w0][p];
-            int bk = cand_k[w0][p];
-            for (int w = w0 + 1; w < w0 + size; ++w) {
-                const float od = cand_d[w][p];
-                const int ok = cand_k[w][p];
-                if (od < bd || (od == bd && ok < bk)) { bd = od; bk = ok; }
+        floatx4 ahead[2][4];
+        uint32_t from[4];                                    // where this lane's rows of the block to load start (K len < 2^25)
+        int load_block = 0, load_j = j0;
+        auto load = [&](floatx4 (&to)[4]) {
+            if (load_j == j0) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) from[q] = (uint32_t)min((part + load_block * size) * 64 + r0 + 16 * q, K - 1) * (uint32_t)row_len;
             }
-            assign[list[g + tid]] = bk < K ? bk : none;
+            const int at_j = min(load_j, row_len - 4);       // (beyond the row: zeros, or nobody's)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) to[q] = *(const floatx4_any*)(C + (from[q] + (uint32_t)at_j));
+            if ((row_len & 7) && load_j + 4 > row_len) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) to[q] = settle32(to[q], load_j, row_len);
+            }
+            load_j += 16;
+            if (load_j >= steps * 16) { load_j = j0; ++load_block; }
+        };
+        auto use = [&](floatx4 (&now)[4], int step, int block, int t) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) *(floatx4*)(tile + (r0 + 16 * q) * kRow + j0) = now[q];
+            __builtin_amdgcn_wave_barrier();                 // LDS runs a wave's operations in order
+            if (step + 2 < all) load(now);
+#pragma unroll
+            for (int e = 0; e < 16; e += 8) {                // (d is a multiple of 8)
+                if (t * 16 + e < d) {
+                    const floatx4 ca = *(const floatx4*)(tile + lane * kRow + e), cb = *(const floatx4*)(tile + lane * kRow + e + 4);
+#pragma unroll
+                    for (int p = 0; p < P; ++p) {
+                        const floatx4 va = *(const floatx4*)(x + p * d + t * 16 + e), vb = *(const floatx4*)(x + p * d + t * 16 + e + 4);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) { const float u = va[i] - ca[i]; D[p] = fmaf(u, u, D[p]); }
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) { const float u = vb[i] - cb[i]; D[p] = fmaf(u, u, D[p]); }
+                    }
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+            if (t + 1 == steps) {
+                const int k = (part + block * size) * 64 + lane;
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    if (k < K && D[p] < best[p]) { best[p] = D[p]; at[p] = k; }
+                    D[p] = 0.f;
+                }
+            }
+        };
+        if (all > 0) load(ahead[0]);
+        if (all > 1) load(ahead[1]);
+        for (int step = 0, block = 0, t = 0; step < all; step += 2) {
+            use(ahead[0], step, block, t);
+            if (++t == steps) { t = 0; ++block; }
+            if (step + 1 < all) use(ahead[1], step + 1, block, t);
+            if (++t == steps) { t = 0; ++block; }
         }
-        __syncthreads();
+        list_merge<DMAX, P>(X, C, list, g, len, assign, min_dist, row_len, K, none, size, held, best, at, cand_d, cand_k);
     }
 }
 
 template <int DMAX>
 __device__ __forceinline__ void list_by_thread(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list, int len,
-    int32_t* __restrict__ assign, int d, int row_len, int K, int none, float* sc) {
+    int32_t* __restrict__ assign, float* __restrict__ min_dist, int d, int row_len, int K, int none, int G, float* sc) {
     constexpr int TK = 32;
-    for (int64_t g = (int64_t)blockIdx.x * 512; g < len; g += (int64_t)gridDim.x * 512) {
+    for (int64_t g = (int64_t)blockIdx.x * 512; g < len; g += (int64_t)G * 512) {
         const int64_t at = g + threadIdx.x;
         const int own = list[min(at, (int64_t)len - 1)];
         float x[DMAX];
@@ -549,60 +934,125 @@ __device__ __forceinline__ void list_by_thread(
             }
         }
         if (at < len) assign[own] = a;
+        if (min_dist) {
+            const int lanes = distance_lanes(row_len), lane = threadIdx.x & 63;
+            for (int p = lane / lanes; p < 64; p += 64 / lanes) {
+                const int i = __shfl(own, p), k = __shfl(a, p);
+                const float D = row_distance<DMAX>(X + (size_t)i * row_len, C + (size_t)k * row_len, row_len);
+                if ((lane & (lanes - 1)) == 0) min_dist[i] = D;      // (past the end of the list: the last point again)
+            }
+        }
+    }
+}
+
+// Points that are open between two centroids, packed in assign: a wave takes as many as its part of LDS holds the
+// differences to both of, in whole rows, and then has a lane add up the squares of each in the direct kernels' order.
+// (From the last workgroup on: the first ones have the points that are measured in full.)
+template <int DMAX>
+__device__ __forceinline__ void list_pairs(
+    const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list_end, int pairs,
+    int32_t* __restrict__ assign, float* __restrict__ min_dist, int d, int row_len, int none, int G, float* diff, int floats) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, row = d + 4;     // (four floats: the lanes' reads spread over the banks)
+    const int held = min((floats - 16) / (2 * row), 16);
+    int* chosen = (int*)diff + floats - 16;
+    const int waves = G * 8, each = min(held, (pairs + waves - 1) / waves);
+    for (int64_t p0 = (int64_t)((G - 1 - blockIdx.x) * 8 + wave) * each; p0 < pairs; p0 += waves * each) {
+        const int n = (int)min((int64_t)each, pairs - p0);
+        const int own = list_end[-(p0 + min(lane, n - 1))];
+        const uint32_t both = (uint32_t)(min_dist ? __float_as_int(min_dist[own]) : assign[own]);
+        const int k1 = (int)(both & 0xFFFFu), k2 = (int)(both >> 16);
+        for (int p = 0; p < n; ++p) {
+            const float* x = X + (size_t)__shfl(own, p) * row_len;
+            const float *c1 = C + (size_t)__shfl(k1, p) * row_len, *c2 = C + (size_t)__shfl(k2, p) * row_len;
+            for (int j = lane * 4; j < d; j += 256) {
+                const floatx4 v = row_piece32(x, j, row_len), u1 = row_piece32(c1, j, row_len), u2 = row_piece32(c2, j, row_len);
+                *(floatx4*)(diff + 2 * p * row + j) = v - u1;
+                *(floatx4*)(diff + (2 * p + 1) * row + j) = v - u2;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();                     // LDS runs a wave's operations in order
+        float D = 0.f;
+        if (lane < 2 * n)
+            for (int j = 0; j < d; j += 8) {
+                const floatx4 a = *(const floatx4*)(diff + lane * row + j), c = *(const floatx4*)(diff + lane * row + j + 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) D = fmaf(a[e], a[e], D);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) D = fmaf(c[e], c[e], D);
+            }
+        __builtin_amdgcn_wave_barrier();
+        const float D1 = __shfl(D, 2 * lane), D2 = __shfl(D, 2 * lane + 1);
+        if (lane < n) {
+            // the lower centroid first, strict '<', from infinity: as the direct kernels go through them
+            const int lo = min(k1, k2), hi = max(k1, k2);
+            const float Dlo = k1 < k2 ? D1 : D2, Dhi = k1 < k2 ? D2 : D1;
+            float best = INFINITY;
+            int at = none;
+            if (Dlo < best) { best = Dlo; at = lo; }
+            if (Dhi < best) { best = Dhi; at = hi; }
+            assign[own] = at;
+            if (min_dist) chosen[lane] = at;
+        }
+        if (min_dist) {
+            __builtin_amdgcn_wave_barrier();
+            const int lanes = distance_lanes(row_len);
+            for (int p = lane / lanes; p < n; p += 64 / lanes) {
+                const int i = list_end[-(p0 + p)];
+                const float s = row_distance<DMAX>(X + (size_t)i * row_len, C + (size_t)chosen[p] * row_len, row_len);
+                if ((lane & (lanes - 1)) == 0) min_dist[i] = s;
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
     }
 }
 
 // `none`: the answer where no distance is finite, that of the direct kernel for the shape.
 // DMAX: 32 or 64 for rows up to that, 0 for wider ones.
+// The first G workgroups of an instance take the lists, the rest, where distances are wanted, measure the points that the
+// filter has decided, in the time that the few open ones take.  A point that one of the lists has meanwhile given a centroid may be among
+// them: both then write the same bits, and what the list still has to read of it (the two centroids, where its distance goes) it
+// has read before it writes the centroid.
 template <int DMAX>
 __global__ __launch_bounds__(512, 4) void assign_f32_list_kernel(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list,
-    const int32_t* __restrict__ list_len, int32_t* __restrict__ assign, int64_t N, int d, int row_len,
-    int K, int none) {
+    const int32_t* __restrict__ list_len, const int32_t* __restrict__ pair_len, int32_t* assign, float* min_dist, int64_t N, int d,
+    int row_len, int K, int none, int G) {
     __shared__ __align__(16) float xs[list_floats<DMAX>()];
     __shared__ float cand_d[8][8];
     __shared__ int cand_k[8][8];
     const int b = blockIdx.y;
-    const int len = list_len[b];
     X += (size_t)b * N * row_len;
     C += (size_t)b * K * row_len;
     assign += (size_t)b * N;
+    if (min_dist) min_dist += (size_t)b * N;
+    if ((int)blockIdx.x >= G) {
+        const int64_t part = blockIdx.x - G, parts = gridDim.x - G;
+        if (DMAX == 32 && row_len <= 16) measure_points<4, 4>(X, C, assign, min_dist, N, row_len, part, parts);
+        else if (DMAX == 32) measure_points<8, 4>(X, C, assign, min_dist, N, row_len, part, parts);
+        else if (DMAX == 64 || row_len <= 128) measure_points<16, 4>(X, C, assign, min_dist, N, row_len, part, parts);
+        else measure_points<16, 2>(X, C, assign, min_dist, N, row_len, part, parts);
+        return;
+    }
+    const int len = list_len[b], pairs = pair_len[b];
     list += (size_t)b * N;
     const int most = K <= 64 ? 8 : K <= 128 ? 4 : K <= 256 ? 2 : 1;
     int thin = most, teams = most;                           // both end at 1 or more (d <= 512)
     while (thin * 8 * d > 4096) thin >>= 1;                  // (short lists: as wide a spread)
     while (teams * 8 * d > list_floats<DMAX>()) teams >>= 1;
-    if (len <= 2 * thin * (int)gridDim.x)
-        list_points<2>(X, C, list, len, assign, d, row_len, K, none, thin, xs, cand_d, cand_k);
-    else if (DMAX == 0 || len < 256 * (int)gridDim.x || (K > 128 && d <= 16))
-        list_points<8>(X, C, list, len, assign, d, row_len, K, none, teams, xs, cand_d, cand_k);
-    else
-        list_by_thread<DMAX == 0 ? 32 : DMAX>(X, C, list, len, assign, d, row_len, K, none, xs);
-}
-
-// min_dist[i] = |x_i - c_a(i)|^2 by direct differences: LANES (4, 8 or 16) lanes a point, enough for a whole
-// row per load where it has up to 64 features.  Infinity where it is not finite, as in the direct
-// kernels, whose minimum starts there.  (The lanes' sums meet in a butterfly: lanes without a piece add
-// zero, so that their number changes no bit.)
-template <int LANES>
-__global__ __launch_bounds__(256) void f32_distance_kernel(
-    const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ assign,
-    float* __restrict__ min_dist, int64_t N, int len, int K) {
-    const int b = blockIdx.y, l = threadIdx.x & (LANES - 1);
-    constexpr int kPoints = 256 / LANES;
-    for (int64_t i = (int64_t)blockIdx.x * kPoints + threadIdx.x / LANES; i < N; i += (int64_t)gridDim.x * kPoints) {
-        const float* x = X + ((size_t)b * N + i) * len;
-        const float* c = C + ((size_t)b * K + assign[(size_t)b * N + i]) * len;
-        float s = 0.f;
-        for (int j = l * 4; j < len; j += 4 * LANES) {
-            const floatx4 u = row_piece32(x, j, len), v = row_piece32(c, j, len);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { const float t = u[e] - v[e]; s = fmaf(t, t, s); }
-        }
-#pragma unroll
-        for (int o = LANES / 2; o > 0; o >>= 1) s += __shfl_xor(s, o);   // (the lanes of a point leave together)
-        if (l == 0) min_dist[(size_t)b * N + i] = s < INFINITY ? s : INFINITY;
+    if (pairs > 0) {
+        constexpr int kOwn = list_floats<DMAX>() / 8;
+        list_pairs<DMAX>(X, C, list + N - 1, pairs, assign, min_dist, d, row_len, none, G, xs + (threadIdx.x >> 6) * kOwn, kOwn);
+        __syncthreads();
     }
+    if (len <= 2 * thin * G) {
+        if (DMAX == 0 && K > 256)
+            list_few<DMAX>(X, C, list, len, assign, min_dist, d, row_len, K, none, thin, G, xs, xs + 4096, cand_d, cand_k);
+        else
+            list_points<DMAX, 2>(X, C, list, len, assign, min_dist, d, row_len, K, none, thin, G, xs, cand_d, cand_k);
+    } else if (DMAX == 0 || len < 256 * G || (K > 128 && d <= 16))
+        list_points<DMAX, 8>(X, C, list, len, assign, min_dist, d, row_len, K, none, teams, G, xs, cand_d, cand_k);
+    else
+        list_by_thread<DMAX == 0 ? 32 : DMAX>(X, C, list, len, assign, min_dist, d, row_len, K, none, G, xs);
 }
 
 // ------------------------------------------------------------------------------------
@@ -633,28 +1083,50 @@ bool f32_filter_enabled(const Geometry& g) {
     return g.K >= 24 && (points * g.K * g.d >= ((int64_t)1 << 28) || g.K * std::max(g.d, 32) >= 8192);
 }
 
+template <int DCH>
+static fk_status launch_filter_few(const Geometry& g, const Workspace& w, const float* X, int32_t* assign, float* min_dist, hipStream_t s) {
+    hipLaunchKernelGGL(assign_f32_filter_few_kernel<DCH>, dim3((unsigned)cdiv(g.N, 32), g.B), dim3(few_waves(DCH) * 64), 0, s, X,
+                       (const uintx4*)w.c_frag, w.c_bias, w.f32_shift, assign, w.sorted_idx, w.f32_list_len, w.digit_off, (int32_t*)min_dist,
+                       g.N, g.d, g.len, g.K, g.ktiles);
+    FK_HIP(hipGetLastError());
+    return FK_OK;
+}
+
 template <int DCH, int WAVES>
-static fk_status launch_filter_t(const Geometry& g, const Workspace& w, const float* X, int32_t* assign, hipStream_t s) {
+static fk_status launch_filter_t(const Geometry& g, const Workspace& w, const float* X, int32_t* assign, float* min_dist, hipStream_t s) {
     dim3 grid((unsigned)cdiv(g.N, WAVES * 32), g.B), block(WAVES * 64);
     hipLaunchKernelGGL((assign_f32_filter_kernel<DCH, WAVES>), grid, block, 0, s, X, (const uintx4*)w.c_frag,
-                       w.c_bias, w.f32_shift, assign, w.sorted_idx, w.f32_list_len, g.N, g.d, g.len, g.K, g.ktiles);
+                       w.c_bias, w.f32_shift, assign, w.sorted_idx, w.f32_list_len, w.digit_off, (int32_t*)min_dist, g.N, g.d, g.len, g.K, g.ktiles);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }
 
 fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* X, const float* C, int32_t* assign,
                             float* min_dist, hipStream_t s) {
-    hipLaunchKernelGGL(f32_split_layout_kernel, dim3(g.ktiles, g.B), dim3(kLayoutThreads), 0, s, C, (uintx4*)w.c_frag, w.c_bias,
-                       w.f32_shift, w.f32_list_len, g.d, g.len, g.K, g.ktiles, g.dchunks);
+    // (groups of eight features a thread, 32 rows of them to a workgroup)
+    const int per = (int)cdiv(64 * g.dchunks, kLayoutThreads);
+#define FK_LAYOUT(RAGGED) (per == 1 ? f32_split_layout_kernel<1, RAGGED> : per == 2 ? f32_split_layout_kernel<2, RAGGED> \
+                           : per == 3 ? f32_split_layout_kernel<3, RAGGED> : f32_split_layout_kernel<4, RAGGED>)
+    auto layout = g.len == g.d ? FK_LAYOUT(false) : FK_LAYOUT(true);
+#undef FK_LAYOUT
+    hipLaunchKernelGGL(layout, dim3(g.ktiles, g.B), dim3(kLayoutThreads), 0, s, C, (uintx4*)w.c_frag, w.c_bias,
+                       w.f32_shift, w.f32_list_len, w.digit_off, g.d, g.len, g.K, g.ktiles, g.dchunks);
     FK_HIP(hipGetLastError());
     // Workgroups of four waves fill the chip best; with very many points eight waves share each
     // copy of the centroids (2^20 points, 64 features, K = 256: 138 against 142 us; 128 features, K =
     // 64: 172 against 182 us) as long as two such workgroups fit a compute unit.
+    // Few points (see assign_f32_filter_few_kernel), fk_assign, us, sweep / few: up to a tile of 32 points per compute unit always (1000, d = 64,
+    // K = 200 22.4 / 20.0; five instances of 1516, d = 256, K = 12 in a fit 28.9 / 25.9), up to two where there are tiles of centroids to share
+    // (16000, d = 256, K = 30 31.6 / 34.0; d = 96, K = 100 23.4 / 22.8; d = 256, K = 1000 93 / 77; d = 32, K = 8000 133 / 82); with 24000 points it
+    // depends (d = 96, K = 1000 48 / 42, d = 256 92 / 94), with 32000 the sweep is faster (d = 128, K = 500 40.6 / 45.2).
+    const int64_t tiles = cdiv(g.N, 32) * g.B;
+    const bool few = tiles <= device_cu_count() || (tiles <= 2 * device_cu_count() && g.ktiles >= 4);
     const bool many = (int64_t)g.B * g.N >= ((int64_t)1 << 19);
 #define FK_FILTER(DCH) \
     case DCH: \
-        if (DCH <= 8 && many) FK_TRY((launch_filter_t<DCH, DCH <= 8 ? 8 : 4>(g, w, X, assign, s))); \
-        else FK_TRY((launch_filter_t<DCH, 4>(g, w, X, assign, s))); \
+        if (few) FK_TRY((launch_filter_few<DCH>(g, w, X, assign, min_dist, s))); \
+        else if (DCH <= 8 && many) FK_TRY((launch_filter_t<DCH, DCH <= 8 ? 8 : 4>(g, w, X, assign, min_dist, s))); \
+        else FK_TRY((launch_filter_t<DCH, 4>(g, w, X, assign, min_dist, s))); \
         break
     switch (g.dchunks) {
         FK_FILTER(1); FK_FILTER(2); FK_FILTER(3); FK_FILTER(4); FK_FILTER(5); FK_FILTER(6); FK_FILTER(7); FK_FILTER(8);
@@ -666,16 +1138,10 @@ fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* 
     const int64_t G = std::max<int64_t>(1, std::min<int64_t>(groups, cdiv((int64_t)device_cu_count() * 2, g.B)));
     auto list_kernel = g.d <= 32 ? assign_f32_list_kernel<32> : g.d <= 64 ? assign_f32_list_kernel<64>
                                                                           : assign_f32_list_kernel<0>;
-    hipLaunchKernelGGL(list_kernel, dim3((unsigned)G, g.B), dim3(512), 0, s, X, C, w.sorted_idx,
-                       w.f32_list_len, assign, g.N, g.d, g.len, g.K, f32_direct_is_split(g) ? g.K - 1 : 0);
+    const int64_t distances = min_dist ? cdiv(f32_distance_blocks(g.N, distance_lanes(g.len)), g.d <= 128 ? 8 : 4) : 0;
+    hipLaunchKernelGGL(list_kernel, dim3((unsigned)(G + distances), g.B), dim3(512), 0, s, X, C, w.sorted_idx,
+                       w.f32_list_len, w.digit_off, assign, min_dist, g.N, g.d, g.len, g.K, f32_direct_is_split(g) ? g.K - 1 : 0, (int)G);
     FK_HIP(hipGetLastError());
-    if (min_dist) {
-        const int lanes = g.d <= 16 ? 4 : g.d <= 32 ? 8 : 16;
-        auto kern = lanes == 4 ? f32_distance_kernel<4> : lanes == 8 ? f32_distance_kernel<8> : f32_distance_kernel<16>;
-        hipLaunchKernelGGL(kern, dim3((unsigned)f32_distance_blocks(g.N, lanes), g.B), dim3(256), 0, s, X, C, assign,
-                           min_dist, g.N, g.len, g.K);
-        FK_HIP(hipGetLastError());
-    }
     return FK_OK;
 }
 
