@@ -561,7 +561,7 @@ int fk_plan(int B, int64_t N, int d, int K, fk_dtype t, char* buf, size_t buf_by
     else if (assign_uses_few_kernel(g))
         snprintf(assign, sizeof(assign), "mfma_few(%s)", assign_few_takes_rows(g) ? "rows" : "fragments");
     else if (g.dchunks > 8)
-        snprintf(assign, sizeof(assign), "mfma_wide(chunks=%d,points_per_wg=256)", g.dchunks);
+        snprintf(assign, sizeof(assign), "mfma_wide(chunks=%d,points_per_wg=%d)", g.dchunks, wide_kernel_waves(g) * 32);
     else if (assign_uses_stream_kernel(g))
         snprintf(assign, sizeof(assign), "mfma_stream(tiles=%d)", g.ktiles);
     else {

@@ -1125,6 +1125,10 @@ bool assign_uses_stream_kernel(const Geometry& g) {
 //   more: 64 points per workgroup, so that each A operand serves two products, while there are
 //     centroids enough for the waves (16384 points, d = 128: K = 256 7.4 against 9.7, K = 4096 24.7
 //     against 74; 32768: K = 1024 14.1 against 22.9, but d = 32, K = 256: 6.6 against 5.7).
+//   Rows of more than 128 features leave little of a wave's registers to a second tile of points: one for as long as 24576
+// points do not fill the chip (9000 points, K = 1100, two / one: d = 150 17.3 14.9, d = 256 19.9 18.5; 20400, K = 300: d = 150 15.2 12.7, d = 256
+// 17.9 15.0; 30000, K = 2000: d = 256 45.4 48.6; with 14 chunks 20400, d = 200, K = 2000: 42.6 44.7), and for 20 chunks, which have no such
+// form, up to 32768 (d = 300, K = 2000: 30000 79 in the sweep, 62 here; K = 300 17.6, 19.9; 24 chunks, d = 384, K = 2000: 85, 100).
 //   t >= 8 U the sweeping kernel's workgroups fill the chip (65536 points, d = 128, K = 1024: 25.5
 //     against 23.7; d = 256: 46 against 49).
 enum FewForm { kFewNone = 0, kFewRows = 1, kFewOne = 2, kFewTwo8 = 3, kFewTwo16 = 4 };
@@ -1160,10 +1164,12 @@ static FewForm choose_few(const Geometry& g, bool have_rows) {
     }
     if (t <= 2 * U) {
         if (dch > 16) return c >= 8 ? kFewOne : kFewNone;
-        if (dch > 8) return c >= 32 ? kFewTwo8 : dch * c >= 24 && c >= 2 ? kFewOne : kFewNone;
+        if (dch > 8) return c >= 32 ? kFewOne : dch * c >= 24 && c >= 2 ? kFewOne : kFewNone;
         if (c < (dch == 2 ? 16 : 8)) return kFewNone;
         return c >= 32 ? kFewTwo16 : kFewTwo8;
     }
+    if (dch > 8 && dch <= 16 && t <= 3 * U && c >= 8 && (dch != 14 || c < 32)) return kFewOne;
+    if (dch == 20 && t <= 4 * U && c >= 32) return kFewOne;
     if (t <= 4 * U) return dch <= 16 && c >= (dch <= 4 ? 16 : 8) ? kFewTwo8 : kFewNone;
     if (t < 8 * U) return dch <= 8 && c >= 32 ? kFewTwo8 : kFewNone;
     return kFewNone;
@@ -1263,15 +1269,20 @@ static fk_status launch_mfma(const Geometry& g, const void* X, const void* frag,
     }
 }
 
+// Rows of more than 128 features: four waves a workgroup where twice as many workgroups still find a compute unit each (us, eight /
+// four: 20563 points, d = 512, K = 45 15.6 / 12.6, 24000, K = 1000 58 / 48; beyond, 37183, K = 229 23.4 / 25.5, 50000, K = 1000 63 / 68).
+int wide_kernel_waves(const Geometry& g) { return 2 * cdiv(g.N, 256) * g.B <= device_cu_count() ? 4 : 8; }
+
 template <bool BF, int DCH>
 static fk_status launch_mfma_wide(const Geometry& g, const void* X, const void* frag,
                                   const float* bias, int32_t* assign, float* min_dist,
                                   hipStream_t s) {
     if (const FewForm few = choose_few(g, false); few != kFewNone)
         return launch_few<BF, DCH>(g, few, X, frag, bias, assign, min_dist, s);
-    constexpr int WAVES = 8;
-    dim3 grid((unsigned)cdiv(g.N, WAVES * 32), g.B), block(WAVES * 64);
-    hipLaunchKernelGGL((assign_mfma_wide_kernel<BF, DCH, WAVES>), grid, block, 0, s,
+    const int waves = wide_kernel_waves(g);
+    dim3 grid((unsigned)cdiv(g.N, waves * 32), g.B), block(waves * 64);
+    auto kern = waves == 4 ? assign_mfma_wide_kernel<BF, DCH, 4> : assign_mfma_wide_kernel<BF, DCH, 8>;
+    hipLaunchKernelGGL(kern, grid, block, 0, s,
                        (const uint16_t*)X, (const uintx4*)frag, bias, assign, min_dist, g.N, g.d,
                        g.len, g.K, g.ktiles);
     FK_HIP(hipGetLastError());

@@ -169,6 +169,7 @@ void set_assign_variant_override(int v);   // -1 = choose from the shape
 // Few centroids: persistent streaming kernel instead of the sweeping one (see fk_assign.hip).
 bool assign_uses_stream_kernel(const Geometry& g);
 void set_assign_stream_option(int v);      // -1 = by shape, 0 = never, 1 = whenever eligible
+int wide_kernel_waves(const Geometry& g);  // of the kernel for rows of more than 128 features
 // Few points: the waves of a workgroup share the centroid tiles of 32 or 64 points (see fk_assign.hip).
 bool assign_uses_few_kernel(const Geometry& g);
 void set_assign_few_option(int v);         // -1 = by shape, 0 = never, 1..4 = one of its forms
