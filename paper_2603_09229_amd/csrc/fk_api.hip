@@ -231,6 +231,7 @@ Workspace carve(const Geometry& g, void* base, bool padded_x) {
     if (fused_rows > 0) w.wg_counts = (int32_t*)take((size_t)g.B * fused_rows * 4);
     // (an update that gathers does not sort: the parts' counts take the place of the sort's totals)
     w.gather_counts = gather_rows <= 2049 ? w.digit_off : (int32_t*)take((size_t)g.B * gather_rows * 4);
+    w.f32_pair_len = gather_rows > 0 ? w.seg_off : w.digit_off;
     w.sums = (float*)take(BKd * 4);
     if (needs_padded_rows(g)) {
         if (padded_x) w.x_pad = take(BN * g.d * elem_size(g.t));
@@ -838,6 +839,7 @@ fk_status fk_lloyd_iter(const void* X, float* C_f32, void* C_lp, int32_t* assign
     void* lp = C_lp ? C_lp : w.c_lp;
     // what the first assignment consumes: the master rounded to the storage type
     FK_TRY(launch_round_centroids(g, C_f32, t == FK_F32 ? nullptr : lp, w.c_frag, w.c_bias, s));
+    bool split = false;                        // fp32: the last update has left the filter's split centroids
     for (int it = 0; it < iters; ++it) {
         timer_mark(s, -1);
         // few clusters: assignment and sums in one pass over X (see run_stream_update)
@@ -846,7 +848,7 @@ fk_status fk_lloyd_iter(const void* X, float* C_f32, void* C_lp, int32_t* assign
             const int rep = timer_repeat();
             for (int r = 0; r < rep; ++r) {
                 if (t == FK_F32)
-                    FK_TRY(launch_assign(g, X, C_f32, nullptr, assign, nullptr, s, &w));
+                    FK_TRY(launch_assign(g, X, C_f32, nullptr, assign, nullptr, s, &w, split && r == 0));
                 else
                     FK_TRY(launch_assign(g, X, w.c_frag, w.c_bias, assign, nullptr, s));
             }
@@ -862,6 +864,14 @@ fk_status fk_lloyd_iter(const void* X, float* C_f32, void* C_lp, int32_t* assign
         fa.sums = nullptr;
         fa.accumulate = false;
         fa.normalise = true;
+        split = t == FK_F32 && !fused && it + 1 < iters && f32_filter_enabled(g);
+        if (split) {
+            fa.c_split = w.c_frag;
+            fa.shift = w.f32_shift;
+            fa.c2 = w.c_bias;
+            fa.list_len = w.f32_list_len;
+            fa.pair_len = w.f32_pair_len;
+        }
         if (fused) {
             FK_TRY(run_stream_update(g, w, X, assign, true, it + 1 == iters, fa, s));
         } else {

@@ -1307,12 +1307,12 @@ static fk_status launch_mfma_d(const Geometry& g, const void* X, const void* fra
 
 fk_status launch_assign(const Geometry& g, const void* X, const void* C_or_frag,
                         const float* c_bias, int32_t* assign, float* min_dist, hipStream_t s,
-                        const Workspace* w) {
+                        const Workspace* w, bool split) {
     if (g.t == FK_F16) return launch_mfma_d<false>(g, X, C_or_frag, c_bias, assign, min_dist, s);
     if (g.t == FK_BF16) return launch_mfma_d<true>(g, X, C_or_frag, c_bias, assign, min_dist, s);
     const float* Xf = (const float*)X;
     const float* Cf = (const float*)C_or_frag;
-    if (w && f32_filter_enabled(g)) return launch_f32_filter(g, *w, Xf, Cf, assign, min_dist, s);
+    if (w && f32_filter_enabled(g)) return launch_f32_filter(g, *w, Xf, Cf, assign, min_dist, split, s);
     if (g.d > 128) {
         auto kern = g.len == g.d ? assign_f32_wide_kernel<false> : assign_f32_wide_kernel<true>;
         hipLaunchKernelGGL(kern, dim3((unsigned)cdiv(g.N, 256), g.B), dim3(256), (size_t)16 * g.d * sizeof(float), s,

@@ -120,6 +120,9 @@ struct Workspace {
     float* sums;         // [B,K,d] accumulated sums (chunked mode)
     float* f32_shift;    // [B,dchunks*16] shift of the filtered fp32 assignment (fk_f32_filter.hip)
     int32_t* f32_list_len; // [B] points it has left open (the points themselves: sorted_idx)
+    int32_t* f32_pair_len; // [B] those of them that are open between two centroids; memory that the update in use does not read
+                           // while it clears this for the next assignment: an update without a sort has no segments, one that
+                           // sorts is done with its totals
     void* x_pad;         // [B,N,d] zero-padded copy of X            (only when needs_padded_rows)
     float* c_pad_f32;    // [B,K,d] zero-padded fp32 centroids       (likewise)
     void* c_pad_lp;      // [B,K,d] zero-padded centroids, dtype t   (likewise)
@@ -149,10 +152,11 @@ fk_status launch_round_centroids(const Geometry& g, const float* C_f32, void* C_
 // buffers and sorted_idx of it; without one (nullptr) the direct kernels.
 fk_status launch_assign(const Geometry& g, const void* X, const void* C_or_frag,
                         const float* c_bias, int32_t* assign, float* min_dist, hipStream_t s,
-                        const Workspace* w = nullptr);
+                        const Workspace* w = nullptr, bool split = false);
 // fp32: candidates from split bf16 products on the matrix cores, the open points by direct differences
+// (`split`: the last update has written the split centroids and cleared the lists, see FinalizeArgs)
 fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* X, const float* C,
-                            int32_t* assign, float* min_dist, hipStream_t s);
+                            int32_t* assign, float* min_dist, bool split, hipStream_t s);
 bool f32_filter_enabled(const Geometry& g);
 // Half workgroups (of 256 threads) that measure distances, `lanes` threads a point.  A launch dimension holds fewer
 // than 2^32 threads, which one point per group of 16 lanes reaches at 2^28 points.
@@ -216,6 +220,11 @@ struct FinalizeArgs {
     const int32_t* late_counts = nullptr;  // one after the other
     int late = 0;
     bool normalise;      // divide and write centroids
+    // fp32, filtered assignment next: its split centroids, which the first assignment of the call has laid out (NULL: not wanted)
+    void* c_split = nullptr;
+    const float* shift = nullptr;
+    float* c2 = nullptr;
+    int32_t *list_len = nullptr, *pair_len = nullptr;
 };
 // With wg_counts (few-cluster path) cluster k owns partial rows [k*G, (k+1)*G) and the counts
 // wg_counts[b][k][0..G) instead of what seg_off / item_off say (those may then be NULL).

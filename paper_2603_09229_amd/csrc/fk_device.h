@@ -127,6 +127,34 @@ __device__ __forceinline__ void load_row32(float (&x)[DMAX], const float* __rest
     }
 }
 
+// Of the filtered fp32 assignment (fk_f32_filter.hip): score bias that every real score loses to / that beats every real score, both
+// bf16 values; and the relative error of a score in units of |x'|^2 + |c'|^2 (derived there).
+constexpr uint16_t kNever = 0xFF62, kAlways = 0x7F62;      // -/+ 3.0e38
+
+__host__ __device__ constexpr float filter_kappa(int width) {
+    return 7.62939453125e-06f + (0.53f * (float)width + 24.f) * 1.1920929e-07f;
+}
+
+// The bias piece of a centroid with squared norm n2 after the shift: -n2 / 2 + kappa n2 as three bf16 values (24 bits), and the norm
+// that goes with it, from above.  A row whose norm overflows always wins with an infinite norm, so that no point is ever certain of
+// it; one that is not finite (or beyond K: `never`) never does.
+__device__ __forceinline__ uintx4 split_bias(double n2, int width, bool never, float* norm) {
+    const bool fine = !never && n2 < 1e38;                   // false for NaN too
+    uint16_t p[3] = {kNever, 0, 0};
+    if (fine) {
+        double left = (-0.5 + (double)filter_kappa(width)) * n2;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            p[q] = float_to_lp((float)left, true);
+            left -= (double)lp_to_float(p[q], true);
+        }
+    } else if (!never) {
+        p[0] = kAlways;
+    }
+    *norm = fine ? (float)(n2 * 1.000001) : never ? 0.f : INFINITY;
+    return uintx4{(uint32_t)p[0] | ((uint32_t)p[1] << 16), p[2], 0u, 0u};
+}
+
 // 32-bit LDS address of a pointer into shared memory (for hand-issued LDS instructions)
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
     return (uint32_t)(uintptr_t)((__attribute__((address_space(3))) const void*)p);

@@ -44,13 +44,6 @@ namespace {
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 
-// score bias that every real score loses to / that beats every real score; both are bf16 values
-constexpr uint16_t kNever = 0xFF62, kAlways = 0x7F62;      // -/+ 3.0e38
-
-__host__ __device__ constexpr float filter_kappa(int width) {
-    return 7.62939453125e-06f + (0.53f * (float)width + 24.f) * 1.1920929e-07f;
-}
-
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{a, b}, bf16x2));
 }
@@ -155,24 +148,13 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
         for (int o = 8; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
         if (c < 2) {
             const bool never = k >= K || odd_row[r] != 0;
-            const bool fine = !never && n2 < 1e38;           // false for NaN too
-            uint16_t p[3] = {kNever, 0, 0};
-            if (fine) {
-                double left = (-0.5 + (double)filter_kappa(width)) * n2;
-#pragma unroll
-                for (int q = 0; q < 3; ++q) {
-                    p[q] = float_to_lp((float)left, true);
-                    left -= (double)lp_to_float(p[q], true);
-                }
-            } else if (!never) {
-                p[0] = kAlways;
-            }
-            uintx4 v = {0u, 0u, 0u, 0u};
+            float norm;
+            uintx4 v = split_bias(n2, width, never, &norm);
             if (c == 0) {
-                v[0] = (uint32_t)p[0] | ((uint32_t)p[1] << 16);
-                v[1] = p[2];
-                fits[r] = fine;
-                c2[((size_t)b * ktiles + kt) * 32 + r] = fine ? (float)(n2 * 1.000001) : never ? 0.f : INFINITY;
+                fits[r] = !never && n2 < 1e38;
+                c2[((size_t)b * ktiles + kt) * 32 + r] = norm;
+            } else {
+                v = uintx4{0u, 0u, 0u, 0u};
             }
             frag[2 * dch * 64 + c * 32 + r] = v;
         }
@@ -1086,7 +1068,7 @@ bool f32_filter_enabled(const Geometry& g) {
 template <int DCH>
 static fk_status launch_filter_few(const Geometry& g, const Workspace& w, const float* X, int32_t* assign, float* min_dist, hipStream_t s) {
     hipLaunchKernelGGL(assign_f32_filter_few_kernel<DCH>, dim3((unsigned)cdiv(g.N, 32), g.B), dim3(few_waves(DCH) * 64), 0, s, X,
-                       (const uintx4*)w.c_frag, w.c_bias, w.f32_shift, assign, w.sorted_idx, w.f32_list_len, w.digit_off, (int32_t*)min_dist,
+                       (const uintx4*)w.c_frag, w.c_bias, w.f32_shift, assign, w.sorted_idx, w.f32_list_len, w.f32_pair_len, (int32_t*)min_dist,
                        g.N, g.d, g.len, g.K, g.ktiles);
     FK_HIP(hipGetLastError());
     return FK_OK;
@@ -1096,22 +1078,24 @@ template <int DCH, int WAVES>
 static fk_status launch_filter_t(const Geometry& g, const Workspace& w, const float* X, int32_t* assign, float* min_dist, hipStream_t s) {
     dim3 grid((unsigned)cdiv(g.N, WAVES * 32), g.B), block(WAVES * 64);
     hipLaunchKernelGGL((assign_f32_filter_kernel<DCH, WAVES>), grid, block, 0, s, X, (const uintx4*)w.c_frag,
-                       w.c_bias, w.f32_shift, assign, w.sorted_idx, w.f32_list_len, w.digit_off, (int32_t*)min_dist, g.N, g.d, g.len, g.K, g.ktiles);
+                       w.c_bias, w.f32_shift, assign, w.sorted_idx, w.f32_list_len, w.f32_pair_len, (int32_t*)min_dist, g.N, g.d, g.len, g.K, g.ktiles);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }
 
 fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* X, const float* C, int32_t* assign,
-                            float* min_dist, hipStream_t s) {
+                            float* min_dist, bool split, hipStream_t s) {
     // (groups of eight features a thread, 32 rows of them to a workgroup)
     const int per = (int)cdiv(64 * g.dchunks, kLayoutThreads);
 #define FK_LAYOUT(RAGGED) (per == 1 ? f32_split_layout_kernel<1, RAGGED> : per == 2 ? f32_split_layout_kernel<2, RAGGED> \
                            : per == 3 ? f32_split_layout_kernel<3, RAGGED> : f32_split_layout_kernel<4, RAGGED>)
     auto layout = g.len == g.d ? FK_LAYOUT(false) : FK_LAYOUT(true);
 #undef FK_LAYOUT
-    hipLaunchKernelGGL(layout, dim3(g.ktiles, g.B), dim3(kLayoutThreads), 0, s, C, (uintx4*)w.c_frag, w.c_bias,
-                       w.f32_shift, w.f32_list_len, w.digit_off, g.d, g.len, g.K, g.ktiles, g.dchunks);
-    FK_HIP(hipGetLastError());
+    if (!split) {
+        hipLaunchKernelGGL(layout, dim3(g.ktiles, g.B), dim3(kLayoutThreads), 0, s, C, (uintx4*)w.c_frag, w.c_bias,
+                           w.f32_shift, w.f32_list_len, w.f32_pair_len, g.d, g.len, g.K, g.ktiles, g.dchunks);
+        FK_HIP(hipGetLastError());
+    }
     // Workgroups of four waves fill the chip best; with very many points eight waves share each
     // copy of the centroids (2^20 points, 64 features, K = 256: 138 against 142 us; 128 features, K =
     // 64: 172 against 182 us) as long as two such workgroups fit a compute unit.
@@ -1140,7 +1124,7 @@ fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* 
                                                                           : assign_f32_list_kernel<0>;
     const int64_t distances = min_dist ? cdiv(f32_distance_blocks(g.N, distance_lanes(g.len)), g.d <= 128 ? 8 : 4) : 0;
     hipLaunchKernelGGL(list_kernel, dim3((unsigned)(G + distances), g.B), dim3(512), 0, s, X, C, w.sorted_idx,
-                       w.f32_list_len, w.digit_off, assign, min_dist, g.N, g.d, g.len, g.K, f32_direct_is_split(g) ? g.K - 1 : 0, (int)G);
+                       w.f32_list_len, w.f32_pair_len, assign, min_dist, g.N, g.d, g.len, g.K, f32_direct_is_split(g) ? g.K - 1 : 0, (int)G);
     FK_HIP(hipGetLastError());
     return FK_OK;
 }

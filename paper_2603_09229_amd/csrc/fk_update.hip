@@ -184,7 +184,45 @@ struct EmitTo {
     const float* late_sums;
     const int32_t* late_counts;
     int d, K, B, ktiles, dch, accumulate, normalise, bf, late, row_len;
+    // fp32: the split centroids of the filtered assignment (fk_f32_filter.hip) with the shift they were given at the
+    // start of the call, c2 their norms; the lengths of its lists, which the next assignment starts from
+    uint16_t* c_split;
+    const float* shift;
+    float* c2;
+    int32_t *list_len, *pair_len;
 };
+
+// Row k of the split centroids, from its shifted values in `row` (d floats of LDS, not yet behind a barrier): what
+// f32_split_layout_kernel writes for it, so that the next assignment of the call needs no launch of that kernel (5 to 8 us).  Rows beyond
+// K and features beyond d keep what the first assignment's launch wrote there, and so does the shift, which only has to be near the
+// data: the centroids move, their mean hardly.
+__device__ __forceinline__ void emit_split(const EmitTo& to, int b, int k, const float* row, bool odd) {
+    const int tid = threadIdx.x, d = to.d, T = (int)blockDim.x;
+    __shared__ int fits;
+    uint16_t* tile = to.c_split + ((size_t)b * to.ktiles + (k >> 5)) * (2 * to.dch + 1) * 512;
+    const int never = __syncthreads_or(odd);
+    if (tid < 64) {
+        double n2 = 0.0;
+        for (int j = tid; j < d; j += 64) n2 += (double)row[j] * (double)row[j];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
+        if (tid == 0) {
+            float norm;
+            *(uintx4*)(tile + (2 * to.dch * 64 + (k & 31)) * 8) = split_bias(n2, to.dch * 16, never != 0, &norm);
+            to.c2[(size_t)b * to.ktiles * 32 + k] = norm;
+            fits = !never && n2 < 1e38;
+            if (k == 0) { to.list_len[b] = 0; to.pair_len[b] = 0; }
+        }
+    }
+    __syncthreads();
+    for (int j = tid; j < d; j += T) {
+        const float v = fits ? row[j] : 0.f;
+        const uint16_t hi = float_to_lp(v, true), lo = float_to_lp(v - lp_to_float(hi, true), true);
+        uint16_t* at = tile + (2 * (j >> 4) * 64 + (((j >> 3) & 1) << 5) + (k & 31)) * 8 + (j & 7);
+        at[0] = hi;
+        at[512] = lo;
+    }
+}
 
 // The end of an update, by the whole workgroup: cluster k of instance b has n points (late ones not among
 // them yet), sum_of(j) is the sum of their feature j.  Optionally added onto sums/counts already stored
@@ -192,13 +230,14 @@ struct EmitTo {
 // normalised into centroids (Algorithm 3, last loop; an empty cluster keeps its previous
 // centroid).  When c_frag is given, the rounded centroid is also
 // written in MFMA fragment order together with its score bias -||c||^2/2, so the next
-// assignment needs no separate re-layout pass.  nrm: d floats of LDS.
-template <bool kLate, bool RAGGED, class Sum>
+// assignment needs no separate re-layout pass; kSplit: so are fp32 ones (emit_split).  nrm: d floats of LDS.
+template <bool kLate, bool RAGGED, bool kSplit, class Sum>
 __device__ __forceinline__ void emit_centroid(const EmitTo& to, int b, int k, int n, float* nrm, Sum sum_of) {
     const int tid = threadIdx.x, d = to.d, K = to.K, T = (int)blockDim.x;
     const int len = RAGGED ? to.row_len : d;
     if constexpr (kLate)
         for (int q = 0; q < to.late; ++q) n += to.late_counts[((size_t)q * to.B + b) * K + k];
+    bool odd = false;
     for (int j = tid; j < d; j += T) {
         float s = sum_of(j);
         const size_t o = ((size_t)b * K + k) * d + j;
@@ -224,6 +263,10 @@ __device__ __forceinline__ void emit_centroid(const EmitTo& to, int b, int k, in
                 const float f = lp_to_float(lp, to.bf);
                 nrm[j] = __fmul_rn(f, f);
             }
+            if (kSplit && to.c_split) {
+                nrm[j] = j < len ? c - to.shift[(size_t)b * to.dch * 16 + j] : 0.f;
+                odd |= !(fabsf(c) < INFINITY);
+            }
         }
     }
     if (tid == 0) to.counts[(size_t)b * K + k] = n;
@@ -242,6 +285,7 @@ __device__ __forceinline__ void emit_centroid(const EmitTo& to, int b, int k, in
             if (tid == 0) to.c_bias[((size_t)b * to.ktiles) * 32 + k] = -0.5f * n2;
         }
     }
+    if (kSplit && to.c_split) emit_split(to, b, k, nrm, odd);
 }
 
 // One workgroup (256 threads, or 1024 when clusters have many items) per cluster: s_k = sum
@@ -319,7 +363,7 @@ __global__ __launch_bounds__(1024) void finalize_kernel(
     } else {
         n += seg_off[k + 1] - seg_off[k];
     }
-    emit_centroid<kLate, RAGGED>(to, b, k, n, nrm, [&](int j) {
+    emit_centroid<kLate, RAGGED, true>(to, b, k, n, nrm, [&](int j) {
         float s = 0.f;
         for (int q = 0; q < sums_left; ++q) s += red[q * dpow + j];   // fixed order
         return s;
@@ -517,7 +561,7 @@ __global__ __launch_bounds__(WAVES * 64) void gather_update_kernel(
         if (tid == 0) wg_counts[row] = n - n_prev;
         return;
     }
-    emit_centroid<false, RAGGED>(to, b, k, n, nrm, sum_of);
+    emit_centroid<false, RAGGED, EPL == 4>(to, b, k, n, nrm, sum_of);
 }
 
 // ------------------------------------------------------------------------------------
@@ -598,6 +642,11 @@ static EmitTo emit_args(const Geometry& g, const FinalizeArgs& a) {
     to.bf = g.t == FK_BF16 ? 1 : 0;
     to.late = a.late;
     to.row_len = g.len;
+    to.c_split = (uint16_t*)a.c_split;
+    to.shift = a.shift;
+    to.c2 = a.c2;
+    to.list_len = a.list_len;
+    to.pair_len = a.pair_len;
     return to;
 }
 
