@@ -5,6 +5,7 @@
 // and segment reduction on the other buffer.  Events order the two streams:
 //   ready[i]  copy into buffer i finished      (compute waits)
 //   freed[i]  compute on buffer i finished     (the next copy into i waits)
+// (Small calls copy on the compute stream instead, see below.)
 // An iteration after the first starts with the two chunks that are still in the buffers, which saves
 // two copies per iteration (all of them with at most two chunks).  The call is bound by its copies
 // below about K = 3000 (57 GB/s from the host: 8 chunks of 2^18 x 128 fp16, K = 1024, two
@@ -15,8 +16,36 @@
 // order in which the chunks are taken -- those of the chunks taken early wait in two arrays of their
 // own until their turn -- so that a call of n iterations gives the bits of n calls of one.
 #include "fk_common.h"
+#include "fk_device.h"
 
 namespace fk {
+
+// Pinned host memory, read over the host link: every thread asks for up to four pieces at once.
+template <typename Piece>
+__global__ __launch_bounds__(256) void copy_bytes_kernel(const Piece* __restrict__ src, Piece* __restrict__ dst, uint32_t n) {
+    const uint32_t step = gridDim.x * 256;
+    for (uint32_t i0 = blockIdx.x * 256 + threadIdx.x; i0 < n; i0 += 4 * step) {
+        Piece v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i0 + u * step < n) v[u] = src[i0 + u * step];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i0 + u * step < n) dst[i0 + u * step] = v[u];
+    }
+}
+
+static fk_status launch_copy_bytes(const void* src, void* dst, size_t bytes, hipStream_t s) {
+    const size_t aligned = ((uintptr_t)src | bytes) & 15;    // dst is a chunk buffer, and rows are whole elements
+    const size_t piece = aligned == 0 ? 16 : (aligned & 3) == 0 ? 4 : 2;
+    const uint32_t n = (uint32_t)(bytes / piece);
+    const dim3 grid((unsigned)std::min<uint32_t>((n + 255) / 256, 1024));
+    if (piece == 16) hipLaunchKernelGGL(copy_bytes_kernel<uintx4>, grid, dim3(256), 0, s, (const uintx4*)src, (uintx4*)dst, n);
+    else if (piece == 4) hipLaunchKernelGGL(copy_bytes_kernel<uint32_t>, grid, dim3(256), 0, s, (const uint32_t*)src, (uint32_t*)dst, n);
+    else hipLaunchKernelGGL(copy_bytes_kernel<uint16_t>, grid, dim3(256), 0, s, (const uint16_t*)src, (uint16_t*)dst, n);
+    FK_HIP(hipGetLastError());
+    return FK_OK;
+}
 
 struct OocLayout {
     size_t chunk_bytes;   // one chunk buffer
@@ -144,6 +173,20 @@ fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_
     float* const C_user = C_f32;
 
     hipStream_t cs = (hipStream_t)stream;
+    // Copies beside the kernels need a stream and events: some 95 us to make and to give back, and waits
+    // in every chunk.  One chunk has nothing to be copied beside; and where all copies of the call are a
+    // few MiB they take less than that: they go to the caller's stream, read by a kernel, which starts
+    // sooner than a copy engine.  us, beside / so: 1000 points, d = 32, K = 8 120 / 38; 24533, d = 32,
+    // K = 13 in three chunks 209 / 114, in eight 360 / 158; 2230 fp32, d = 512, K = 16, two iterations of
+    // eight, 9 MiB 763 / 649; 16000, d = 256, K = 100, 8 MiB 312 / 280; 40000, d = 200, K = 100, 15 MiB
+    // 511 / 505; 200000, d = 64 in one chunk, 24 MiB by the copy engine 595 / 532.
+    const size_t copied = (size_t)N * row_bytes * (size_t)(nchunks == 1 ? 1 : iters);
+    const void* X_dev = nullptr;
+    if (!pad && copied <= ((size_t)16 << 20) && hipHostGetDevicePointer((void**)&X_dev, (void*)X_host, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        X_dev = nullptr;
+    }
+    const bool beside = !X_dev && (pad || nchunks > 1);
     hipStream_t side = nullptr;
     hipEvent_t ready[2] = {nullptr, nullptr}, freed[2] = {nullptr, nullptr};
     fk_status st = FK_OK;
@@ -174,8 +217,8 @@ fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_
         }                                                  \
     } while (0)
 
-    OOC_HIP(hipStreamCreateWithFlags(&side, hipStreamNonBlocking));
-    for (int i = 0; i < 2; ++i) {
+    if (beside) OOC_HIP(hipStreamCreateWithFlags(&side, hipStreamNonBlocking));
+    for (int i = 0; beside && i < 2; ++i) {
         OOC_HIP(hipEventCreateWithFlags(&ready[i], hipEventDisableTiming));
         OOC_HIP(hipEventCreateWithFlags(&freed[i], hipEventDisableTiming));
     }
@@ -205,18 +248,20 @@ fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_
             const int64_t rows = (N - r0) < chunk_rows ? (N - r0) : chunk_rows;
             if (held[bi] != c) {
                 // side stream: refill buffer bi once its previous consumer is done
-                if (used[bi]) OOC_HIP(hipStreamWaitEvent(side, freed[bi], 0));
-                if (pad)
+                if (beside && used[bi]) OOC_HIP(hipStreamWaitEvent(side, freed[bi], 0));
+                if (X_dev)
+                    OOC_TRY(launch_copy_bytes((const char*)X_dev + (size_t)r0 * row_bytes, xbuf[bi], (size_t)rows * row_bytes, cs));
+                else if (pad)
                     OOC_HIP(hipMemcpy2DAsync(xbuf[bi], dev_row_bytes, (const char*)X_host + (size_t)r0 * row_bytes,
                                              row_bytes, row_bytes, (size_t)rows, hipMemcpyHostToDevice, side));
                 else
                     OOC_HIP(hipMemcpyAsync(xbuf[bi], (const char*)X_host + (size_t)r0 * row_bytes,
-                                           (size_t)rows * row_bytes, hipMemcpyHostToDevice, side));
-                OOC_HIP(hipEventRecord(ready[bi], side));
+                                           (size_t)rows * row_bytes, hipMemcpyHostToDevice, beside ? side : cs));
+                if (beside) OOC_HIP(hipEventRecord(ready[bi], side));
                 held[bi] = c;
             }
             // compute stream
-            OOC_HIP(hipStreamWaitEvent(cs, ready[bi], 0));
+            if (beside) OOC_HIP(hipStreamWaitEvent(cs, ready[bi], 0));
             // A shorter tail chunk keeps the full chunk's tiling parameters and buffers
             // (every buffer is sized for chunk_rows); only the row-dependent counts shrink.
             Geometry g = gfull;
@@ -254,12 +299,12 @@ fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_
                 OOC_TRY(launch_segment_reduce(g, w, xbuf[bi], w.sorted_idx, w.seg_off, w.item_off, cs));
                 OOC_TRY(launch_finalize(g, w, w.seg_off, w.item_off, fa, cs));
             }
-            OOC_HIP(hipEventRecord(freed[bi], cs));
+            if (beside) OOC_HIP(hipEventRecord(freed[bi], cs));
             used[bi] = true;
         }
     }
     if (pad) OOC_TRY(launch_copy_rows(C_f32, C_user, K, gfull.d, gfull.d_user, 4, cs));
-    OOC_HIP(hipStreamSynchronize(side));
+    if (beside) OOC_HIP(hipStreamSynchronize(side));
     OOC_HIP(hipStreamSynchronize(cs));
     cleanup();
     return FK_OK;
