@@ -208,9 +208,9 @@ Workspace carve(const Geometry& g, void* base, bool padded_x) {
     w.block_hist = (int32_t*)take((size_t)g.B * g.sort_blocks * nbmax * 4);
     w.digit_off = (int32_t*)take((size_t)g.B * 2049 * 4);
     if (g.sort_passes == 2) {
-        w.keys_tmp = (int32_t*)take(BN * 4);
+        w.keys_tmp = (uint16_t*)take(BN * 4);
         w.vals_tmp = (int32_t*)take(BN * 4);
-        w.keys_sorted = (int32_t*)take(BN * 4);
+        w.keys_sorted = (uint16_t*)take(BN * 4);
     }
     const size_t sort_end = off;
     (void)sort_end;

@@ -111,9 +111,9 @@ struct Workspace {
     int32_t* item_off;   // [B,K+1] exclusive scan of ceil(n_k / R)
     int32_t* block_hist; // [B,bins,sort_blocks] per-workgroup digit histograms
     int32_t* digit_off;  // [B,2048+1] digit offsets of the current radix pass
-    int32_t* keys_tmp;   // [B,N] keys after pass 1 (two-pass sort only)
+    uint16_t* keys_tmp;  // [B,N] keys after pass 1 (two-pass sort only)
     int32_t* vals_tmp;   // [B,N] values after pass 1 (two-pass sort only)
-    int32_t* keys_sorted;// [B,N] sorted keys (two-pass sort only)
+    uint16_t* keys_sorted;// [B,N] sorted keys (two-pass sort only)
     float* partial;      // [B,max(max_items, K*(largest one-pass grid cap)),d] per-item segment sums
     int32_t* wg_counts;  // [B,K,grid cap] per-workgroup counts (one-pass updates only)
     int32_t* gather_counts;  // [B,K,gather_parts] the same of an update without a sort

@@ -125,8 +125,8 @@ __device__ void block_scan_tables(int* v, int n, int* scratch, int R, int32_t* s
 constexpr int kSubTile = 4096;
 
 // Keys come back clamped to [0, kmax]; -1 marks a lane past the end of the array.
-template <int kBatches>
-__device__ __forceinline__ void load_round(const int32_t* __restrict__ keys, int64_t base,
+template <int kBatches, typename Key>
+__device__ __forceinline__ void load_round(const Key* __restrict__ keys, int64_t base,
                                            int64_t N, int lane, int kmax, int (&k)[kBatches]) {
 #pragma unroll
     for (int j = 0; j < kBatches; ++j) {
@@ -142,9 +142,9 @@ __device__ __forceinline__ void load_round(const int32_t* __restrict__ keys, int
 
 // Per-workgroup digit histogram, written transposed, H[b][bin][blk], for the scan kernel, or
 // (by_block) H[b][blk][bin] for scatter workgroups that add the earlier ones' up themselves.
-template <int kSortWaves>
+template <int kSortWaves, typename Key>
 __global__ __launch_bounds__(kSortWaves * 64) void sort_hist_kernel(
-    const int32_t* __restrict__ keys, int32_t* __restrict__ H, int64_t N, int rounds, int NB,
+    const Key* __restrict__ keys, int32_t* __restrict__ H, int64_t N, int rounds, int NB,
     int shift, int mask, int kmax, int nbits, int by_block) {
     constexpr int kSortThreads = kSortWaves * 64, kBatches = kSubTile / kSortThreads;
     extern __shared__ int lds[];
@@ -234,11 +234,14 @@ __global__ __launch_bounds__(256) void sort_binscan_kernel(int32_t* __restrict__
 // tables of the first workgroup in one scan, and each loop over LDS reads before it writes.
 //   keys_out may be NULL.  seg_off / item_off are written by workgroup 0 when non-NULL
 //   (single-pass sort: bins are cluster ids, so the bin offsets are the segment table).
-template <int kSortWaves, bool kScans>
+//   Key: the ids as the caller has them, or the 16-bit copies (K is at most 65536) that a first pass leaves for the second:
+//   2^23 keys, K = 4096, both histograms, both scatters, boundaries 27 + 73 + 11 us -> 20 + 61 + 6; fk_update, d = 128, there
+//   491 -> 478, 2^25 x 16 1137 -> 1027, 30000 x 64, K = 5000 43.0 -> 40.6.
+template <int kSortWaves, bool kScans, typename Key>
 __global__ __launch_bounds__(kSortWaves * 64, kSortWaves == 8 ? 6 : 1) void sort_scatter_kernel(
-    const int32_t* __restrict__ keys, const int32_t* __restrict__ vals_in,
+    const Key* __restrict__ keys, const int32_t* __restrict__ vals_in,
     const int32_t* __restrict__ H, const int32_t* __restrict__ tot,
-    int32_t* __restrict__ vals_out, int32_t* __restrict__ keys_out,
+    int32_t* __restrict__ vals_out, uint16_t* __restrict__ keys_out,
     int32_t* __restrict__ seg_off, int32_t* __restrict__ item_off, int64_t N, int rounds,
     int NB, int shift, int mask, int kmax, int nbits, int R, int staged, int solo) {
     constexpr int kSortThreads = kSortWaves * 64, kBatches = kSubTile / kSortThreads;
@@ -422,7 +425,7 @@ __global__ __launch_bounds__(kSortWaves * 64, kSortWaves == 8 ? 6 : 1) void sort
             for (int j = 0; j < kBatches; ++j) {
                 if (tid + j * kSortThreads < live) {
                     vals_out[pos[j]] = info[j];
-                    if (keys_out) keys_out[pos[j]] = k[j];
+                    if (keys_out) keys_out[pos[j]] = (uint16_t)k[j];
                 }
             }
             return;
@@ -452,7 +455,7 @@ __global__ __launch_bounds__(kSortWaves * 64, kSortWaves == 8 ? 6 : 1) void sort
             if (k[j] >= 0) {
                 const int pos = start[j] + pre[j] + info[j];
                 vals_out[pos] = vals_in ? v[j] : (int32_t)(base0 + j * 64 + lane);
-                if (keys_out) keys_out[pos] = k[j];
+                if (keys_out) keys_out[pos] = (uint16_t)k[j];
             }
         }
         return;
@@ -528,7 +531,7 @@ __global__ __launch_bounds__(kSortWaves * 64, kSortWaves == 8 ? 6 : 1) void sort
             __builtin_amdgcn_wave_barrier();
             if (valid) {
                 vals_out[pos] = vals_in ? v[j] : (int32_t)(base + j * 64 + lane);
-                if (keys_out) keys_out[pos] = key;
+                if (keys_out) keys_out[pos] = (uint16_t)key;
                 if (rank == 0) mine[digit] += cnt;
             }
             __builtin_amdgcn_wave_barrier();
@@ -538,18 +541,28 @@ __global__ __launch_bounds__(kSortWaves * 64, kSortWaves == 8 ? 6 : 1) void sort
 
 // Two-pass sort only: segment table from the sorted id sequence.  Position j opens the
 // segments of every id in (ks[j-1], ks[j]]; ids above the last key get N.
-__global__ void sort_boundaries_kernel(const int32_t* __restrict__ ks,
-                                       int32_t* __restrict__ seg_off, int64_t N, int K) {
+constexpr int kBoundaryKeys = 1024;      // of a workgroup: four of each thread, requested together
+__global__ __launch_bounds__(256) void sort_boundaries_kernel(const uint16_t* __restrict__ ks,
+                                                              int32_t* __restrict__ seg_off, int64_t N, int K) {
     const int b = blockIdx.y;
     ks += (size_t)b * N;
     seg_off += (size_t)b * (K + 1);
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= N) return;
-    const int cur = ks[j];
-    const int prev = j == 0 ? -1 : ks[j - 1];
-    for (int k = prev + 1; k <= cur; ++k) seg_off[k] = (int32_t)j;
-    if (j == N - 1)
-        for (int k = cur + 1; k <= K; ++k) seg_off[k] = (int32_t)N;
+    const int64_t j0 = (int64_t)blockIdx.x * kBoundaryKeys + threadIdx.x;
+    int cur[kBoundaryKeys / 256], prev[kBoundaryKeys / 256];
+#pragma unroll
+    for (int u = 0; u < kBoundaryKeys / 256; ++u) {
+        const int64_t j = j0 + u * 256;
+        cur[u] = j < N ? ks[j] : 0;
+        prev[u] = j < N && j > 0 ? ks[j - 1] : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < kBoundaryKeys / 256; ++u) {
+        const int64_t j = j0 + u * 256;
+        if (j >= N) break;
+        for (int k = prev[u] + 1; k <= cur[u]; ++k) seg_off[k] = (int32_t)j;
+        if (j == N - 1)
+            for (int k = cur[u] + 1; k <= K; ++k) seg_off[k] = (int32_t)N;
+    }
 }
 
 // Two-pass sort only: item_off = exclusive scan of ceil(n_k / R) for K up to 65536.
@@ -587,8 +600,9 @@ static std::atomic<int> g_stage_max_bins{1024};
 
 void set_sort_stage_bins(int v) { g_stage_max_bins.store(v < 0 ? 1024 : v, std::memory_order_relaxed); }
 
-static fk_status sort_pass(const Geometry& g, const Workspace& w, const int32_t* keys,
-                           const int32_t* vals_in, int32_t* vals_out, int32_t* keys_out,
+template <typename Key>
+static fk_status sort_pass(const Geometry& g, const Workspace& w, const Key* keys,
+                           const int32_t* vals_in, int32_t* vals_out, uint16_t* keys_out,
                            int32_t* seg_off, int32_t* item_off, int NB, int shift, int mask,
                            hipStream_t s) {
     const int nbits = ceil_log2(NB) < 1 ? 1 : ceil_log2(NB);
@@ -596,17 +610,19 @@ static fk_status sort_pass(const Geometry& g, const Workspace& w, const int32_t*
     int32_t* H = w.block_hist;
     int32_t* tot = w.digit_off;
     dim3 grid(g.sort_blocks, g.B);
-    const bool wide = NB > 1024;       // 8 waves of counters would not fit in LDS
+    // 8 waves of counters would not fit in LDS (ids as they come only: a second pass has at most 256 bins)
+    constexpr int kWide = sizeof(Key) == 4 ? 4 : 8;
+    const bool wide = kWide == 4 && NB > 1024;
     // one workgroup per instance: the scatter kernel counts for itself
     const int solo = g.sort_blocks == 1 ? 1 : 0;
     const int by_block = rounds == 1 && sort_scatter_scans(g.B, g.sort_blocks, NB) ? 1 : 0;
     if (!solo) {
         const size_t hist_lds = (size_t)NB * (NB <= 64 ? 16 : 1) * sizeof(int);
         if (wide)
-            hipLaunchKernelGGL(sort_hist_kernel<4>, grid, dim3(256), hist_lds, s, keys, H, g.N,
+            hipLaunchKernelGGL((sort_hist_kernel<kWide, Key>), grid, dim3(256), hist_lds, s, keys, H, g.N,
                                rounds, NB, shift, mask, g.K - 1, nbits, by_block);
         else
-            hipLaunchKernelGGL(sort_hist_kernel<8>, grid, dim3(512), hist_lds, s, keys, H, g.N,
+            hipLaunchKernelGGL((sort_hist_kernel<8, Key>), grid, dim3(512), hist_lds, s, keys, H, g.N,
                                rounds, NB, shift, mask, g.K - 1, nbits, by_block);
         FK_HIP(hipGetLastError());
         if (!by_block && g.sort_blocks > 512)
@@ -624,7 +640,7 @@ static fk_status sort_pass(const Geometry& g, const Workspace& w, const int32_t*
     // 2x on the 64..256-bin passes of the two-pass sort.
     const int staged = rounds == 1 && NB >= 32 && NB <= g_stage_max_bins.load(std::memory_order_relaxed) ? 1 : 0;
     const size_t lds = (size_t)(NB + 40 + waves * NB + (staged ? NB + 2 * kSubTile : 0)) * sizeof(int);
-    auto kern = wide ? sort_scatter_kernel<4, false> : by_block ? sort_scatter_kernel<8, true> : sort_scatter_kernel<8, false>;
+    auto kern = wide ? sort_scatter_kernel<kWide, false, Key> : by_block ? sort_scatter_kernel<8, true, Key> : sort_scatter_kernel<8, false, Key>;
     if (lds > 64 * 1024) {
         static PerDeviceInt attr_set[3];
         PerDeviceInt& set = attr_set[wide ? 0 : 1 + by_block];
@@ -652,7 +668,7 @@ fk_status launch_sort_inverse(const Geometry& g, const Workspace& w, const int32
     st = sort_pass(g, w, w.keys_tmp, w.vals_tmp, sorted_idx, w.keys_sorted, nullptr, nullptr,
                    1 << hb, lb, (1 << hb) - 1, s);
     if (st != FK_OK) return st;
-    hipLaunchKernelGGL(sort_boundaries_kernel, dim3((unsigned)cdiv(g.N, 256), g.B), dim3(256), 0,
+    hipLaunchKernelGGL(sort_boundaries_kernel, dim3((unsigned)cdiv(g.N, kBoundaryKeys), g.B), dim3(256), 0,
                        s, w.keys_sorted, seg_off, g.N, g.K);
     FK_HIP(hipGetLastError());
     if (item_off) {

@@ -1,0 +1,45 @@
+"""More clusters than one sort pass takes (K > 2048): ids up to the largest in 16 bits, points and clusters around the shares of
+a workgroup of the boundary and item kernels (1024 each, csrc/fk_sort.hip), odd batch offsets, and the update over the tables."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_09229_amd import binding as fk
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _labels(B, N, K, seed):
+    g = torch.Generator().manual_seed(seed)
+    a = torch.randint(0, K, (B, N), generator=g)
+    a[torch.rand((B, N), generator=g) < 0.3] = K - 1        # the largest id, many items
+    a[a == 1024] = 1023                                     # an empty cluster at a share's edge
+    return a.to(torch.int32)
+
+
+@pytest.mark.parametrize("B,N,K", [(1, 1, 65536), (3, 1023, 2049), (3, 1025, 65536), (1, 4096, 3072), (3, 4097, 65535), (1, 70001, 3073),
+                                   (2, 50001, 65536)])
+def test_sort_with_many_clusters(B, N, K):
+    a = _labels(B, N, K, N + K)
+    idx, off = fk.fk_sort_inverse(a.to(DEV), K)
+    for b in range(B):
+        assert np.array_equal(idx[b].cpu().numpy(), np.argsort(a[b].numpy(), kind="stable"))
+        assert off[b].tolist() == [0] + torch.bincount(a[b], minlength=K).cumsum(0).tolist()
+
+
+@pytest.mark.parametrize("B,N,d,K", [(2, 30001, 16, 2049), (1, 50000, 24, 3072), (1, 50000, 24, 3073), (2, 40001, 8, 65536)])
+def test_update_with_many_clusters(B, N, d, K):
+    a = _labels(B, N, K, N)
+    g = torch.Generator().manual_seed(K)
+    X = torch.randn((B, N, d), generator=g).half()
+    C0 = torch.randn((B, K, d), generator=g)
+    C, _, n = fk.fk_update(X.to(DEV), a.to(DEV), C0.to(DEV))
+    for b in range(B):
+        cnt = torch.bincount(a[b], minlength=K)
+        assert torch.equal(n[b].cpu().long(), cnt)
+        s = torch.zeros((K, d), dtype=torch.float64).index_add_(0, a[b].long(), X[b].double())
+        ref = torch.where(cnt[:, None] > 0, s / cnt.clamp(min=1)[:, None], C0[b].double())
+        size = torch.zeros((K, d), dtype=torch.float64).index_add_(0, a[b].long(), X[b].double().abs()) / cnt.clamp(min=1)[:, None]
+        # sums of n terms: at most n 2^-24 of their sizes' sum, and one rounding each of 1 / n and of the product
+        assert ((C[b].cpu().double() - ref).abs() <= (cnt[:, None] + 3) * 2.0 ** -24 * size).all()
