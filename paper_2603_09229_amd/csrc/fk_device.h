@@ -13,6 +13,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t uintx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t uintx2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
 // the same 16 bytes at any element's address
 typedef uint32_t uintx4_any __attribute__((ext_vector_type(4), aligned(2)));
 typedef float floatx4_any __attribute__((ext_vector_type(4), aligned(4)));

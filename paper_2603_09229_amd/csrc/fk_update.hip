@@ -677,10 +677,109 @@ fk_status launch_gather_update(const Geometry& g, const Workspace& w, const void
     return (wide ? launch_gather_w<8, true, 8> : launch_gather_w<8, true, 4>)(g, w, X, assign, to, G, merged, s);
 }
 
+// The same for many clusters of few partial rows each (see launch_finalize), in core: a wave per cluster and
+// four to a workgroup, sums, centroid and squared norm in registers, so that every read and write is one
+// instruction and no barrier lies in the chain of latencies that bounds this.  32 instances, d = 64, K = 8192 132 us -> 93; 32, d = 128, K = 256, eight rows each 14.2 -> 11.6.
+__global__ __launch_bounds__(256) void finalize_wave_kernel(const float* __restrict__ partial, const int32_t* __restrict__ seg_off,
+                                                            const int32_t* __restrict__ item_off, EmitTo to, int R, float balance,
+                                                            int64_t max_items, const int32_t* __restrict__ wg_counts, int G) {
+    const int d = to.d, K = to.K, lane = threadIdx.x & 63;
+    const int b = blockIdx.y, k = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    if (k >= K) return;
+    int lr_log2 = 0;
+    while ((4 << lr_log2) < d) ++lr_log2;
+    const int LR = 1 << lr_log2, slots = 64 >> lr_log2, slot = lane >> lr_log2, col = (lane & (LR - 1)) * 4;
+    int i0, i1, n;
+    if (wg_counts) {
+        i0 = k * G;
+        i1 = i0 + G;
+        n = 0;
+        for (int g = lane; g < G; g += 64) n += wg_counts[((size_t)b * K + k) * G + g];
+    } else {
+        seg_off += (size_t)b * (K + 1);
+        item_off += (size_t)b * (K + 1);
+        i0 = item_off[k];
+        n = seg_off[k + 1] - seg_off[k];
+        const int length = item_length(n, R, balance);
+        i1 = length == R ? item_off[k + 1] : i0 + (n + length - 1) / length;
+    }
+    // eight rows in flight per lane, the eight sums and then the slots' added in a fixed order
+    const float* P = partial + (size_t)b * max_items * d;
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    if (col < d) {
+        floatx4 a8[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) a8[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int it = i0 + slot; it < i1; it += 8 * slots) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int r = it + u * slots;
+                if (r < i1) a8[u] += *(const floatx4*)(P + (size_t)r * d + col);
+            }
+        }
+        acc = ((a8[0] + a8[1]) + (a8[2] + a8[3])) + ((a8[4] + a8[5]) + (a8[6] + a8[7]));
+    }
+    if (wg_counts)
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
+    for (int o = 1; o < slots && (o == 1 || o < i1 - i0); o <<= 1) {      // (slots 0 and 1 end with all)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o << lr_log2);
+    }
+    // each of them ends two of a lane's four features
+    const bool second = (slot & 1) != 0, mine = slot < 2 && col < d;
+    const int j = col + (second ? 2 : 0);
+    const size_t at = ((size_t)b * K + k) * d + j;
+    floatx2 c = {0.f, 0.f};
+    if (n > 0) {
+        c[0] = (float)((double)(second ? acc[2] : acc[0]) / (double)n);
+        c[1] = (float)((double)(second ? acc[3] : acc[1]) / (double)n);
+    } else if (mine) {
+        c = *(const floatx2*)(to.C_prev + at);
+    }
+    const uint16_t lp[2] = {float_to_lp(c[0], to.bf), float_to_lp(c[1], to.bf)};
+    const uint32_t packed = lp[0] | (uint32_t)lp[1] << 16;
+    if (mine) {
+        *(floatx2*)(to.C_out + at) = c;
+        if (to.C_lp_out) *(uint32_t*)(to.C_lp_out + at) = packed;
+        if (to.C_lp_f32_out) *(floatx2*)(to.C_lp_f32_out + at) = c;
+    }
+    if (lane == 0) to.counts[(size_t)b * K + k] = n;
+    if (!to.c_frag) return;
+    if (mine)      // fragment order, see emit_centroid
+        *(uint32_t*)(to.c_frag + ((((size_t)b * to.ktiles + (k >> 5)) * to.dch + (j >> 4)) * 64 + (((j >> 3) & 1) << 5) + (k & 31)) * 8 +
+                     (j & 7)) = packed;
+    // the norm as emit_centroid adds it: groups of 8 features one after the other (of an even lane's slots 0 and 1, then of its odd
+    // neighbour's), then the groups in order
+    float sq[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const float f = lp_to_float(lp[e], to.bf);
+        sq[e] = __fmul_rn(f, f);
+    }
+    float ss = __fadd_rn(sq[0], sq[1]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) ss = __fadd_rn(__fadd_rn(__shfl_xor(ss, q == 1 ? LR ^ 1 : LR), sq[0]), sq[1]);
+    float n2 = 0.f;
+    for (int g0 = 0; g0 * 8 < d; ++g0) n2 = __fadd_rn(n2, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(ss), LR + 2 * g0 + 1)));
+    if (lane == 0) to.c_bias[(size_t)b * to.ktiles * 32 + k] = -0.5f * n2;
+}
+
 fk_status launch_finalize(const Geometry& g, const Workspace& w, const int32_t* seg_off,
                           const int32_t* item_off, const FinalizeArgs& a, hipStream_t s,
                           const int32_t* wg_counts, int wg_per_cluster) {
     const int threads = merge_threads(g);
+    // A wave per cluster: where merge_threads says so, and where a pass left every cluster up to sixteen rows, one batch of
+    // loads, and there are more than four clusters to a compute unit.  us, a workgroup per cluster / so, four iterations: 32 instances of
+    // 3000 points, d = 40, K = 100 84 / 70 (the merge 9.2 -> 5.6), 16 of 20000, d = 128, K = 200 218 / 207, 32 of 20000, K = 40 245.4 / 243.6;
+    // but 32, K = 16 140.6 / 141.2, 16, d = 64, K = 64 102.3 / 102.9; with 32 rows each 8 of 30000, K = 100 142 / 151.
+    const bool one_batch = wg_counts && g.d <= 128 && wg_per_cluster <= 16 && (int64_t)g.K * g.B > 1024;
+    if ((threads == 64 || one_batch) && g.len == g.d && a.late == 0 && !a.sums && a.normalise && !a.c_split) {
+        hipLaunchKernelGGL(finalize_wave_kernel, dim3((unsigned)cdiv(g.K, 4), g.B), dim3(256), 0, s, w.partial, seg_off, item_off,
+                           emit_args(g, a), g.rows_per_item, item_balance(g), g.max_items, wg_counts, wg_per_cluster);
+        FK_HIP(hipGetLastError());
+        return FK_OK;
+    }
     const size_t lds = ((size_t)4 * threads + g.d) * sizeof(float);
     // (parts that wait and split centroids never come together: the one is out of core, the other in core)
     const bool ragged = g.len != g.d;

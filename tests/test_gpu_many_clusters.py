@@ -43,3 +43,32 @@ def test_update_with_many_clusters(B, N, d, K):
         size = torch.zeros((K, d), dtype=torch.float64).index_add_(0, a[b].long(), X[b].double().abs()) / cnt.clamp(min=1)[:, None]
         # sums of n terms: at most n 2^-24 of their sizes' sum, and one rounding each of 1 / n and of the product
         assert ((C[b].cpu().double() - ref).abs() <= (cnt[:, None] + 3) * 2.0 ** -24 * size).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("B,N,d,K,rows", [(1, 9000, 8, 4097, 1), (1, 20001, 128, 4099, 3), (2, 30000, 16, 2051, 300), (32, 700, 40, 37, 1),
+                                          (33, 2000, 104, 34, 1), (16, 5000, 128, 70, 1)])
+def test_merge_by_a_wave_per_cluster(dtype, B, N, d, K, rows):
+    """Many clusters of few partial rows (finalize_wave_kernel), some empty, one with `rows` rows in every ten; the fit's next
+    iteration multiplies what the merge laid out, so that it must give a new call's assignment."""
+    g = torch.Generator().manual_seed(N + d + K)
+    a = torch.randint(0, K, (B, N), generator=g)
+    a[torch.rand((B, N), generator=g) < rows / (rows + 10.0)] = K // 2
+    a[a == K - 1] = 0
+    X = torch.randn((B, N, d), generator=g).to(dtype)
+    C0 = torch.randn((B, K, d), generator=g)
+    C, lp, n = fk.fk_update(X.to(DEV), a.int().to(DEV), C0.to(DEV))
+    assert torch.equal(lp.cpu(), C.cpu().to(dtype))
+    for b in range(0, B, 7):
+        cnt = torch.bincount(a[b], minlength=K)
+        assert torch.equal(n[b].cpu().long(), cnt)
+        assert torch.equal(C[b, K - 1].cpu(), C0[b, K - 1])
+        s = torch.zeros((K, d), dtype=torch.float64).index_add_(0, a[b], X[b].double())
+        size = torch.zeros((K, d), dtype=torch.float64).index_add_(0, a[b], X[b].double().abs()) / cnt.clamp(min=1)[:, None]
+        ref = torch.where(cnt[:, None] > 0, s / cnt.clamp(min=1)[:, None], C0[b].double())
+        assert ((C[b].cpu().double() - ref).abs() <= (cnt[:, None] + 3) * 2.0 ** -24 * size).all()
+    two, one = C0.to(DEV), C0.to(DEV)
+    a2, n2, _ = fk.fk_lloyd_iter(X.to(DEV), two, 2)
+    fk.fk_lloyd_iter(X.to(DEV), one, 1)
+    a1, n1, _ = fk.fk_lloyd_iter(X.to(DEV), one, 1)
+    assert torch.equal(a2, a1) and torch.equal(n2, n1) and torch.equal(two, one)
