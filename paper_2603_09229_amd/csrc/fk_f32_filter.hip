@@ -742,7 +742,7 @@ __device__ __forceinline__ void list_points(
     const int size = 8 / teams, team = wave / size, part = wave - team * size;   // waves of a team share the centroids
     const int held = teams * P;
     const float* x = xs + team * P * d;
-    for (int64_t g = (int64_t)blockIdx.x * held; g < len; g += (int64_t)G * held) {
+    for (int64_t g = (int64_t)blockIdx.y * held; g < len; g += (int64_t)G * held) {
         // one wave per row (past the end of the list: the last point again)
         for (int r = wave; r < held; r += 8) {
             const int own = list[min(g + r, (int64_t)len - 1)];
@@ -815,7 +815,7 @@ __device__ __forceinline__ void list_few(
     const float* x = xs + team * P * d;
     float* tile = tiles + wave * 64 * kRow;
     const int r0 = lane >> 2, j0 = (lane & 3) * 4;           // this lane's pieces: rows r0 + 16 q, features j0 .. j0 + 3
-    for (int64_t g = (int64_t)blockIdx.x * held; g < len; g += (int64_t)G * held) {
+    for (int64_t g = (int64_t)blockIdx.y * held; g < len; g += (int64_t)G * held) {
         for (int r = wave; r < held; r += 8) {
             const int own = list[min(g + r, (int64_t)len - 1)];
             for (int j = lane * 4; j < d; j += 256) *(floatx4*)(xs + r * d + j) = row_piece32(X + (size_t)own * row_len, j, row_len);
@@ -889,7 +889,7 @@ __device__ __forceinline__ void list_by_thread(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list, int len,
     int32_t* __restrict__ assign, float* __restrict__ min_dist, int d, int row_len, int K, int none, int G, float* sc) {
     constexpr int TK = 32;
-    for (int64_t g = (int64_t)blockIdx.x * 512; g < len; g += (int64_t)G * 512) {
+    for (int64_t g = (int64_t)blockIdx.y * 512; g < len; g += (int64_t)G * 512) {
         const int64_t at = g + threadIdx.x;
         const int own = list[min(at, (int64_t)len - 1)];
         float x[DMAX];
@@ -938,7 +938,7 @@ __device__ __forceinline__ void list_pairs(
     const int held = min((floats - 16) / (2 * row), 16);
     int* chosen = (int*)diff + floats - 16;
     const int waves = G * 8, each = min(held, (pairs + waves - 1) / waves);
-    for (int64_t p0 = (int64_t)((G - 1 - blockIdx.x) * 8 + wave) * each; p0 < pairs; p0 += waves * each) {
+    for (int64_t p0 = (int64_t)((G - 1 - blockIdx.y) * 8 + wave) * each; p0 < pairs; p0 += waves * each) {
         const int n = (int)min((int64_t)each, pairs - p0);
         const int own = list_end[-(p0 + min(lane, n - 1))];
         const uint32_t both = (uint32_t)(min_dist ? __float_as_int(min_dist[own]) : assign[own]);
@@ -994,6 +994,8 @@ __device__ __forceinline__ void list_pairs(
 // filter has decided, in the time that the few open ones take.  A point that one of the lists has meanwhile given a centroid may be among
 // them: both then write the same bits, and what the list still has to read of it (the two centroids, where its distance goes) it
 // has read before it writes the centroid.
+// The instances lie along x, so that the lists of all of them start before any measuring: one instance after the other the last
+// one's list started last (fk_assign, distances, 32 instances of 19499 points, d = 39, K = 282 151 -> 132 us).
 template <int DMAX>
 __global__ __launch_bounds__(512, 4) void assign_f32_list_kernel(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list,
@@ -1002,13 +1004,13 @@ __global__ __launch_bounds__(512, 4) void assign_f32_list_kernel(
     __shared__ __align__(16) float xs[list_floats<DMAX>()];
     __shared__ float cand_d[8][8];
     __shared__ int cand_k[8][8];
-    const int b = blockIdx.y;
+    const int b = blockIdx.x;
     X += (size_t)b * N * row_len;
     C += (size_t)b * K * row_len;
     assign += (size_t)b * N;
     if (min_dist) min_dist += (size_t)b * N;
-    if ((int)blockIdx.x >= G) {
-        const int64_t part = blockIdx.x - G, parts = gridDim.x - G;
+    if ((int)blockIdx.y >= G) {
+        const int64_t part = blockIdx.y - G, parts = gridDim.y - G;
         if (DMAX == 32 && row_len <= 16) measure_points<4, 4>(X, C, assign, min_dist, N, row_len, part, parts);
         else if (DMAX == 32) measure_points<8, 4>(X, C, assign, min_dist, N, row_len, part, parts);
         else if (DMAX == 64 || row_len <= 128) measure_points<16, 4>(X, C, assign, min_dist, N, row_len, part, parts);
@@ -1122,8 +1124,9 @@ fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* 
     const int64_t G = std::max<int64_t>(1, std::min<int64_t>(groups, cdiv((int64_t)device_cu_count() * 2, g.B)));
     auto list_kernel = g.d <= 32 ? assign_f32_list_kernel<32> : g.d <= 64 ? assign_f32_list_kernel<64>
                                                                           : assign_f32_list_kernel<0>;
-    const int64_t distances = min_dist ? cdiv(f32_distance_blocks(g.N, distance_lanes(g.len)), g.d <= 128 ? 8 : 4) : 0;
-    hipLaunchKernelGGL(list_kernel, dim3((unsigned)(G + distances), g.B), dim3(512), 0, s, X, C, w.sorted_idx,
+    int64_t distances = min_dist ? cdiv(f32_distance_blocks(g.N, distance_lanes(g.len)), g.d <= 128 ? 8 : 4) : 0;
+    distances = std::min<int64_t>(distances, 65535 - G);       // (a launch's second dimension)
+    hipLaunchKernelGGL(list_kernel, dim3(g.B, (unsigned)(G + distances)), dim3(512), 0, s, X, C, w.sorted_idx,
                        w.f32_list_len, w.f32_pair_len, assign, min_dist, g.N, g.d, g.len, g.K, f32_direct_is_split(g) ? g.K - 1 : 0, (int)G);
     FK_HIP(hipGetLastError());
     return FK_OK;
