@@ -679,7 +679,10 @@ fk_status launch_gather_update(const Geometry& g, const Workspace& w, const void
 
 // The same for many clusters of few partial rows each (see launch_finalize), in core: a wave per cluster and
 // four to a workgroup, sums, centroid and squared norm in registers, so that every read and write is one
-// instruction and no barrier lies in the chain of latencies that bounds this.  32 instances, d = 64, K = 8192 132 us -> 93; 32, d = 128, K = 256, eight rows each 14.2 -> 11.6.
+// instruction and no barrier lies in the chain of latencies that bounds this.  32 instances, d = 64, K = 8192 132 us -> 92; 32, d = 128, K = 256, eight rows each 14.2 -> 11.6.
+// The slots' sums are added one after the other as finalize_kernel's single wave does, so that rows read as stored and padded ones, and
+// a fit's last iteration and those that write split centroids, give the same bits.
+template <bool RAGGED>
 __global__ __launch_bounds__(256) void finalize_wave_kernel(const float* __restrict__ partial, const int32_t* __restrict__ seg_off,
                                                             const int32_t* __restrict__ item_off, EmitTo to, int R, float balance,
                                                             int64_t max_items, const int32_t* __restrict__ wg_counts, int G) {
@@ -722,24 +725,44 @@ __global__ __launch_bounds__(256) void finalize_wave_kernel(const float* __restr
     if (wg_counts)
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
-    for (int o = 1; o < slots && (o == 1 || o < i1 - i0); o <<= 1) {      // (slots 0 and 1 end with all)
+    floatx4 total;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[e] += __shfl_xor(acc[e], o << lr_log2);
+    for (int e = 0; e < 4; ++e) total[e] = __shfl(acc[e], lane & (LR - 1));
+    for (int q = 1; q < slots && q < i1 - i0; ++q) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) total[e] += __shfl(acc[e], (q << lr_log2) + (lane & (LR - 1)));
     }
-    // each of them ends two of a lane's four features
+    // slots 0 and 1 end two of a lane's four features each; past the end of a caller's row everything is zero
     const bool second = (slot & 1) != 0, mine = slot < 2 && col < d;
     const int j = col + (second ? 2 : 0);
-    const size_t at = ((size_t)b * K + k) * d + j;
+    const int len = RAGGED ? to.row_len : d;
+    const size_t at = ((size_t)b * K + k) * len + j;
+    const bool here[2] = {mine && (!RAGGED || j < len), mine && (!RAGGED || j + 1 < len)};
     floatx2 c = {0.f, 0.f};
     if (n > 0) {
-        c[0] = (float)((double)(second ? acc[2] : acc[0]) / (double)n);
-        c[1] = (float)((double)(second ? acc[3] : acc[1]) / (double)n);
+        c[0] = (float)((double)(second ? total[2] : total[0]) / (double)n);
+        c[1] = (float)((double)(second ? total[3] : total[1]) / (double)n);
+        if (RAGGED) {
+            if (!here[0]) c[0] = 0.f;
+            if (!here[1]) c[1] = 0.f;
+        }
+    } else if (RAGGED) {
+        if (here[0]) c[0] = to.C_prev[at];
+        if (here[1]) c[1] = to.C_prev[at + 1];
     } else if (mine) {
         c = *(const floatx2*)(to.C_prev + at);
     }
     const uint16_t lp[2] = {float_to_lp(c[0], to.bf), float_to_lp(c[1], to.bf)};
     const uint32_t packed = lp[0] | (uint32_t)lp[1] << 16;
-    if (mine) {
+    if (RAGGED) {
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            if (!here[e]) continue;
+            to.C_out[at + e] = c[e];
+            if (to.C_lp_out) to.C_lp_out[at + e] = lp[e];
+            if (to.C_lp_f32_out) to.C_lp_f32_out[at + e] = c[e];
+        }
+    } else if (mine) {
         *(floatx2*)(to.C_out + at) = c;
         if (to.C_lp_out) *(uint32_t*)(to.C_lp_out + at) = packed;
         if (to.C_lp_f32_out) *(floatx2*)(to.C_lp_f32_out + at) = c;
@@ -773,9 +796,11 @@ fk_status launch_finalize(const Geometry& g, const Workspace& w, const int32_t* 
     // loads, and there are more than four clusters to a compute unit.  us, a workgroup per cluster / so, four iterations: 32 instances of
     // 3000 points, d = 40, K = 100 84 / 70 (the merge 9.2 -> 5.6), 16 of 20000, d = 128, K = 200 218 / 207, 32 of 20000, K = 40 245.4 / 243.6;
     // but 32, K = 16 140.6 / 141.2, 16, d = 64, K = 64 102.3 / 102.9; with 32 rows each 8 of 30000, K = 100 142 / 151.
-    const bool one_batch = wg_counts && g.d <= 128 && wg_per_cluster <= 16 && (int64_t)g.K * g.B > 1024;
-    if ((threads == 64 || one_batch) && g.len == g.d && a.late == 0 && !a.sums && a.normalise && !a.c_split) {
-        hipLaunchKernelGGL(finalize_wave_kernel, dim3((unsigned)cdiv(g.K, 4), g.B), dim3(256), 0, s, w.partial, seg_off, item_off,
+    // (A one-pass update only: all iterations of a fit take it or none.)
+    const bool one_batch = wg_counts && wg_counts == w.wg_counts && g.d <= 128 && wg_per_cluster <= 16 && (int64_t)g.K * g.B > 1024;
+    if ((threads == 64 || one_batch) && a.late == 0 && !a.sums && a.normalise && !a.c_split) {
+        auto wave_kernel = g.len == g.d ? finalize_wave_kernel<false> : finalize_wave_kernel<true>;
+        hipLaunchKernelGGL(wave_kernel, dim3((unsigned)cdiv(g.K, 4), g.B), dim3(256), 0, s, w.partial, seg_off, item_off,
                            emit_args(g, a), g.rows_per_item, item_balance(g), g.max_items, wg_counts, wg_per_cluster);
         FK_HIP(hipGetLastError());
         return FK_OK;

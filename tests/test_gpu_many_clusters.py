@@ -72,3 +72,23 @@ def test_merge_by_a_wave_per_cluster(dtype, B, N, d, K, rows):
     fk.fk_lloyd_iter(X.to(DEV), one, 1)
     a1, n1, _ = fk.fk_lloyd_iter(X.to(DEV), one, 1)
     assert torch.equal(a2, a1) and torch.equal(n2, n1) and torch.equal(two, one)
+
+
+@pytest.mark.parametrize("dtype,N,d,K", [(torch.float32, 20000, 16, 1500), (torch.float32, 30000, 33, 1200), (torch.float16, 20000, 9, 900),
+                                         (torch.float32, 60000, 8, 3000)])
+def test_merge_adds_in_one_order(dtype, N, d, K):
+    """Clusters of several partial rows: rows as stored and padded ones, and three iterations in one call and in three (where the
+    merges before a call's last may write split centroids by another kernel), give the same bits."""
+    g = torch.Generator().manual_seed(N + d)
+    size = torch.rand((K,), generator=g) ** 6               # a few large clusters
+    lab = torch.multinomial(size + 1e-3, N, replacement=True, generator=g)
+    centre = 8 * torch.randn((K, d), generator=g)
+    X = (centre[lab] + torch.randn((N, d), generator=g)).to(dtype)[None].to(DEV)
+    C0 = centre[None].to(DEV)
+    pad = -d % 8
+    three, steps, padded = C0.clone(), C0.clone(), torch.nn.functional.pad(C0, (0, pad))
+    fk.fk_lloyd_iter(X, three, 3)
+    for _ in range(3):
+        fk.fk_lloyd_iter(X, steps, 1)
+    fk.fk_lloyd_iter(torch.nn.functional.pad(X, (0, pad)), padded, 3)
+    assert torch.equal(three, steps) and torch.equal(three, padded[..., :d])
