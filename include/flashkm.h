@@ -173,7 +173,7 @@ fk_status fk_lloyd_iter(const void* X, float* C_f32, void* C_lp, int32_t* assign
  *              copied with hipMemcpyAsync on a side stream owned by the call into two
  *              device buffers carved from dev_ws while the previous chunk is assigned and
  *              reduced on `stream`.  An iteration after the first reuses the two chunks that are still
- *              in the buffers.
+ *              in the buffers.  (One chunk, or up to 16 MiB of copies in all: copied on `stream`.)
  *   C_f32      device in/out, [K,d] float.  The centroids are frozen during an iteration:
  *              sums and counts accumulate over the chunks, one normalisation per iteration
  *              (same result as the in-core path up to fp32 summation order, and a call of n
