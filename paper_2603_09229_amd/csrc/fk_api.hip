@@ -123,6 +123,7 @@ bool make_geometry(int B, int64_t N, int d_user, int K, fk_dtype t, Geometry* g)
     }
     g->ktiles = (int)cdiv(K, 32);
     g->one_pass = fused_update_allowed();
+    g->f32_filter = f32_filter_option();
     int nbmax;
     if (K <= 2048) {
         g->sort_passes = 1;
@@ -839,11 +840,12 @@ fk_status fk_lloyd_iter(const void* X, float* C_f32, void* C_lp, int32_t* assign
     void* lp = C_lp ? C_lp : w.c_lp;
     // what the first assignment consumes: the master rounded to the storage type
     FK_TRY(launch_round_centroids(g, C_f32, t == FK_F32 ? nullptr : lp, w.c_frag, w.c_bias, s));
-    bool split = false;                        // fp32: the last update has left the filter's split centroids
+    // few clusters: assignment and sums in one pass over X (see run_stream_update)
+    const bool fused = fused_update_enabled(g) || table_update_enabled(g) || f32_update_enabled(g);
+    const bool filtered = !fused && f32_filter_enabled(g);
+    bool split = false;                        // the last update has left the filter's split centroids
     for (int it = 0; it < iters; ++it) {
         timer_mark(s, -1);
-        // few clusters: assignment and sums in one pass over X (see run_stream_update)
-        const bool fused = fused_update_enabled(g) || table_update_enabled(g) || f32_update_enabled(g);
         if (!fused) {
             const int rep = timer_repeat();
             for (int r = 0; r < rep; ++r) {
@@ -864,7 +866,7 @@ fk_status fk_lloyd_iter(const void* X, float* C_f32, void* C_lp, int32_t* assign
         fa.sums = nullptr;
         fa.accumulate = false;
         fa.normalise = true;
-        split = t == FK_F32 && !fused && it + 1 < iters && f32_filter_enabled(g);
+        split = filtered && it + 1 < iters;
         if (split) {
             fa.c_split = w.c_frag;
             fa.shift = w.f32_shift;

@@ -76,6 +76,8 @@ struct Geometry {
                       // was filled in.  A call asks it once: whether rows are padded and which kernel
                       // reads them must follow from one answer (the kernel for few clusters reads rows
                       // of width d, past the end of X where they were not padded)
+    int f32_filter;   // the option of the filtered fp32 assignment, likewise: an update writes the split centroids of
+                      // the next assignment only if the one before it has laid them out
     // counting sort
     int sort_bits;    // bits of a cluster id, ceil(log2 K), >= 1
     int sort_passes;  // 1 when K <= 2048, else 2
@@ -158,6 +160,7 @@ fk_status launch_assign(const Geometry& g, const void* X, const void* C_or_frag,
 fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* X, const float* C,
                             int32_t* assign, float* min_dist, bool split, hipStream_t s);
 bool f32_filter_enabled(const Geometry& g);
+int f32_filter_option();
 // Half workgroups (of 256 threads) that measure distances, `lanes` threads a point.  A launch dimension holds fewer
 // than 2^32 threads, which one point per group of 16 lanes reaches at 2^28 points.
 inline int64_t f32_distance_blocks(int64_t N, int lanes) {

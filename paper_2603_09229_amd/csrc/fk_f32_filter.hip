@@ -1043,6 +1043,7 @@ __global__ __launch_bounds__(512, 4) void assign_f32_list_kernel(
 static std::atomic<int> g_filter_option{-1};   // -1: by shape, 0: never, 1: always
 
 void set_f32_filter_option(int v) { g_filter_option.store(v, std::memory_order_relaxed); }
+int f32_filter_option() { return g_filter_option.load(std::memory_order_relaxed); }
 
 // Where the filter wins, measured against the direct kernels over d = 16 .. 512, K = 8 .. 256 and
 // 10^3 .. 2^20 points: its three launches take 14 us at least and read X at the same rate, so the
@@ -1053,7 +1054,7 @@ void set_f32_filter_option(int v) { g_filter_option.store(v, std::memory_order_r
 // again for every 16 centroids: from the second such group (65536 points, d = 256, K = 512: 89
 // against 1340 us), or with few points.
 bool f32_filter_enabled(const Geometry& g) {
-    const int opt = g_filter_option.load(std::memory_order_relaxed);
+    const int opt = g.f32_filter;              // as it stood when the call began
     if (g.t != FK_F32 || opt == 0) return false;
     // two threads per point, and a launch dimension holds fewer than 2^32
     if (cdiv(g.N, 256) * 512 > (int64_t)UINT32_MAX) return false;

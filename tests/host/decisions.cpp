@@ -26,6 +26,27 @@ static int option_is_read_once() {
     return fk_set_option("fused_update", -1) == FK_OK ? 0 : 1;
 }
 
+// The same for the filtered fp32 assignment: an update that writes what the next assignment multiplies rests on the assignment
+// before it having laid that out.
+static int filter_is_chosen_once() {
+    struct { int64_t N; int d, K; bool by_shape; } shapes[] = {
+        {300000, 96, 400, true}, {5000, 256, 40, true}, {1000, 32, 4, false}, {2000, 1, 918, false}, {100000, 7, 200, false},
+    };
+    for (auto& s : shapes)
+        for (int before : {-1, 0, 1})
+            for (int after : {-1, 0, 1}) {
+                fk::Geometry g;
+                CHECK(fk_set_option("assign_f32_filter", before) == FK_OK);
+                CHECK(fk::make_geometry(1, s.N, s.d, s.K, FK_F32, &g));
+                CHECK(fk_set_option("assign_f32_filter", after) == FK_OK);
+                CHECK(fk::f32_filter_enabled(g) == (before < 0 ? s.by_shape : before == 1));
+                fk::Geometry part = g;               // a chunk of an out-of-core call
+                part.N = s.N / 3;
+                CHECK(before < 0 || fk::f32_filter_enabled(part) == (before == 1));
+            }
+    return fk_set_option("assign_f32_filter", -1) == FK_OK ? 0 : 1;
+}
+
 // A launch dimension holds fewer than 2^32 threads.
 static int launches_fit() {
     for (int lanes : {4, 8, 16})
@@ -58,7 +79,7 @@ static int few_counts_in_a_row() {
 }
 
 int main() {
-    if (option_is_read_once() || launches_fit() || few_counts_in_a_row()) return 1;
+    if (option_is_read_once() || filter_is_chosen_once() || launches_fit() || few_counts_in_a_row()) return 1;
     printf("host decisions ok\n");
     return 0;
 }
