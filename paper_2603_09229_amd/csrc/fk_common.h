@@ -32,6 +32,11 @@ constexpr int kWave = 64;
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+// Whether `bytes` bytes from `at` on all lie in the allocation of `size` bytes at `base`.
+inline bool lies_within(const void* at, size_t bytes, const void* base, size_t size) {
+    const uintptr_t a = (uintptr_t)at, b = (uintptr_t)base;
+    return a >= b && a - b <= size && bytes <= size - (a - b);
+}
 inline size_t elem_size(fk_dtype t) { return t == FK_F32 ? 4 : 2; }
 // What the host-side choices need to know about the current device, asked of the runtime once
 // per device: compute units, LDS per compute unit, and the size of the last-level cache (the

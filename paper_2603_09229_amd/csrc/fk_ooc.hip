@@ -98,12 +98,14 @@ fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_
         set_error("fk_lloyd_ooc: NULL or misaligned pointer");
         return FK_EINVAL;
     }
+    bool pinned_here = false;                    // through the current device
     {
         // X_host must be pinned (page-locked) host memory: from pageable memory hipMemcpyAsync
         // stages through a bounce buffer and the copies no longer overlap the kernels.  Both ends
         // of the array are looked up.
         const size_t bytes = (size_t)N * (size_t)d * elem_size(t);
         const char* ends[2] = {(const char*)X_host, (const char*)X_host + (bytes ? bytes - 1 : 0)};
+        pinned_here = true;
         for (const char* p : ends) {
             hipPointerAttribute_t attr;
             const hipError_t pe = hipPointerGetAttributes(&attr, p);
@@ -118,6 +120,7 @@ fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_
                           (int)attr.type);
                 return FK_EINVAL;
             }
+            pinned_here &= attr.device == current_device();
         }
     }
     Geometry gfull;
@@ -181,10 +184,18 @@ fk_status fk_lloyd_ooc(const void* X_host, float* C_f32, int32_t* assign, int32_
     // eight, 9 MiB 763 / 649; 16000, d = 256, K = 100, 8 MiB 312 / 280; 40000, d = 200, K = 100, 15 MiB
     // 511 / 505; 200000, d = 64 in one chunk, 24 MiB by the copy engine 595 / 532.
     const size_t copied = (size_t)N * row_bytes * (size_t)(nchunks == 1 ? 1 : iters);
-    const void* X_dev = nullptr;
-    if (!pad && copied <= ((size_t)16 << 20) && hipHostGetDevicePointer((void**)&X_dev, (void*)X_host, 0) != hipSuccess) {
-        (void)hipGetLastError();
-        X_dev = nullptr;
+    // The kernel reads what it is told to.  Both ends of X_host are pinned, but they may be the ends of two allocations with
+    // anything between them, or of memory that another device has mapped: those go to a copy, which the runtime checks.
+    void* X_dev = nullptr;
+    if (!pad && copied <= ((size_t)16 << 20) && pinned_here) {
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        if (hipHostGetDevicePointer(&X_dev, (void*)X_host, 0) != hipSuccess ||
+            hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)X_dev) != hipSuccess ||
+            !lies_within(X_dev, (size_t)N * row_bytes, base, size)) {
+            (void)hipGetLastError();
+            X_dev = nullptr;
+        }
     }
     const bool beside = !X_dev && (pad || nchunks > 1);
     hipStream_t side = nullptr;

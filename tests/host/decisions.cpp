@@ -1,5 +1,6 @@
 // Driver for tests/test_host_decisions.py: what the library decides on the host before it launches anything,
 // asked of the functions that decide it.  No kernel is launched and no GPU is needed.
+#include <stdint.h>
 #include <stdio.h>
 
 #include "fk_common.h"
@@ -78,8 +79,23 @@ static int few_counts_in_a_row() {
     return 0;
 }
 
+// Host rows that a kernel reads lie in one allocation as a whole.
+static int host_rows_lie_in_one_allocation() {
+    const char* const base = (const char*)0x100000;
+    const size_t size = 1 << 16;
+    for (size_t off : {(size_t)0, (size_t)16, size - 16, size}) {
+        const size_t left = size - off;
+        CHECK(fk::lies_within(base + off, left, base, size) && fk::lies_within(base + off, 0, base, size));
+        CHECK(!fk::lies_within(base + off, left + 1, base, size) && !fk::lies_within(base + off, SIZE_MAX, base, size));
+        CHECK(!fk::lies_within(base + off, 2 * size, base, size));       // ... whose other end is in the next one
+    }
+    CHECK(!fk::lies_within(base - 16, 16, base, size) && !fk::lies_within(base - 16, 32, base, size));
+    CHECK(!fk::lies_within(base + size + 16, 1, base, size) && !fk::lies_within(base, 1, nullptr, 0));
+    return 0;
+}
+
 int main() {
-    if (option_is_read_once() || filter_is_chosen_once() || launches_fit() || few_counts_in_a_row()) return 1;
+    if (option_is_read_once() || filter_is_chosen_once() || launches_fit() || few_counts_in_a_row() || host_rows_lie_in_one_allocation()) return 1;
     printf("host decisions ok\n");
     return 0;
 }
