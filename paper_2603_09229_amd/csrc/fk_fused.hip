@@ -38,6 +38,13 @@ constexpr int kOnce = 2;
 // K = 32 12.7 / 13.0 / 14.3.
 constexpr int stream_per_cu(int dch, bool assigns) { return dch == 8 || (dch == 4 && !assigns) ? 1 : 2; }
 
+// Few workgroups make a wave's share long, 16384 of 2^24 points, and one chain of additions over all of it loses what is small
+// beside its sum: some 1e-5 of a mean of ones and a few values of 2^-11 (test_long_chains in tests/test_gpu_few_clusters.py); 2.2e-7 of one of
+// normally distributed numbers about zero, 1.4e-7 with three times as many workgroups, 1.2e-7 so: where a wave has more than this many batches,
+// sums of so many are added up in a second set of registers.  fk_update, 2^24 points, d = 64, K = 16 308.4 us without and with it, d = 32, K = 30 171.8
+// and 172.6; two iterations there 367 and 371.  (Rows of 128 features that are assigned too leave no registers: one workgroup a unit, as always.)
+constexpr int kStreamRun = 32;
+
 // BF: bf16 (else fp16).  DCH: feature chunks of 16 per point (2, 4 or 8).  ASSIGN: compute
 // the assignment here (argmax of x.c_k - ||c_k||^2/2 over the single centroid tile, same
 // packed-score rules as the assignment kernels) and, where `keep` says so, write it; otherwise read it.
@@ -45,7 +52,8 @@ constexpr int stream_per_cu(int dch, bool assigns) { return dch == 8 || (dch == 
 // Grid (G, B).  Wave w of workgroup g handles the 32-point batches g*WAVES + w,
 // + G*WAVES, ...: a fixed partition, so the partial tables are reproducible.
 // partial: [B][K][G][d] floats, wg_counts: [B][K][G].
-template <bool BF, int DCH, int WAVES, bool ASSIGN>
+// RUNS: sums of kStreamRun batches at a time, and of those.
+template <bool BF, int DCH, int WAVES, bool ASSIGN, bool RUNS>
 __global__ __launch_bounds__(WAVES * 64, stream_per_cu(DCH, ASSIGN)) void stream_update_kernel(
     const uint16_t* __restrict__ X, const uintx4* __restrict__ c_frag,
     const float* __restrict__ c_bias, int32_t* assign, float* __restrict__ partial,
@@ -145,12 +153,10 @@ __global__ __launch_bounds__(WAVES * 64, stream_per_cu(DCH, ASSIGN)) void stream
                 t_at[s2][cb][u] = ((uint32_t)(row * ppr + (min(4 * cb + 2 * nb + ((L & 3) >> 1), ppr - 1) ^ (row & swz))) << 4) + ((L & 1) << 3);
             }
 
-    floatx16 accS[CB];
+    floatx16 accS[CB], whole[RUNS ? CB : 1];
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) accS[cb][i] = 0.f;
-    int cnt = 0;
+    for (int cb = 0; cb < CB; ++cb) accS[cb] = whole[RUNS ? cb : 0] = floatx16{};
+    int cnt = 0, run = 0;
 
     // A batch is read into registers as a whole, so that its buffer takes the batch after the next at once: two
     // batches are in flight while one is worked on (a third buffer, filled an iteration later, kept as many).  Copies and stores of a
@@ -281,6 +287,12 @@ __global__ __launch_bounds__(WAVES * 64, stream_per_cu(DCH, ASSIGN)) void stream
                 accS[cb] = mfma32<BF>(A, Bt, accS[cb]);
             }
         }
+        if (RUNS && ++run == kStreamRun) {
+            run = 0;
+            asm volatile("");                          // (a branch, or the compiler selects in every batch)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) { whole[RUNS ? cb : 0] += accS[cb]; accS[cb] = floatx16{}; }
+        }
 
         // the next batch must have landed before it is read (wave-private buffers: no barrier)
         if (issued && ASSIGN && keep) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(loads + 1) : "memory");
@@ -300,7 +312,7 @@ __global__ __launch_bounds__(WAVES * 64, stream_per_cu(DCH, ASSIGN)) void stream
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-            comb[(wave * 32 + 8 * (i >> 2) + 4 * h + (i & 3)) * dpad + 32 * cb + n] = accS[cb][i];
+            comb[(wave * 32 + 8 * (i >> 2) + 4 * h + (i & 3)) * dpad + 32 * cb + n] = RUNS ? whole[RUNS ? cb : 0][i] + accS[cb][i] : accS[cb][i];
     if (h == 0) ccnt[wave * 32 + n] = cnt;
     __syncthreads();
     for (int o = tid; o < K * d; o += kThreads) {
@@ -329,20 +341,23 @@ template <bool BF, int DCH, bool ASSIGN>
 static fk_status launch_stream_update_t(const Geometry& g, const Workspace& w, const void* X,
                                         int32_t* assign, bool keep_assign, int* grid_out, hipStream_t s) {
     constexpr int WAVES = 4;
-    auto kern = stream_update_kernel<BF, DCH, WAVES, ASSIGN>;
+    const int64_t nbatches = cdiv(g.N, 32), wgs = (int64_t)device_cu_count() * stream_per_cu(DCH, ASSIGN);
+    int64_t G = cdiv(wgs, g.B);
+    G = std::min<int64_t>(G, g.fused_grid_cap);
+    G = std::min<int64_t>(G, cdiv(nbatches, WAVES));
+    const bool runs = !(ASSIGN && DCH == 8) && nbatches > G * WAVES * kStreamRun;
+    // (no more of those than run at once)
+    if (runs) G = std::min<int64_t>(G, wgs / g.B);
+    G = std::max<int64_t>(G, 1);
+    auto kern = runs ? stream_update_kernel<BF, DCH, WAVES, ASSIGN, !(ASSIGN && DCH == 8)> : stream_update_kernel<BF, DCH, WAVES, ASSIGN, false>;
     // two batch buffers per wave; at the end the waves' tables and counts
     const size_t lds = std::max((size_t)WAVES * 2 * (DCH * 64 + (ASSIGN ? 0 : 16)) * 16, (size_t)WAVES * 32 * (DCH * 16 + 1) * 4);
     // set once per kernel and device: the launch path stays free of runtime calls afterwards
-    static PerDeviceInt attr_set;
-    if (attr_set.get() == 0) {
+    static PerDeviceInt attr_set[2];
+    if (attr_set[runs].get() == 0) {
         FK_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        attr_set.set(1);
+        attr_set[runs].set(1);
     }
-    const int64_t nbatches = cdiv(g.N, 32);
-    int64_t G = cdiv((int64_t)device_cu_count() * stream_per_cu(DCH, ASSIGN), g.B);
-    G = std::min<int64_t>(G, g.fused_grid_cap);
-    G = std::min<int64_t>(G, cdiv(nbatches, WAVES));
-    G = std::max<int64_t>(G, 1);
     dim3 grid((unsigned)G, g.B), block(WAVES * 64);
     hipLaunchKernelGGL(kern, grid, block, lds, s, (const uint16_t*)X, (const uintx4*)w.c_frag,
                        (const float*)w.c_bias, assign, w.partial, w.wg_counts, g.N, g.d, g.K, keep_assign ? 1 : 0);

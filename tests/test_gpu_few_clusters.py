@@ -42,3 +42,29 @@ def test_few_cluster_batches(dtype, B, N, d, K):
     for _ in range(3):
         b, _, _ = fk.fk_lloyd_iter(X, ones, 1)
     assert torch.equal(a, b) and torch.equal(three, ones)
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("B,N,d,few", [(1, 1 << 24, 64, 11), (1, (1 << 24) - 45, 40, 11), (2, (1 << 23) - 3, 24, 12), (1, 1 << 23, 128, 12)])
+def test_long_chains(dtype, B, N, d, few):
+    """Of sixteen points of a batch 15 are ones and one is 3/4 of half a place of a sum of half the points that a wave adds up: one chain
+    over all of them drops it there, 5 to 12 parts in 10^6 of the mean."""
+    small = 0.75 * 2.0 ** -few
+    X = torch.ones((B, N, d), dtype=dtype, device=DEV)
+    X[:, 5::16] = small
+    want = 1 + (small - 1) * len(range(5, N, 16)) / N
+    # Small values are multiples of 2^-(few + 2) and a run of 32 batches adds up to less than 2^10; whole runs are multiples of 2^(4 - few)
+    # and a workgroup's add up to 2^(27 - few) at the most: all exact.  What rounds is what ends a wave's share, the four waves' sums where
+    # N is ragged, fewer than 34 additions of positive numbers in the merge, its division and the conversion.
+    bound = 42 * 2.0 ** -24
+    C0 = torch.full((B, 2, d), -5.0, device=DEV)
+    C0[:, 0] = 1.0
+    C, _, n = fk.fk_update(X, torch.zeros((B, N), dtype=torch.int32, device=DEV), C0)
+    assert n.tolist() == [[N, 0]] * B
+    assert ((C[:, 0].double() / want - 1).abs() <= bound).all()
+    if d > 64:
+        return               # (the fit has no registers for a second level there; its chains are as they always were)
+    C = C0.clone()
+    _, n, _ = fk.fk_lloyd_iter(X, C, 1)
+    assert n.tolist() == [[N, 0]] * B
+    assert ((C[:, 0].double() / want - 1).abs() <= bound).all()
