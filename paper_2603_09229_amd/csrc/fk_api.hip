@@ -866,7 +866,7 @@ fk_status fk_lloyd_iter(const void* X, float* C_f32, void* C_lp, int32_t* assign
         fa.sums = nullptr;
         fa.accumulate = false;
         fa.normalise = true;
-        split = filtered && it + 1 < iters;
+        split = filtered && it + 1 < iters && !f32_lays_out_anew(it + 1);
         if (split) {
             fa.c_split = w.c_frag;
             fa.shift = w.f32_shift;

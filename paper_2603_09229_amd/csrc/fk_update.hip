@@ -184,8 +184,8 @@ struct EmitTo {
     const float* late_sums;
     const int32_t* late_counts;
     int d, K, B, ktiles, dch, accumulate, normalise, bf, late, row_len;
-    // fp32: the split centroids of the filtered assignment (fk_f32_filter.hip) with the shift they were given at the
-    // start of the call, c2 their norms; the lengths of its lists, which the next assignment starts from
+    // fp32: the split centroids of the filtered assignment (fk_f32_filter.hip) with the shift that their last
+    // layout in the call has left, c2 their norms; the lengths of its lists, which the next assignment starts from
     uint16_t* c_split;
     const float* shift;
     float* c2;
@@ -194,8 +194,8 @@ struct EmitTo {
 
 // Row k of the split centroids, from its shifted values in `row` (d floats of LDS, not yet behind a barrier): what
 // f32_split_layout_kernel writes for it, so that the next assignment of the call needs no launch of that kernel (5 to 8 us).  Rows beyond
-// K and features beyond d keep what the first assignment's launch wrote there, and so does the shift, which only has to be near the
-// data: the centroids move, their mean hardly.
+// K and features beyond d keep what that kernel's last launch in the call wrote there, and so does the shift, which only has to be near
+// the data (see f32_lays_out_anew).
 __device__ __forceinline__ void emit_split(const EmitTo& to, int b, int k, const float* row, bool odd) {
     const int tid = threadIdx.x, d = to.d, T = (int)blockDim.x;
     __shared__ int fits;

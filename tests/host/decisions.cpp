@@ -48,6 +48,17 @@ static int filter_is_chosen_once() {
     return fk_set_option("assign_f32_filter", -1) == FK_OK ? 0 : 1;
 }
 
+// A shift is taken from starting centroids for one iteration, and from later ones for eight at the most.
+static int shifts_are_renewed() {
+    CHECK(fk::f32_lays_out_anew(0) && fk::f32_lays_out_anew(1));
+    int kept = 0;
+    for (int it = 2; it < 1000; ++it) {
+        kept = fk::f32_lays_out_anew(it) ? 0 : kept + 1;
+        CHECK(kept < 8);
+    }
+    return 0;
+}
+
 // A launch dimension holds fewer than 2^32 threads.
 static int launches_fit() {
     for (int lanes : {4, 8, 16})
@@ -95,7 +106,7 @@ static int host_rows_lie_in_one_allocation() {
 }
 
 int main() {
-    if (option_is_read_once() || filter_is_chosen_once() || launches_fit() || few_counts_in_a_row() || host_rows_lie_in_one_allocation()) return 1;
+    if (option_is_read_once() || filter_is_chosen_once() || shifts_are_renewed() || launches_fit() || few_counts_in_a_row() || host_rows_lie_in_one_allocation()) return 1;
     printf("host decisions ok\n");
     return 0;
 }
