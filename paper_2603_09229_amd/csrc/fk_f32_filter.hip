@@ -482,14 +482,14 @@ __global__ __launch_bounds__(WAVES * 64, filter_occupancy(DCH, WAVES)) void assi
 // ahead of their use.  Same scores, same verdicts.  fk_assign, us, in the sweep / here: 2415 points, d = 128, K = 3561 116 / 37; 2 x 5764,
 // d = 415, K = 767 138 / 103; 8000, d = 512, K = 4000 551 / 309; an iteration of 2 x 3027, d = 242, K = 609 69 / 47.
 constexpr int few_ahead(int dch) { return dch % 4 == 0 ? 4 : dch % 3 == 0 ? 3 : dch % 5 == 0 ? 5 : dch % 7 == 0 ? 7 : dch % 2 == 0 ? 2 : 1; }
-constexpr int few_waves(int dch) { return 8; }
+constexpr int kFewWaves = 8;
 
 template <int DCH>
-__global__ __launch_bounds__(few_waves(DCH) * 64, DCH <= 3 ? 4 : 2) void assign_f32_filter_few_kernel(
+__global__ __launch_bounds__(kFewWaves * 64, DCH <= 3 ? 4 : 2) void assign_f32_filter_few_kernel(
     const float* __restrict__ X, const uintx4* __restrict__ frag, const float* __restrict__ c2,
     const float* __restrict__ shift, int32_t* __restrict__ assign, int32_t* __restrict__ list,
     int32_t* __restrict__ list_len, int32_t* __restrict__ pair_len, int32_t* __restrict__ pair_at, int64_t N, int d, int len, int K, int ktiles) {
-    constexpr int WAVES = few_waves(DCH), kTile = 2 * DCH + 1, GC = few_ahead(DCH), NG = DCH / GC;
+    constexpr int WAVES = kFewWaves, kTile = 2 * DCH + 1, GC = few_ahead(DCH), NG = DCH / GC;
     constexpr bool kThree = filter_keeps_three(DCH);
     constexpr bool kHeld = DCH <= 16 && DCH != 14;           // the points' operands stay in registers (14: they would spill)
     // heads and tails of the 32 points, as B operands; at the end the waves' best scores
@@ -588,14 +588,14 @@ __global__ __launch_bounds__(few_waves(DCH) * 64, DCH <= 3 ? 4 : 2) void assign_
     const bool mine = h == 0 && point < N;
     leave_verdict(top.t1, top.t2, verdict, mine, point, K, assign, pair_at);
     const uint64_t below = (1ull << lane) - 1ull;
-    const uint64_t open = __ballot(mine && verdict == 2), pair = __ballot(mine && verdict == 1);
+    const uint64_t open = __ballot(mine && verdict == 2), pair = kThree ? __ballot(mine && verdict == 1) : 0;
     int at = 0, pair_from = 0;
     if (lane == 0 && open) at = atomicAdd(list_len + b, __popcll(open));
     if (lane == 0 && pair) pair_from = atomicAdd(pair_len + b, __popcll(pair));
     at = __builtin_amdgcn_readfirstlane(at);
     pair_from = __builtin_amdgcn_readfirstlane(pair_from);
     if (mine && verdict == 2) list[at + __popcll(open & below)] = (int32_t)point;
-    if (mine && verdict == 1) list[N - 1 - (pair_from + __popcll(pair & below))] = (int32_t)point;
+    if (kThree && mine && verdict == 1) list[N - 1 - (pair_from + __popcll(pair & below))] = (int32_t)point;
 }
 
 // The points on the list against all centroids by direct differences: ascending features, one
@@ -605,7 +605,9 @@ __global__ __launch_bounds__(few_waves(DCH) * 64, DCH <= 3 ? 4 : 2) void assign_
 // a wave holds P points.  The eight waves of a workgroup share out the centroids or, where those
 // are too few, take points of their own (`teams` of 8 / teams waves each).  With P = 2 a short
 // list is spread thin and over in the time that a few rows take to arrive (5 to 20 us); with P =
-// 8 a long one is bound by the two vector instructions per term, as the direct kernels are.
+// 8 a long one is bound by reading its points from LDS, a pass of which serves 64 centroids, so that its waves take points of their
+// own as soon as all workgroups have some: waves that share 400 rows leave one of eight idle, 300 three (every centroid twice, 300000 points,
+// d = 96, K = 400 1306 -> 885 us, 400000, d = 80, K = 300 1460 -> 710, 20000 94 -> 69).
 //   Long lists of rows of up to 64 features, where that form spends its time on reading centroid
 // rows: one point per thread with its features in registers, centroid tiles through LDS.  (Not rows of
 // up to 16 against many centroids: it multiplies 32 features.  7 x 294694 points, d = 8, K = 14868: 60.1 ms
@@ -613,16 +615,23 @@ __global__ __launch_bounds__(few_waves(DCH) * 64, DCH <= 3 ? 4 : 2) void assign_
 //   Points that are open between two centroids only, nineteen of twenty where the filter keeps three scores, are on a list of
 // their own and cost two rows each (list_pairs).  fk_assign of 65536 points, d = 256, K = 512, distances: 1837 such points and 42 others,
 // list and distances 44 -> 22 us.
-//   What open points cost is then about the direct kernel's time for them on top of the filter's.
-// Every centroid twice, so that all points are open, fk_assign against the direct kernels alone: 2^20 points,
-// d = K = 64: 292 us, 222 (one addition to the list's length per wave: 610); d = 64, K = 256: 924, 814
-// (in the first form: 1896); d = 128, K = 64: 950, 656 (4 teams: 1350); 300000 points, d = 96, K = 400:
-// 1238, 1149; 65536, d = 256, K = 512: 696, 1323.
+//   What other open points cost is about the direct kernel's time for them, or less, on top of the filter's.
+// All points open, fk_assign against the direct kernels alone, us.  Every centroid twice: 2^20 points,
+// d = K = 64: 275, 221 (one addition to the list's length per wave: 610); d = 64, K = 256: 860, 811
+// (in the first form: 1896); d = 128, K = 64: 386, 640 (pairs); 300000 points, d = 96, K = 400:
+// 890, 1154; 65536, d = 256, K = 512: 89, 1341 (pairs).  Four times: d = 128, K = 64: 985, 640; 65536, d = 256, K = 512: 586, 1348.
 
 // |x - c|^2 by direct differences for every point whose distance is wanted: LANES (4, 8 or 16) lanes a point, enough for a whole
 // row per load where it has up to 64 features.  Infinity where it is not finite, as in the direct kernels, whose
 // minimum starts there.  (The lanes' sums meet in a butterfly: lanes without a piece add zero, so that their number changes no bit.)
 constexpr int distance_lanes(int len) { return len <= 16 ? 4 : len <= 32 ? 8 : 16; }
+
+template <int LANES>
+__device__ __forceinline__ float sum_of_lanes(float s) {
+#pragma unroll
+    for (int o = LANES / 2; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    return s < INFINITY ? s : INFINITY;
+}
 
 template <int LANES, int U>
 __device__ __forceinline__ void row_distances(const float* const (&x)[U], const float* const (&c)[U], int len, int l, float (&s)[U]) {
@@ -638,40 +647,30 @@ __device__ __forceinline__ void row_distances(const float* const (&x)[U], const 
             for (int e = 0; e < 4; ++e) { const float t = v[u][e] - w[u][e]; s[u] = fmaf(t, t, s[u]); }
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-#pragma unroll
-        for (int o = LANES / 2; o > 0; o >>= 1) s[u] += __shfl_xor(s[u], o);
-        s[u] = s[u] < INFINITY ? s[u] : INFINITY;
-    }
-}
-
-template <int DMAX>
-__device__ __forceinline__ float row_distance(const float* x, const float* c, int len) {
-    const float* const xs[1] = {x};
-    const float* const cs[1] = {c};
-    float s[1];
-    if (DMAX == 32 && len <= 16) row_distances<4, 1>(xs, cs, len, threadIdx.x & 3, s);
-    else if (DMAX == 32) row_distances<8, 1>(xs, cs, len, threadIdx.x & 7, s);
-    else row_distances<16, 1>(xs, cs, len, threadIdx.x & 15, s);
-    return s[0];
+    for (int u = 0; u < U; ++u) s[u] = sum_of_lanes<LANES>(s[u]);
 }
 
 // Share `part` of `parts` of the points, by 512 threads, U points at a time a group of lanes; open points (-1) are left out.
 // fk_assign with distances, K = 200, us, one / two / four at a time: 400000 points, d = 64 97 / 86 / 81, d = 128 145 / 130 / 125; d = 256,
-// 65536, K = 512 84.6 / 85.9 / 86.6, 200000, K = 100 120 / 111 / 111.
+// 65536, K = 512 84.6 / 85.9 / 86.6, 200000, K = 100 120 / 111 / 111.  The assignment of the next ones is asked for before these are measured,
+// and no more than sixteen workgroups a compute unit take turns: 1353626 points, d = 59, K = 26, a workgroup for every 128 points without that
+// 213, four / eight / sixteen a unit with it 219 / 205 / 197.
 template <int LANES, int U>
 __device__ __forceinline__ void measure_points(const float* __restrict__ X, const float* __restrict__ C, const int32_t* assign,
                                                float* min_dist, int64_t N, int len, int64_t part, int64_t parts) {
     constexpr int each = 512 / LANES;
     const int l = threadIdx.x & (LANES - 1);
+    int next[U];
+    auto ids = [&](int64_t i0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) next[u] = __hip_atomic_load(assign + min(i0 + u * each, N - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    ids(part * (U * each) + threadIdx.x / LANES);
     for (int64_t i0 = part * (U * each) + threadIdx.x / LANES; i0 < N; i0 += parts * (U * each)) {
         int k[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t i = min(i0 + u * each, N - 1);
-            k[u] = __hip_atomic_load(assign + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (i0 + u * each >= N) k[u] = -1;
-        }
+        for (int u = 0; u < U; ++u) k[u] = i0 + u * each < N ? next[u] : -1;
+        ids(i0 + parts * (U * each));
         const float *x[U], *c[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -692,10 +691,10 @@ template <int DMAX>
 constexpr int list_floats() { return DMAX == 0 ? 15360 : 4096; }
 
 // The end of a round of `held` points, P to a team of `size` waves: the lanes' best meet in the waves, the waves' in LDS.
-template <int DMAX, int P>
+template <int DMAX, bool DIST, int P>
 __device__ __forceinline__ void list_merge(
-    const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list, int64_t g, int len,
-    int32_t* __restrict__ assign, float* __restrict__ min_dist, int row_len, int K, int none, int size, int held,
+    const float* __restrict__ C, const int* ids, int64_t g, int len,
+    int32_t* __restrict__ assign, float* __restrict__ min_dist, const float* xs, int d, int row_len, int K, int none, int size, int held,
     float (&best)[P], int (&at)[P], float (*cand_d)[8], int (*cand_k)[8]) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 #pragma unroll
@@ -719,25 +718,38 @@ __device__ __forceinline__ void list_merge(
             if (od < bd || (od == bd && ok < bk)) { bd = od; bk = ok; }
         }
         bk = bk < K ? bk : none;
-        assign[list[g + tid]] = bk;
+        assign[ids[tid]] = bk;
         cand_k[w0][p] = bk;
     }
     __syncthreads();
-    if (min_dist) {
-        const int lanes = distance_lanes(row_len), l = tid & (lanes - 1);
-        for (int q = tid / lanes; q < held && g + q < len; q += 512 / lanes) {
-            const int own = list[g + q], k = cand_k[q / P * size][q % P];
-            const float D = row_distance<DMAX>(X + (size_t)own * row_len, C + (size_t)k * row_len, row_len);
-            if (l == 0) min_dist[own] = D;
-        }
+    if constexpr (DIST) {
+        const int here = (int)min((int64_t)held, len - g);
+        auto measure = [&](auto group) {
+            constexpr int LANES = decltype(group)::value;
+            for (int q = tid / LANES; q < here; q += 512 / LANES) {
+                const float *x = xs + q * d, *c = C + (size_t)cand_k[q / P * size][q % P] * row_len;
+                const int own = ids[q], l = tid & (LANES - 1);
+                float D = 0.f;                               // (zeros past the end of both rows)
+                for (int j = l * 4; j < row_len; j += 4 * LANES) {
+                    const floatx4 v = *(const floatx4*)(x + j), w = row_piece32(c, j, row_len);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { const float t = v[e] - w[e]; D = fmaf(t, t, D); }
+                }
+                D = sum_of_lanes<LANES>(D);
+                if (l == 0) min_dist[own] = D;
+            }
+        };
+        if (DMAX == 32 && row_len <= 16) measure(std::integral_constant<int, 4>());
+        else if (DMAX == 32) measure(std::integral_constant<int, 8>());
+        else measure(std::integral_constant<int, 16>());
         __syncthreads();
     }
 }
 
-template <int DMAX, int P>
+template <int DMAX, bool DIST, int P>
 __device__ __forceinline__ void list_points(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list, int len,
-    int32_t* __restrict__ assign, float* __restrict__ min_dist, int d, int row_len, int K, int none, int teams, int G, float* xs, float (*cand_d)[8], int (*cand_k)[8]) {
+    int32_t* __restrict__ assign, float* __restrict__ min_dist, int d, int row_len, int K, int none, int teams, int G, float* xs, int* ids, float (*cand_d)[8], int (*cand_k)[8]) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int size = 8 / teams, team = wave / size, part = wave - team * size;   // waves of a team share the centroids
     const int held = teams * P;
@@ -746,6 +758,7 @@ __device__ __forceinline__ void list_points(
         // one wave per row (past the end of the list: the last point again)
         for (int r = wave; r < held; r += 8) {
             const int own = list[min(g + r, (int64_t)len - 1)];
+            if (lane == 0) ids[r] = own;
             for (int j = lane * 4; j < d; j += 256) *(floatx4*)(xs + r * d + j) = row_piece32(X + (size_t)own * row_len, j, row_len);
         }
         float best[P];
@@ -793,7 +806,7 @@ __device__ __forceinline__ void list_points(
                     if (D[p] < best[p]) { best[p] = D[p]; at[p] = k; }
             }
         }
-        list_merge<DMAX, P>(X, C, list, g, len, assign, min_dist, row_len, K, none, size, held, best, at, cand_d, cand_k);
+        list_merge<DMAX, DIST, P>(C, ids, g, len, assign, min_dist, xs, d, row_len, K, none, size, held, best, at, cand_d, cand_k);
     }
 }
 
@@ -802,11 +815,11 @@ __device__ __forceinline__ void list_points(
 // step touches every line eight times, which a few workgroups alone feel: 11 points of d = 415 against 767 rows took 186 us,
 // here 50.  Up to 256 centroids a wave has one block of rows, and the shorter chain of list_points is as fast or faster (fk_assign,
 // us, this / that: 16000 points, d = 512, K = 230 60.6 / 55.2, d = 256, K = 100 36.2 / 34.3, d = 128, K = 200 27.7 / 29.2).
-template <int DMAX>
+template <int DMAX, bool DIST>
 __device__ __forceinline__ void list_few(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list, int len,
     int32_t* __restrict__ assign, float* __restrict__ min_dist, int d, int row_len, int K, int none, int teams, int G, float* xs, float* tiles,
-    float (*cand_d)[8], int (*cand_k)[8]) {
+    int* ids, float (*cand_d)[8], int (*cand_k)[8]) {
     constexpr int P = 2, kRow = 20;                          // (four floats of padding: 16 lanes' reads hit all banks)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int size = 8 / teams, team = wave / size, part = wave - team * size;
@@ -818,6 +831,7 @@ __device__ __forceinline__ void list_few(
     for (int64_t g = (int64_t)blockIdx.y * held; g < len; g += (int64_t)G * held) {
         for (int r = wave; r < held; r += 8) {
             const int own = list[min(g + r, (int64_t)len - 1)];
+            if (lane == 0) ids[r] = own;
             for (int j = lane * 4; j < d; j += 256) *(floatx4*)(xs + r * d + j) = row_piece32(X + (size_t)own * row_len, j, row_len);
         }
         float best[P], D[P];
@@ -880,11 +894,33 @@ __device__ __forceinline__ void list_few(
             if (step + 1 < all) use(ahead[1], step + 1, block, t);
             if (++t == steps) { t = 0; ++block; }
         }
-        list_merge<DMAX, P>(X, C, list, g, len, assign, min_dist, row_len, K, none, size, held, best, at, cand_d, cand_k);
+        list_merge<DMAX, DIST, P>(C, ids, g, len, assign, min_dist, xs, d, row_len, K, none, size, held, best, at, cand_d, cand_k);
     }
 }
 
-template <int DMAX>
+// Every lane's point `own`, whose centroid is k: the wave measures four a group of lanes at a time.
+template <int LANES>
+__device__ __forceinline__ void distances_of(const float* __restrict__ X, const float* __restrict__ C, float* __restrict__ min_dist, int own, int k, int len) {
+    constexpr int U = 4, groups = 64 / LANES;
+    const int lane = threadIdx.x & 63, l = lane & (LANES - 1);
+    for (int p0 = lane / LANES; p0 < 64; p0 += U * groups) {
+        int i[U];
+        const float *x[U], *c[U];
+        float s[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            i[u] = __shfl(own, p0 + u * groups);
+            x[u] = X + (size_t)i[u] * len;
+            c[u] = C + (size_t)__shfl(k, p0 + u * groups) * len;
+        }
+        row_distances<LANES, U>(x, c, len, l, s);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (l == 0) min_dist[i[u]] = s[u];
+    }
+}
+
+template <int DMAX, bool DIST>
 __device__ __forceinline__ void list_by_thread(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list, int len,
     int32_t* __restrict__ assign, float* __restrict__ min_dist, int d, int row_len, int K, int none, int G, float* sc) {
@@ -904,25 +940,30 @@ __device__ __forceinline__ void list_by_thread(
             }
             __syncthreads();
             const int nk = min(TK, K - k0);
-            for (int r = 0; r < nk; ++r) {
-                float D = 0.f;
+            // (two chains at a time: a single one took 791 or 937 us, 200000 points, d = 64, K = 1000, every centroid twice, as the compiler
+            // happened to choose registers; 714 so.  Past K the second one's row is zeros, and not looked at.)
+            for (int r = 0; r < nk; r += 2) {
+                float D[2] = {0.f, 0.f};
 #pragma unroll
                 for (int j = 0; j < DMAX; j += 4) {
-                    const floatx4 c = *(const floatx4*)(sc + r * DMAX + j);
+                    const floatx4 c = *(const floatx4*)(sc + r * DMAX + j), c1 = *(const floatx4*)(sc + (r + 1) * DMAX + j);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) { const float t = x[j + e] - c[e]; D = fmaf(t, t, D); }
+                    for (int e = 0; e < 4; ++e) {
+                        const float t = x[j + e] - c[e], t1 = x[j + e] - c1[e];
+                        D[0] = fmaf(t, t, D[0]);
+                        D[1] = fmaf(t1, t1, D[1]);
+                    }
                 }
-                if (D < m) { m = D; a = k0 + r; }
+                if (D[0] < m) { m = D[0]; a = k0 + r; }
+                if (D[1] < m && r + 1 < nk) { m = D[1]; a = k0 + r + 1; }
             }
         }
         if (at < len) assign[own] = a;
-        if (min_dist) {
-            const int lanes = distance_lanes(row_len), lane = threadIdx.x & 63;
-            for (int p = lane / lanes; p < 64; p += 64 / lanes) {
-                const int i = __shfl(own, p), k = __shfl(a, p);
-                const float D = row_distance<DMAX>(X + (size_t)i * row_len, C + (size_t)k * row_len, row_len);
-                if ((lane & (lanes - 1)) == 0) min_dist[i] = D;      // (past the end of the list: the last point again)
-            }
+        if constexpr (DIST) {
+            // (past the end of the list: the last point again)
+            if (DMAX == 32 && row_len <= 16) distances_of<4>(X, C, min_dist, own, a, row_len);
+            else if (DMAX == 32) distances_of<8>(X, C, min_dist, own, a, row_len);
+            else distances_of<16>(X, C, min_dist, own, a, row_len);
         }
     }
 }
@@ -930,7 +971,7 @@ __device__ __forceinline__ void list_by_thread(
 // Points that are open between two centroids, packed in assign: a wave takes as many as its part of LDS holds the
 // differences to both of, in whole rows, and then has a lane add up the squares of each in the direct kernels' order.
 // (From the last workgroup on: the first ones have the points that are measured in full.)
-template <int DMAX>
+template <bool DIST>
 __device__ __forceinline__ void list_pairs(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list_end, int pairs,
     int32_t* __restrict__ assign, float* __restrict__ min_dist, int d, int row_len, int none, int G, float* diff, int floats) {
@@ -941,7 +982,7 @@ __device__ __forceinline__ void list_pairs(
     for (int64_t p0 = (int64_t)((G - 1 - blockIdx.y) * 8 + wave) * each; p0 < pairs; p0 += waves * each) {
         const int n = (int)min((int64_t)each, pairs - p0);
         const int own = list_end[-(p0 + min(lane, n - 1))];
-        const uint32_t both = (uint32_t)(min_dist ? __float_as_int(min_dist[own]) : assign[own]);
+        const uint32_t both = (uint32_t)(DIST ? __float_as_int(min_dist[own]) : assign[own]);
         const int k1 = (int)(both & 0xFFFFu), k2 = (int)(both >> 16);
         for (int p = 0; p < n; ++p) {
             const float* x = X + (size_t)__shfl(own, p) * row_len;
@@ -973,15 +1014,17 @@ __device__ __forceinline__ void list_pairs(
             if (Dlo < best) { best = Dlo; at = lo; }
             if (Dhi < best) { best = Dhi; at = hi; }
             assign[own] = at;
-            if (min_dist) chosen[lane] = at;
+            if (DIST) chosen[lane] = at;
         }
-        if (min_dist) {
+        if constexpr (DIST) {
             __builtin_amdgcn_wave_barrier();
-            const int lanes = distance_lanes(row_len);
-            for (int p = lane / lanes; p < n; p += 64 / lanes) {
+            for (int p = lane >> 4; p < n; p += 4) {
                 const int i = list_end[-(p0 + p)];
-                const float s = row_distance<DMAX>(X + (size_t)i * row_len, C + (size_t)chosen[p] * row_len, row_len);
-                if ((lane & (lanes - 1)) == 0) min_dist[i] = s;
+                const float* const x[1] = {X + (size_t)i * row_len};
+                const float* const c[1] = {C + (size_t)chosen[p] * row_len};
+                float s[1];
+                row_distances<16, 1>(x, c, row_len, lane & 15, s);
+                if ((lane & 15) == 0) min_dist[i] = s[0];
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -989,27 +1032,30 @@ __device__ __forceinline__ void list_pairs(
 }
 
 // `none`: the answer where no distance is finite, that of the direct kernel for the shape.
-// DMAX: 32 or 64 for rows up to that, 0 for wider ones.
+// DMAX: 32 or 64 for rows up to that, 0 for wider ones.  PAIRS: where the filter keeps three scores, DIST: where distances are wanted, and the
+// code for either only there: what it takes of the registers the long lists spill (four of each centroid, 2^20 points, d = 128, K = 64 945 us
+// in a kernel of its own, 990 with all of it, 983 so; distances, there a pass of its own, 1053, 1215, 1172; in all other shapes
+// tried it is no slower than the two kernels were).
 // The first G workgroups of an instance take the lists, the rest, where distances are wanted, measure the points that the
 // filter has decided, in the time that the few open ones take.  A point that one of the lists has meanwhile given a centroid may be among
 // them: both then write the same bits, and what the list still has to read of it (the two centroids, where its distance goes) it
 // has read before it writes the centroid.
 // The instances lie along x, so that the lists of all of them start before any measuring: one instance after the other the last
 // one's list started last (fk_assign, distances, 32 instances of 19499 points, d = 39, K = 282 151 -> 132 us).
-template <int DMAX>
+template <int DMAX, bool PAIRS, bool DIST>
 __global__ __launch_bounds__(512, 4) void assign_f32_list_kernel(
     const float* __restrict__ X, const float* __restrict__ C, const int32_t* __restrict__ list,
     const int32_t* __restrict__ list_len, const int32_t* __restrict__ pair_len, int32_t* assign, float* min_dist, int64_t N, int d,
     int row_len, int K, int none, int G) {
     __shared__ __align__(16) float xs[list_floats<DMAX>()];
     __shared__ float cand_d[8][8];
-    __shared__ int cand_k[8][8];
+    __shared__ int cand_k[8][8], ids[64];                    // (most points held: eight teams' eight)
     const int b = blockIdx.x;
     X += (size_t)b * N * row_len;
     C += (size_t)b * K * row_len;
     assign += (size_t)b * N;
-    if (min_dist) min_dist += (size_t)b * N;
-    if ((int)blockIdx.y >= G) {
+    if (DIST) min_dist += (size_t)b * N;
+    if (DIST && (int)blockIdx.y >= G) {
         const int64_t part = blockIdx.y - G, parts = gridDim.y - G;
         if (DMAX == 32 && row_len <= 16) measure_points<4, 4>(X, C, assign, min_dist, N, row_len, part, parts);
         else if (DMAX == 32) measure_points<8, 4>(X, C, assign, min_dist, N, row_len, part, parts);
@@ -1017,26 +1063,38 @@ __global__ __launch_bounds__(512, 4) void assign_f32_list_kernel(
         else measure_points<16, 2>(X, C, assign, min_dist, N, row_len, part, parts);
         return;
     }
-    const int len = list_len[b], pairs = pair_len[b];
+    const int len = list_len[b];
     list += (size_t)b * N;
     const int most = K <= 64 ? 8 : K <= 128 ? 4 : K <= 256 ? 2 : 1;
-    int thin = most, teams = most;                           // both end at 1 or more (d <= 512)
+    // waves with points of their own: where the centroids are too few to share, and where the list is long enough
+    int thin = most, teams = 8;                              // both end at 1 or more (d <= 512)
+    while (teams > most && len < teams * 8 * G) teams >>= 1;
     while (thin * 8 * d > 4096) thin >>= 1;                  // (short lists: as wide a spread)
     while (teams * 8 * d > list_floats<DMAX>()) teams >>= 1;
-    if (pairs > 0) {
-        constexpr int kOwn = list_floats<DMAX>() / 8;
-        list_pairs<DMAX>(X, C, list + N - 1, pairs, assign, min_dist, d, row_len, none, G, xs + (threadIdx.x >> 6) * kOwn, kOwn);
-        __syncthreads();
+    if constexpr (PAIRS) {
+        if (const int pairs = pair_len[b]; pairs > 0) {
+            constexpr int kOwn = list_floats<DMAX>() / 8;
+            list_pairs<DIST>(X, C, list + N - 1, pairs, assign, min_dist, d, row_len, none, G, xs + (threadIdx.x >> 6) * kOwn, kOwn);
+            __syncthreads();
+        }
     }
     if (len <= 2 * thin * G) {
-        if (DMAX == 0 && K > 256)
-            list_few<DMAX>(X, C, list, len, assign, min_dist, d, row_len, K, none, thin, G, xs, xs + 4096, cand_d, cand_k);
-        else
-            list_points<DMAX, 2>(X, C, list, len, assign, min_dist, d, row_len, K, none, thin, G, xs, cand_d, cand_k);
-    } else if (DMAX == 0 || len < 256 * G || (K > 128 && d <= 16))
-        list_points<DMAX, 8>(X, C, list, len, assign, min_dist, d, row_len, K, none, teams, G, xs, cand_d, cand_k);
-    else
-        list_by_thread<DMAX == 0 ? 32 : DMAX>(X, C, list, len, assign, min_dist, d, row_len, K, none, G, xs);
+        if constexpr (DMAX == 0) {
+            if (K > 256) {
+                list_few<DMAX, DIST>(X, C, list, len, assign, min_dist, d, row_len, K, none, thin, G, xs, xs + 4096, ids, cand_d, cand_k);
+                return;
+            }
+        }
+        list_points<DMAX, DIST, 2>(X, C, list, len, assign, min_dist, d, row_len, K, none, thin, G, xs, ids, cand_d, cand_k);
+        return;
+    }
+    if constexpr (DMAX != 0) {
+        if (len >= 256 * G && (K <= 128 || d > 16)) {
+            list_by_thread<DMAX, DIST>(X, C, list, len, assign, min_dist, d, row_len, K, none, G, xs);
+            return;
+        }
+    }
+    list_points<DMAX, DIST, 8>(X, C, list, len, assign, min_dist, d, row_len, K, none, teams, G, xs, ids, cand_d, cand_k);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1070,7 +1128,7 @@ bool f32_filter_enabled(const Geometry& g) {
 
 template <int DCH>
 static fk_status launch_filter_few(const Geometry& g, const Workspace& w, const float* X, int32_t* assign, float* min_dist, hipStream_t s) {
-    hipLaunchKernelGGL(assign_f32_filter_few_kernel<DCH>, dim3((unsigned)cdiv(g.N, 32), g.B), dim3(few_waves(DCH) * 64), 0, s, X,
+    hipLaunchKernelGGL(assign_f32_filter_few_kernel<DCH>, dim3((unsigned)cdiv(g.N, 32), g.B), dim3(kFewWaves * 64), 0, s, X,
                        (const uintx4*)w.c_frag, w.c_bias, w.f32_shift, assign, w.sorted_idx, w.f32_list_len, w.f32_pair_len, (int32_t*)min_dist,
                        g.N, g.d, g.len, g.K, g.ktiles);
     FK_HIP(hipGetLastError());
@@ -1123,10 +1181,13 @@ fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* 
 #undef FK_FILTER
     const int64_t groups = cdiv(g.N, 2);
     const int64_t G = std::max<int64_t>(1, std::min<int64_t>(groups, cdiv((int64_t)device_cu_count() * 2, g.B)));
-    auto list_kernel = g.d <= 32 ? assign_f32_list_kernel<32> : g.d <= 64 ? assign_f32_list_kernel<64>
-                                                                          : assign_f32_list_kernel<0>;
+    const bool pairs = filter_keeps_three(g.dchunks);
+#define FK_LIST(DIST) (g.d <= 32 ? assign_f32_list_kernel<32, false, DIST> : g.d <= 64 ? assign_f32_list_kernel<64, false, DIST> \
+                       : pairs ? assign_f32_list_kernel<0, true, DIST> : assign_f32_list_kernel<0, false, DIST>)
+    auto list_kernel = min_dist ? FK_LIST(true) : FK_LIST(false);
+#undef FK_LIST
     int64_t distances = min_dist ? cdiv(f32_distance_blocks(g.N, distance_lanes(g.len)), g.d <= 128 ? 8 : 4) : 0;
-    distances = std::min<int64_t>(distances, 65535 - G);       // (a launch's second dimension)
+    distances = std::min<int64_t>(distances, 16 * device_cu_count());      // (see measure_points)
     hipLaunchKernelGGL(list_kernel, dim3(g.B, (unsigned)(G + distances)), dim3(512), 0, s, X, C, w.sorted_idx,
                        w.f32_list_len, w.f32_pair_len, assign, min_dist, g.N, g.d, g.len, g.K, f32_direct_is_split(g) ? g.K - 1 : 0, (int)G);
     FK_HIP(hipGetLastError());

@@ -33,3 +33,11 @@ def test_few_points(both, kind, d, B, N, K):  # noqa: F811
                                      (7, 2400, 264, 300), (1, 40001, 512, 290), (1, 30000, 130, 1100)])
 def test_on_both_sides_of_the_line_and_with_both_lists(both, kind, B, N, d, K):  # noqa: F811
     _same(both, *_data(kind, B, N, d, K, seed=N + d + K))
+
+
+@pytest.mark.parametrize("kind,d", [("twins", 72), ("twins", 93), ("twins", 48), ("triples", 200), ("triples", 509)])
+@pytest.mark.parametrize("B,N,K", [(1, 8191, 300), (1, 8192, 270), (1, 16384, 400), (1, 32767, 130), (1, 32773, 300), (2, 16390, 100)])
+def test_long_lists(both, kind, d, B, N, K):  # noqa: F811
+    """Every point on the list of those that are measured in full, around the lengths from which two, four and eight waves of a
+    workgroup have points of their own."""
+    _same(both, *_data(kind, B, N, d, K, seed=N + d + K))
