@@ -607,7 +607,7 @@ __global__ __launch_bounds__(kFewWaves * 64, DCH <= 3 ? 4 : 2) void assign_f32_f
 // list is spread thin and over in the time that a few rows take to arrive (5 to 20 us); with P =
 // 8 a long one is bound by reading its points from LDS, a pass of which serves 64 centroids, so that its waves take points of their
 // own as soon as all workgroups have some: waves that share 400 rows leave one of eight idle, 300 three (every centroid twice, 300000 points,
-// d = 96, K = 400 1306 -> 885 us, 400000, d = 80, K = 300 1460 -> 710, 20000 94 -> 69).
+// d = 96, K = 400 1306 -> 890 us, 400000, d = 80, K = 300 1460 -> 710, 20000 94 -> 69).
 //   Long lists of rows of up to 64 features, where that form spends its time on reading centroid
 // rows: one point per thread with its features in registers, centroid tiles through LDS.  (Not rows of
 // up to 16 against many centroids: it multiplies 32 features.  7 x 294694 points, d = 8, K = 14868: 60.1 ms
@@ -617,9 +617,9 @@ __global__ __launch_bounds__(kFewWaves * 64, DCH <= 3 ? 4 : 2) void assign_f32_f
 // list and distances 44 -> 22 us.
 //   What other open points cost is about the direct kernel's time for them, or less, on top of the filter's.
 // All points open, fk_assign against the direct kernels alone, us.  Every centroid twice: 2^20 points,
-// d = K = 64: 275, 221 (one addition to the list's length per wave: 610); d = 64, K = 256: 860, 811
-// (in the first form: 1896); d = 128, K = 64: 386, 640 (pairs); 300000 points, d = 96, K = 400:
-// 890, 1154; 65536, d = 256, K = 512: 89, 1341 (pairs).  Four times: d = 128, K = 64: 985, 640; 65536, d = 256, K = 512: 586, 1348.
+// d = K = 64: 278, 221 (one addition to the list's length per wave: 610); d = 64, K = 256: 831, 811
+// (in the first form: 1896); d = 128, K = 64: 389, 640 (pairs); 300000 points, d = 96, K = 400:
+// 874, 1154; 65536, d = 256, K = 512: 89, 1341 (pairs).  Four times: d = 128, K = 64: 871, 640; 65536, d = 256, K = 512: 557, 1348.
 
 // |x - c|^2 by direct differences for every point whose distance is wanted: LANES (4, 8 or 16) lanes a point, enough for a whole
 // row per load where it has up to 64 features.  Infinity where it is not finite, as in the direct kernels, whose
@@ -696,17 +696,28 @@ __device__ __forceinline__ void list_merge(
     const float* __restrict__ C, const int* ids, int64_t g, int len,
     int32_t* __restrict__ assign, float* __restrict__ min_dist, const float* xs, int d, int row_len, int K, int none, int size, int held,
     float (&best)[P], int (&at)[P], float (*cand_d)[8], int (*cand_k)[8]) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));                            // (or addresses made of it are kept through the round, in spilled registers)
+    const int lane = tid & 63, wave = tid >> 6;
+    // half of the lanes keep half of the points, then half of those, then the lanes of a point meet: ten exchanges for eight points where a
+    // butterfly for each takes 48
+    auto meet = [&](float d0, int k0, float d1, int k1, int o, int to) {     // (0: kept, 1: handed over)
+        const float od = __shfl_xor(d1, o);
+        const int ok = __shfl_xor(k1, o);
+        const bool other = od < d0 || (od == d0 && ok < k0);
+        best[to] = other ? od : d0;
+        at[to] = other ? ok : k0;
+    };
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
+    for (int n = P / 2, o = 32; n > 0; n >>= 1, o >>= 1) {
+        const bool upper = (lane & o) != 0;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const float od = __shfl_xor(best[p], o);
-            const int ok = __shfl_xor(at[p], o);
-            if (od < best[p] || (od == best[p] && ok < at[p])) { best[p] = od; at[p] = ok; }
-        }
-        if (lane == 0) { cand_d[wave][p] = best[p]; cand_k[wave][p] = at[p]; }
+        for (int p = 0; p < n; ++p)
+            meet(upper ? best[n + p] : best[p], upper ? at[n + p] : at[p], upper ? best[p] : best[n + p], upper ? at[p] : at[n + p], o, p);
     }
+#pragma unroll
+    for (int o = 32 / P; o > 0; o >>= 1) meet(best[0], at[0], best[0], at[0], o, 0);
+    if (lane % (64 / P) == 0) { cand_d[wave][lane * P / 64] = best[0]; cand_k[wave][lane * P / 64] = at[0]; }
     __syncthreads();
     if (tid < held && g + tid < len) {
         const int p = tid % P, w0 = tid / P * size;
@@ -725,18 +736,29 @@ __device__ __forceinline__ void list_merge(
     if constexpr (DIST) {
         const int here = (int)min((int64_t)held, len - g);
         auto measure = [&](auto group) {
-            constexpr int LANES = decltype(group)::value;
-            for (int q = tid / LANES; q < here; q += 512 / LANES) {
-                const float *x = xs + q * d, *c = C + (size_t)cand_k[q / P * size][q % P] * row_len;
-                const int own = ids[q], l = tid & (LANES - 1);
-                float D = 0.f;                               // (zeros past the end of both rows)
-                for (int j = l * 4; j < row_len; j += 4 * LANES) {
-                    const floatx4 v = *(const floatx4*)(x + j), w = row_piece32(c, j, row_len);
+            constexpr int LANES = decltype(group)::value, groups = 512 / LANES;
+            for (int q0 = tid / LANES; q0 < here; q0 += 2 * groups) {        // (past the end: the last point again)
+                const int q[2] = {q0, min(q0 + groups, here - 1)}, l = tid & (LANES - 1);
+                const float* c[2];
+                float D[2] = {0.f, 0.f};                     // (zeros past the end of both rows)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) { const float t = v[e] - w[e]; D = fmaf(t, t, D); }
+                for (int u = 0; u < 2; ++u) c[u] = C + (size_t)cand_k[q[u] / P * size][q[u] % P] * row_len;
+                for (int j = l * 4; j < row_len; j += 4 * LANES) {
+                    floatx4 w[2];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) w[u] = row_piece32(c[u], j, row_len);
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const floatx4 v = *(const floatx4*)(xs + q[u] * d + j);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) { const float t = v[e] - w[u][e]; D[u] = fmaf(t, t, D[u]); }
+                    }
                 }
-                D = sum_of_lanes<LANES>(D);
-                if (l == 0) min_dist[own] = D;
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    D[u] = sum_of_lanes<LANES>(D[u]);
+                    if (l == 0) min_dist[ids[q[u]]] = D[u];
+                }
             }
         };
         if (DMAX == 32 && row_len <= 16) measure(std::integral_constant<int, 4>());
@@ -1033,9 +1055,9 @@ __device__ __forceinline__ void list_pairs(
 
 // `none`: the answer where no distance is finite, that of the direct kernel for the shape.
 // DMAX: 32 or 64 for rows up to that, 0 for wider ones.  PAIRS: where the filter keeps three scores, DIST: where distances are wanted, and the
-// code for either only there: what it takes of the registers the long lists spill (four of each centroid, 2^20 points, d = 128, K = 64 945 us
-// in a kernel of its own, 990 with all of it, 983 so; distances, there a pass of its own, 1053, 1215, 1172; in all other shapes
-// tried it is no slower than the two kernels were).
+// code for either only there: with all of it in one kernel, and addresses of list_merge kept through its rounds, the long lists' registers did not
+// suffice (four of each centroid, 2^20 points, d = 128, K = 64 943 us before pairs and distances had joined, 990 with them, 978 with the
+// code apart, 871 with nothing spilled and the shorter merge; distances, once a pass of its own, 1050, 1211, 1169, 1007).
 // The first G workgroups of an instance take the lists, the rest, where distances are wanted, measure the points that the
 // filter has decided, in the time that the few open ones take.  A point that one of the lists has meanwhile given a centroid may be among
 // them: both then write the same bits, and what the list still has to read of it (the two centroids, where its distance goes) it
