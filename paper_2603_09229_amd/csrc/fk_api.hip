@@ -850,7 +850,7 @@ fk_status fk_lloyd_iter(const void* X, float* C_f32, void* C_lp, int32_t* assign
             const int rep = timer_repeat();
             for (int r = 0; r < rep; ++r) {
                 if (t == FK_F32)
-                    FK_TRY(launch_assign(g, X, C_f32, nullptr, assign, nullptr, s, &w, split && r == 0));
+                    FK_TRY(launch_assign(g, X, C_f32, nullptr, assign, nullptr, s, &w, split && r == 0 ? F32Split::kWritten : F32Split::kAmongPoints));
                 else
                     FK_TRY(launch_assign(g, X, w.c_frag, w.c_bias, assign, nullptr, s));
             }
@@ -866,7 +866,7 @@ fk_status fk_lloyd_iter(const void* X, float* C_f32, void* C_lp, int32_t* assign
         fa.sums = nullptr;
         fa.accumulate = false;
         fa.normalise = true;
-        split = filtered && it + 1 < iters && !f32_lays_out_anew(it + 1);
+        split = filtered && it + 1 < iters;
         if (split) {
             fa.c_split = w.c_frag;
             fa.shift = w.f32_shift;

@@ -1307,7 +1307,7 @@ static fk_status launch_mfma_d(const Geometry& g, const void* X, const void* fra
 
 fk_status launch_assign(const Geometry& g, const void* X, const void* C_or_frag,
                         const float* c_bias, int32_t* assign, float* min_dist, hipStream_t s,
-                        const Workspace* w, bool split) {
+                        const Workspace* w, F32Split split) {
     if (g.t == FK_F16) return launch_mfma_d<false>(g, X, C_or_frag, c_bias, assign, min_dist, s);
     if (g.t == FK_BF16) return launch_mfma_d<true>(g, X, C_or_frag, c_bias, assign, min_dist, s);
     const float* Xf = (const float*)X;

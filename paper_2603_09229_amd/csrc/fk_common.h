@@ -157,23 +157,22 @@ fk_status launch_round_centroids(const Geometry& g, const float* C_f32, void* C_
 // Fused distance + online argmin.  16-bit: reads c_frag/c_bias; fp32: reads C directly.
 // fp32 with a workspace may take the filtered form (fk_f32_filter.hip), which uses the centroid
 // buffers and sorted_idx of it; without one (nullptr) the direct kernels.
+enum class F32Split {
+    kAmongCentroids,     // laid out by the assignment, shifted by a mean of the centroids
+    kAmongPoints,        // by a mean of the points: the first assignment of a fit
+    kWritten             // the last update has written them, with the shift of the first assignment, and cleared the lists (FinalizeArgs)
+};
 fk_status launch_assign(const Geometry& g, const void* X, const void* C_or_frag,
                         const float* c_bias, int32_t* assign, float* min_dist, hipStream_t s,
-                        const Workspace* w = nullptr, bool split = false);
+                        const Workspace* w = nullptr, F32Split split = F32Split::kAmongCentroids);
 // fp32: candidates from split bf16 products on the matrix cores, the open points by direct differences
-// (`split`: the last update has written the split centroids and cleared the lists, see FinalizeArgs)
 fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* X, const float* C,
-                            int32_t* assign, float* min_dist, bool split, hipStream_t s);
+                            int32_t* assign, float* min_dist, F32Split split, hipStream_t s);
 bool f32_filter_enabled(const Geometry& g);
 int f32_filter_option();
-// Whether iteration `it` of a fit lays its split centroids out anew, with a shift taken from the centroids as they are then, instead of
-// multiplying those that the update before it has written with the shift of an earlier iteration: the first, whose starting
-// centroids may lie anywhere; the second, whose centroids lie among the points; and every eighth after it.  The bound grows with the
-// squared distance of points and centroids from the shift, and a shift far from both leaves every point open in every iteration that it is
-// kept for.  A launch of 5 to 8 us each.  Ten iterations, us, never anew after the first / so: 300000 normally distributed points, d = 96,
-// K = 400, which start from rows of theirs with one feature 300 off 13065 / 2279 (anew every time 2279), 30 off 1909 / 1427 (1485), from
-// the rows themselves 1405 / 1414 (1476).
-inline bool f32_lays_out_anew(int it) { return it == 0 || it % 8 == 1; }
+// Which of N points a fit's shift is taken from: the fractional parts of multiples of the golden ratio, spread evenly and met by no
+// period of the data.
+__host__ __device__ inline uint32_t sampled_row(uint32_t i, uint32_t N) { return (uint32_t)((uint64_t)(i * 0x9E3779B9u) * N >> 32); }
 // Half workgroups (of 256 threads) that measure distances, `lanes` threads a point.  A launch dimension holds fewer
 // than 2^32 threads, which one point per group of 16 lanes reaches at 2^28 points.
 inline int64_t f32_distance_blocks(int64_t N, int lanes) {
@@ -236,7 +235,7 @@ struct FinalizeArgs {
     const int32_t* late_counts = nullptr;  // one after the other
     int late = 0;
     bool normalise;      // divide and write centroids
-    // fp32, filtered assignment next: its split centroids, which an assignment before it in the call has laid out (NULL: not wanted)
+    // fp32, filtered assignment next: its split centroids, which the first assignment of the call has laid out (NULL: not wanted)
     void* c_split = nullptr;
     const float* shift = nullptr;
     float* c2 = nullptr;

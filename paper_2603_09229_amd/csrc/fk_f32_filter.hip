@@ -3,7 +3,7 @@
 // Direct differences cost two vector instructions per (point, centroid, feature) and leave the
 // matrix cores idle.  Here a first kernel only NARROWS the choice: it computes, for every pair,
 //     s_k = x'.c'_k - |c'_k|^2 / 2          x' = x - m,  c' = c - m
-// (the argmin of |x - c_k|^2 is the argmax of s_k; m, the mean of up to 32 of the centroids, keeps
+// (the argmin of |x - c_k|^2 is the argmax of s_k; m, the mean of some of the centroids or points, keeps
 // the numbers as small as the data's spread) with x' and c' each split into two bf16 values,
 //     x'.c' ~ xh.ch + xl.ch + xh.cl,
 // and keeps the best and the second best score of every point.  Where the two are further apart
@@ -67,15 +67,34 @@ __device__ __forceinline__ void split8(const float (&v)[8], uintx4& hi, uintx4& 
 // c2 = inf, so that no point is ever certain of it; rows past K one that never wins.  Rows with a NaN
 // or an infinity get that too -- no distance to them is below infinity, where the direct form's minimum
 // starts -- and stay out of the mean: one such centroid would leave every point open.
+// The mean of up to 32 of the centroids or, where X is given (fits, whose later iterations keep the shift, see emit_split in
+// fk_update.hip), of half of 32 of the points (point_mean): the centroids that a fit starts from may lie anywhere, the
+// later ones lie among the points.
 // Tile 0 also leaves the shift m and clears the lengths of the instance's lists.
 // A few microseconds of dependent loads, and of instructions that no cache holds yet: the rows of the mean are asked for eight at a
 // time and the own rows before the mean is needed, and nothing is in the code that the shape has no use for (kGroups, RAGGED; d = 128, K = 211
 // 7.2 -> 5.5 us; with all 32 rows of the mean asked for at once 7.6).
 constexpr int kLayoutThreads = 512;
 
+// Feature x of 32 of N rows (sampled_row).  Of four means of eight the largest and the smallest stay out, and with them a row far off.
+// (64 rows: a fit of 300000 points, d = 96, K = 400 takes 2 us more.)
+__device__ __forceinline__ float point_mean(const float* __restrict__ x, uint32_t N, int len) {
+    float a = 0.f, b = 0.f, c = 0.f, e = 0.f;
+#pragma unroll 1
+    for (uint32_t i0 = 0; i0 < 32; i0 += 8) {
+        float v[8], s = 0.f;
+#pragma unroll
+        for (uint32_t i = 0; i < 8; ++i) v[i] = x[(size_t)sampled_row(i0 + i, N) * len];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s += fabsf(v[i]) < INFINITY ? v[i] * 0.125f : 0.f;
+        a = b; b = c; c = e; e = s;
+    }
+    return 0.5f * (fmaxf(fminf(a, b), fminf(c, e)) + fminf(fmaxf(a, b), fmaxf(c, e)));
+}
+
 template <int kGroups, bool RAGGED>
 __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
-    const float* __restrict__ C, uintx4* __restrict__ frag, float* __restrict__ c2,
+    const float* __restrict__ X, uint32_t N, const float* __restrict__ C, uintx4* __restrict__ frag, float* __restrict__ c2,
     float* __restrict__ shift, int32_t* __restrict__ list_len, int32_t* __restrict__ pair_len, int d, int row_len, int K, int ktiles, int dch) {
     const int len = RAGGED ? row_len : d;
     __shared__ float m[512];
@@ -102,7 +121,9 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
     const int rows = min(K, 32);
     if (tid < width) {
         float s = 0.f;
-        if (tid < len) {
+        if (tid < len && X) {
+            s = point_mean(X + (size_t)b * N * len + tid, N, len);
+        } else if (tid < len) {
 #pragma unroll 1
             for (int i0 = 0; i0 < rows; i0 += 8) {
                 float v[8];
@@ -111,8 +132,8 @@ __global__ __launch_bounds__(kLayoutThreads) void f32_split_layout_kernel(
 #pragma unroll
                 for (int i = 0; i < 8; ++i) s += i0 + i < rows && fabsf(v[i]) < INFINITY ? v[i] : 0.f;
             }
+            s /= (float)rows;
         }
-        s /= (float)rows;
         m[tid] = s;
         if (kt == 0) shift[(size_t)b * width + tid] = s;
     }
@@ -1167,15 +1188,15 @@ static fk_status launch_filter_t(const Geometry& g, const Workspace& w, const fl
 }
 
 fk_status launch_f32_filter(const Geometry& g, const Workspace& w, const float* X, const float* C, int32_t* assign,
-                            float* min_dist, bool split, hipStream_t s) {
+                            float* min_dist, F32Split split, hipStream_t s) {
     // (groups of eight features a thread, 32 rows of them to a workgroup)
     const int per = (int)cdiv(64 * g.dchunks, kLayoutThreads);
 #define FK_LAYOUT(RAGGED) (per == 1 ? f32_split_layout_kernel<1, RAGGED> : per == 2 ? f32_split_layout_kernel<2, RAGGED> \
                            : per == 3 ? f32_split_layout_kernel<3, RAGGED> : f32_split_layout_kernel<4, RAGGED>)
     auto layout = g.len == g.d ? FK_LAYOUT(false) : FK_LAYOUT(true);
 #undef FK_LAYOUT
-    if (!split) {
-        hipLaunchKernelGGL(layout, dim3(g.ktiles, g.B), dim3(kLayoutThreads), 0, s, C, (uintx4*)w.c_frag, w.c_bias,
+    if (split != F32Split::kWritten) {
+        hipLaunchKernelGGL(layout, dim3(g.ktiles, g.B), dim3(kLayoutThreads), 0, s, split == F32Split::kAmongPoints ? X : nullptr, (uint32_t)g.N, C, (uintx4*)w.c_frag, w.c_bias,
                            w.f32_shift, w.f32_list_len, w.f32_pair_len, g.d, g.len, g.K, g.ktiles, g.dchunks);
         FK_HIP(hipGetLastError());
     }

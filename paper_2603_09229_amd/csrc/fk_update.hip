@@ -184,8 +184,8 @@ struct EmitTo {
     const float* late_sums;
     const int32_t* late_counts;
     int d, K, B, ktiles, dch, accumulate, normalise, bf, late, row_len;
-    // fp32: the split centroids of the filtered assignment (fk_f32_filter.hip) with the shift that their last
-    // layout in the call has left, c2 their norms; the lengths of its lists, which the next assignment starts from
+    // fp32: the split centroids of the filtered assignment (fk_f32_filter.hip) with the shift that the first
+    // assignment of the call has left, c2 their norms; the lengths of its lists, which the next assignment starts from
     uint16_t* c_split;
     const float* shift;
     float* c2;
@@ -194,8 +194,12 @@ struct EmitTo {
 
 // Row k of the split centroids, from its shifted values in `row` (d floats of LDS, not yet behind a barrier): what
 // f32_split_layout_kernel writes for it, so that the next assignment of the call needs no launch of that kernel (5 to 8 us).  Rows beyond
-// K and features beyond d keep what that kernel's last launch in the call wrote there, and so does the shift, which only has to be near
-// the data (see f32_lays_out_anew).
+// K and features beyond d keep what that kernel's launch in the first assignment wrote there, and so does the shift, a mean of
+// points: the bound grows with the squared distances from it of points and centroids.  With a mean of the starting centroids instead a start
+// away from the points left every point open in every iteration; laid out anew in the second and every eighth iteration it cost 4 to 6 us
+// a launch.  300000 normally distributed points, d = 96, K = 400, ten iterations from rows of theirs, us, mean of the starting centroids / of
+// points: 1435 / 1434; one feature of the start 300 off 10938 / 1597, 30 off 2043 / 1417, every feature 10 off 5862 / 1518; one row in 997 a thousand
+// times as long 13338 / 1370.
 __device__ __forceinline__ void emit_split(const EmitTo& to, int b, int k, const float* row, bool odd) {
     const int tid = threadIdx.x, d = to.d, T = (int)blockDim.x;
     __shared__ int fits;

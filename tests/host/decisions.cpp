@@ -48,13 +48,26 @@ static int filter_is_chosen_once() {
     return fk_set_option("assign_f32_filter", -1) == FK_OK ? 0 : 1;
 }
 
-// A shift is taken from starting centroids for one iteration, and from later ones for eight at the most.
-static int shifts_are_renewed() {
-    CHECK(fk::f32_lays_out_anew(0) && fk::f32_lays_out_anew(1));
-    int kept = 0;
-    for (int it = 2; it < 1000; ++it) {
-        kept = fk::f32_lays_out_anew(it) ? 0 : kept + 1;
-        CHECK(kept < 8);
+// A fit keeps one shift, a mean of some of 32 of its points: they lie in X, in every sixteenth of it, and where the clusters take turns in rows of
+// data no more than a quarter of them belong to one of eight or more.
+static int shifts_lie_among_points() {
+    for (uint32_t N : {1u, 2u, 31u, 32u, 1000u, 65536u, 1u << 20, 16777217u, 0x7FFFFFFFu}) {
+        bool met[16] = {};
+        for (uint32_t i = 0; i < 32; ++i) {
+            const uint32_t row = fk::sampled_row(i, N);
+            CHECK(row < N);
+            met[(uint64_t)row * 16 / N] = true;
+        }
+        for (bool m : met) CHECK(m || N < 32);
+        for (uint32_t clusters : {8u, 64u, 256u, 1000u, 1024u, 4096u}) {
+            int most = 0;
+            for (uint32_t i = 0; i < 32; ++i) {
+                int same = 0;
+                for (uint32_t j = 0; j < 32; ++j) same += fk::sampled_row(i, N) % clusters == fk::sampled_row(j, N) % clusters;
+                most = same > most ? same : most;
+            }
+            CHECK(most <= 8 || N < 1000);
+        }
     }
     return 0;
 }
@@ -106,7 +119,7 @@ static int host_rows_lie_in_one_allocation() {
 }
 
 int main() {
-    if (option_is_read_once() || filter_is_chosen_once() || shifts_are_renewed() || launches_fit() || few_counts_in_a_row() || host_rows_lie_in_one_allocation()) return 1;
+    if (option_is_read_once() || filter_is_chosen_once() || shifts_lie_among_points() || launches_fit() || few_counts_in_a_row() || host_rows_lie_in_one_allocation()) return 1;
     printf("host decisions ok\n");
     return 0;
 }
