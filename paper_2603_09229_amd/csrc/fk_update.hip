@@ -801,7 +801,7 @@ fk_status launch_finalize(const Geometry& g, const Workspace& w, const int32_t* 
     // 3000 points, d = 40, K = 100 84 / 70 (the merge 9.2 -> 5.6), 16 of 20000, d = 128, K = 200 218 / 207, 32 of 20000, K = 40 245.4 / 243.6;
     // but 32, K = 16 140.6 / 141.2, 16, d = 64, K = 64 102.3 / 102.9; with 32 rows each 8 of 30000, K = 100 142 / 151.
     // (A one-pass update only: all iterations of a fit take it or none.)
-    const bool one_batch = wg_counts && wg_counts == w.wg_counts && g.d <= 128 && wg_per_cluster <= 16 && (int64_t)g.K * g.B > 1024;
+    const bool one_batch = wg_counts && wg_counts == w.wg_counts && g.d <= 128 && wg_per_cluster <= 16 && (int64_t)g.K * g.B > 4 * device_cu_count();
     if ((threads == 64 || one_batch) && a.late == 0 && !a.sums && a.normalise && !a.c_split) {
         auto wave_kernel = g.len == g.d ? finalize_wave_kernel<false> : finalize_wave_kernel<true>;
         hipLaunchKernelGGL(wave_kernel, dim3((unsigned)cdiv(g.K, 4), g.B), dim3(256), 0, s, w.partial, seg_off, item_off,
