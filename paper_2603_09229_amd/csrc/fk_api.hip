@@ -208,6 +208,7 @@ Workspace carve(const Geometry& g, void* base, bool padded_x) {
     w.item_off = (int32_t*)take((size_t)g.B * (g.K + 1) * 4);
     w.block_hist = (int32_t*)take((size_t)g.B * g.sort_blocks * nbmax * 4);
     w.digit_off = (int32_t*)take((size_t)g.B * 2049 * 4);
+    // (the 16-bit ids have room for 32 bits: by default an out-of-core call's chunks follow from these sizes, and the order of its sums from them)
     if (g.sort_passes == 2) {
         w.keys_tmp = (uint16_t*)take(BN * 4);
         w.vals_tmp = (int32_t*)take(BN * 4);

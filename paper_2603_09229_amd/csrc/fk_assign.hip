@@ -1164,7 +1164,7 @@ static FewForm choose_few(const Geometry& g, bool have_rows) {
     }
     if (t <= 2 * U) {
         if (dch > 16) return c >= 8 ? kFewOne : kFewNone;
-        if (dch > 8) return c >= 32 ? kFewOne : dch * c >= 24 && c >= 2 ? kFewOne : kFewNone;
+        if (dch > 8) return dch * c >= 24 && c >= 2 ? kFewOne : kFewNone;
         if (c < (dch == 2 ? 16 : 8)) return kFewNone;
         return c >= 32 ? kFewTwo16 : kFewTwo8;
     }
