@@ -1147,11 +1147,12 @@ void set_f32_filter_option(int v) { g_filter_option.store(v, std::memory_order_r
 int f32_filter_option() { return g_filter_option.load(std::memory_order_relaxed); }
 
 // Where the filter wins, measured against the direct kernels over d = 16 .. 512, K = 8 .. 256 and
-// 10^3 .. 2^20 points: its three launches take 14 us at least and read X at the same rate, so the
-// sweep has to be worth it.  Rows of up to 128: from 2^28 terms (32768 points, d = 128, K = 64: 21.1
-// against 27.2 us; 131072, d = 64, K = 32: 20.1 against 29.1), or, with fewer points, where one
-// wave's walk through the centroids alone is long enough (1000 points, d = 128, K = 64: 19.4
-// against 22.1 us; d = 32, K = 128: 15.4 against 13.9).  Wider rows, which the direct kernel reads
+// 10^3 .. 2^20 points: its three launches take 18 us at least (20 with distances) and read X at the same rate, so the
+// sweep has to be worth it.  Rows of up to 128: from 2^28 terms (32768 points, d = 128, K = 64: 19.1
+// against 27.8 us; 131072, d = 64, K = 32: 21.7 against 27.7; below, 16384, d = K = 64: 19.2 against 13.5), or, with fewer
+// points, where one wave's walk through the centroids alone is long enough (1000 points, d = 128, K = 64: 18.0
+// against 22.2 us; d = 32, K = 128: 18.1 against 13.8).  (In a fit's later iterations it has two launches and would win
+// sooner, which the rule does not tell apart: ten iterations there 164 against 213, 8192 points, d = 64, K = 100 268 against 324.)  Wider rows, which the direct kernel reads
 // again for every 16 centroids: from the second such group (65536 points, d = 256, K = 512: 89
 // against 1340 us), or with few points.
 bool f32_filter_enabled(const Geometry& g) {

@@ -31,7 +31,7 @@ namespace fk {
 // X is read once: copies of whole lines that ask for no place in the caches (the non-temporal hint).
 constexpr int kOnce = 2;
 
-// Workgroups per compute unit: no more than keep about 32 KiB of X in flight there (64 KiB of wide rows).  More make memory
+// Workgroups per compute unit: no more than keep 32 KiB of X in flight there, 64 where rows of 64 features are assigned too and of wider rows.  More make memory
 // slower, and the merge longer.  fk_update, us, one / two / three: 2^24 points, d = 64, K = 16 309 / 327 / 354; 8 million, d = 128, K = 30
 // 306 / 319; 16 million, d = 32, K = 30 204 / 165 / 186.  An iteration: 2^20, d = 128, K = 32 52 / 57; 3 million, d = 48, K = 12 63 / 54 /
 // 58 (one wave per SIMD is too few for the work on rows that are not swizzled); 16 million, d = 32 238 / 175 / 172; 200000, d = 32,

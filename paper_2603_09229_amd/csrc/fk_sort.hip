@@ -235,8 +235,8 @@ __global__ __launch_bounds__(256) void sort_binscan_kernel(int32_t* __restrict__
 //   keys_out may be NULL.  seg_off / item_off are written by workgroup 0 when non-NULL
 //   (single-pass sort: bins are cluster ids, so the bin offsets are the segment table).
 //   Key: the ids as the caller has them, or the 16-bit copies (K is at most 65536) that a first pass leaves for the second:
-//   2^23 keys, K = 4096, both histograms, both scatters, boundaries 27 + 73 + 11 us -> 20 + 61 + 6; fk_update, d = 128, there
-//   491 -> 478, 2^25 x 16 1137 -> 1027, 30000 x 64, K = 5000 43.0 -> 40.6.
+//   2^23 keys, K = 4096, both histograms, both scatters, boundaries 27 + 73 + 11 us -> 20 + 61 + 6; evenly drawn ids, fk_sort_inverse there
+//   110 -> 95, fk_update, d = 128, 494 -> 480, 2^25 x 16 1139 -> 1028, 30000 x 64, K = 5000 44 -> 42.
 template <int kSortWaves, bool kScans, typename Key>
 __global__ __launch_bounds__(kSortWaves * 64, kSortWaves == 8 ? 6 : 1) void sort_scatter_kernel(
     const Key* __restrict__ keys, const int32_t* __restrict__ vals_in,
