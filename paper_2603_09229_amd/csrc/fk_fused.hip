@@ -35,7 +35,8 @@ constexpr int kOnce = 2;
 // slower, and the merge longer.  fk_update, us, one / two / three: 2^24 points, d = 64, K = 16 309 / 327 / 354; 8 million, d = 128, K = 30
 // 306 / 319; 16 million, d = 32, K = 30 204 / 165 / 186.  An iteration: 2^20, d = 128, K = 32 52 / 57; 3 million, d = 48, K = 12 63 / 54 /
 // 58 (one wave per SIMD is too few for the work on rows that are not swizzled); 16 million, d = 32 238 / 175 / 172; 200000, d = 32,
-// K = 32 12.7 / 13.0 / 14.3.
+// K = 32 12.7 / 13.0 / 14.3.  (Rows of 40 features, which are not stored swizzled and of which one has 20 KiB in flight, always take two: fk_update,
+// K = 20, one / two: 60 MB of them 22 / 20, 260 MB 56 / 51, 1200 MB 217 / 192; rows of 48 take as long either way.)
 constexpr int stream_per_cu(int dch, bool assigns) { return dch == 8 || (dch == 4 && !assigns) ? 1 : 2; }
 
 // Few workgroups make a wave's share long, 16384 of 2^24 points, and one chain of additions over all of it loses what is small
@@ -341,7 +342,7 @@ template <bool BF, int DCH, bool ASSIGN>
 static fk_status launch_stream_update_t(const Geometry& g, const Workspace& w, const void* X,
                                         int32_t* assign, bool keep_assign, int* grid_out, hipStream_t s) {
     constexpr int WAVES = 4;
-    const int64_t nbatches = cdiv(g.N, 32), wgs = (int64_t)device_cu_count() * stream_per_cu(DCH, ASSIGN);
+    const int64_t nbatches = cdiv(g.N, 32), wgs = (int64_t)device_cu_count() * (DCH == 4 && g.d <= 40 ? 2 : stream_per_cu(DCH, ASSIGN));
     int64_t G = cdiv(wgs, g.B);
     G = std::min<int64_t>(G, g.fused_grid_cap);
     G = std::min<int64_t>(G, cdiv(nbatches, WAVES));
